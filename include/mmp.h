@@ -374,7 +374,11 @@ typedef struct {
                              else Pz/z_lanes).  Same arithmetic per column */
   int32_t field_zplanes;  /* z cells per thread of the field kernel        */
   uint32_t kinds;         /* out: bits 0/1/2 set when the x/y/z passes use
-                             the power-of-two register kernels             */
+                             the power-of-two register kernels (a 3-D grid
+                             of up to 8 layers whose padded y lines of all
+                             layers fit a block's LDS runs y and z as one
+                             pass, whatever bits 1 and 2 and the y and z
+                             launch shapes say)                            */
   int32_t lds_axes;       /* bits 0/1/2: run the x/y/z passes through the
                              mixed-radix LDS kernels even where the pad is
                              a power of two (0 = the register kernels

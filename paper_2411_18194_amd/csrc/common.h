@@ -66,6 +66,31 @@ __device__ __forceinline__ V cconj(V a) { V r; r.x = a.x; r.y = -a.y; return r; 
 template <typename V, typename S>
 __device__ __forceinline__ V cscale(V a, S s) { V r; r.x = a.x * s; r.y = a.y * s; return r; }
 
+// two consecutive complex values as one 16-byte access where they fit (the
+// load is the x inverse pass's single read of its spectrum: non-temporal)
+template <typename T>
+__device__ __forceinline__ void store2(cpx<T>* o, cpx<T> a, cpx<T> b) {
+  if constexpr (sizeof(cpx<T>) == 8) {
+    float4 v;
+    v.x = a.x; v.y = a.y; v.z = b.x; v.w = b.y;
+    *reinterpret_cast<float4*>(o) = v;
+  } else {
+    o[0] = a;
+    o[1] = b;
+  }
+}
+template <typename T>
+__device__ __forceinline__ void load2(const cpx<T>* i, cpx<T>& a, cpx<T>& b) {
+  if constexpr (sizeof(cpx<T>) == 8) {
+    const nt_f4 v = __builtin_nontemporal_load(reinterpret_cast<const nt_f4*>(i));
+    a = cmk<T>(v.x, v.y);
+    b = cmk<T>(v.z, v.w);
+  } else {
+    a = ntload(i);
+    b = ntload(i + 1);
+  }
+}
+
 // ------------------------------------------------ embedded RK pairs --
 // The five pairs of Table 2, as run on the device.  Stage s (1-based) of an
 // attempt evaluates k_s at stage input s = y_n + h sum_{j<s} a[s-1][j] k_j;
@@ -198,18 +223,6 @@ inline int smooth_pad(int n) {
       while (q % f == 0) q /= f;
     if (q == 1) return p;
   }
-}
-
-// factor L into FFT radices (8 first, then 4, 2, 7, 5, 3)
-inline int fft_radices(int L, int* out) {
-  int n = 0;
-  while (L % 8 == 0) { out[n++] = 8; L /= 8; }
-  while (L % 4 == 0) { out[n++] = 4; L /= 4; }
-  while (L % 2 == 0) { out[n++] = 2; L /= 2; }
-  while (L % 7 == 0) { out[n++] = 7; L /= 7; }
-  while (L % 5 == 0) { out[n++] = 5; L /= 5; }
-  while (L % 3 == 0) { out[n++] = 3; L /= 3; }
-  return L == 1 ? n : -1;
 }
 
 void set_error(const std::string& msg);

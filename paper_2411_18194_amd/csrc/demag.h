@@ -4,7 +4,7 @@
 #include <vector>
 
 #include "common.h"
-#include "fft_engine.h"
+#include "fft_lines.h"
 #include "prof.h"
 
 namespace mmp {
@@ -23,7 +23,10 @@ struct DemagPlan {
   int nx = 0, ny = 0, nz = 0;
   int Px = 0, Py = 0, Pz = 0, Hx = 0, Hy = 0, Hz = 0;
   int ldy = 0;                      // multiple of 16, so any x block shape fits
-  Rad rx{}, ry{}, rz{};
+  LineFft fx{}, fy{}, fz{};         // mixed-radix line transforms of the axes
+  // 3-D grids: y, z and multiply as one pass over the layers of a kx column
+  // in LDS (see yz_fits); S2 is then not used
+  bool fuse = false;
   // power-of-two axes use the register four-step kernels
   bool p2x = false, p2y = false, p2z = false;
   // launch shapes
@@ -50,16 +53,19 @@ int demag_plan(int nx, int ny, int nz, int real_bytes, const int* pads, DemagPla
 // 0 if every launch shape of p is within the kernels' limits.
 int demag_plan_check(const DemagPlan& p, int real_bytes);
 
-enum DemagPass { DP_XF = 0, DP_YF, DP_Z, DP_YI, DP_XI, DP_M2, DP_COUNT };
+enum DemagPass { DP_XF = 0, DP_YF, DP_Z, DP_YI, DP_XI, DP_M2, DP_YZ, DP_COUNT };
 
 template <typename T>
 struct DemagBufs {
   cpx<T>* S1 = nullptr;
   cpx<T>* S2 = nullptr;
   T* K = nullptr;           // octant spectrum, scaled by -mu0/(Px Py Pz)
-  cpx<T>* twx = nullptr;    // exp(-2 pi i j/P) tables
+  cpx<T>* twx = nullptr;    // stage twiddles of the line transforms
   cpx<T>* twy = nullptr;
   cpx<T>* twz = nullptr;
+  int* posx = nullptr;      // LDS places of their bins
+  int* posy = nullptr;
+  int* posz = nullptr;
   cpx<T>* tw4x = nullptr;   // four-step tables [k1][t] = exp(-2 pi i t k1/L)
   cpx<T>* tw4y = nullptr;
   T* Bd = nullptr;          // output field [3][N]
@@ -143,8 +149,9 @@ class DemagMulti {
   Impl* impl = nullptr;
 };
 
+// tables of one axis: line_tw_elems(L) twiddles and L places
 template <typename T>
-void build_twiddles(cpx<T>* tw, int L, hipStream_t st);
+void build_line_tables(const LineFft& f, cpx<T>* tw, int* pos, hipStream_t st);
 template <typename T>
 void build_twiddles4(cpx<T>* tw, int L, hipStream_t st);
 int split_l2(int L);

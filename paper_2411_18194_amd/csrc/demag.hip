@@ -9,31 +9,58 @@
 //   z  fwd * K * inv  per (kx, ky) column, with the real octant kernel
 //   y  inverse  Py -> crop ny
 //   x  inverse  C2R (two rows per complex line), crop nx -> B_d
-// A 2-D grid (nz == 1) fuses y forward, multiply and y inverse in one pass.
+// The y, z and y passes are one pass where the lines of a kx column fit in
+// LDS (2-D grids always do).
 // Zero padding is never materialised in memory: the pads exist only in LDS.
 #include "demag.h"
 #include "demag4.h"
 
+#include <algorithm>
 #include <vector>
 
 namespace mmp {
 
-// ------------------------------------------------------------- twiddles --
+// largest blocks of the mixed-radix passes; the fused y-z pass holds the
+// 3 PZ values of a column per thread and needs their registers (at most 96
+// of 256 leave room for two waves per SIMD)
+constexpr int kLineThreads = 256;
+constexpr int yz_max_threads(int real_bytes, int pz) {
+  return 3 * pz * 2 * (real_bytes / 4) <= 96 ? 512 : 256;
+}
+// complex elements of one block of the batched passes
+constexpr long kMultiElems = 4096;
+
+// ----------------------------------------------------------------- tables --
+// Stage twiddles of a line transform and the places of its bins in LDS.
 template <typename T>
-__global__ void k_twiddles(cpx<T>* tw, int L) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= L) return;
-  double s, c;
-  sincospi(-2.0 * (double)j / (double)L, &s, &c);
-  tw[j] = cmk<T>((T)c, (T)s);
+__global__ void k_line_tables(LineFft f, cpx<T>* tw, int* pos) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= f.L) return;
+  for (int s = 0; s + 1 < f.n; ++s) {
+    const LineStage t = f.stage(s);
+    const int m = t.r * t.M;   // length of the sub-transform of this stage
+    if (i < m) {
+      const int q = i / t.M, lo = i - q * t.M;
+      double sn, cs;
+      sincospi(-2.0 * (double)(q * lo) / (double)m, &sn, &cs);
+      tw[t.tw + i] = cmk<T>((T)cs, (T)sn);
+    }
+  }
+  int e = 0, k = i;
+  for (int s = 0; s < f.n; ++s) {
+    const LineStage t = f.stage(s);
+    e += (k % t.r) * t.M;
+    k /= t.r;
+  }
+  pos[i] = e + (e / f.rl) * f.pad;
 }
 
 template <typename T>
-void build_twiddles(cpx<T>* tw, int L, hipStream_t st) {
-  hipLaunchKernelGGL(k_twiddles<T>, dim3((L + 255) / 256), dim3(256), 0, st, tw, L);
+void build_line_tables(const LineFft& f, cpx<T>* tw, int* pos, hipStream_t st) {
+  hipLaunchKernelGGL(k_line_tables<T>, dim3((f.L + 255) / 256), dim3(256), 0, st, f, tw, pos);
 }
-template void build_twiddles<float>(cpx<float>*, int, hipStream_t);
-template void build_twiddles<double>(cpx<double>*, int, hipStream_t);
+template void build_line_tables<float>(const LineFft&, cpx<float>*, int*, hipStream_t);
+template void build_line_tables<double>(const LineFft&, cpx<double>*, int*, hipStream_t);
 
 // --------------------------------------------------------------- x pass --
 template <typename T>
@@ -46,14 +73,17 @@ struct XArgs {
   cpx<T>* S1;
   T* Bd;
   const cpx<T>* tw;
-  int nx, ny, nz, Px, Hx, ldy, ty;
-  Rad rad;
+  const int* pos;
+  int nx, ny, nz, Hx, ldy, ty;
+  int lnl;    // log2(ty / 2)
+  int half;   // the line is at least twice its data (an open axis)
+  LineFft f;
 };
 
 // The pass bodies take the block's coordinates (and the stage) as
 // arguments: the single-grid kernels pass blockIdx, the batched kernels
 // the entry of their work table.
-template <typename T, bool P2, bool TWL>
+template <typename T>
 __device__ __forceinline__ void fftx_fwd_body(const XArgs<T>& a, int stage, int bx, int by,
                                               int bz) {
   using V = cpx<T>;
@@ -67,55 +97,44 @@ __device__ __forceinline__ void fftx_fwd_body(const XArgs<T>& a, int stage, int 
   const gcptr<T> m = (gcptr<T>)stage_in(a.tbl, stage);
   const gcptr<T> m0 = m + (long)c * N + (long)z * a.ny * a.nx;
   const gcptr<T> m1 = m0 + 3 * N;
-  for (int idx = tid; idx < nl * a.Px; idx += nthr) {
-    const int q = idx / a.Px, x = idx - q * a.Px;
+  // rows past ny and cells past nx: a clamped load, zeroed afterwards
+  auto ld = [&](int q, int x) -> V {
     const int ya = y0 + 2 * q, yb = ya + 1;
-    T re = 0, im = 0;
-    if (x < a.nx) {
-      if (ya < a.ny) {
-        re = a.ms0 * m0[(long)ya * a.nx + x];
-        if (a.nsub >= 2) re += a.ms1 * m1[(long)ya * a.nx + x];
-        if (a.nsub == 3) re += a.ms2 * m1[3 * N + (long)ya * a.nx + x];
-      }
-      if (yb < a.ny) {
-        im = a.ms0 * m0[(long)yb * a.nx + x];
-        if (a.nsub >= 2) im += a.ms1 * m1[(long)yb * a.nx + x];
-        if (a.nsub == 3) im += a.ms2 * m1[3 * N + (long)yb * a.nx + x];
-      }
+    const int xc = x < a.nx ? x : 0;
+    const int ia = (ya < a.ny ? ya : 0) * a.nx + xc, ib = (yb < a.ny ? yb : 0) * a.nx + xc;
+    T re = a.ms0 * m0[ia], im = a.ms0 * m0[ib];
+    if (a.nsub >= 2) {
+      re += a.ms1 * m1[ia];
+      im += a.ms1 * m1[ib];
     }
-    buf[q * a.Px + x] = cmk<T>(re, im);
-  }
-  const V* tw = a.tw;
-  if constexpr (TWL) {
-    // the twiddle table in LDS beside the lines: every stage reads it there
-    V* twl = buf + (nl * a.Px);
-    for (int i = tid; i < a.Px; i += nthr) twl[i] = a.tw[i];
-    tw = twl;
-  }
-  __syncthreads();
-  lds_fft<T, false, P2>(buf, tw, a.Px, nl, a.Px, a.rad.n, a.rad.code, tid, nthr);
+    if (a.nsub == 3) {
+      re += a.ms2 * m1[3 * N + ia];
+      im += a.ms2 * m1[3 * N + ib];
+    }
+    const bool in = x < a.nx;
+    return cmk<T>(in && ya < a.ny ? re : T(0), in && yb < a.ny ? im : T(0));
+  };
+  line_fft_fwd<T>(a.f, buf, a.tw, nl, a.half != 0, tid, nthr, ld);
   // unpack the two real spectra and store them transposed
   V* out = a.S1 + ((long)(c * a.nz + z) * a.Hx) * a.ldy + y0;
   for (int idx = tid; idx < nl * a.Hx; idx += nthr) {
-    const int q = idx % nl, kx = idx / nl;
-    const V zk = buf[q * a.Px + kx];
-    const int km = kx == 0 ? 0 : a.Px - kx;
-    const V zm = buf[q * a.Px + km];
+    const int q = idx & (nl - 1), kx = idx >> a.lnl;
+    const int km = kx == 0 ? 0 : a.f.L - kx;
+    const V* b = buf + q * a.f.pitch;
+    const V zk = b[a.pos[kx]], zm = b[a.pos[km]];
     const T h = T(0.5);
-    V xa = cmk<T>(h * (zk.x + zm.x), h * (zk.y - zm.y));
-    V xb = cmk<T>(h * (zk.y + zm.y), h * (zm.x - zk.x));
-    V* o = out + (long)kx * a.ldy + 2 * q;
-    o[0] = xa;
-    o[1] = xb;
+    store2<T>(out + (long)kx * a.ldy + 2 * q,
+              cmk<T>(h * (zk.x + zm.x), h * (zk.y - zm.y)),
+              cmk<T>(h * (zk.y + zm.y), h * (zm.x - zk.x)));
   }
 }
 
-template <typename T, bool P2, bool TWL>
-__global__ void k_fftx_fwd(XArgs<T> a) {
-  fftx_fwd_body<T, P2, TWL>(a, a.stage, blockIdx.x, blockIdx.y, blockIdx.z);
+template <typename T>
+__global__ __launch_bounds__(kLineThreads) void k_fftx_fwd(XArgs<T> a) {
+  fftx_fwd_body<T>(a, a.stage, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-template <typename T, bool P2, bool TWL>
+template <typename T>
 __device__ __forceinline__ void fftx_inv_body(const XArgs<T>& a, int bx, int by, int bz) {
   using V = cpx<T>;
   if (ctrl_stopped(a.ctrl)) return;
@@ -126,36 +145,31 @@ __device__ __forceinline__ void fftx_inv_body(const XArgs<T>& a, int bx, int by,
   const int nl = a.ty >> 1;
   const V* in = a.S1 + ((long)(c * a.nz + z) * a.Hx) * a.ldy + y0;
   for (int idx = tid; idx < nl * a.Hx; idx += nthr) {
-    const int q = idx % nl, kx = idx / nl;
-    const V* ip = in + (long)kx * a.ldy + 2 * q;
-    const V xa = ip[0], xb = ip[1];
-    buf[q * a.Px + kx] = cmk<T>(xa.x - xb.y, xa.y + xb.x);
-    if (kx > 0 && 2 * kx < a.Px)
-      buf[q * a.Px + a.Px - kx] = cmk<T>(xa.x + xb.y, xb.x - xa.y);
-  }
-  const V* tw = a.tw;
-  if constexpr (TWL) {
-    // the twiddle table in LDS beside the lines: every stage reads it there
-    V* twl = buf + (nl * a.Px);
-    for (int i = tid; i < a.Px; i += nthr) twl[i] = a.tw[i];
-    tw = twl;
+    const int q = idx & (nl - 1), kx = idx >> a.lnl;
+    V xa, xb;
+    load2<T>(in + (long)kx * a.ldy + 2 * q, xa, xb);
+    // past the last row S1 holds the forward pass's rounding of a zero row,
+    // unscaled by the kernel: left in, it would leak into the row before
+    if (y0 + 2 * q + 1 >= a.ny) xb = cmk<T>(T(0), T(0));
+    V* b = buf + q * a.f.pitch;
+    b[a.pos[kx]] = cmk<T>(xa.x - xb.y, xa.y + xb.x);
+    if (kx > 0 && 2 * kx < a.f.L) b[a.pos[a.f.L - kx]] = cmk<T>(xa.x + xb.y, xb.x - xa.y);
   }
   __syncthreads();
-  lds_fft<T, true, P2>(buf, tw, a.Px, nl, a.Px, a.rad.n, a.rad.code, tid, nthr);
   const long N = (long)a.nx * a.ny * a.nz;
   T* out = a.Bd + (long)c * N + (long)z * a.ny * a.nx;
-  for (int idx = tid; idx < nl * a.nx; idx += nthr) {
-    const int q = idx / a.nx, x = idx - q * a.nx;
+  line_fft_inv<T>(a.f, buf, a.tw, nl, a.half != 0, tid, nthr, [&](int q, int x, V v) {
     const int ya = y0 + 2 * q;
-    const V v = buf[q * a.Px + x];
-    if (ya < a.ny) out[(long)ya * a.nx + x] = v.x;
-    if (ya + 1 < a.ny) out[(long)(ya + 1) * a.nx + x] = v.y;
-  }
+    if (x < a.nx) {
+      if (ya < a.ny) out[ya * a.nx + x] = v.x;
+      if (ya + 1 < a.ny) out[(ya + 1) * a.nx + x] = v.y;
+    }
+  });
 }
 
-template <typename T, bool P2, bool TWL>
-__global__ void k_fftx_inv(XArgs<T> a) {
-  fftx_inv_body<T, P2, TWL>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+template <typename T>
+__global__ __launch_bounds__(kLineThreads) void k_fftx_inv(XArgs<T> a) {
+  fftx_inv_body<T>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // --------------------------------------------------------------- y pass --
@@ -165,145 +179,193 @@ struct YArgs {
   const cpx<T>* in;
   cpx<T>* out;
   const cpx<T>* tw;
-  int nlines, nvalid_in, ld_in, nvalid_out, ld_out, L, nl;
-  Rad rad;
+  const int* pos;
+  int nlines, nvalid_in, ld_in, nvalid_out, ld_out, nl;
+  int half;
+  FastDiv dL;
+  LineFft f;
 };
 
-template <typename T, bool INV, bool P2, bool TWL>
+template <typename T, bool INV>
 __device__ __forceinline__ void ffty_body(const YArgs<T>& a, int bx) {
   using V = cpx<T>;
   if (ctrl_stopped(a.ctrl)) return;
   extern __shared__ char smem_raw[];
   V* buf = reinterpret_cast<V*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
-  const int l0 = bx * a.nl;
-  for (int idx = tid; idx < a.nl * a.L; idx += nthr) {
-    const int q = idx / a.L, e = idx - q * a.L;
-    const int gl = l0 + q;
-    V v = cmk<T>(0, 0);
-    if (gl < a.nlines && e < a.nvalid_in) v = a.in[(long)gl * a.ld_in + e];
-    buf[q * a.L + e] = v;
-  }
-  const V* tw = a.tw;
-  if constexpr (TWL) {
-    // the twiddle table in LDS beside the lines: every stage reads it there
-    V* twl = buf + (a.nl * a.L);
-    for (int i = tid; i < a.L; i += nthr) twl[i] = a.tw[i];
-    tw = twl;
-  }
-  __syncthreads();
-  lds_fft<T, INV, P2>(buf, tw, a.L, a.nl, a.L, a.rad.n, a.rad.code, tid, nthr);
-  for (int idx = tid; idx < a.nl * a.nvalid_out; idx += nthr) {
-    const int q = idx / a.nvalid_out, e = idx - q * a.nvalid_out;
-    const int gl = l0 + q;
-    if (gl < a.nlines) a.out[(long)gl * a.ld_out + e] = buf[q * a.L + e];
+  const int l0 = bx * a.nl, L = a.f.L;
+  if constexpr (!INV) {
+    line_fft_fwd<T>(a.f, buf, a.tw, a.nl, a.half != 0, tid, nthr, [&](int l, int n) -> V {
+      const bool in = l0 + l < a.nlines && n < a.nvalid_in;
+      const V v = a.in[in ? (long)(l0 + l) * a.ld_in + n : 0];
+      return in ? v : cmk<T>(T(0), T(0));
+    });
+    for (int idx = tid; idx < a.nl * L; idx += nthr) {
+      const int l = a.dL.div(idx), k = idx - l * L;
+      if (l0 + l < a.nlines) a.out[(long)(l0 + l) * a.ld_out + k] = buf[l * a.f.pitch + a.pos[k]];
+    }
+  } else {
+    for (int idx = tid; idx < a.nl * L; idx += nthr) {
+      const int l = a.dL.div(idx), k = idx - l * L;
+      const bool in = l0 + l < a.nlines;
+      const V v = a.in[in ? (long)(l0 + l) * a.ld_in + k : 0];
+      buf[l * a.f.pitch + a.pos[k]] = v;
+    }
+    __syncthreads();
+    line_fft_inv<T>(a.f, buf, a.tw, a.nl, a.half != 0, tid, nthr, [&](int l, int n, V v) {
+      if (l0 + l < a.nlines && n < a.nvalid_out) a.out[(long)(l0 + l) * a.ld_out + n] = v;
+    });
   }
 }
 
-template <typename T, bool INV, bool P2, bool TWL>
-__global__ void k_ffty(YArgs<T> a) {
-  ffty_body<T, INV, P2, TWL>(a, blockIdx.x);
+template <typename T, bool INV>
+__global__ __launch_bounds__(kLineThreads) void k_ffty(YArgs<T> a) {
+  ffty_body<T, INV>(a, blockIdx.x);
 }
 
-// Symmetric 3x3 multiply with the octant kernel; sy/sz flip the odd parts.
+// Symmetric 3x3 multiply with the octant kernel; sy/sz flip the odd parts
+// (kxz = kyz = 0 on a 2-D grid).
 template <typename T>
-__device__ __forceinline__ void kmul(cpx<T>& mx, cpx<T>& my, cpx<T>& mz, const T* __restrict__ K,
-                                     long kidx, long kstride, T sy, T sz, bool three_d) {
-  const T kxx = K[kidx], kyy = K[kidx + kstride], kzz = K[kidx + 2 * kstride];
-  const T kxy = sy * K[kidx + 3 * kstride];
-  T kxz = 0, kyz = 0;
-  if (three_d) {
-    kxz = sz * K[kidx + 4 * kstride];
-    kyz = sy * sz * K[kidx + 5 * kstride];
-  }
-  const cpx<T> bx = cmk<T>(kxx * mx.x + kxy * my.x + kxz * mz.x, kxx * mx.y + kxy * my.y + kxz * mz.y);
-  const cpx<T> by = cmk<T>(kxy * mx.x + kyy * my.x + kyz * mz.x, kxy * mx.y + kyy * my.y + kyz * mz.y);
-  const cpx<T> bz = cmk<T>(kxz * mx.x + kyz * my.x + kzz * mz.x, kxz * mx.y + kyz * my.y + kzz * mz.y);
-  mx = bx;
-  my = by;
-  mz = bz;
+__device__ __forceinline__ void sym3(cpx<T>& mx, cpx<T>& my, cpx<T>& mz, T kxx, T kyy, T kzz,
+                                     T kxy, T kxz, T kyz) {
+  const cpx<T> x = mx, y = my, z = mz;
+  mx = cmk<T>(kxx * x.x + kxy * y.x + kxz * z.x, kxx * x.y + kxy * y.y + kxz * z.y);
+  my = cmk<T>(kxy * x.x + kyy * y.x + kyz * z.x, kxy * x.y + kyy * y.y + kyz * z.y);
+  mz = cmk<T>(kxz * x.x + kyz * y.x + kzz * z.x, kxz * x.y + kyz * y.y + kzz * z.y);
 }
 
-// 2-D grids: y forward, multiply, y inverse for nk kx columns x 3 components.
+// ------------------------------------------- fused y, z and multiply pass --
+// One block carries nk kx columns of all 3 nz (component, layer) lines in
+// LDS: y forward, then each ky column's z transform, kernel product and
+// inverse z transform in the registers of one thread, then y inverse, in
+// place in S1.  On a 2-D grid the column is the three components alone.
+// Against separate y, z and y passes the padded spectrum never reaches
+// memory (S2 is 2 (Py/ny) times S1, written twice and read twice) and two
+// launches go.  Measured: 183x77x5 FP32 86.1 us in three passes -> 11.4 us;
+// 64x64x4 FP32 15.1 (register kernels) -> 9.8 us; 333x130x1 FP64 57.1 ->
+// 11.8 us.  One kx column per block: few grids have more than a few hundred.
 template <typename T>
-struct M2Args {
+struct YzArgs {
   const Ctrl* ctrl;
-  cpx<T>* S1;     // [3][1][Hx][ldy]
-  const T* K;     // [6][1][Hx][Hy]
+  cpx<T>* S1;     // [3][nz][Hx][ldy]
+  const T* K;     // [6][Hz][Hx][Hy]
   const cpx<T>* tw;
-  int ny, Py, Hx, Hy, ldy, nk;
-  Rad rad;
+  const int* pos;
+  int ny, nz, Pz, Hx, Hy, Hz, ldy, nk, lnk;
+  int half;
+  FastDiv dL;
+  LineFft f;
 };
 
-template <typename T, bool P2, bool TWL>
-__device__ __forceinline__ void ffty_mul2d_body(const M2Args<T>& a, int bx) {
+template <typename T, int PZ>
+__device__ __forceinline__ void yz_columns(const YzArgs<T>& a, cpx<T>* buf, int kx0, int tid,
+                                           int nthr) {
+  using V = cpx<T>;
+  const int L = a.f.L;
+  const int zl = a.nk * a.f.pitch, cl = a.nz * zl;   // LDS strides of layer, component
+  const long ks = (long)a.Hz * a.Hx * a.Hy, kzs = (long)a.Hx * a.Hy;
+  for (int idx = tid; idx < a.nk * L; idx += nthr) {
+    const int j = a.dL.div(idx), ky = idx - j * L;
+    const int kx = kx0 + j;
+    if (kx >= a.Hx) continue;
+    const bool mir = ky > L / 2;
+    const int kyo = mir ? L - ky : ky;
+    const T sy = mir ? T(-1) : T(1);
+    const T* K = a.K + (long)kx * a.Hy + kyo;
+    V* col = buf + j * a.f.pitch + a.pos[ky];
+    if constexpr (PZ == 1) {
+      V mx = col[0], my = col[cl], mz = col[2 * cl];
+      sym3<T>(mx, my, mz, K[0], K[ks], K[2 * ks], sy * K[3 * ks], T(0), T(0));
+      col[0] = mx;
+      col[cl] = my;
+      col[2 * cl] = mz;
+    } else {
+      V v[3][PZ];
+#pragma unroll
+      for (int z = 0; z < PZ / 2; ++z) {
+        const bool in = z < a.nz;
+        const int o = in ? z * zl : 0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          const V x = col[c * cl + o];
+          v[c][z] = in ? x : cmk<T>(T(0), T(0));
+        }
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) dft_hz<T, PZ>(v[c]);
+      // plane kz and its mirror PZ - kz share their kernel values, the
+      // components odd along z with opposite signs
+#pragma unroll
+      for (int kz = 0; kz <= PZ / 2; ++kz) {
+        const T* q = K + kz * kzs;
+        const T kxx = q[0], kyy = q[ks], kzz = q[2 * ks];
+        const T kxy = sy * q[3 * ks], kxz = q[4 * ks], kyz = sy * q[5 * ks];
+        sym3<T>(v[0][kz], v[1][kz], v[2][kz], kxx, kyy, kzz, kxy, kxz, kyz);
+        if (kz > 0 && 2 * kz < PZ)
+          sym3<T>(v[0][PZ - kz], v[1][PZ - kz], v[2][PZ - kz], kxx, kyy, kzz, kxy, -kxz, -kyz);
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        dft<T, PZ, true>(v[c]);
+#pragma unroll
+        for (int z = 0; z < PZ / 2; ++z)
+          if (z < a.nz) col[c * cl + z * zl] = v[c][z];
+      }
+    }
+  }
+}
+
+// z lengths the fused pass is built for (every pad up to 16 of a grid of
+// up to 8 layers; longer columns would not fit a thread's registers beside
+// enough waves)
+#define MMP_YZ_SMALL(X) X(1) X(4) X(6) X(8)
+#define MMP_YZ_LARGE(X) X(10) X(12) X(14) X(16)
+
+template <typename T, typename COL>
+__device__ __forceinline__ void yz_body(const YzArgs<T>& a, int bx, COL&& columns) {
   using V = cpx<T>;
   if (ctrl_stopped(a.ctrl)) return;
   extern __shared__ char smem_raw[];
   V* buf = reinterpret_cast<V*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int kx0 = bx * a.nk;
-  const int L = a.Py;
-  const int nl = 3 * a.nk;
-  for (int idx = tid; idx < nl * L; idx += nthr) {
-    const int line = idx / L, e = idx - line * L;
-    const int c = line / a.nk, j = line - c * a.nk;
-    const int kx = kx0 + j;
-    V v = cmk<T>(0, 0);
-    if (kx < a.Hx && e < a.ny) v = a.S1[((long)c * a.Hx + kx) * a.ldy + e];
-    buf[line * L + e] = v;
-  }
-  const V* tw = a.tw;
-  if constexpr (TWL) {
-    // the twiddle table in LDS beside the lines: every stage reads it there
-    V* twl = buf + (nl * L);
-    for (int i = tid; i < L; i += nthr) twl[i] = a.tw[i];
-    tw = twl;
-  }
+  const int lines = 3 * a.nz * a.nk;
+  line_fft_fwd<T>(a.f, buf, a.tw, lines, a.half != 0, tid, nthr, [&](int l, int n) -> V {
+    const int kx = kx0 + (l & (a.nk - 1));
+    const bool in = kx < a.Hx && n < a.ny;
+    const V v = a.S1[in ? ((long)(l >> a.lnk) * a.Hx + kx) * a.ldy + n : 0];
+    return in ? v : cmk<T>(T(0), T(0));
+  });
+  columns(buf, kx0, tid, nthr);
   __syncthreads();
-  lds_fft<T, false, P2>(buf, tw, L, nl, L, a.rad.n, a.rad.code, tid, nthr);
-  const long kstride = (long)a.Hx * a.Hy;
-  for (int idx = tid; idx < a.nk * L; idx += nthr) {
-    const int j = idx / L, ky = idx - j * L;
-    const int kx = kx0 + j;
-    if (kx >= a.Hx) continue;
-    const int kyo = ky <= L / 2 ? ky : L - ky;
-    const T sy = ky <= L / 2 ? T(1) : T(-1);
-    V mx = buf[(0 * a.nk + j) * L + ky];
-    V my = buf[(1 * a.nk + j) * L + ky];
-    V mz = buf[(2 * a.nk + j) * L + ky];
-    kmul<T>(mx, my, mz, a.K, (long)kx * a.Hy + kyo, kstride, sy, T(1), false);
-    buf[(0 * a.nk + j) * L + ky] = mx;
-    buf[(1 * a.nk + j) * L + ky] = my;
-    buf[(2 * a.nk + j) * L + ky] = mz;
-  }
-  __syncthreads();
-  lds_fft<T, true, P2>(buf, tw, L, nl, L, a.rad.n, a.rad.code, tid, nthr);
-  for (int idx = tid; idx < nl * a.ny; idx += nthr) {
-    const int line = idx / a.ny, e = idx - line * a.ny;
-    const int c = line / a.nk, j = line - c * a.nk;
-    const int kx = kx0 + j;
-    if (kx < a.Hx) a.S1[((long)c * a.Hx + kx) * a.ldy + e] = buf[line * L + e];
-  }
+  line_fft_inv<T>(a.f, buf, a.tw, lines, a.half != 0, tid, nthr, [&](int l, int n, V v) {
+    const int kx = kx0 + (l & (a.nk - 1));
+    if (kx < a.Hx && n < a.ny) a.S1[((long)(l >> a.lnk) * a.Hx + kx) * a.ldy + n] = v;
+  });
 }
 
-template <typename T, bool P2, bool TWL>
-__global__ void k_ffty_mul2d(M2Args<T> a) {
-  ffty_mul2d_body<T, P2, TWL>(a, blockIdx.x);
+template <typename T, int PZ>
+__global__ __launch_bounds__(yz_max_threads((int)sizeof(T), PZ)) void k_yz(YzArgs<T> a) {
+  yz_body<T>(a, blockIdx.x, [&](cpx<T>* buf, int kx0, int tid, int nthr) {
+    yz_columns<T, PZ>(a, buf, kx0, tid, nthr);
+  });
 }
 
-// 3-D grids: z forward, multiply, z inverse for tk ky values of one kx.
+// ---------------------------------------------------------------- z pass --
+// 3-D grids whose lines do not fit the fused pass: z forward, multiply, z
+// inverse for tk ky values of one kx, lines in LDS.
 template <typename T>
 struct ZArgs {
   const Ctrl* ctrl;
   cpx<T>* S2;     // [3][nz][Hx][Py]
   const T* K;     // [6][Hz][Hx][Hy]
   const cpx<T>* tw;
-  int nz, Pz, Hx, Py, Hy, Hz, tk, ls;
-  Rad rad;
+  const int* pos;
+  int nz, Hx, Py, Hy, Hz, tk, ltk;
+  LineFft f;
 };
 
-template <typename T, bool P2, bool TWL>
+template <typename T>
 __device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int bx, int by) {
   using V = cpx<T>;
   if (ctrl_stopped(a.ctrl)) return;
@@ -311,59 +373,53 @@ __device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int bx, int by)
   V* buf = reinterpret_cast<V*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int kx = by, ky0 = bx * a.tk;
-  const int L = a.Pz;
-  const int nl = 3 * a.tk;
+  const int L = a.f.L, pitch = a.f.pitch, tk = a.tk;
   const long zstride = (long)a.Hx * a.Py;
   const long cstride = (long)a.nz * zstride;
-  const V* base = a.S2 + (long)kx * a.Py + ky0;
-  for (int idx = tid; idx < nl * L; idx += nthr) {
-    const int j = idx % a.tk;
-    const int r = idx / a.tk;
-    const int z = r % L, c = r / L;
-    V v = cmk<T>(0, 0);
-    if (z < a.nz && ky0 + j < a.Py) v = base[c * cstride + z * zstride + j];
-    buf[(c * a.tk + j) * a.ls + z] = v;
-  }
-  const V* tw = a.tw;
-  if constexpr (TWL) {
-    // the twiddle table in LDS beside the lines: every stage reads it there
-    V* twl = buf + (nl * a.ls);
-    for (int i = tid; i < L; i += nthr) twl[i] = a.tw[i];
-    tw = twl;
-  }
+  V* base = a.S2 + (long)kx * a.Py + ky0;
+  // planes in natural order, columns fastest (coalesced along ky)
+  for (int c = 0; c < 3; ++c)
+    for (int idx = tid; idx < tk * L; idx += nthr) {
+      const int j = idx & (tk - 1), z = idx >> a.ltk;
+      const bool in = z < a.nz && ky0 + j < a.Py;
+      const V v = base[in ? c * cstride + z * zstride + j : 0];
+      buf[(c * tk + j) * pitch + z + a.f.drl.div(z) * a.f.pad] = in ? v : cmk<T>(T(0), T(0));
+    }
   __syncthreads();
-  lds_fft<T, false, P2>(buf, tw, L, nl, a.ls, a.rad.n, a.rad.code, tid, nthr);
-  const long kstride = (long)a.Hz * a.Hx * a.Hy;
-  for (int idx = tid; idx < a.tk * L; idx += nthr) {
-    const int j = idx % a.tk, kz = idx / a.tk;
+  line_fft_fwd_lds<T>(a.f, buf, a.tw, 3 * tk, tid, nthr);
+  const long ks = (long)a.Hz * a.Hx * a.Hy;
+  for (int idx = tid; idx < tk * L; idx += nthr) {
+    const int j = idx & (tk - 1), kz = idx >> a.ltk;
     const int ky = ky0 + j;
     if (ky >= a.Py) continue;
     const int kyo = ky <= a.Py / 2 ? ky : a.Py - ky;
     const T sy = ky <= a.Py / 2 ? T(1) : T(-1);
     const int kzo = kz <= L / 2 ? kz : L - kz;
     const T sz = kz <= L / 2 ? T(1) : T(-1);
-    V mx = buf[(0 * a.tk + j) * a.ls + kz];
-    V my = buf[(1 * a.tk + j) * a.ls + kz];
-    V mz = buf[(2 * a.tk + j) * a.ls + kz];
-    kmul<T>(mx, my, mz, a.K, ((long)kzo * a.Hx + kx) * a.Hy + kyo, kstride, sy, sz, true);
-    buf[(0 * a.tk + j) * a.ls + kz] = mx;
-    buf[(1 * a.tk + j) * a.ls + kz] = my;
-    buf[(2 * a.tk + j) * a.ls + kz] = mz;
+    V* p = buf + j * pitch + a.pos[kz];
+    const int cl = tk * pitch;
+    const T* K = a.K + ((long)kzo * a.Hx + kx) * a.Hy + kyo;
+    V mx = p[0], my = p[cl], mz = p[2 * cl];
+    sym3<T>(mx, my, mz, K[0], K[ks], K[2 * ks], sy * K[3 * ks], sz * K[4 * ks],
+            sy * sz * K[5 * ks]);
+    p[0] = mx;
+    p[cl] = my;
+    p[2 * cl] = mz;
   }
   __syncthreads();
-  lds_fft<T, true, P2>(buf, tw, L, nl, a.ls, a.rad.n, a.rad.code, tid, nthr);
-  V* obase = a.S2 + (long)kx * a.Py + ky0;
-  for (int idx = tid; idx < 3 * a.tk * a.nz; idx += nthr) {
-    const int j = idx % a.tk;
-    const int r = idx / a.tk;
-    const int z = r % a.nz, c = r / a.nz;
-    if (ky0 + j < a.Py) obase[c * cstride + z * zstride + j] = buf[(c * a.tk + j) * a.ls + z];
-  }
+  line_fft_inv_lds<T>(a.f, buf, a.tw, 3 * tk, tid, nthr);
+  for (int c = 0; c < 3; ++c)
+    for (int idx = tid; idx < tk * a.nz; idx += nthr) {
+      const int j = idx & (tk - 1), z = idx >> a.ltk;
+      if (ky0 + j < a.Py)
+        base[c * cstride + z * zstride + j] =
+            buf[(c * tk + j) * pitch + z + a.f.drl.div(z) * a.f.pad];
+    }
 }
 
-template <typename T, bool P2, bool TWL>
-__global__ void k_fftz_mul(ZArgs<T> a) {
-  fftz_mul_body<T, P2, TWL>(a, blockIdx.x, blockIdx.y);
+template <typename T>
+__global__ __launch_bounds__(kLineThreads) void k_fftz_mul(ZArgs<T> a) {
+  fftz_mul_body<T>(a, blockIdx.x, blockIdx.y);
 }
 
 // --------------------------------------------------------- batched passes --
@@ -377,51 +433,77 @@ template <typename T>
 __global__ __launch_bounds__(kMultiThreads) void k_fftx_fwd_multi(
     const XArgs<T>* __restrict__ args, const int4* __restrict__ work, int stage) {
   const int4 w = work[blockIdx.x];
-  fftx_fwd_body<T, false, true>(args[w.x], stage, w.y, w.z, w.w);
+  fftx_fwd_body<T>(args[w.x], stage, w.y, w.z, w.w);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kMultiThreads) void k_fftx_inv_multi(
     const XArgs<T>* __restrict__ args, const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
-  fftx_inv_body<T, false, true>(args[w.x], w.y, w.z, w.w);
+  fftx_inv_body<T>(args[w.x], w.y, w.z, w.w);
 }
 
 template <typename T, bool INV>
 __global__ __launch_bounds__(kMultiThreads) void k_ffty_multi(const YArgs<T>* __restrict__ args,
                                                               const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
-  ffty_body<T, INV, false, true>(args[w.x], w.y);
+  ffty_body<T, INV>(args[w.x], w.y);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kMultiThreads) void k_fftz_mul_multi(
     const ZArgs<T>* __restrict__ args, const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
-  fftz_mul_body<T, false, true>(args[w.x], w.y, w.z);
+  fftz_mul_body<T>(args[w.x], w.y, w.z);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kMultiThreads) void k_ffty_mul2d_multi(
-    const M2Args<T>* __restrict__ args, const int4* __restrict__ work) {
+// LARGE: the members with z pads of 10..16 (one launch for them and one for
+// the others, so that the short columns do not hold the long ones' registers)
+template <typename T, bool LARGE>
+__global__ __launch_bounds__(kMultiThreads) void k_yz_multi(const YzArgs<T>* __restrict__ args,
+                                                            const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
-  ffty_mul2d_body<T, false, true>(args[w.x], w.y);
+  const YzArgs<T>& a = args[w.x];
+  yz_body<T>(a, w.y, [&](cpx<T>* buf, int kx0, int tid, int nthr) {
+#define X(P) case P: yz_columns<T, P>(a, buf, kx0, tid, nthr); break;
+    if constexpr (LARGE) {
+      switch (a.Pz) { MMP_YZ_LARGE(X) }
+    } else {
+      switch (a.Pz) { MMP_YZ_SMALL(X) }
+    }
+#undef X
+  });
 }
 
 // ------------------------------------------------------------------ plan --
 constexpr long kMixedTarget = 2048;
-constexpr size_t kLdsMax = 65536;   // dynamic LDS of one block
+constexpr size_t kLdsMax = 65536;   // dynamic LDS of one block of the register z pass
 
+// complex elements one block may hold in LDS (64 KiB before row padding)
+static long lds_cap(int real_bytes) { return 65536 / (2 * real_bytes); }
 
-static int threads_for(long elems) {
-  long t = (elems + kMaxE - 1) / kMaxE;
-  t = (t + 63) / 64 * 64;
-  if (t < 64) t = 64;
-  return (int)t;
+// threads of a block of `lines` mixed-radix line transforms: one butterfly
+// of the longest stage each, at most `most`
+static int line_threads(const LineFft& f, long lines, int most) {
+  int nb = 1;
+  for (const LineStage* t : {&f.s0, &f.s1, &f.s2, &f.s3})
+    if (t->nb > nb) nb = t->nb;
+  const long t = (lines * nb + 63) / 64 * 64;
+  return (int)std::min<long>(t, most);
 }
 
-// complex elements one block may hold in LDS (64 KiB)
-static long lds_cap(int real_bytes) { return 65536 / (2 * real_bytes); }
+// The fused y-z pass takes a 3-D grid when its z length is one it is built
+// for and the 3 nz lines of a kx column fit the LDS of a block (128 of the
+// 160 KiB of a CU; a block that size still moves a quarter of what the
+// separate passes move through memory).
+static constexpr long kYzLds = 131072;
+static bool yz_fits(int nz, int Pz, const LineFft& fy, int real_bytes) {
+  bool built = false;
+#define X(P) built = built || (P > 1 && Pz == P);
+  MMP_YZ_SMALL(X) MMP_YZ_LARGE(X)
+#undef X
+  return nz > 1 && built && 3L * nz * fy.pitch * 2 * real_bytes <= kYzLds;
+}
 
 // An open axis is zero-padded to P >= 2n - 1; a periodic one is cyclic
 // with P = n.  P is 1 or even and 7-smooth, at most 4096.
@@ -429,22 +511,22 @@ static bool pad_ok(int n, int P, bool periodic = false) {
   if (n == 1) return P == 1;
   if (periodic ? P != n : P < 2 * n - 1) return false;
   if ((P & 1) || P > 4096) return false;
-  int r[16];
-  const int nr = fft_radices(P, r);
-  return nr >= 0 && nr <= 15;
+  int r[kMaxStages];
+  return line_radices(P, r) > 0;
 }
 
-// threads and LDS bytes of each pass for the plan's shapes
+// threads of each pass for the plan's shapes
 static int x_threads(const DemagPlan& p, int ty) {
-  return p.p2x ? (ty / 2) * split_l2(p.Px) : threads_for((long)(ty / 2) * p.Px);
+  return p.p2x ? (ty / 2) * split_l2(p.Px) : line_threads(p.fx, ty / 2, kLineThreads);
 }
 static int y_threads(const DemagPlan& p, int nl) {
-  return p.p2y ? nl * split_l2(p.Py) : threads_for((long)nl * p.Py);
+  return p.p2y ? nl * split_l2(p.Py) : line_threads(p.fy, nl, kLineThreads);
 }
-static int m2_threads(const DemagPlan& p) {
-  return p.p2y ? 3 * p.nk * split_l2(p.Py) : threads_for((long)3 * p.nk * p.Py);
+static int m2_threads(const DemagPlan& p, int real_bytes) {
+  return p.p2y ? 3 * p.nk * split_l2(p.Py)
+               : line_threads(p.fy, 3L * p.nk, yz_max_threads(real_bytes, 1));
 }
-static int z_threads(const DemagPlan& p) { return threads_for((long)3 * p.tk * p.Pz); }
+static int z_threads(const DemagPlan& p) { return line_threads(p.fz, 3L * p.tk, kLineThreads); }
 
 static bool pow2_in(int v, int lo, int hi) { return v >= lo && v <= hi && is_pow2(v); }
 
@@ -452,15 +534,15 @@ int demag_plan_check(const DemagPlan& p, int real_bytes) {
   const long cap = lds_cap(real_bytes);
   for (int ty : {p.tyf, p.tyi}) {
     if (!pow2_in(ty, 2, 16) || (long)(ty / 2) * p.Px > cap) return -1;
-    if (x_threads(p, ty) > (p.p2x ? 256 : 1024)) return -1;
+    if (p.p2x && x_threads(p, ty) > 256) return -1;
   }
   if (p.nz == 1) {
     if (!pow2_in(p.nk, 1, 64) || (long)3 * p.nk * p.Py > cap) return -1;
-    if (m2_threads(p) > (p.p2y ? 256 : 1024)) return -1;
+    if (p.p2y && m2_threads(p, real_bytes) > 256) return -1;
   } else {
     for (int nl : {p.nlyf, p.nlyi}) {
       if (!pow2_in(nl, 1, 64) || (long)nl * p.Py > cap) return -1;
-      if (y_threads(p, nl) > (p.p2y ? 256 : 1024)) return -1;
+      if (p.p2y && y_threads(p, nl) > 256) return -1;
     }
     if (p.p2z) {
       if (!zreg_waves_ok(real_bytes, p.Pz, p.zq, p.zw)) return -1;
@@ -471,7 +553,6 @@ int demag_plan_check(const DemagPlan& p, int real_bytes) {
         return -1;
     } else {
       if (!pow2_in(p.tk, 1, 64) || (long)3 * p.tk * (p.Pz + 1) > cap) return -1;
-      if (z_threads(p) > 1024) return -1;
     }
   }
   return 0;
@@ -495,10 +576,8 @@ int demag_plan(int nx, int ny, int nz, int real_bytes, const int* pads, DemagPla
     if (!pad_ok(nx, d.Px, px) || !pad_ok(ny, d.Py, py) || !pad_ok(nz, d.Pz)) return -1;
   }
   d.Hx = d.Px / 2 + 1; d.Hy = d.Py / 2 + 1; d.Hz = d.Pz / 2 + 1;
-  int rr[3][16];
-  d.rx = make_rad(rr[0], fft_radices(d.Px, rr[0]));
-  d.ry = make_rad(rr[1], fft_radices(d.Py, rr[1]));
-  d.rz = make_rad(rr[2], fft_radices(d.Pz, rr[2]));
+  if (!make_line_fft(d.Px, &d.fx) || !make_line_fft(d.Py, &d.fy) || !make_line_fft(d.Pz, &d.fz))
+    return -1;
   // power-of-two axes: register four-step kernels (FP64 lines up to 2048
   // points); the register z pass spreads a column over zq lanes
   const int lmax = real_bytes == 8 ? 2048 : 4096;
@@ -516,7 +595,7 @@ int demag_plan(int nx, int ny, int nz, int real_bytes, const int* pads, DemagPla
   int ty = 2;
   const long xcap = d.p2x ? cap : mcap;
   while (ty < 16 && (long)ty * d.Px <= xcap && ty < ny + (ny & 1)) ty *= 2;
-  while (ty > 2 && ((long)(ty / 2) * d.Px > cap || x_threads(d, ty) > (d.p2x ? 256 : 1024)))
+  while (ty > 2 && ((long)(ty / 2) * d.Px > cap || (d.p2x && x_threads(d, ty) > 256)))
     ty /= 2;
   d.tyf = d.tyi = ty;
   // y passes: lines per block
@@ -565,7 +644,8 @@ int demag_plan(int nx, int ny, int nz, int real_bytes, const int* pads, DemagPla
     if (d.p2z && !zreg_ok(real_bytes, d.Pz, d.zq)) d.p2z = false;
   }
   d.s1_elems = (size_t)3 * nz * d.Hx * d.ldy;
-  d.s2_elems = nz > 1 ? (size_t)3 * nz * d.Hx * d.Py : 0;
+  d.fuse = yz_fits(nz, d.Pz, d.fy, real_bytes);
+  d.s2_elems = nz > 1 && !d.fuse ? (size_t)3 * nz * d.Hx * d.Py : 0;
   d.k_elems = (size_t)6 * d.Hz * d.Hx * d.Hy;
   if (demag_plan_check(d, real_bytes) != 0) return -1;
   *p = d;
@@ -573,6 +653,44 @@ int demag_plan(int nx, int ny, int nz, int real_bytes, const int* pads, DemagPla
 }
 
 // --------------------------------------------------------------- passes --
+static int log2i(int v) {
+  int l = 0;
+  while ((1 << l) < v) ++l;
+  return l;
+}
+
+// argument blocks of the mixed-radix passes
+template <typename T>
+static XArgs<T> x_args(const DemagPlan& p, const DemagBufs<T>& b, const Table<T>* tbl, int stage,
+                       const Ctrl* ctrl, T ms0, T ms1, T ms2, int nsub, int ty) {
+  XArgs<T> a{};
+  a.tbl = tbl; a.ctrl = ctrl; a.stage = stage;
+  a.ms0 = ms0; a.ms1 = ms1; a.ms2 = ms2; a.nsub = nsub;
+  a.S1 = b.S1; a.Bd = b.Bd; a.tw = b.twx; a.pos = b.posx;
+  a.nx = p.nx; a.ny = p.ny; a.nz = p.nz; a.Hx = p.Hx; a.ldy = p.ldy;
+  a.ty = ty; a.lnl = log2i(ty / 2); a.half = p.rep[0] > 0 || p.Px == 1 ? 0 : 1; a.f = p.fx;
+  return a;
+}
+
+template <typename T>
+static YzArgs<T> yz_args(const DemagPlan& p, const DemagBufs<T>& b, const Ctrl* ctrl, int nk) {
+  YzArgs<T> a{};
+  a.ctrl = ctrl; a.S1 = b.S1; a.K = b.K; a.tw = b.twy; a.pos = b.posy;
+  a.ny = p.ny; a.nz = p.nz; a.Pz = p.Pz; a.Hx = p.Hx; a.Hy = p.Hy; a.Hz = p.Hz; a.ldy = p.ldy;
+  a.nk = nk; a.lnk = log2i(nk); a.half = p.rep[1] > 0 || p.Py == 1 ? 0 : 1;
+  a.dL = make_div(p.Py); a.f = p.fy;
+  return a;
+}
+
+template <typename T>
+static ZArgs<T> z_args(const DemagPlan& p, const DemagBufs<T>& b, const Ctrl* ctrl, int tk) {
+  ZArgs<T> a{};
+  a.ctrl = ctrl; a.S2 = b.S2; a.K = b.K; a.tw = b.twz; a.pos = b.posz;
+  a.nz = p.nz; a.Hx = p.Hx; a.Py = p.Py; a.Hy = p.Hy; a.Hz = p.Hz;
+  a.tk = tk; a.ltk = log2i(tk); a.f = p.fz;
+  return a;
+}
+
 template <typename T>
 void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table<T>* tbl,
                 int stage, const Ctrl* ctrl, T ms0, T ms1, int nsub, hipStream_t st, T ms2) {
@@ -583,7 +701,6 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
       const bool inv = pass == DP_XI;
       const int ty = inv ? p.tyi : p.tyf;
       const dim3 g((p.ny + ty - 1) / ty, p.nz, 3);
-      const size_t lds = (size_t)(ty / 2) * p.Px * sizeof(V);
       if (p.p2x) {
         const size_t lds4 = x4_lds_bytes(p.Px, ty / 2, inv, (int)sizeof(V));
         X4Args<T> a;
@@ -595,21 +712,11 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
         while ((2 << a.lnl) < ty) ++a.lnl;
         launch_x4<T>(p.Px, inv, p.rep[0] > 0, g, x_threads(p, ty), lds4, st, a);
       } else {
-        XArgs<T> a;
-        a.tbl = tbl; a.ctrl = ctrl; a.stage = stage; a.ms0 = ms0; a.ms1 = ms1; a.nsub = nsub;
-        a.ms2 = ms2;
-        a.S1 = b.S1; a.Bd = b.Bd; a.tw = b.twx;
-        a.nx = p.nx; a.ny = p.ny; a.nz = p.nz; a.Px = p.Px; a.Hx = p.Hx; a.ldy = p.ldy;
-        a.ty = ty; a.rad = p.rx;
+        const XArgs<T> a = x_args<T>(p, b, tbl, stage, ctrl, ms0, ms1, ms2, nsub, ty);
         const dim3 blk(x_threads(p, ty));
-        const size_t ldt = lds + (size_t)p.Px * sizeof(V);   // with the twiddle table
-        if (ldt <= kLdsMax) {
-          if (inv) hipLaunchKernelGGL((k_fftx_inv<T, false, true>), g, blk, ldt, st, a);
-          else hipLaunchKernelGGL((k_fftx_fwd<T, false, true>), g, blk, ldt, st, a);
-        } else {
-          if (inv) hipLaunchKernelGGL((k_fftx_inv<T, false, false>), g, blk, lds, st, a);
-          else hipLaunchKernelGGL((k_fftx_fwd<T, false, false>), g, blk, lds, st, a);
-        }
+        const size_t lds = (size_t)(ty / 2) * p.fx.pitch * sizeof(V);
+        if (inv) hipLaunchKernelGGL((k_fftx_inv<T>), g, blk, lds, st, a);
+        else hipLaunchKernelGGL((k_fftx_fwd<T>), g, blk, lds, st, a);
       }
       break;
     }
@@ -620,17 +727,23 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
         M4Args<T> a;
         a.ctrl = ctrl; a.S1 = b.S1; a.K = b.K; a.tw4 = b.tw4y;
         a.ny = p.ny; a.Hx = p.Hx; a.Hy = p.Hy; a.ldy = p.ldy; a.nk = p.nk;
-        launch_m4<T>(p.Py, p.rep[1] > 0, g, m2_threads(p), lds, st, a);
+        launch_m4<T>(p.Py, p.rep[1] > 0, g, m2_threads(p, (int)sizeof(T)), lds, st, a);
       } else {
-        M2Args<T> a;
-        a.ctrl = ctrl; a.S1 = b.S1; a.K = b.K; a.tw = b.twy;
-        a.ny = p.ny; a.Py = p.Py; a.Hx = p.Hx; a.Hy = p.Hy; a.ldy = p.ldy; a.nk = p.nk;
-        a.rad = p.ry;
-        const size_t ldt = lds + (size_t)p.Py * sizeof(V);
-        if (ldt <= kLdsMax)
-          hipLaunchKernelGGL((k_ffty_mul2d<T, false, true>), g, dim3(m2_threads(p)), ldt, st, a);
-        else
-          hipLaunchKernelGGL((k_ffty_mul2d<T, false, false>), g, dim3(m2_threads(p)), lds, st, a);
+        hipLaunchKernelGGL((k_yz<T, 1>), g, dim3(m2_threads(p, (int)sizeof(T))),
+                           (size_t)3 * p.nk * p.fy.pitch * sizeof(V), st,
+                           yz_args<T>(p, b, ctrl, p.nk));
+      }
+      break;
+    }
+    case DP_YZ: {
+      const dim3 g(p.Hx);
+      const dim3 blk(line_threads(p.fy, 3L * p.nz, yz_max_threads((int)sizeof(T), p.Pz)));
+      const size_t lds = (size_t)3 * p.nz * p.fy.pitch * sizeof(V);
+      const YzArgs<T> a = yz_args<T>(p, b, ctrl, 1);
+      switch (p.Pz) {
+#define X(P) case P: hipLaunchKernelGGL((k_yz<T, P>), g, blk, lds, st, a); break;
+        MMP_YZ_SMALL(X) MMP_YZ_LARGE(X)
+#undef X
       }
       break;
     }
@@ -652,19 +765,14 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
         a.nl = nl;
         launch_y4<T>(p.Py, inv, p.rep[1] > 0, g, y_threads(p, nl), lds, st, a);
       } else {
-        YArgs<T> a;
-        a.ctrl = ctrl; a.in = in; a.out = out; a.tw = b.twy;
+        YArgs<T> a{};
+        a.ctrl = ctrl; a.in = in; a.out = out; a.tw = b.twy; a.pos = b.posy;
         a.nlines = nlines; a.nvalid_in = nvi; a.ld_in = ldi; a.nvalid_out = nvo; a.ld_out = ldo;
-        a.L = p.Py; a.nl = nl; a.rad = p.ry;
+        a.nl = nl; a.half = p.rep[1] > 0 || p.Py == 1 ? 0 : 1; a.dL = make_div(p.Py); a.f = p.fy;
         const dim3 blk(y_threads(p, nl));
-        const size_t ldt = lds + (size_t)p.Py * sizeof(V);
-        if (ldt <= kLdsMax) {
-          if (inv) hipLaunchKernelGGL((k_ffty<T, true, false, true>), g, blk, ldt, st, a);
-          else hipLaunchKernelGGL((k_ffty<T, false, false, true>), g, blk, ldt, st, a);
-        } else {
-          if (inv) hipLaunchKernelGGL((k_ffty<T, true, false, false>), g, blk, lds, st, a);
-          else hipLaunchKernelGGL((k_ffty<T, false, false, false>), g, blk, lds, st, a);
-        }
+        const size_t ldm = (size_t)nl * p.fy.pitch * sizeof(V);
+        if (inv) hipLaunchKernelGGL((k_ffty<T, true>), g, blk, ldm, st, a);
+        else hipLaunchKernelGGL((k_ffty<T, false>), g, blk, ldm, st, a);
       }
       break;
     }
@@ -678,15 +786,9 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
         a.nb_pad = round_up(nblk, 8);
         launch_z4<T>(p.Pz, p.zq, p.zw, p.zmode, dim3(a.nb_pad), p.zt, st, a);
       } else {
-        ZArgs<T> a;
-        a.ctrl = ctrl; a.S2 = b.S2; a.K = b.K; a.tw = b.twz;
-        a.nz = p.nz; a.Pz = p.Pz; a.Hx = p.Hx; a.Py = p.Py; a.Hy = p.Hy; a.Hz = p.Hz;
-        a.tk = p.tk; a.ls = p.Pz + 1; a.rad = p.rz;
         const dim3 g((p.Py + p.tk - 1) / p.tk, p.Hx), blk(z_threads(p));
-        const size_t lds = (size_t)3 * p.tk * (p.Pz + 1) * sizeof(V);
-        const size_t ldt = lds + (size_t)p.Pz * sizeof(V);
-        if (ldt <= kLdsMax) hipLaunchKernelGGL((k_fftz_mul<T, false, true>), g, blk, ldt, st, a);
-        else hipLaunchKernelGGL((k_fftz_mul<T, false, false>), g, blk, lds, st, a);
+        hipLaunchKernelGGL((k_fftz_mul<T>), g, blk, (size_t)3 * p.tk * p.fz.pitch * sizeof(V), st,
+                           z_args<T>(p, b, ctrl, p.tk));
       }
       break;
     }
@@ -700,18 +802,18 @@ struct DemagMulti<T>::Impl {
   std::vector<XArgs<T>> xf;
   std::vector<YArgs<T>> yf, yi;
   std::vector<ZArgs<T>> z;
-  std::vector<M2Args<T>> m2;
-  std::vector<int4> wxf, wxi, wyf, wyi, wz, wm2;
+  std::vector<YzArgs<T>> yz;
+  std::vector<int4> wxf, wxi, wyf, wyi, wz, wyz[2];   // wyz: short, long z columns
   char* dev = nullptr;
   const XArgs<T>* d_xf = nullptr;
   const XArgs<T>* d_xi = nullptr;
   const YArgs<T>* d_yf = nullptr;
   const YArgs<T>* d_yi = nullptr;
   const ZArgs<T>* d_z = nullptr;
-  const M2Args<T>* d_m2 = nullptr;
+  const YzArgs<T>* d_yz = nullptr;
   const int4 *d_wxf = nullptr, *d_wxi = nullptr, *d_wyf = nullptr, *d_wyi = nullptr,
-             *d_wz = nullptr, *d_wm2 = nullptr;
-  size_t lds_x = 0, lds_y = 0, lds_z = 0, lds_m2 = 0;
+             *d_wz = nullptr, *d_wyz[2] = {nullptr, nullptr};
+  size_t lds_x = 0, lds_y = 0, lds_z = 0, lds_yz[2] = {0, 0};
 };
 
 template <typename T>
@@ -733,11 +835,11 @@ static int pow2_floor(long cap, int hi) {
 }
 
 bool demag_multi_fits(const DemagPlan& p) {
-  // one line and its twiddle table per block
-  const long cap = (long)kMaxE * kMultiThreads;
-  if (2L * p.Px > cap || 2L * p.Py > cap) return false;
-  if (p.nz == 1) return 4L * p.Py <= cap;
-  return 3L * (p.Pz + 1) + p.Pz <= cap;
+  // a block takes at least one line
+  const long cap = kMultiElems;
+  if (p.Px > cap || p.Py > cap) return false;
+  if (p.nz == 1) return 3L * p.Py <= cap;
+  return 3L * p.Pz <= cap;
 }
 
 template <typename T>
@@ -752,46 +854,36 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
     }
   impl = new Impl();
   Impl& I = *impl;
-  const long cap = (long)kMaxE * kMultiThreads;   // complex elements per block
+  const long cap = kMultiElems;   // complex elements per block
   for (size_t g = 0; g < members.size(); ++g) {
     const DemagMember<T>& mb = members[g];
     const DemagPlan& p = *mb.plan;
     const int gi = (int)g;
     // x passes: the most rows per block (<= 16) that fit
-    // (the twiddle table of the line length sits in LDS beside the lines)
     int ty = 2;
-    while (ty < 16 && (long)(ty + 1) * p.Px <= cap && ty < p.ny + (p.ny & 1)) ty *= 2;
-    XArgs<T> xa{};
-    xa.tbl = mb.tbl; xa.ctrl = mb.ctrl; xa.stage = 0;
-    xa.ms0 = mb.ms0; xa.ms1 = mb.ms1; xa.ms2 = mb.ms2; xa.nsub = mb.nsub;
-    xa.S1 = mb.bufs.S1; xa.Bd = mb.bufs.Bd; xa.tw = mb.bufs.twx;
-    xa.nx = p.nx; xa.ny = p.ny; xa.nz = p.nz; xa.Px = p.Px; xa.Hx = p.Hx; xa.ldy = p.ldy;
-    xa.ty = ty; xa.rad = p.rx;
-    I.xf.push_back(xa);
-    const int xf_idx = (int)I.xf.size() - 1;
+    while (ty < 16 && (long)ty * p.Px <= cap && ty < p.ny + (p.ny & 1)) ty *= 2;
+    I.xf.push_back(x_args<T>(p, mb.bufs, mb.tbl, 0, mb.ctrl, mb.ms0, mb.ms1, mb.ms2, mb.nsub, ty));
     for (int c = 0; c < 3; ++c)
       for (int z = 0; z < p.nz; ++z)
         for (int b = 0; b < (p.ny + ty - 1) / ty; ++b) {
-          I.wxf.push_back(make_int4(xf_idx, b, z, c));
-          I.wxi.push_back(make_int4(xf_idx, b, z, c));
+          I.wxf.push_back(make_int4(gi, b, z, c));
+          I.wxi.push_back(make_int4(gi, b, z, c));
         }
-    I.lds_x = std::max(I.lds_x, (size_t)(ty / 2 + 1) * p.Px * sizeof(V));
-    if (p.nz == 1) {
-      const int nk = pow2_floor((cap / p.Py - 1) / 3, 64);
-      M2Args<T> a{};
-      a.ctrl = mb.ctrl; a.S1 = mb.bufs.S1; a.K = mb.bufs.K; a.tw = mb.bufs.twy;
-      a.ny = p.ny; a.Py = p.Py; a.Hx = p.Hx; a.Hy = p.Hy; a.ldy = p.ldy; a.nk = nk;
-      a.rad = p.ry;
-      I.m2.push_back(a);
-      const int idx = (int)I.m2.size() - 1;
-      for (int b = 0; b < (p.Hx + nk - 1) / nk; ++b) I.wm2.push_back(make_int4(idx, b, 0, 0));
-      I.lds_m2 = std::max(I.lds_m2, (size_t)(3 * nk + 1) * p.Py * sizeof(V));
+    I.lds_x = std::max(I.lds_x, (size_t)(ty / 2) * p.fx.pitch * sizeof(V));
+    if (p.nz == 1 || p.fuse) {
+      const int nk = p.fuse ? 1 : pow2_floor(cap / (3L * p.Py), 64);
+      I.yz.push_back(yz_args<T>(p, mb.bufs, mb.ctrl, nk));
+      const int idx = (int)I.yz.size() - 1, cls = p.Pz >= 10 ? 1 : 0;
+      for (int b = 0; b < (p.Hx + nk - 1) / nk; ++b)
+        I.wyz[cls].push_back(make_int4(idx, b, 0, 0));
+      I.lds_yz[cls] =
+          std::max(I.lds_yz[cls], (size_t)3 * p.nz * nk * p.fy.pitch * sizeof(V));
     } else {
-      const int nl = pow2_floor(cap / p.Py - 1, 64);
+      const int nl = pow2_floor(cap / p.Py, 64);
       const int nlines = 3 * p.nz * p.Hx;
       YArgs<T> a{};
-      a.ctrl = mb.ctrl; a.tw = mb.bufs.twy; a.nlines = nlines; a.L = p.Py; a.nl = nl;
-      a.rad = p.ry;
+      a.ctrl = mb.ctrl; a.tw = mb.bufs.twy; a.pos = mb.bufs.posy; a.nlines = nlines; a.nl = nl;
+      a.half = p.rep[1] > 0 || p.Py == 1 ? 0 : 1; a.dL = make_div(p.Py); a.f = p.fy;
       YArgs<T> f = a, i = a;
       f.in = mb.bufs.S1; f.out = mb.bufs.S2;
       f.nvalid_in = p.ny; f.ld_in = p.ldy; f.nvalid_out = p.Py; f.ld_out = p.Py;
@@ -804,17 +896,13 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
         I.wyf.push_back(make_int4(idx, b, 0, 0));
         I.wyi.push_back(make_int4(idx, b, 0, 0));
       }
-      I.lds_y = std::max(I.lds_y, (size_t)(nl + 1) * p.Py * sizeof(V));
-      const int tk = pow2_floor((cap - p.Pz) / (3L * (p.Pz + 1)), 64);
-      ZArgs<T> za{};
-      za.ctrl = mb.ctrl; za.S2 = mb.bufs.S2; za.K = mb.bufs.K; za.tw = mb.bufs.twz;
-      za.nz = p.nz; za.Pz = p.Pz; za.Hx = p.Hx; za.Py = p.Py; za.Hy = p.Hy; za.Hz = p.Hz;
-      za.tk = tk; za.ls = p.Pz + 1; za.rad = p.rz;
-      I.z.push_back(za);
+      I.lds_y = std::max(I.lds_y, (size_t)nl * p.fy.pitch * sizeof(V));
+      const int tk = pow2_floor(cap / (3L * p.Pz), 64);
+      I.z.push_back(z_args<T>(p, mb.bufs, mb.ctrl, tk));
       const int zi = (int)I.z.size() - 1;
       for (int kx = 0; kx < p.Hx; ++kx)
         for (int b = 0; b < (p.Py + tk - 1) / tk; ++b) I.wz.push_back(make_int4(zi, b, kx, 0));
-      I.lds_z = std::max(I.lds_z, ((size_t)3 * tk * (p.Pz + 1) + p.Pz) * sizeof(V));
+      I.lds_z = std::max(I.lds_z, (size_t)3 * tk * p.fz.pitch * sizeof(V));
     }
   }
   // one device allocation, 256-byte aligned segments
@@ -828,13 +916,14 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
   const size_t o_yf = seg(I.yf.size() * sizeof(YArgs<T>));
   const size_t o_yi = seg(I.yi.size() * sizeof(YArgs<T>));
   const size_t o_z = seg(I.z.size() * sizeof(ZArgs<T>));
-  const size_t o_m2 = seg(I.m2.size() * sizeof(M2Args<T>));
+  const size_t o_yz = seg(I.yz.size() * sizeof(YzArgs<T>));
   const size_t o_wxf = seg(I.wxf.size() * sizeof(int4));
   const size_t o_wxi = seg(I.wxi.size() * sizeof(int4));
   const size_t o_wyf = seg(I.wyf.size() * sizeof(int4));
   const size_t o_wyi = seg(I.wyi.size() * sizeof(int4));
   const size_t o_wz = seg(I.wz.size() * sizeof(int4));
-  const size_t o_wm2 = seg(I.wm2.size() * sizeof(int4));
+  const size_t o_wyz0 = seg(I.wyz[0].size() * sizeof(int4));
+  const size_t o_wyz1 = seg(I.wyz[1].size() * sizeof(int4));
   hipError_t ae;
   {
     DeviceLock lk(device_mutex());
@@ -854,13 +943,14 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
                  put(o_yf, I.yf.data(), I.yf.size() * sizeof(YArgs<T>)),
                  put(o_yi, I.yi.data(), I.yi.size() * sizeof(YArgs<T>)),
                  put(o_z, I.z.data(), I.z.size() * sizeof(ZArgs<T>)),
-                 put(o_m2, I.m2.data(), I.m2.size() * sizeof(M2Args<T>)),
+                 put(o_yz, I.yz.data(), I.yz.size() * sizeof(YzArgs<T>)),
                  put(o_wxf, I.wxf.data(), I.wxf.size() * sizeof(int4)),
                  put(o_wxi, I.wxi.data(), I.wxi.size() * sizeof(int4)),
                  put(o_wyf, I.wyf.data(), I.wyf.size() * sizeof(int4)),
                  put(o_wyi, I.wyi.data(), I.wyi.size() * sizeof(int4)),
                  put(o_wz, I.wz.data(), I.wz.size() * sizeof(int4)),
-                 put(o_wm2, I.wm2.data(), I.wm2.size() * sizeof(int4))})
+                 put(o_wyz0, I.wyz[0].data(), I.wyz[0].size() * sizeof(int4)),
+                 put(o_wyz1, I.wyz[1].data(), I.wyz[1].size() * sizeof(int4))})
     if (r != hipSuccess) e = r;
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
@@ -874,13 +964,14 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
   I.d_yf = reinterpret_cast<const YArgs<T>*>(I.dev + o_yf);
   I.d_yi = reinterpret_cast<const YArgs<T>*>(I.dev + o_yi);
   I.d_z = reinterpret_cast<const ZArgs<T>*>(I.dev + o_z);
-  I.d_m2 = reinterpret_cast<const M2Args<T>*>(I.dev + o_m2);
+  I.d_yz = reinterpret_cast<const YzArgs<T>*>(I.dev + o_yz);
   I.d_wxf = reinterpret_cast<const int4*>(I.dev + o_wxf);
   I.d_wxi = reinterpret_cast<const int4*>(I.dev + o_wxi);
   I.d_wyf = reinterpret_cast<const int4*>(I.dev + o_wyf);
   I.d_wyi = reinterpret_cast<const int4*>(I.dev + o_wyi);
   I.d_wz = reinterpret_cast<const int4*>(I.dev + o_wz);
-  I.d_wm2 = reinterpret_cast<const int4*>(I.dev + o_wm2);
+  I.d_wyz[0] = reinterpret_cast<const int4*>(I.dev + o_wyz0);
+  I.d_wyz[1] = reinterpret_cast<const int4*>(I.dev + o_wyz1);
   return 0;
 }
 
@@ -891,9 +982,12 @@ void DemagMulti<T>::launch(int stage, hipStream_t st) const {
   const dim3 b(kMultiThreads);
   hipLaunchKernelGGL((k_fftx_fwd_multi<T>), dim3((unsigned)I.wxf.size()), b, I.lds_x, st, I.d_xf,
                      I.d_wxf, stage);
-  if (!I.wm2.empty())
-    hipLaunchKernelGGL((k_ffty_mul2d_multi<T>), dim3((unsigned)I.wm2.size()), b, I.lds_m2, st,
-                       I.d_m2, I.d_wm2);
+  if (!I.wyz[0].empty())
+    hipLaunchKernelGGL((k_yz_multi<T, false>), dim3((unsigned)I.wyz[0].size()), b, I.lds_yz[0], st,
+                       I.d_yz, I.d_wyz[0]);
+  if (!I.wyz[1].empty())
+    hipLaunchKernelGGL((k_yz_multi<T, true>), dim3((unsigned)I.wyz[1].size()), b, I.lds_yz[1], st,
+                       I.d_yz, I.d_wyz[1]);
   if (!I.wyf.empty()) {
     hipLaunchKernelGGL((k_ffty_multi<T, false>), dim3((unsigned)I.wyf.size()), b, I.lds_y, st,
                        I.d_yf, I.d_wyf);
@@ -909,14 +1003,16 @@ void DemagMulti<T>::launch(int stage, hipStream_t st) const {
 template class DemagMulti<float>;
 template class DemagMulti<double>;
 
-static const int kPassProf[DP_COUNT] = {P_FFTX_FWD, P_FFTY_FWD, P_FFTZ_MUL,
-                                        P_FFTY_INV, P_FFTX_INV, P_FFTY_MUL2D};
+static const int kPassProf[DP_COUNT] = {P_FFTX_FWD, P_FFTY_FWD, P_FFTZ_MUL,  P_FFTY_INV,
+                                        P_FFTX_INV, P_FFTY_MUL2D, P_FFTZ_MUL};
 
 static int demag_passes(const DemagPlan& p, int* out) {
   int n = 0;
   out[n++] = DP_XF;
   if (p.nz == 1) {
     out[n++] = DP_M2;
+  } else if (p.fuse) {
+    out[n++] = DP_YZ;
   } else {
     out[n++] = DP_YF;
     out[n++] = DP_Z;
@@ -1009,6 +1105,9 @@ double demag_tune(DemagPlan* pp, const DemagBufs<T>& b, const Table<T>* tbl, T m
           c.nk = k;
           add(c);
         }
+        break;
+      case DP_YZ:   // one shape
+        add(best);
         break;
       case DP_Z:
         if (best.p2z) {

@@ -69,31 +69,6 @@ __device__ __forceinline__ void fs_step3(cpx<T> (*u)[L2], const cpx<T>* line, in
   }
 }
 
-// two consecutive complex values as one 16-byte access where they fit (the
-// load is the x inverse pass's single read of its spectrum: non-temporal)
-template <typename T>
-__device__ __forceinline__ void store2(cpx<T>* o, cpx<T> a, cpx<T> b) {
-  if constexpr (sizeof(cpx<T>) == 8) {
-    float4 v;
-    v.x = a.x; v.y = a.y; v.z = b.x; v.w = b.y;
-    *reinterpret_cast<float4*>(o) = v;
-  } else {
-    o[0] = a;
-    o[1] = b;
-  }
-}
-template <typename T>
-__device__ __forceinline__ void load2(const cpx<T>* i, cpx<T>& a, cpx<T>& b) {
-  if constexpr (sizeof(cpx<T>) == 8) {
-    const nt_f4 v = __builtin_nontemporal_load(reinterpret_cast<const nt_f4*>(i));
-    a = cmk<T>(v.x, v.y);
-    b = cmk<T>(v.z, v.w);
-  } else {
-    a = ntload(i);
-    b = ntload(i + 1);
-  }
-}
-
 // ------------------------------------------------------------ y lines --
 // FULL: the input line fills the whole transform length (a periodic axis);
 // otherwise a forward line is zero-padded to at least twice its data.
@@ -376,12 +351,16 @@ __global__ __launch_bounds__(256) void k4_fftx_inv(X4Args<T> a) {
   }
   const bool nyq = tid < nl;
   load2<T>(in + (long)nh * a.ldy + 2 * (nyq ? tid : 0), qa, qb);
+  // past the last row S1 holds the forward pass's rounding of a zero row,
+  // unscaled by the kernel: left in, it would leak into the row before
+  const int last = (a.ny - y0) >> 1;   // first pair without a second row
+  if (nyq && tid >= last) qb = cmk<T>(0, 0);
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     const int idx = tid + j * nthr;
     if (idx < npair) {
       const int qq = idx & (nl - 1), kx = idx >> a.lnl;
-      const V xa = pa[j], xb = pb[j];
+      const V xa = pa[j], xb = qq < last ? pb[j] : cmk<T>(0, 0);
       lds[qq * L + (kx ^ xsw<L>(qq))] = cmk<T>(xa.x - xb.y, xa.y + xb.x);
       if (kx > 0 && 2 * kx < L)
         lds[qq * L + ((L - kx) ^ xsw<L>(qq))] = cmk<T>(xa.x + xb.y, xb.x - xa.y);

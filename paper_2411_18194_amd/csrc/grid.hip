@@ -147,6 +147,7 @@ struct Grid final : GridBase {
   DemagPlan plan{};
   DemagBufs<T> db{};
   Buf<cpx<T>> S1, S2, tw;
+  Buf<int> pos;
   Buf<T> K;
   bool demag_built = false;
   // layout of the current allocation
@@ -182,7 +183,7 @@ struct Grid final : GridBase {
     dctrl.release();
     sctrl.release();
     sres.release();
-    S1.release(); S2.release(); tw.release();
+    S1.release(); S2.release(); tw.release(); pos.release();
     plan = DemagPlan{};
     allocated = false;
     demag_built = false;
@@ -327,14 +328,15 @@ struct Grid final : GridBase {
                       np.s1_elems == plan.s1_elems && np.s2_elems == plan.s2_elems;
     if (!same) {
       if (stream) MMP_HIP_TRY(hipStreamSynchronize(stream));
-      S1.release(); S2.release(); K.release(); tw.release();
+      S1.release(); S2.release(); K.release(); tw.release(); pos.release();
       int rc = 0;
       rc |= S1.alloc(np.s1_elems);
       rc |= S2.alloc(np.s2_elems);
       rc |= K.alloc(np.k_elems);
-      rc |= tw.alloc((size_t)2 * (np.Px + np.Py) + np.Pz);
+      rc |= tw.alloc(demag_tw_elems(np));
+      rc |= pos.alloc((size_t)np.Px + np.Py + np.Pz);
       if (rc) {
-        S1.release(); S2.release(); K.release(); tw.release();
+        S1.release(); S2.release(); K.release(); tw.release(); pos.release();
         plan = DemagPlan{};
         set_error("device allocation failed");
         return MMP_E_NOMEM;
@@ -343,21 +345,32 @@ struct Grid final : GridBase {
       k1_valid = false;
     }
     plan = np;
-    set_demag_ptrs(db, S1.p, S2.p, K.p, tw.p, plan);
+    set_demag_ptrs(db, S1.p, S2.p, K.p, tw.p, pos.p, plan);
     return 0;
   }
 
-  static void set_demag_ptrs(DemagBufs<T>& b, cpx<T>* s1, cpx<T>* s2, T* k, cpx<T>* t,
+  // twiddles: the line transforms' tables of the three axes, then the
+  // four-step tables of x and y
+  static size_t demag_tw_elems(const DemagPlan& pl) {
+    return (size_t)line_tw_elems(pl.Px) + line_tw_elems(pl.Py) + line_tw_elems(pl.Pz) + pl.Px +
+           pl.Py;
+  }
+
+  static void set_demag_ptrs(DemagBufs<T>& b, cpx<T>* s1, cpx<T>* s2, T* k, cpx<T>* t, int* pos,
                              const DemagPlan& pl) {
     b.S1 = s1; b.S2 = s2; b.K = k;
-    b.twx = t; b.twy = t + pl.Px; b.twz = t + pl.Px + pl.Py;
-    b.tw4x = b.twz + pl.Pz; b.tw4y = b.tw4x + pl.Px;
+    b.twx = t;
+    b.twy = b.twx + line_tw_elems(pl.Px);
+    b.twz = b.twy + line_tw_elems(pl.Py);
+    b.tw4x = b.twz + line_tw_elems(pl.Pz);
+    b.tw4y = b.tw4x + pl.Px;
+    b.posx = pos; b.posy = pos + pl.Px; b.posz = b.posy + pl.Py;
   }
 
   void build_all_twiddles(const DemagBufs<T>& b, const DemagPlan& pl) {
-    build_twiddles<T>(b.twx, pl.Px, stream);
-    build_twiddles<T>(b.twy, pl.Py, stream);
-    build_twiddles<T>(b.twz, pl.Pz, stream);
+    build_line_tables<T>(pl.fx, b.twx, b.posx, stream);
+    build_line_tables<T>(pl.fy, b.twy, b.posy, stream);
+    build_line_tables<T>(pl.fz, b.twz, b.posz, stream);
     build_twiddles4<T>(b.tw4x, pl.Px, stream);
     build_twiddles4<T>(b.tw4y, pl.Py, stream);
   }
@@ -571,7 +584,11 @@ struct Grid final : GridBase {
           const bool cur = c.Px == plan.Px && c.Py == plan.Py && c.Pz == plan.Pz;
           DemagBufs<T> tb = db;
           Buf<cpx<T>> s1, s2, twb;
+          Buf<int> pb;
           Buf<T> kb;
+          auto drop = [&] {
+            s1.release(); s2.release(); kb.release(); twb.release(); pb.release();
+          };
           if (cur) {
             c.tyf = plan.tyf; c.tyi = plan.tyi; c.nlyf = plan.nlyf; c.nlyi = plan.nlyi;
             c.nk = plan.nk; c.tk = plan.tk;
@@ -579,17 +596,17 @@ struct Grid final : GridBase {
             if (demag_plan_check(c, (int)sizeof(T)) != 0) c = plan;
           } else {
             if (s1.alloc(c.s1_elems) || s2.alloc(c.s2_elems) || kb.alloc(c.k_elems) ||
-                twb.alloc((size_t)2 * (c.Px + c.Py) + c.Pz)) {
-              s1.release(); s2.release(); kb.release(); twb.release();
+                twb.alloc(demag_tw_elems(c)) || pb.alloc((size_t)c.Px + c.Py + c.Pz)) {
+              drop();
               continue;  // this pad set does not fit next to the grid
             }
-            set_demag_ptrs(tb, s1.p, s2.p, kb.p, twb.p, c);
+            set_demag_ptrs(tb, s1.p, s2.p, kb.p, twb.p, pb.p, c);
             MMP_HIP_TRY(hipMemsetAsync(kb.p, 0, c.k_elems * sizeof(T), stream));
             build_all_twiddles(tb, c);
           }
           const double ms = demag_tune<T>(&c, tb, dtbl.p, ms0, ms1, p.nsub, stream, ms2);
           const hipError_t e = hipStreamSynchronize(stream);
-          s1.release(); s2.release(); kb.release(); twb.release();
+          drop();
           if (e != hipSuccess) {
             set_error(std::string("autotune: ") + hipGetErrorString(e));
             return MMP_E_HIP;
