@@ -314,8 +314,9 @@ mmp_status mmp_get_demag_tensor(mmp_grid g, double* n6);
  * tensor at the layer's vertical offsets).  b_out: 3*nx*ny doubles
  * [comp][y][x], tesla, caller-owned.  MMP_E_ARG for height < dz/2 (the
  * layer would overlap the magnet).  A direct FP64 sum over all cell pairs
- * on the device (cost ~ (nx ny)^2 nz); allocates its tensor table
- * (6 nz (2nx-1)(2ny-1) doubles) for the call.  Synchronous. */
+ * on the device (cost ~ (nx ny)^2 nz); allocates its tensor table and
+ * partial sums (6 nx ny nz doubles, and 3 nx ny for each of up to 4096 parts
+ * of the sum on the smallest grids) for the call.  Synchronous. */
 mmp_status mmp_stray_field(mmp_grid g, double height, double* b_out);
 
 /* Allocation-free variant of mmp_stray_field, for callers that cannot call

@@ -866,19 +866,32 @@ __global__ void k_sample_part(const Ctrl* c, const Table<T>* tbl, int nsub, long
   if (threadIdx.x < 9) part[blockIdx.x * 9 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-__global__ void k_sample_final(Ctrl* c, const double* part, int nblk, long N, int nsub,
-                               double* sample_t, double* sample_m, int cap) {
+// sum of up to any number of partial sums by one 256-thread block, to thread 0
+__device__ __forceinline__ double block_sum(const double* part, int n, int stride, double* red) {
+  double acc = 0.0;
+  for (int b = threadIdx.x; b < n; b += 256) acc += part[(long)b * stride];
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  return red[0] + red[1] + red[2] + red[3];
+}
+
+// One block: the averages of one output time.  (One thread walking the
+// partial sums took 84 us for 240 of them, a block under 4.)
+__global__ __launch_bounds__(256) void k_sample_final(Ctrl* c, const double* part, int nblk,
+                                                      long N, int nsub, double* sample_t,
+                                                      double* sample_m, int cap) {
   if (!c->sample_pending) return;
-  if (threadIdx.x != 0) return;
+  __shared__ double red[4];
   const int k = c->nsamples;
-  if (k < cap) {
-    sample_t[k] = c->t;
-    for (int q = 0; q < 3 * nsub; ++q) {
-      double acc = 0.0;
-      for (int b = 0; b < nblk; ++b) acc += part[b * 9 + q];
-      sample_m[k * 3 * nsub + q] = acc / (double)N;
-    }
+  for (int q = 0; q < 3 * nsub; ++q) {
+    const double acc = block_sum(part + q, nblk, 9, red);
+    if (threadIdx.x == 0 && k < cap) sample_m[k * 3 * nsub + q] = acc / (double)N;
   }
+  __syncthreads();   // every thread has read the controller
+  if (threadIdx.x != 0) return;
+  if (k < cap) sample_t[k] = c->t;
   c->nsamples = k + 1;
   c->sample_pending = 0;
 }
@@ -888,20 +901,19 @@ void launch_sample(Ctrl* ctrl, const Table<T>* tbl, int nsub, long N, double* pa
                    double* sample_t, double* sample_m, int cap, hipStream_t st, Prof* prof) {
   ProfScope ps(prof, P_REDUCE, st);
   hipLaunchKernelGGL((k_sample_part<T>), dim3(nblk), dim3(256), 0, st, ctrl, tbl, nsub, N, part);
-  hipLaunchKernelGGL(k_sample_final, dim3(1), dim3(64), 0, st, ctrl, part, nblk, N, nsub, sample_t,
+  hipLaunchKernelGGL(k_sample_final, dim3(1), dim3(256), 0, st, ctrl, part, nblk, N, nsub, sample_t,
                      sample_m, cap);
 }
 
-__global__ void k_energy_final(const double* epart, int nblk, double* out) {
-  const int t = threadIdx.x;
-  if (t >= kNE) return;
-  double acc = 0.0;
-  for (int b = 0; b < nblk; ++b) acc += epart[(long)b * kNE + t];
-  out[t] = acc;
+// one block per energy term
+__global__ __launch_bounds__(256) void k_energy_final(const double* epart, int nblk, double* out) {
+  __shared__ double red[4];
+  const double acc = block_sum(epart + blockIdx.x, nblk, kNE, red);
+  if (threadIdx.x == 0) out[blockIdx.x] = acc;
 }
 
 void launch_energy_final(const double* epart, int nblk, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(64), 0, st, epart, nblk, out);
+  hipLaunchKernelGGL(k_energy_final, dim3(kNE), dim3(256), 0, st, epart, nblk, out);
 }
 
 #define INST(T)                                                                              \

@@ -1318,13 +1318,14 @@ struct Grid final : GridBase {
     return 0;
   }
 
-  // tensor table into k6, then the field into dout, on the grid's stream
+  // tensor table into k6 (the partial images behind it), then the field into
+  // dout, on the grid's stream
   hipError_t stray_launch(double height, double* k6, double* dout) {
     const double zt = (nz - 0.5) * d[2] + height;
     if (stray_kernel_build(nx, ny, nz, d[0], d[1], d[2], zt, k6, stream))
       return hipErrorLaunchFailure;
     launch_stray<T>(yn_slot(), p.nsub, p.sub[0].Ms, p.nsub >= 2 ? p.sub[1].Ms : 0.0,
-                    p.nsub == 3 ? p.sub[2].Ms : 0.0, k6, nx, ny, nz, dout, stream);
+                    p.nsub == 3 ? p.sub[2].Ms : 0.0, k6, k6 + 6L * N, nx, ny, nz, dout, stream);
     return hipGetLastError();
   }
 
@@ -1332,8 +1333,8 @@ struct Grid final : GridBase {
   // surface (synchronous; host output [3][ny][nx])
   int stray(double height, double* out) override {
     if (int rc = stray_check(height)) return rc;
-    const size_t nk = (size_t)6 * nz * (2 * ny - 1) * (2 * nx - 1);
     const size_t no = (size_t)3 * nx * ny;
+    const size_t nk = (size_t)6 * N + no * stray_splits(nx, ny, nz);
     double *k6 = nullptr, *dout = nullptr;
     DeviceLock lk(device_mutex());
     MMP_HIP_TRY(hipStreamSynchronize(stream));

@@ -5,97 +5,142 @@
 //
 // B_t(x, y) = -mu0 sum_z sum_{x', y'} N(x - x', y - y', z_t - z) M(x', y', z),
 // M = sum_s Ms_s m_s, with the cell-pair tensor table of stray_kernel_build.
-// A direct tiled sum: a block owns 16x16 target cells and walks the source
-// tiles of every layer, staging the 3x16x16 moments and the 6x31x31 tensor
-// window of the tile pair in LDS; sums in FP64.  This is an output-time
-// operation (one image per call), not part of a step.
+// The table holds the offsets X, Y >= 0; the components odd along an axis
+// change sign with the offset.  This is an output-time operation (one image
+// per call), not part of a step.
+//
+// The sum as FP64 matrix products: for a fixed row offset dy the tensor
+// between a row of 16 targets and 4 sources is a 16x4 slice of a Toeplitz
+// matrix, and it serves 16 target rows y at once with the sources of rows
+// y - dy (zero outside the grid).  So a wave owns 16x16 targets (three
+// accumulators of the 16x16x4 FP64 matrix instruction) and per 4 sources
+// loads six tensor and three moment values per lane for nine instructions of
+// 2048 operations.  The (layer, dy) pairs are split over enough waves to fill
+// the chip, whose partial sums a second kernel adds in order.
+// Before, a block per 16x16 targets walked every source with nine LDS reads
+// per pair: 1736 us for 128x96x2 (48 blocks on 256 CUs), 241 + 14 now.
+#include <algorithm>
 #include <mutex>
 
 #include "stray.h"
 
 namespace mmp {
 
-constexpr int kST = 16;               // tile edge
-constexpr int kSW = 2 * kST - 1;      // offsets between two tiles
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kST = 16;   // tile edge
 
 // The state is read through its slot in the grid's device pointer table
 // (the controller swaps that table after accepted steps), so a launch needs
 // no host read-back of the table.
 template <typename T>
-__global__ __launch_bounds__(256) void k_stray(const T* const* __restrict__ mslot, int nsub,
-                                              double ms0, double ms1, double ms2,
-                                              const double* __restrict__ k6, int nx, int ny,
-                                              int nz, double* __restrict__ out) {
-  const T* __restrict__ m = *mslot;
-  __shared__ double sm[3][kST * kST];
-  __shared__ double sk[6][kSW * kSW];
-  const int tx = threadIdx.x % kST, ty = threadIdx.x / kST;
-  const int x0 = blockIdx.x * kST, y0 = blockIdx.y * kST;
-  const int xt = x0 + tx, yt = y0 + ty;
+__global__ __launch_bounds__(64) void k_stray(const T* const* __restrict__ mslot, int nsub,
+                                             double ms0, double ms1, double ms2,
+                                             const double* __restrict__ k6, int nx, int ny, int nz,
+                                             double* __restrict__ part) {
+  const gcptr<T> m = (gcptr<T>)*mslot;
+  const int ntx = (nx + kST - 1) / kST;
+  const int x0 = (int)(blockIdx.x % ntx) * kST, y0 = (int)(blockIdx.x / ntx) * kST;
+  const int lane = threadIdx.x, li = lane & 15, lk = lane >> 4;
   const long N = (long)nx * ny * nz;
-  const int wx = 2 * nx - 1, wy = 2 * ny - 1;
-  const long ktot = (long)wx * wy * nz;
-  double acc[3] = {0.0, 0.0, 0.0};
-  const int ntx = (nx + kST - 1) / kST, nty = (ny + kST - 1) / kST;
-  for (int z = 0; z < nz; ++z)
-    for (int sty = 0; sty < nty; ++sty)
-      for (int stx = 0; stx < ntx; ++stx) {
-        const int sx0 = stx * kST, sy0 = sty * kST;
-        __syncthreads();
-        {
-          // moments of the source tile (zero outside the grid)
-          const int xs = sx0 + tx, ys = sy0 + ty;
-          double v[3] = {0.0, 0.0, 0.0};
-          if (xs < nx && ys < ny) {
-            const long i = ((long)z * ny + ys) * nx + xs;
-            for (int c = 0; c < 3; ++c) {
-              v[c] = ms0 * (double)m[c * N + i];
-              if (nsub >= 2) v[c] += ms1 * (double)m[3 * N + c * N + i];
-              if (nsub == 3) v[c] += ms2 * (double)m[6 * N + c * N + i];
-            }
-          }
-          for (int c = 0; c < 3; ++c) sm[c][threadIdx.x] = v[c];
-        }
-        // tensor window: offsets X = x0 - sx0 - 15 + ox, Y likewise
-        for (int w = threadIdx.x; w < kSW * kSW; w += blockDim.x) {
-          const int ox = w % kSW, oy = w / kSW;
-          const int X = x0 - sx0 - (kST - 1) + ox, Y = y0 - sy0 - (kST - 1) + oy;
-          const bool in = X > -nx && X < nx && Y > -ny && Y < ny;
-          const long k = ((long)z * wy + (Y + ny - 1)) * wx + (X + nx - 1);
-          for (int c = 0; c < 6; ++c) sk[c][w] = in ? k6[c * ktot + k] : 0.0;
-        }
-        __syncthreads();
-        for (int j = 0; j < kST * kST; ++j) {
-          const int sxl = j % kST, syl = j / kST;
-          // offset (xt - xs, yt - ys) in window coordinates
-          const int w = (ty - syl + kST - 1) * kSW + (tx - sxl + kST - 1);
-          const double Mx = sm[0][j], My = sm[1][j], Mz = sm[2][j];
-          const double nxx = sk[0][w], nyy = sk[1][w], nzz = sk[2][w];
-          const double nxy = sk[3][w], nxz = sk[4][w], nyz = sk[5][w];
-          acc[0] += nxx * Mx + nxy * My + nxz * Mz;
-          acc[1] += nxy * Mx + nyy * My + nyz * Mz;
-          acc[2] += nxz * Mx + nyz * My + nzz * Mz;
-        }
+  // row offsets that pair a target row of the tile with a source row
+  const int dlo = y0 - (ny - 1), dhi = min(y0 + kST - 1, ny - 1);
+  const int nd = dhi - dlo + 1;
+  const int units = nz * nd, ns = gridDim.y;
+  const int u0 = (int)((long)units * blockIdx.y / ns);
+  const int u1 = (int)((long)units * (blockIdx.y + 1) / ns);
+  f64x4 acc[3] = {};
+  for (int u = u0; u < u1; ++u) {
+    const int z = u / nd, dy = dlo + (u - z * nd);
+    const double sy = dy < 0 ? -1.0 : 1.0;
+    const double* kr = k6 + ((long)z * ny + abs(dy)) * nx;
+    const int ys = y0 + li - dy;
+    const bool iny = ys >= 0 && ys < ny;
+    const long mr = ((long)z * ny + (iny ? ys : 0)) * nx;
+#pragma unroll 2
+    for (int s = 0; s < nx; s += 4) {
+      const int xs = s + lk;
+      const bool in = iny && xs < nx;
+      const long mi = mr + (xs < nx ? xs : 0);
+      double v[3];
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        v[c] = ms0 * (double)m[c * N + mi];
+        if (nsub >= 2) v[c] += ms1 * (double)m[(3 + c) * N + mi];
+        if (nsub == 3) v[c] += ms2 * (double)m[(6 + c) * N + mi];
+        v[c] = in ? v[c] : 0.0;
       }
-  if (xt < nx && yt < ny) {
-    const long o = (long)yt * nx + xt;
-    const long P = (long)nx * ny;
-    for (int c = 0; c < 3; ++c) out[c * P + o] = -kMu0 * acc[c];
+      // (targets and sources past the grid read a valid offset; their
+      // results are not kept, their moments are zero)
+      const int dx = x0 + li - xs, ax = min(abs(dx), nx - 1);
+      const double sx = dx < 0 ? -1.0 : 1.0;
+      const double txx = kr[ax], tyy = kr[N + ax], tzz = kr[2 * N + ax];
+      const double txy = sx * sy * kr[3 * N + ax], txz = sx * kr[4 * N + ax],
+                   tyz = sy * kr[5 * N + ax];
+      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(txx, v[0], acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(txy, v[0], acc[1], 0, 0, 0);
+      acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(txz, v[0], acc[2], 0, 0, 0);
+      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(txy, v[1], acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(tyy, v[1], acc[1], 0, 0, 0);
+      acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(tyz, v[1], acc[2], 0, 0, 0);
+      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(txz, v[2], acc[0], 0, 0, 0);
+      acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(tyz, v[2], acc[1], 0, 0, 0);
+      acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(tzz, v[2], acc[2], 0, 0, 0);
+    }
   }
+  // accumulator row (target x) 4 r + lane / 16, column (target y) lane % 16
+  const long P = (long)nx * ny;
+  double* out = part + (long)blockIdx.y * 3 * P;
+  const int yt = y0 + li;
+  if (yt < ny)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int xt = x0 + 4 * r + lk;
+      if (xt < nx)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) out[c * P + (long)yt * nx + xt] = acc[c][r];
+    }
+}
+
+// out = -mu0 times the sum of the ns partial images (which may be out itself)
+__global__ __launch_bounds__(256) void k_stray_sum(const double* part, int ns, long n,
+                                                  double* out) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  double acc = 0.0;
+  for (int s = 0; s < ns; ++s) acc += part[s * n + i];
+  out[i] = -kMu0 * acc;
+}
+
+// Waves per 16x16 targets: enough for four on every SIMD of the chip, at most
+// one per (layer, row offset), and no more than the partial images that fit
+// beside the tensor in the fixed table where the allocation-free call would
+// use it (both calls take the same split, so they agree bitwise).
+int stray_splits(int nx, int ny, int nz) {
+  const long tiles = (long)((nx + kST - 1) / kST) * ((ny + kST - 1) / kST);
+  long s = std::max<long>(1, std::min<long>(4096 / tiles, (long)nz * ny));
+  if (6L * nz * (2L * nx - 1) * (2L * ny - 1) <= kStrayScratchDoubles)
+    s = std::min(s, (kStrayScratchDoubles - 6L * nz * nx * ny) / (3L * nx * ny));
+  return (int)std::max<long>(1, s);
 }
 
 template <typename T>
 void launch_stray(const T* const* mslot, int nsub, double ms0, double ms1, double ms2,
-                  const double* k6, int nx, int ny, int nz, double* out, hipStream_t st) {
-  const dim3 g((nx + kST - 1) / kST, (ny + kST - 1) / kST);
-  hipLaunchKernelGGL((k_stray<T>), g, dim3(kST * kST), 0, st, mslot, nsub, ms0, ms1, ms2, k6, nx,
-                     ny, nz, out);
+                  const double* k6, double* part, int nx, int ny, int nz, double* out,
+                  hipStream_t st) {
+  const int ns = stray_splits(nx, ny, nz);
+  const dim3 g((unsigned)(((nx + kST - 1) / kST) * ((ny + kST - 1) / kST)), (unsigned)ns);
+  double* p = ns > 1 ? part : out;
+  hipLaunchKernelGGL((k_stray<T>), g, dim3(64), 0, st, mslot, nsub, ms0, ms1, ms2, k6, nx, ny, nz,
+                     p);
+  const long n = 3L * nx * ny;
+  hipLaunchKernelGGL(k_stray_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, ns, n,
+                     out);
 }
 
 template void launch_stray<float>(const float* const*, int, double, double, double,
-                                  const double*, int, int, int, double*, hipStream_t);
+                                  const double*, double*, int, int, int, double*, hipStream_t);
 template void launch_stray<double>(const double* const*, int, double, double, double,
-                                   const double*, int, int, int, double*, hipStream_t);
+                                   const double*, double*, int, int, int, double*, hipStream_t);
 
 // ------------------------------------------------ fixed tensor table --
 // Tensor table of the allocation-free stray-field call: one array per GPU,

@@ -20,9 +20,11 @@
 // mean of +n/2 and -n/2 at the half period); the transform then runs over
 // the cyclic offsets only.
 // Each component has a definite parity per axis, so its DFT on the padded
-// grid is a product of cosine/sine sums evaluated here directly in FP64
-// (exact integer phase indexes into FP64 trig tables), then scaled by
-// -mu0/(Px Py Pz) (and -1 for the odd-odd components, from (-i)^2).
+// grid is a product of cosine/sine sums: along x and y dense FP64 matrix
+// products with the matrices of cosines or sines (exact integer phase
+// indexes into FP64 trig tables), along z a short sum per column; then
+// scaled by -mu0/(Px Py Pz) (and -1 for the odd-odd components, from
+// (-i)^2).
 #include "demag.h"
 
 namespace mmp {
@@ -67,27 +69,31 @@ __device__ double newell_g(double x, double y, double z) {
   return sgn * out;
 }
 
+// term t (0..26) of the second difference: weight times f or g at the cell
+// pair's corner (a, b, c) = (t / 9, t / 3 % 3, t % 3) - 1
+template <bool OFFDIAG>
+__device__ double second_difference_term(int t, double X, double Y, double Z, double dx, double dy,
+                                         double dz) {
+  const int a = t / 9 - 1, b = t / 3 % 3 - 1, c = t % 3 - 1;
+  const double w = (a == 0 ? 2.0 : -1.0) * (b == 0 ? 2.0 : -1.0) * (c == 0 ? 2.0 : -1.0);
+  return w * (OFFDIAG ? newell_g(X + a * dx, Y + b * dy, Z + c * dz)
+                      : newell_f(X + a * dx, Y + b * dy, Z + c * dz));
+}
+
 template <bool OFFDIAG>
 __device__ double second_difference(double X, double Y, double Z, double dx, double dy, double dz) {
   double acc = 0.0;
-  for (int a = -1; a <= 1; ++a) {
-    const double wa = a == 0 ? 2.0 : -1.0;
-    for (int b = -1; b <= 1; ++b) {
-      const double wb = b == 0 ? 2.0 : -1.0;
-      for (int c = -1; c <= 1; ++c) {
-        const double wc = c == 0 ? 2.0 : -1.0;
-        const double f = OFFDIAG ? newell_g(X + a * dx, Y + b * dy, Z + c * dz)
-                                 : newell_f(X + a * dx, Y + b * dy, Z + c * dz);
-        acc += wa * wb * wc * f;
-      }
-    }
-  }
+  for (int t = 0; t < 27; ++t) acc += second_difference_term<OFFDIAG>(t, X, Y, Z, dx, dy, dz);
   return acc / (4.0 * kPi * dx * dy * dz);
 }
 
+// Offsets 0 <= X < nx, 0 <= Y < ny along x and y; vertical offset z0 + Z zs,
+// Z < nz: the grid's own (0, dz), or a layer above it seen from layer Z (its
+// height above layer 0, -dz).
 struct TensorArgs {
   int nx, ny, nz;
   double dx, dy, dz, dmax;
+  double z0, zs;
   double* n6;          // [6][nz][ny][nx]
   int bx, by, bz;      // box of offsets this launch covers
   int nq;              // quadrature points per axis (2n)
@@ -95,60 +101,97 @@ struct TensorArgs {
   int rx, ry;          // image repetitions along x and y (0: open axis)
 };
 
-__global__ void k_tensor_near(TensorArgs a) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long nbox = (long)a.bx * a.by * a.bz;
-  if (i >= nbox) return;
-  const int X = (int)(i % a.bx), Y = (int)((i / a.bx) % a.by), Z = (int)(i / ((long)a.bx * a.by));
-  const double x = X * a.dx, y = Y * a.dy, z = Z * a.dz;
+// Newell's formula: one block per offset of the box.  Each of the 6 x 27
+// terms has its own thread (an evaluation takes microseconds of dependent
+// FP64 logarithms and arctangents, so an offset per thread ran 162 of them
+// back to back: 302 us for any grid, 10 now), summed in order by six threads.
+constexpr int kNearThreads = 192;
+__global__ __launch_bounds__(kNearThreads) void k_tensor_near(TensorArgs a) {
+  const int i = blockIdx.x;
+  const int X = i % a.bx, Y = (i / a.bx) % a.by, Z = i / (a.bx * a.by);
+  const double x = X * a.dx, y = Y * a.dy, z = a.z0 + Z * a.zs;
   const double r = sqrt(x * x + y * y + z * z) / a.dmax;
   if (r >= kRNear) return;
-  const long N = (long)a.nx * a.ny * a.nz;
-  const long o = ((long)Z * a.ny + Y) * a.nx + X;
-  a.n6[o] = second_difference<false>(x, y, z, a.dx, a.dy, a.dz);
-  a.n6[N + o] = second_difference<false>(y, x, z, a.dy, a.dx, a.dz);
-  a.n6[2 * N + o] = second_difference<false>(z, y, x, a.dz, a.dy, a.dx);
-  a.n6[3 * N + o] = second_difference<true>(x, y, z, a.dx, a.dy, a.dz);
-  a.n6[4 * N + o] = second_difference<true>(x, z, y, a.dx, a.dz, a.dy);
-  a.n6[5 * N + o] = second_difference<true>(y, z, x, a.dy, a.dz, a.dx);
+  __shared__ double term[6 * 27];
+  const int t = threadIdx.x;
+  if (t < 6 * 27) {
+    const int c = t / 27, k = t % 27;
+    // axes of the component: the formula is written for xx and xy
+    const double p[3] = {x, y, z}, d[3] = {a.dx, a.dy, a.dz};
+    const int i0 = c == 0 || c == 3 || c == 4 ? 0 : (c == 2 ? 2 : 1);
+    const int i1 = c == 0 || c == 2 || c == 3 ? 1 : (c == 1 ? 0 : 2);
+    const int i2 = 3 - i0 - i1;
+    auto pick = [](const double* v, int j) { return j == 0 ? v[0] : (j == 1 ? v[1] : v[2]); };
+    const double px = pick(p, i0), py = pick(p, i1), pz = pick(p, i2);
+    const double ex = pick(d, i0), ey = pick(d, i1), ez = pick(d, i2);
+    term[t] = c < 3 ? second_difference_term<false>(k, px, py, pz, ex, ey, ez)
+                    : second_difference_term<true>(k, px, py, pz, ex, ey, ez);
+  }
+  __syncthreads();
+  if (t < 6) {
+    double acc = 0.0;
+    for (int k = 0; k < 27; ++k) acc += term[t * 27 + k];
+    const long N = (long)a.nx * a.ny * a.nz;
+    a.n6[t * N + ((long)Z * a.ny + Y) * a.nx + X] =
+        acc / (4.0 * kPi * a.dx * a.dy * a.dz);
+  }
 }
 
-// One block per offset of the middle regime; threads split the points.
-__global__ void k_tensor_quad(TensorArgs a) {
-  const long i = blockIdx.x;
-  const int X = (int)(i % a.bx), Y = (int)((i / a.bx) % a.by), Z = (int)(i / ((long)a.bx * a.by));
-  const double x = X * a.dx, y = Y * a.dy, z = Z * a.dz;
+// The middle regime, one block per offset.  A thread takes points of one
+// (x, y) node pair and sums w r^-5 times 1, sz and sz^2 over the z nodes:
+// with sx and sy fixed these give all six components, so a point costs one
+// reciprocal square root and a few multiplications (92 us for 41x41x4
+// offsets with a division and six sums per point, 31 now).
+constexpr int kQuadThreads = 256;
+__global__ __launch_bounds__(kQuadThreads) void k_tensor_quad(TensorArgs a) {
+  const int i = blockIdx.x;
+  const int X = i % a.bx, Y = (i / a.bx) % a.by, Z = i / (a.bx * a.by);
+  const double x = X * a.dx, y = Y * a.dy, z = a.z0 + Z * a.zs;
   const double r = sqrt(x * x + y * y + z * z) / a.dmax;
   if (r < kRNear || r >= kRFar) return;
   const int nq = a.nq;
-  const int npt = nq * nq * nq;
-  double acc[6] = {0, 0, 0, 0, 0, 0};
-  for (int p = threadIdx.x; p < npt; p += blockDim.x) {
-    const int ia = p % nq, ib = (p / nq) % nq, ic = p / (nq * nq);
-    const double w = a.qw[ia] * a.qw[ib] * a.qw[ic];
-    const double sx = x + a.qt[ia] * a.dx, sy = y + a.qt[ib] * a.dy, sz = z + a.qt[ic] * a.dz;
-    const double s2 = sx * sx + sy * sy + sz * sz;
-    const double inv5 = w / (s2 * s2 * sqrt(s2));
-    acc[0] += (3.0 * sx * sx - s2) * inv5;
-    acc[1] += (3.0 * sy * sy - s2) * inv5;
-    acc[2] += (3.0 * sz * sz - s2) * inv5;
-    acc[3] += 3.0 * sx * sy * inv5;
-    acc[4] += 3.0 * sx * sz * inv5;
-    acc[5] += 3.0 * sy * sz * inv5;
+  __shared__ double node[24], wgt[24];
+  if ((int)threadIdx.x < nq) {
+    node[threadIdx.x] = a.qt[threadIdx.x];
+    wgt[threadIdx.x] = a.qw[threadIdx.x];
   }
-  __shared__ double red[6][256];
-  for (int c = 0; c < 6; ++c) red[c][threadIdx.x] = acc[c];
   __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s)
-      for (int c = 0; c < 6; ++c) red[c][threadIdx.x] += red[c][threadIdx.x + s];
-    __syncthreads();
+  double acc[6] = {0, 0, 0, 0, 0, 0};
+  for (int p = threadIdx.x; p < nq * nq; p += kQuadThreads) {
+    const int ia = p % nq, ib = p / nq;
+    const double sx = x + node[ia] * a.dx, sy = y + node[ib] * a.dy;
+    const double rho2 = sx * sx + sy * sy;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    for (int ic = 0; ic < nq; ++ic) {
+      const double sz = z + node[ic] * a.dz;
+      const double q = rsqrt(rho2 + sz * sz), q2 = q * q;
+      const double w5 = wgt[ic] * (q2 * q2 * q);
+      s0 += w5;
+      s1 += w5 * sz;
+      s2 += w5 * sz * sz;
+    }
+    const double w = wgt[ia] * wgt[ib];
+    acc[0] += w * ((2.0 * sx * sx - sy * sy) * s0 - s2);
+    acc[1] += w * ((2.0 * sy * sy - sx * sx) * s0 - s2);
+    acc[2] += w * (2.0 * s2 - rho2 * s0);
+    acc[3] += w * (3.0 * sx * sy * s0);
+    acc[4] += w * (3.0 * sx * s1);
+    acc[5] += w * (3.0 * sy * s1);
   }
-  if (threadIdx.x == 0) {
+  __shared__ double red[6][kQuadThreads / 64];
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    double v = acc[c];
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if ((threadIdx.x & 63) == 0) red[c][threadIdx.x >> 6] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    const int c = threadIdx.x;
+    double v = 0.0;
+    for (int k = 0; k < kQuadThreads / 64; ++k) v += red[c][k];
     const long N = (long)a.nx * a.ny * a.nz;
-    const long o = ((long)Z * a.ny + Y) * a.nx + X;
-    const double pref = -(a.dx * a.dy * a.dz) / (4.0 * kPi);
-    for (int c = 0; c < 6; ++c) a.n6[c * N + o] = pref * red[c][0];
+    a.n6[c * N + ((long)Z * a.ny + Y) * a.nx + X] = -(a.dx * a.dy * a.dz) / (4.0 * kPi) * v;
   }
 }
 
@@ -212,7 +255,7 @@ __global__ void k_tensor_far(TensorArgs a) {
   const long N = (long)a.nx * a.ny * a.nz;
   if (i >= N) return;
   const int X = (int)(i % a.nx), Y = (int)((i / a.nx) % a.ny), Z = (int)(i / ((long)a.nx * a.ny));
-  const double x = X * a.dx, y = Y * a.dy, z = Z * a.dz;
+  const double x = X * a.dx, y = Y * a.dy, z = a.z0 + Z * a.zs;
   const double r = sqrt(x * x + y * y + z * z) / a.dmax;
   if (r < kRFar) return;
   double o6[6];
@@ -301,66 +344,120 @@ __device__ __forceinline__ double offset_weight(int X, int n, int per) {
   return (X == 0 || (per && 2 * X == n)) ? 1.0 : 2.0;
 }
 
-// F1[c][Z][Y][kx] = sum_X w_X N[c][Z][Y][X] trig(kx X); a periodic axis
-// sums 0 <= X <= nx/2 (the cyclic offsets), an open one 0 <= X < nx
-__global__ void k_trig_x(const double* n6, double* f1, const double* cs, const double* sn,
-                         int nx, int ny, int nz, int Px, int Hx, int per) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long tot = 6L * nz * ny * Hx;
-  if (i >= tot) return;
-  const int kx = (int)(i % Hx);
-  const long row = i / Hx;  // (c, Z, Y)
-  const int c = (int)(row / ((long)nz * ny));
-  const double* tab = kOddX[c] ? sn : cs;
-  const double* in = n6 + row * nx;
-  const int xe = per ? nx / 2 + 1 : nx;
-  double acc = 0.0;
-  for (int X = 0; X < xe; ++X)
-    acc += offset_weight(X, nx, per) * in[X] * tab[(int)(((long)kx * X) % Px)];
-  f1[i] = acc;
-}
+// ---- cosine and sine sums along x and y as FP64 matrix products --------
+// C[m][n] = sum_k A(m, k) w_k trig(k n), n = 0..P/2.  Along x the rows m are
+// the (Z, Y) rows of a component's tensor; along y they are the kx of one
+// (component, Z) plane, read transposed, so that the result lies with ky
+// contiguous as the kernel spectrum does.  A weight and a sign-free phase
+// index per (k, n) cost far more than the multiplication they feed, so a
+// block forms each tile of the trig matrix once for 64 rows and multiplies
+// with the FP64 matrix instruction (16x16x4): 64x64 outputs per block, four
+// waves of 32x32, 16 of the sum at a time through LDS.  Thread-per-output
+// sums took 16.8 + 12.0 ms for 512x512x16 (1.5 TFLOP/s), this 1.0 + 1.2.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kTrigTile = 64, kTrigK = 16;
 
-// F2[c][Z][ky][kx] = sum_Y w_Y F1[c][Z][Y][kx] trig(ky Y), ky <= Py/2
-__global__ void k_trig_y(const double* f1, double* f2, const double* cs, const double* sn,
-                         int ny, int nz, int Py, int Hx, int Hy, int per) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long tot = 6L * nz * Hy * Hx;
-  if (i >= tot) return;
-  const int kx = (int)(i % Hx);
-  const int ky = (int)((i / Hx) % Hy);
-  const long cz = i / ((long)Hx * Hy);  // (c, Z)
-  const int c = (int)(cz / nz);
-  const double* tab = kOddY[c] ? sn : cs;
-  const double* in = f1 + cz * ny * Hx + kx;
-  const int ye = per ? ny / 2 + 1 : ny;
-  double acc = 0.0;
-  for (int Y = 0; Y < ye; ++Y)
-    acc += offset_weight(Y, ny, per) * in[(long)Y * Hx] * tab[(int)(((long)ky * Y) % Py)];
-  f2[i] = acc;
-}
+struct TrigArgs {
+  const double* in;    // x: [6 planes][M][K]; y: [planes][K][M]
+  double* out;         // [planes][M][N]
+  const double* cs;
+  const double* sn;
+  int M, N, K;         // K offsets 0..K-1 enter the sum
+  int ldk;             // stride of a plane's rows: x M rows of ldk, y ldk rows of M
+  int P, per, nk;      // transform length, periodic axis, its cells
+  int nz;              // planes per component
+};
 
-// K[c][kz][kx][ky] = scale_c sum_Z w_Z F2[c][Z][ky][kx] trig(kz Z), kz <= Pz/2
-template <typename T>
-__global__ void k_trig_z(const double* f2, T* kout, double* k64, const double* cs,
-                         const double* sn, int nz, int Pz, int Hx, int Hy, int Hz, double scale) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long tot = 6L * Hz * Hy * Hx;
-  if (i >= tot) return;
-  const int kx = (int)(i % Hx);
-  const int ky = (int)((i / Hx) % Hy);
-  const int kz = (int)((i / ((long)Hx * Hy)) % Hz);
-  const int c = (int)(i / ((long)Hx * Hy * Hz));
-  const double* tab = kOddZ[c] ? sn : cs;
-  const double* in = f2 + (long)c * nz * Hy * Hx + (long)ky * Hx + kx;
-  double acc = 0.0;
-  for (int Z = 0; Z < nz; ++Z) {
-    const double w = Z == 0 ? 1.0 : 2.0;
-    acc += w * in[(long)Z * Hy * Hx] * tab[(int)(((long)kz * Z) % Pz)];
+template <bool ALONG_Y>
+__global__ __launch_bounds__(256) void k_trig_gemm(TrigArgs a) {
+  // rows padded to 66 doubles: the four k of a fragment start 4 banks apart
+  __shared__ double As[kTrigK][kTrigTile + 2], Bs[kTrigK][kTrigTile + 2];
+  const int plane = blockIdx.z, c = plane / a.nz;
+  const double* tab = (ALONG_Y ? kOddY[c] : kOddX[c]) ? a.sn : a.cs;
+  const double* in = a.in + (long)plane * a.ldk * a.M;
+  const int m0 = blockIdx.x * kTrigTile, n0 = blockIdx.y * kTrigTile;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
+  const int li = lane & 15, lk = lane >> 4;
+  f64x4 acc[2][2] = {};
+  for (int k0 = 0; k0 < a.K; k0 += kTrigK) {
+    for (int e = tid; e < kTrigK * kTrigTile; e += 256) {
+      // consecutive threads read consecutive addresses of either layout
+      const int kk = ALONG_Y ? e / kTrigTile : e % kTrigK;
+      const int mm = ALONG_Y ? e % kTrigTile : e / kTrigK;
+      const int k = k0 + kk, m = m0 + mm;
+      const bool ok = k < a.K && m < a.M;
+      const long o = ALONG_Y ? (long)k * a.M + m : (long)m * a.ldk + k;
+      const double v = in[ok ? o : 0];
+      As[kk][mm] = ok ? v * offset_weight(k, a.nk, a.per) : 0.0;
+    }
+    for (int e = tid; e < kTrigK * kTrigTile; e += 256) {
+      const int kk = e / kTrigTile, nn = e % kTrigTile;
+      Bs[kk][nn] = tab[(uint32_t)((k0 + kk) * (n0 + nn)) % (uint32_t)a.P];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < kTrigK; ks += 4) {
+      double fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        fa[i] = As[ks + lk][wm + 16 * i + li];
+        fb[i] = Bs[ks + lk][wn + 16 * i + li];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
   }
+  double* out = a.out + (long)plane * a.M * a.N;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + wm + 16 * i + 4 * r + lk, n = n0 + wn + 16 * j + li;
+        if (m < a.M && n < a.N) out[(long)m * a.N + n] = acc[i][j][r];
+      }
+}
+
+// K[c][kz][kx][ky] = scale_c sum_Z w_Z F2[c][Z][kx][ky] trig(kz Z), kz <= Pz/2.
+// A thread takes a (kx, ky) column of one component: its layers are read
+// once (up to kTrigZ of them at a time) for all kz.
+constexpr int kTrigZ = 16;
+template <typename T>
+__global__ __launch_bounds__(256) void k_trig_z(const double* f2, T* kout, const double* cs,
+                                                const double* sn, int nz, int Pz, long plane,
+                                                int Hz, double scale) {
+  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= plane) return;
+  const int c = blockIdx.y;
+  const double* tab = kOddZ[c] ? sn : cs;
+  const double* in = f2 + (long)c * nz * plane + i;
+  T* out = kout + (long)c * Hz * plane + i;
   const double sc = c >= 3 ? -scale : scale;
-  const long o = (((long)c * Hz + kz) * Hx + kx) * Hy + ky;
-  kout[o] = (T)(sc * acc);
-  if (k64) k64[o] = sc * acc;
+  if (nz <= kTrigZ) {
+    double v[kTrigZ];
+#pragma unroll
+    for (int Z = 0; Z < kTrigZ; ++Z) v[Z] = Z < nz ? in[Z * plane] * (Z == 0 ? 1.0 : 2.0) : 0.0;
+    for (int kz = 0; kz < Hz; ++kz) {
+      double acc = 0.0;
+#pragma unroll
+      for (int Z = 0; Z < kTrigZ; ++Z)
+        if (Z < nz) acc += v[Z] * tab[(uint32_t)(kz * Z) % (uint32_t)Pz];
+      out[kz * plane] = (T)(sc * acc);
+    }
+  } else {
+    for (int kz = 0; kz < Hz; ++kz) {
+      double acc = 0.0;
+      for (int Z = 0; Z < nz; ++Z)
+        acc += (Z == 0 ? 1.0 : 2.0) * in[Z * plane] * tab[(uint32_t)(kz * Z) % (uint32_t)Pz];
+      out[kz * plane] = (T)(sc * acc);
+    }
+  }
 }
 
 // ---------------------------------------------------------- host side --
@@ -409,8 +506,8 @@ static void triangle_rule(int n, double* t, double* w) {
   }
 }
 
-static int fill_tensor(int nx, int ny, int nz, double dx, double dy, double dz, double* n6,
-                       hipStream_t st) {
+static TensorArgs tensor_args(int nx, int ny, int nz, double dx, double dy, double dz, double z0,
+                              double zs, double* n6) {
   TensorArgs a{};
   a.nx = nx; a.ny = ny; a.nz = nz;
   a.dx = dx; a.dy = dy; a.dz = dz;
@@ -419,23 +516,37 @@ static int fill_tensor(int nx, int ny, int nz, double dx, double dy, double dz, 
   const int n = (a.dmax / dmin <= 1.25) ? 8 : 12;
   a.nq = 2 * n;
   triangle_rule(n, a.qt, a.qw);
+  a.z0 = z0; a.zs = zs;
   a.n6 = n6;
+  return a;
+}
+
+// The tensor at every offset of a, regime by regime (a block takes one
+// offset of the boxes that hold the near and middle ones).
+static int launch_tensor(TensorArgs a, hipStream_t st) {
   auto box = [&](double rcut, int nn, double d) {
     const int b = (int)std::ceil(rcut * a.dmax / d) + 1;
     return b < nn ? b : nn;
   };
-  // near
-  a.bx = box(kRNear, nx, dx); a.by = box(kRNear, ny, dy); a.bz = box(kRNear, nz, dz);
-  long nb = (long)a.bx * a.by * a.bz;
-  hipLaunchKernelGGL(k_tensor_near, dim3((unsigned)((nb + 127) / 128)), dim3(128), 0, st, a);
-  // middle
-  a.bx = box(kRFar, nx, dx); a.by = box(kRFar, ny, dy); a.bz = box(kRFar, nz, dz);
-  nb = (long)a.bx * a.by * a.bz;
-  hipLaunchKernelGGL(k_tensor_quad, dim3((unsigned)nb), dim3(256), 0, st, a);
-  // far
-  const long N = (long)nx * ny * nz;
+  // layers of the box: from the offset nearest to zero upwards on the grid's
+  // own offsets; a layer above the grid is nearest to the last one
+  const bool own = a.z0 == 0.0;
+  a.bx = box(kRNear, a.nx, a.dx); a.by = box(kRNear, a.ny, a.dy);
+  a.bz = own ? box(kRNear, a.nz, a.dz) : a.nz;
+  hipLaunchKernelGGL(k_tensor_near, dim3((unsigned)(a.bx * a.by * a.bz)), dim3(kNearThreads), 0,
+                     st, a);
+  a.bx = box(kRFar, a.nx, a.dx); a.by = box(kRFar, a.ny, a.dy);
+  a.bz = own ? box(kRFar, a.nz, a.dz) : a.nz;
+  hipLaunchKernelGGL(k_tensor_quad, dim3((unsigned)((long)a.bx * a.by * a.bz)),
+                     dim3(kQuadThreads), 0, st, a);
+  const long N = (long)a.nx * a.ny * a.nz;
   hipLaunchKernelGGL(k_tensor_far, dim3((unsigned)((N + 127) / 128)), dim3(128), 0, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+static int fill_tensor(int nx, int ny, int nz, double dx, double dy, double dz, double* n6,
+                       hipStream_t st) {
+  return launch_tensor(tensor_args(nx, ny, nz, dx, dy, dz, 0.0, dz, n6), st);
 }
 
 int demag_tensor_only(int nx, int ny, int nz, double dx, double dy, double dz, double* n6,
@@ -446,15 +557,7 @@ int demag_tensor_only(int nx, int ny, int nz, double dx, double dy, double dz, d
 // The image-summed tensor of a grid periodic along x and/or y.
 static int fill_tensor_images(int nx, int ny, int nz, double dx, double dy, double dz, int rx,
                               int ry, double* n6, hipStream_t st) {
-  TensorArgs a{};
-  a.nx = nx; a.ny = ny; a.nz = nz;
-  a.dx = dx; a.dy = dy; a.dz = dz;
-  a.dmax = std::fmax(dx, std::fmax(dy, dz));
-  const double dmin = std::fmin(dx, std::fmin(dy, dz));
-  const int n = (a.dmax / dmin <= 1.25) ? 8 : 12;
-  a.nq = 2 * n;
-  triangle_rule(n, a.qt, a.qw);
-  a.n6 = n6;
+  TensorArgs a = tensor_args(nx, ny, nz, dx, dy, dz, 0.0, dz, n6);
   a.rx = rx; a.ry = ry;
   a.bx = rx > 0 ? nx / 2 + 1 : nx;
   a.by = ry > 0 ? ny / 2 + 1 : ny;
@@ -464,34 +567,12 @@ static int fill_tensor_images(int nx, int ny, int nz, double dx, double dy, doub
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Tensor between the cells of a layer at height z_t (centre, layer 0 of the
-// grid centred at 0) and the grid's cells: k6[c][z][Y + ny - 1][X + nx - 1]
-// = N(X dx, Y dy, z_t - z dz) for |X| < nx, |Y| < ny.
-__global__ void k_tensor_layer(TensorArgs a, double zt, double* k6) {
-  const int wx = 2 * a.nx - 1, wy = 2 * a.ny - 1;
-  const long tot = (long)wx * wy * a.nz;
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= tot) return;
-  const int ix = (int)(i % wx), iy = (int)((i / wx) % wy), z = (int)(i / ((long)wx * wy));
-  double o6[6];
-  tensor_at((ix - (a.nx - 1)) * a.dx, (iy - (a.ny - 1)) * a.dy, zt - z * a.dz, a, o6);
-  for (int c = 0; c < 6; ++c) k6[(long)c * tot + i] = o6[c];
-}
-
+// Tensor between a cell of a layer at height zt (centre, layer 0 of the grid
+// centred at 0) and the cells of the grid at offsets (X dx, Y dy) >= 0:
+// k6[c][z][Y][X] = N(X dx, Y dy, zt - z dz).
 int stray_kernel_build(int nx, int ny, int nz, double dx, double dy, double dz, double zt,
                        double* k6, hipStream_t st) {
-  TensorArgs a{};
-  a.nx = nx; a.ny = ny; a.nz = nz;
-  a.dx = dx; a.dy = dy; a.dz = dz;
-  a.dmax = std::fmax(dx, std::fmax(dy, dz));
-  const double dmin = std::fmin(dx, std::fmin(dy, dz));
-  const int n = (a.dmax / dmin <= 1.25) ? 8 : 12;
-  a.nq = 2 * n;
-  triangle_rule(n, a.qt, a.qw);
-  const long tot = (long)(2 * nx - 1) * (2 * ny - 1) * nz;
-  hipLaunchKernelGGL(k_tensor_layer, dim3((unsigned)((tot + 63) / 64)), dim3(64), 0, st, a, zt,
-                     k6);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
+  return launch_tensor(tensor_args(nx, ny, nz, dx, dy, dz, zt, -dz, k6), st);
 }
 
 template <typename T>
@@ -518,13 +599,26 @@ int demag_kernel_build(const DemagPlan& p, double dx, double dy, double dz, doub
   hipLaunchKernelGGL(k_trig_table, dim3((p.Px + 255) / 256), dim3(256), 0, st, cx, sx, p.Px);
   hipLaunchKernelGGL(k_trig_table, dim3((p.Py + 255) / 256), dim3(256), 0, st, cy, sy, p.Py);
   hipLaunchKernelGGL(k_trig_table, dim3((p.Pz + 255) / 256), dim3(256), 0, st, cz, sz, p.Pz);
-  hipLaunchKernelGGL(k_trig_x, dim3((unsigned)((n1 + 255) / 256)), dim3(256), 0, st, n6, f1, cx,
-                     sx, p.nx, p.ny, p.nz, p.Px, p.Hx, p.rep[0] > 0 ? 1 : 0);
-  hipLaunchKernelGGL(k_trig_y, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, st, f1, f2, cy,
-                     sy, p.ny, p.nz, p.Py, p.Hx, p.Hy, p.rep[1] > 0 ? 1 : 0);
+  auto tiles = [](int v) { return (unsigned)((v + kTrigTile - 1) / kTrigTile); };
+  TrigArgs x{};
+  x.in = n6; x.out = f1; x.cs = cx; x.sn = sx;
+  x.M = p.nz * p.ny; x.N = p.Hx; x.ldk = p.nx;
+  x.per = p.rep[0] > 0 ? 1 : 0;
+  x.K = x.per ? p.nx / 2 + 1 : p.nx;
+  x.P = p.Px; x.nk = p.nx; x.nz = 1;
+  hipLaunchKernelGGL(k_trig_gemm<false>, dim3(tiles(x.M), tiles(x.N), 6), dim3(256), 0, st, x);
+  TrigArgs y{};
+  y.in = f1; y.out = f2; y.cs = cy; y.sn = sy;
+  y.M = p.Hx; y.N = p.Hy; y.ldk = p.ny;
+  y.per = p.rep[1] > 0 ? 1 : 0;
+  y.K = y.per ? p.ny / 2 + 1 : p.ny;
+  y.P = p.Py; y.nk = p.ny; y.nz = p.nz;
+  hipLaunchKernelGGL(k_trig_gemm<true>, dim3(tiles(y.M), tiles(y.N), 6 * p.nz), dim3(256), 0, st,
+                     y);
   const double scale = -kMu0 / ((double)p.Px * p.Py * p.Pz);
-  hipLaunchKernelGGL((k_trig_z<T>), dim3((unsigned)((p.k_elems + 255) / 256)), dim3(256), 0, st,
-                     f2, kout, (double*)nullptr, cz, sz, p.nz, p.Pz, p.Hx, p.Hy, p.Hz, scale);
+  const long plane = (long)p.Hx * p.Hy;
+  hipLaunchKernelGGL((k_trig_z<T>), dim3((unsigned)((plane + 255) / 256), 6), dim3(256), 0, st, f2,
+                     kout, cz, sz, p.nz, p.Pz, plane, p.Hz, scale);
   const hipError_t e = hipStreamSynchronize(st);
   (void)hipFree(f1);
   (void)hipFree(f2);
