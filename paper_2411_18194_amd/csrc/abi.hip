@@ -69,6 +69,39 @@ Prof::~Prof() {
 
 using namespace mmp;
 
+// Streams of destroyed grids, kept for the next ones (creating one takes
+// 175 us): at most kIdleStreams per process, each idle when it is given back.
+// Taken and given under the device lock.
+namespace {
+constexpr size_t kIdleStreams = 16;
+struct IdleStream { int dev; hipStream_t st; };
+std::vector<IdleStream> g_idle;
+
+hipError_t stream_take(hipStream_t* out) {
+  DeviceLock lk(device_mutex());
+  int dev = 0;
+  (void)hipGetDevice(&dev);
+  for (size_t i = 0; i < g_idle.size(); ++i)
+    if (g_idle[i].dev == dev) {
+      *out = g_idle[i].st;
+      g_idle.erase(g_idle.begin() + i);
+      return hipSuccess;
+    }
+  return hipStreamCreateWithFlags(out, hipStreamNonBlocking);
+}
+
+void stream_give(hipStream_t st) {
+  DeviceLock lk(device_mutex());
+  int dev = -1;
+  if (g_idle.size() < kIdleStreams && hipStreamSynchronize(st) == hipSuccess &&
+      hipStreamGetDevice(st, &dev) == hipSuccess) {
+    g_idle.push_back({dev, st});
+    return;
+  }
+  (void)hipStreamDestroy(st);
+}
+}  // namespace
+
 #define MMP_GUARD_BEGIN try {
 #define MMP_GUARD_END                                    \
   }                                                      \
@@ -126,10 +159,7 @@ mmp_status mmp_grid_destroy(mmp_grid g) {
     (void)hipStreamSynchronize(g->impl->stream);
     hipStream_t own = g->impl->own_stream;
     g->impl.reset();
-    if (own) {
-      DeviceLock lk(device_mutex());
-      (void)hipStreamDestroy(own);
-    }
+    if (own) stream_give(own);
   }
   delete g;
   return MMP_OK;
@@ -205,21 +235,14 @@ mmp_status mmp_set_params(mmp_grid g, const mmp_params* p) {
       (void)hipStreamSynchronize(g->impl->stream);
       hipStream_t own = g->impl->own_stream;
       g->impl.reset();
-      if (own) {
-        DeviceLock lk(device_mutex());
-        (void)hipStreamDestroy(own);
-      }
+      if (own) stream_give(own);
     }
     GridBase* b = make_grid(p->precision);
     b->nx = g->nx; b->ny = g->ny; b->nz = g->nz;
     for (int i = 0; i < 3; ++i) b->d[i] = g->d[i];
     b->N = N;
     b->precision = p->precision;
-    hipError_t se;
-    {
-      DeviceLock lk(device_mutex());
-      se = hipStreamCreateWithFlags(&b->own_stream, hipStreamNonBlocking);
-    }
+    const hipError_t se = stream_take(&b->own_stream);
     if (se != hipSuccess) {
       delete b;
       set_error("stream creation failed");

@@ -93,10 +93,12 @@ double demag_tune(DemagPlan* p, const DemagBufs<T>& b, const Table<T>* tbl, T ms
                   int nsub, hipStream_t st, T ms2 = T(0));
 
 // FP64 tensor on the non-negative offsets and its transformed octant
-// spectrum.  n6 (6*N doubles, device) receives the tensor; kout the scaled
-// spectrum (k_elems values of type T, device).
+// spectrum: kout receives the scaled spectrum (k_elems values of type T,
+// device); scratch holds demag_build_doubles(p) doubles (device).  Returns
+// after the build has finished.
+size_t demag_build_doubles(const DemagPlan& p);
 template <typename T>
-int demag_kernel_build(const DemagPlan& p, double dx, double dy, double dz, double* n6,
+int demag_kernel_build(const DemagPlan& p, double dx, double dy, double dz, double* scratch,
                        T* kout, hipStream_t st);
 
 // The tensor from the cells of the grid to a layer of cells centred at

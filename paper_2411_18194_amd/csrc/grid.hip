@@ -114,19 +114,44 @@ template <typename T>
 struct Buf {
   T* p = nullptr;
   size_t n = 0;
+  bool own = true;   // false: part of an Arena's block
   int alloc(size_t count) {
     n = count;
+    own = true;
     if (count == 0) return 0;
     DeviceLock lk(device_mutex());
     return hipMalloc(&p, count * sizeof(T)) == hipSuccess ? 0 : -1;
   }
   void release() {
-    if (p) {
+    if (p && own) {
       DeviceLock lk(device_mutex());
       (void)hipFree(p);
     }
     p = nullptr;
     n = 0;
+  }
+};
+
+// Many buffers in one device allocation.  A call of hipMalloc takes about
+// 30 us and one of hipFree 11, whatever the size: the 28 buffers of a grid
+// were 1.2 ms of the 1.7 that setting one up for a single field took.  `place`
+// is called for every buffer twice, first to add the sizes up, then (after
+// `alloc`) to hand out the addresses.
+struct Arena {
+  char* base = nullptr;
+  size_t off = 0;
+  template <typename U>
+  void place(Buf<U>& b, size_t count) {
+    b.p = base && count ? reinterpret_cast<U*>(base + off) : nullptr;
+    b.n = count;
+    b.own = false;
+    off += (count * sizeof(U) + 255) / 256 * 256;
+  }
+  int alloc(Buf<char>& block) {
+    if (block.alloc(off)) return -1;
+    base = block.p;
+    off = 0;
+    return 0;
   }
 };
 
@@ -149,9 +174,11 @@ struct Grid final : GridBase {
   Buf<cpx<T>> S1, S2, tw;
   Buf<int> pos;
   Buf<T> K;
+  Buf<char> mem, fft_mem;  // the blocks that hold the buffers above
   bool demag_built = false;
   // layout of the current allocation
   bool allocated = false;
+  int a_rk = -1;           // pair in the device table
   int a_nsub = 0, a_elastic = 0, a_demag = 0, a_pbc[2] = {0, 0};
   bool k1_valid = false;
   double t_host = 0.0, dt_host = 0.0;
@@ -174,7 +201,7 @@ struct Grid final : GridBase {
   void free_all() {
     drop_graphs();
     for (auto* b : {&y[0], &y[1], &sa, &sb, &u[0], &u[1], &v[0], &v[1], &usa, &usb, &vsa, &vsb,
-                    &eps, &epsv, &sig, &Bd, &gax, &K, &evalb})
+                    &eps, &epsv, &sig, &Bd, &gax, &K})
       b->release();
     for (int i = 0; i < 7; ++i) { k[i].release(); ku[i].release(); kv[i].release(); }
     gid.release();
@@ -184,6 +211,8 @@ struct Grid final : GridBase {
     sctrl.release();
     sres.release();
     S1.release(); S2.release(); tw.release(); pos.release();
+    mem.release();
+    fft_mem.release();
     plan = DemagPlan{};
     allocated = false;
     demag_built = false;
@@ -203,29 +232,40 @@ struct Grid final : GridBase {
     free_all();
     const int ns = p.nsub;
     const size_t nm = (size_t)ns * 3 * N;
-    int rc = 0;
-    rc |= y[0].alloc(nm); rc |= y[1].alloc(nm); rc |= sa.alloc(nm); rc |= sb.alloc(nm);
-    for (int i = 0; i < 7; ++i) rc |= k[i].alloc(nm);
-    if (p.elastic) {
-      const size_t n3 = 3 * (size_t)N;
-      rc |= u[0].alloc(n3); rc |= u[1].alloc(n3); rc |= v[0].alloc(n3); rc |= v[1].alloc(n3);
-      rc |= usa.alloc(n3); rc |= usb.alloc(n3); rc |= vsa.alloc(n3); rc |= vsb.alloc(n3);
-      for (int i = 0; i < 7; ++i) { rc |= ku[i].alloc(n3); rc |= kv[i].alloc(n3); }
-      rc |= eps.alloc(6 * (size_t)N);
-      rc |= epsv.alloc(6 * (size_t)N);
-      rc |= sig.alloc(6 * (size_t)N);
-    }
     // partial sums for the smallest z chunk (one plane per thread)
     const int nbx = (nx + kTileX - 1) / kTileX, nby = (ny + kTileY - 1) / kTileY;
     const int nb_max = round_up(nbx * nby * nz, 8);
-    rc |= errpart.alloc(nb_max);
-    rc |= epart.alloc((size_t)nb_max * kNE);
-    rc |= eout.alloc(kNE);
     nsamp_blk = (int)std::min<long>(256, (N + 255) / 256);
-    rc |= spart.alloc((size_t)nsamp_blk * 9);
-    rc |= elpart.alloc((N + 255) / 256);
-    rc |= dtbl.alloc(1);
-    rc |= dctrl.alloc(1);
+    auto layout = [&](Arena& a) {
+      for (auto* b : {&y[0], &y[1], &sa, &sb}) a.place(*b, nm);
+      for (int i = 0; i < 7; ++i) a.place(k[i], nm);
+      if (p.elastic) {
+        const size_t n3 = 3 * (size_t)N;
+        for (auto* b : {&u[0], &u[1], &v[0], &v[1], &usa, &usb, &vsa, &vsb}) a.place(*b, n3);
+        for (int i = 0; i < 7; ++i) { a.place(ku[i], n3); a.place(kv[i], n3); }
+        for (auto* b : {&eps, &epsv, &sig}) a.place(*b, 6 * (size_t)N);
+      }
+      if (p.demag) a.place(Bd, 3 * (size_t)N);
+      a.place(errpart, nb_max);
+      a.place(epart, (size_t)nb_max * kNE);
+      a.place(eout, kNE);
+      a.place(spart, (size_t)nsamp_blk * 9);
+      a.place(elpart, (N + 255) / 256);
+      a.place(dtbl, 1);
+      a.place(dctrl, 1);
+    };
+    int rc = 0;
+    {
+      Arena a;
+      layout(a);
+      rc = a.alloc(mem);
+      if (!rc) layout(a);
+    }
+    if (rc) {
+      set_error("device allocation failed");
+      free_all();
+      return MMP_E_NOMEM;
+    }
     bool cached = false;
     DemagPlan np;
     {
@@ -246,9 +286,8 @@ struct Grid final : GridBase {
         free_all();
         return MMP_E_ARG;
       }
-      rc |= Bd.alloc(3 * (size_t)N);
       db.Bd = Bd.p;
-      if (!rc) rc |= install_plan(np);
+      rc = install_plan(np);
     }
     if (rc) {
       set_error("device allocation failed");
@@ -261,6 +300,8 @@ struct Grid final : GridBase {
     }
     // pointer table
     Table<T> t{};
+    t.ns = RK::t[p.solver].ns;
+    t.rk = a_rk = p.solver;
     t.yn = y[0].p; t.ynew = y[1].p; t.sa = sa.p; t.sb = sb.p;
     for (int i = 0; i < 7; ++i) t.k[i] = k[i].p;
     if (p.elastic) {
@@ -328,13 +369,18 @@ struct Grid final : GridBase {
                       np.s1_elems == plan.s1_elems && np.s2_elems == plan.s2_elems;
     if (!same) {
       if (stream) MMP_HIP_TRY(hipStreamSynchronize(stream));
-      S1.release(); S2.release(); K.release(); tw.release(); pos.release();
-      int rc = 0;
-      rc |= S1.alloc(np.s1_elems);
-      rc |= S2.alloc(np.s2_elems);
-      rc |= K.alloc(np.k_elems);
-      rc |= tw.alloc(demag_tw_elems(np));
-      rc |= pos.alloc((size_t)np.Px + np.Py + np.Pz);
+      fft_mem.release();
+      auto layout = [&](Arena& a) {
+        a.place(S1, np.s1_elems);
+        a.place(S2, np.s2_elems);
+        a.place(K, np.k_elems);
+        a.place(tw, demag_tw_elems(np));
+        a.place(pos, (size_t)np.Px + np.Py + np.Pz);
+      };
+      Arena a;
+      layout(a);
+      const int rc = a.alloc(fft_mem);
+      if (!rc) layout(a);
       if (rc) {
         S1.release(); S2.release(); K.release(); tw.release(); pos.release();
         plan = DemagPlan{};
@@ -378,11 +424,11 @@ struct Grid final : GridBase {
   // twiddles and the transformed kernel for the current pads
   int build_demag() {
     DeviceLock lk(device_mutex());
-    double* n6 = nullptr;
-    MMP_HIP_TRY(hipMalloc(&n6, 6 * (size_t)N * sizeof(double)));
+    double* scratch = nullptr;
+    MMP_HIP_TRY(hipMalloc(&scratch, demag_build_doubles(plan) * sizeof(double)));
     build_all_twiddles(db, plan);
-    const int rc = demag_kernel_build<T>(plan, d[0], d[1], d[2], n6, db.K, stream);
-    (void)hipFree(n6);
+    const int rc = demag_kernel_build<T>(plan, d[0], d[1], d[2], scratch, db.K, stream);
+    (void)hipFree(scratch);
     if (rc) {
       set_error("demag kernel build failed");
       return MMP_E_HIP;
@@ -714,8 +760,9 @@ struct Grid final : GridBase {
     fa = a;
     set_field_zc(field_zc > 0 ? field_zc : default_field_zc());
     // the pair in use: its stage count and index, read by every stage kernel
-    {
+    if (a_rk != p.solver) {
       const int v[2] = {RK::t[p.solver].ns, p.solver};
+      a_rk = p.solver;
       MMP_HIP_TRY(hipMemcpy(reinterpret_cast<char*>(dtbl.p) + offsetof(Table<T>, ns), v,
                             sizeof(v), hipMemcpyHostToDevice));
     }
@@ -751,9 +798,12 @@ struct Grid final : GridBase {
     // the pointer table may have been swapped by earlier steps: reset it
     Table<T> tb{};
     MMP_HIP_TRY(hipMemcpy(&tb, dtbl.p, sizeof(tb), hipMemcpyDeviceToHost));
-    std::vector<T> tmp(nm);
-    for (size_t i = 0; i < nm; ++i) tmp[i] = (T)m[i];
-    MMP_HIP_TRY(hipMemcpy(tb.yn, tmp.data(), nm * sizeof(T), hipMemcpyHostToDevice));
+    if constexpr (sizeof(T) == sizeof(double)) {
+      MMP_HIP_TRY(hipMemcpy(tb.yn, m, nm * sizeof(T), hipMemcpyHostToDevice));
+    } else {
+      std::vector<T> tmp(m, m + nm);
+      MMP_HIP_TRY(hipMemcpy(tb.yn, tmp.data(), nm * sizeof(T), hipMemcpyHostToDevice));
+    }
     if (p.elastic) {
       std::vector<T> t3(3 * (size_t)N);
       for (size_t i = 0; i < t3.size(); ++i) t3[i] = uu ? (T)uu[i] : T(0);
@@ -801,6 +851,18 @@ struct Grid final : GridBase {
     return 0;
   }
 
+  // n values of a device buffer as FP64
+  static int to_host(const T* src, double* dst, size_t n) {
+    if constexpr (sizeof(T) == sizeof(double)) {
+      MMP_HIP_TRY(hipMemcpy(dst, src, n * sizeof(T), hipMemcpyDeviceToHost));
+    } else {
+      std::vector<T> tmp(n);
+      MMP_HIP_TRY(hipMemcpy(tmp.data(), src, n * sizeof(T), hipMemcpyDeviceToHost));
+      for (size_t i = 0; i < n; ++i) dst[i] = (double)tmp[i];
+    }
+    return 0;
+  }
+
   int get_state(double* m, double* uu, double* vv, double* t, double* dt) override {
     MMP_HIP_TRY(hipStreamSynchronize(stream));
     Table<T> tb{};
@@ -808,10 +870,7 @@ struct Grid final : GridBase {
     Ctrl c{};
     MMP_HIP_TRY(hipMemcpy(&c, dctrl.p, sizeof(c), hipMemcpyDeviceToHost));
     if (m) {
-      const size_t nm = (size_t)p.nsub * 3 * N;
-      std::vector<T> tmp(nm);
-      MMP_HIP_TRY(hipMemcpy(tmp.data(), tb.yn, nm * sizeof(T), hipMemcpyDeviceToHost));
-      for (size_t i = 0; i < nm; ++i) m[i] = (double)tmp[i];
+      if (int rc = to_host(tb.yn, m, (size_t)p.nsub * 3 * N)) return rc;
     }
     if (p.elastic && (uu || vv)) {
       std::vector<T> t3(3 * (size_t)N);
@@ -1124,12 +1183,13 @@ struct Grid final : GridBase {
     return 0;
   }
 
+  // Field outputs are formed in the stage buffer sb: it holds stage inputs
+  // within an attempt and nothing between calls (a run's first stage input
+  // is formed anew in sa), and the table never swaps it.
   int eval(uint32_t mask, double* b, double* e) override {
     int rc = ensure_ready();
     if (rc) return rc;
     const size_t nm = (size_t)p.nsub * 3 * N;
-    Buf<T> bout;
-    if (b && bout.alloc(nm)) { set_error("device allocation failed"); return MMP_E_NOMEM; }
     if (p.elastic) {
       ElasticArgs<T> ee = ea;
       ee.stage = 1;
@@ -1145,7 +1205,7 @@ struct Grid final : GridBase {
     a.mask = mask & MMP_T_ALL;
     a.add_zl = (mask & MMP_T_ZL) ? 1 : 0;
     a.out_torque = (mask & MMP_OUT_TORQUE) ? 1 : 0;
-    a.bout = b ? bout.p : nullptr;
+    a.bout = b ? sb.p : nullptr;
     a.epart = epart.p;
     launch_field<T>(a, true, stream, &prof);
     launch_energy_final(epart.p, nblk, eout.p, stream);
@@ -1159,10 +1219,7 @@ struct Grid final : GridBase {
     MMP_HIP_TRY(hipGetLastError());
     MMP_HIP_TRY(hipStreamSynchronize(stream));
     if (b) {
-      std::vector<T> tmp(nm);
-      MMP_HIP_TRY(hipMemcpy(tmp.data(), bout.p, nm * sizeof(T), hipMemcpyDeviceToHost));
-      for (size_t i = 0; i < nm; ++i) b[i] = (double)tmp[i];
-      bout.release();
+      if ((rc = to_host(sb.p, b, nm))) return rc;
     }
     if (e) {
       MMP_HIP_TRY(hipMemcpy(e, eout.p, kNE * sizeof(double), hipMemcpyDeviceToHost));
@@ -1178,9 +1235,7 @@ struct Grid final : GridBase {
   }
 
   // B of the selected terms (or the torque) in the grid's precision, widened
-  // into the caller's FP64 device buffer; the grid keeps the precision-sized
-  // output buffer from the first call on
-  Buf<T> evalb;
+  // into the caller's FP64 device buffer
   int eval_device(uint32_t mask, double* b) override {
     int rc = ensure_ready();
     if (rc) return rc;
@@ -1190,11 +1245,7 @@ struct Grid final : GridBase {
     if constexpr (sizeof(T) == sizeof(double)) {
       out = reinterpret_cast<T*>(b);
     } else {
-      if (evalb.n < nm) {
-        evalb.release();
-        if (evalb.alloc(nm)) { set_error("device allocation failed"); return MMP_E_NOMEM; }
-      }
-      out = evalb.p;
+      out = sb.p;
     }
     if (p.elastic) {
       ElasticArgs<T> ee = ea;

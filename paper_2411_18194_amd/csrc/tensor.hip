@@ -575,23 +575,32 @@ int stray_kernel_build(int nx, int ny, int nz, double dx, double dy, double dz, 
   return launch_tensor(tensor_args(nx, ny, nz, dx, dy, dz, zt, -dz, k6), st);
 }
 
+// scratch of demag_kernel_build: the tensor, its x and its x-y sums, trig tables
+static void build_sizes(const DemagPlan& p, size_t* n0, size_t* n1, size_t* n2, size_t* nt) {
+  *n0 = (size_t)6 * p.nx * p.ny * p.nz;
+  *n1 = (size_t)6 * p.nz * p.ny * p.Hx;
+  *n2 = (size_t)6 * p.nz * p.Hy * p.Hx;
+  *nt = (size_t)2 * (p.Px + p.Py + p.Pz);
+}
+size_t demag_build_doubles(const DemagPlan& p) {
+  size_t n0, n1, n2, nt;
+  build_sizes(p, &n0, &n1, &n2, &nt);
+  return n0 + n1 + n2 + nt;
+}
+
 template <typename T>
-int demag_kernel_build(const DemagPlan& p, double dx, double dy, double dz, double* n6, T* kout,
-                       hipStream_t st) {
+int demag_kernel_build(const DemagPlan& p, double dx, double dy, double dz, double* scratch,
+                       T* kout, hipStream_t st) {
+  size_t n0, n1, n2, nt;
+  build_sizes(p, &n0, &n1, &n2, &nt);
+  double* n6 = scratch;
+  double* f1 = n6 + n0;
+  double* f2 = f1 + n1;
+  double* tabs = f2 + n2;
   if (p.rep[0] > 0 || p.rep[1] > 0) {
     if (fill_tensor_images(p.nx, p.ny, p.nz, dx, dy, dz, p.rep[0], p.rep[1], n6, st)) return -1;
   } else if (fill_tensor(p.nx, p.ny, p.nz, dx, dy, dz, n6, st)) {
     return -1;
-  }
-  DeviceLock lk(device_mutex());
-  double *f1 = nullptr, *f2 = nullptr, *tabs = nullptr;
-  const size_t n1 = (size_t)6 * p.nz * p.ny * p.Hx;
-  const size_t n2 = (size_t)6 * p.nz * p.Hy * p.Hx;
-  const int Pm = p.Px + p.Py + p.Pz;
-  if (hipMalloc(&f1, n1 * sizeof(double)) != hipSuccess) return -2;
-  if (hipMalloc(&f2, n2 * sizeof(double)) != hipSuccess) { (void)hipFree(f1); return -2; }
-  if (hipMalloc(&tabs, (size_t)2 * Pm * sizeof(double)) != hipSuccess) {
-    (void)hipFree(f1); (void)hipFree(f2); return -2;
   }
   double* cx = tabs;            double* sx = cx + p.Px;
   double* cy = sx + p.Px;       double* sy = cy + p.Py;
@@ -619,11 +628,7 @@ int demag_kernel_build(const DemagPlan& p, double dx, double dy, double dz, doub
   const long plane = (long)p.Hx * p.Hy;
   hipLaunchKernelGGL((k_trig_z<T>), dim3((unsigned)((plane + 255) / 256), 6), dim3(256), 0, st, f2,
                      kout, cz, sz, p.nz, p.Pz, plane, p.Hz, scale);
-  const hipError_t e = hipStreamSynchronize(st);
-  (void)hipFree(f1);
-  (void)hipFree(f2);
-  (void)hipFree(tabs);
-  return e == hipSuccess ? 0 : -1;
+  return hipStreamSynchronize(st) == hipSuccess ? 0 : -1;
 }
 
 template int demag_kernel_build<float>(const DemagPlan&, double, double, double, double*, float*,
