@@ -1,0 +1,204 @@
+// Device side of the elastic stages shared by the elastic kernels and the
+// field kernel that carries the force (paper, Methods "Elasticity" and
+// "Magnetoelasticity").
+//
+// Derivatives: 4th-order central (-f2 + 8 f1 - 8 f-1 + f-2)/(12 d) in the
+// bulk, 2nd-order central one cell in from a face, 1st-order one-sided on a
+// face cell (the paper uses lower-order schemes near and at boundaries); an
+// axis with one cell has no derivative.
+#pragma once
+
+#include "elastic.h"
+
+namespace mmp {
+
+// The scheme of one cell along one axis: df = w1 (f[p1] - f[m1]) + w2 (f[p2] -
+// f[m2]) at offsets clamped to the axis, so that the same two differences
+// serve every position: (8, -1)/12d in the bulk, (1, 0)/2d one cell in, and
+// on a face, where the clamped neighbour is the cell itself, (1, 0)/d.  The
+// weights are formed once per cell and axis; a division per derivative and
+// scheme (108 divisions per cell of the force) was most of that kernel.
+template <typename T>
+struct Diff {
+  int m2, m1, p1, p2;
+  T w1, w2;
+};
+template <typename T>
+__device__ __forceinline__ Diff<T> diff_at(int i, int n, int stride, T h) {
+  Diff<T> d;
+  d.m2 = (max(i - 2, 0) - i) * stride;
+  d.m1 = (max(i - 1, 0) - i) * stride;
+  d.p1 = (min(i + 1, n - 1) - i) * stride;
+  d.p2 = (min(i + 2, n - 1) - i) * stride;
+  const bool face = i == 0 || i == n - 1, in1 = i == 1 || i == n - 2;
+  const T r = T(1) / h;
+  d.w1 = face ? r : (in1 ? T(0.5) * r : T(2.0 / 3.0) * r);
+  d.w2 = face || in1 ? T(0) : -r * T(1.0 / 12.0);
+  return d;
+}
+template <typename T>
+__device__ __forceinline__ T deriv(gcptr<T> f, const Diff<T>& d) {
+  return d.w1 * (f[d.p1] - f[d.m1]) + d.w2 * (f[d.p2] - f[d.m2]);
+}
+
+template <typename T>
+__device__ __forceinline__ const T* u_in(const Table<T>* t, int s) {
+  if (s == 0 || s == 1) return t->un;
+  if (s == t->ns) return t->unew;
+  return (s & 1) ? t->usb : t->usa;
+}
+template <typename T>
+__device__ __forceinline__ const T* v_in(const Table<T>* t, int s) {
+  if (s == 0 || s == 1) return t->vn;
+  if (s == t->ns) return t->vnew;
+  return (s & 1) ? t->vsb : t->vsa;
+}
+template <typename T>
+__device__ __forceinline__ T* u_out(const Table<T>* t, int s) {
+  const int n = s + 1;
+  if (n == t->ns) return t->unew;
+  return (n & 1) ? t->usb : t->usa;
+}
+template <typename T>
+__device__ __forceinline__ T* v_out(const Table<T>* t, int s) {
+  const int n = s + 1;
+  if (n == t->ns) return t->vnew;
+  return (n & 1) ? t->vsb : t->vsa;
+}
+
+// cell of thread t in 64x4 tile w of the plane-major tiles
+__device__ __forceinline__ bool tile_cell(int w, int nbx, int nby, int nx, int ny, int* x, int* y,
+                                          int* z) {
+  const int tx = w % nbx, r = w / nbx;
+  *x = tx * 64 + (int)(threadIdx.x & 63);
+  *y = (r % nby) * 4 + (int)(threadIdx.x >> 6);
+  *z = r / nby;
+  return *x < nx && *y < ny;
+}
+
+// y_n + sum_{j<NJ} c_j k_j at one cell, every load issued before the first sum
+template <typename T, int NJ>
+__device__ __forceinline__ void stage_sum(const gcptr<T> yn, const gcptr<T>* k, const T* c, long i,
+                                          long N, T* acc) {
+  T kv[NJ > 0 ? NJ : 1][3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) acc[q] = yn[i + q * N];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) kv[j][q] = k[j][i + q * N];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int q = 0; q < 3; ++q) acc[q] += c[j] * kv[j][q];
+}
+template <typename T>
+__device__ __forceinline__ void stage_sum_n(int nj, const gcptr<T> yn, const gcptr<T>* k,
+                                            const T* c, long i, long N, T* acc) {
+  switch (nj) {
+    case 0: stage_sum<T, 0>(yn, k, c, i, N, acc); break;
+    case 1: stage_sum<T, 1>(yn, k, c, i, N, acc); break;
+    case 2: stage_sum<T, 2>(yn, k, c, i, N, acc); break;
+    case 3: stage_sum<T, 3>(yn, k, c, i, N, acc); break;
+    case 4: stage_sum<T, 4>(yn, k, c, i, N, acc); break;
+    default: stage_sum<T, 5>(yn, k, c, i, N, acc); break;
+  }
+}
+
+// Tile w of the force: divergence of the stress, magnetoelastic force of Eq.
+// 8 per sublattice, k_u and k_v, and the next stage's u and v.
+template <typename T>
+__device__ __forceinline__ void force_block(const ElasticArgs<T>& a, int w) {
+  int x, y, z;
+  if (!tile_cell(w, a.nbx, a.nby, a.nx, a.ny, &x, &y, &z)) return;
+  const long N = a.N;
+  const long i = ((long)z * a.ny + y) * a.nx + x;
+  const int stage = a.stage;
+  const Diff<T> dx = diff_at<T>(x, a.nx, 1, a.dx), dy = diff_at<T>(y, a.ny, a.nx, a.dy),
+                dz = diff_at<T>(z, a.nz, a.nx * a.ny, a.dz);
+  const bool flat = a.nz == 1;   // no derivative along z
+  const gcptr<T> sg = (gcptr<T>)a.sig + i;
+  T f[3];
+  f[0] = deriv<T>(sg, dx) + deriv<T>(sg + 3 * N, dy);
+  f[1] = deriv<T>(sg + 3 * N, dx) + deriv<T>(sg + N, dy);
+  f[2] = deriv<T>(sg + 4 * N, dx) + deriv<T>(sg + 5 * N, dy);
+  if (!flat) {
+    f[0] += deriv<T>(sg + 4 * N, dz);
+    f[1] += deriv<T>(sg + 5 * N, dz);
+    f[2] += deriv<T>(sg + 2 * N, dz);
+  }
+  const gcptr<T> m = (gcptr<T>)stage_in(a.tbl, stage) + i;
+  for (int s = 0; s < a.nsub; ++s) {
+    if (!a.mel[s]) continue;
+    const gcptr<T> ms = m + (long)s * 3 * N;
+    T mv[3], g[3][3];  // g[j][c] = d_j m_c
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      mv[c] = ms[c * N];
+      g[0][c] = deriv<T>(ms + c * N, dx);
+      g[1][c] = deriv<T>(ms + c * N, dy);
+      g[2][c] = T(0);
+    }
+    if (!flat) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) g[2][c] = deriv<T>(ms + c * N, dz);
+    }
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      T acc = T(2) * a.B1[s] * mv[r] * g[r][r];
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (j != r) acc += a.B2[s] * (mv[r] * g[j][j] + mv[j] * g[j][r]);
+      f[r] += acc;
+    }
+  }
+  const gcptr<T> v = (gcptr<T>)v_in(a.tbl, stage) + i;
+  T ku[3], kv[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    ku[c] = v[c * N];
+    kv[c] = (f[c] - a.eta * ku[c]) * a.inv_rho;
+  }
+  const gptr<T> KU = (gptr<T>)a.tbl->ku[stage - 1] + i, KV = (gptr<T>)a.tbl->kv[stage - 1] + i;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    KU[c * N] = ku[c];
+    KV[c * N] = kv[c];
+  }
+  const double h = a.ctrl->h;
+  const RKTab& rk = RK::t[a.tbl->rk];
+  const int nj = stage - 1;
+  if (stage < a.tbl->ns) {
+    T c[5];
+    gcptr<T> pu[5], pv[5];
+    for (int j = 0; j < 5; ++j) {
+      c[j] = T(0);
+      pu[j] = pv[j] = nullptr;
+      if (j < nj) {
+        c[j] = (T)(rk.a[stage][j] * h);
+        pu[j] = (gcptr<T>)a.tbl->ku[j];
+        pv[j] = (gcptr<T>)a.tbl->kv[j];
+      }
+    }
+    T au[3], av[3];
+    stage_sum_n<T>(nj, (gcptr<T>)a.tbl->un, pu, c, i, N, au);
+    stage_sum_n<T>(nj, (gcptr<T>)a.tbl->vn, pv, c, i, N, av);
+    const gptr<T> uo = (gptr<T>)u_out(a.tbl, stage) + i, vo = (gptr<T>)v_out(a.tbl, stage) + i;
+    const T cs = (T)(rk.a[stage][nj] * h);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      uo[q * N] = au[q] + cs * ku[q];
+      vo[q * N] = av[q] + cs * kv[q];
+    }
+  } else if (a.fuse2) {
+    const gcptr<T> u = (gcptr<T>)u_in(a.tbl, stage) + i;
+    const T c21 = (T)(rk.a[1][0] * h);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      ((gptr<T>)a.tbl->usa)[i + c * N] = u[c * N] + c21 * ku[c];
+      ((gptr<T>)a.tbl->vsa)[i + c * N] = ku[c] + c21 * kv[c];
+    }
+  }
+}
+
+}  // namespace mmp

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.h"
+#include "elastic.h"
 #include "prof.h"
 
 namespace mmp {
@@ -67,6 +68,12 @@ struct FieldArgs {
 
 template <typename T>
 void launch_field(const FieldArgs<T>& a, bool eval, hipStream_t st, Prof* prof);
+
+// one stage's field and elastic force (one launch where the plain field
+// kernel applies)
+template <typename T>
+void launch_field_force(const FieldArgs<T>& a, const ElasticArgs<T>& e, hipStream_t st,
+                        Prof* prof);
 
 // Per-grid pointers of a batch for the step controller and the stage-2
 // combination (one entry per grid).

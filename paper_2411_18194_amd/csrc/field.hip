@@ -22,6 +22,7 @@
 // periodic axis (x or y) the neighbour of a boundary cell is the cell at the
 // opposite end, for every stencil, and no boundary condition applies.
 #include "field.h"
+#include "elastic_dev.h"
 
 namespace mmp {
 
@@ -216,7 +217,8 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         cur[s][c] = m[s * N3 + c * N + i0];
-        zm[s][c] = m[s * N3 + c * N + i0 + dz0];
+        // (a single layer has no other: its z neighbour is the cell itself)
+        zm[s][c] = a.nz > 1 ? m[s * N3 + c * N + i0 + dz0] : cur[s][c];
       }
     for (int z = z0; z < z1; ++z) {
       const long i = (long)z * plane + col;
@@ -241,7 +243,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) zp[s][c] = m[s * N3 + c * N + i + dzp];
+        for (int c = 0; c < 3; ++c) zp[s][c] = a.nz > 1 ? m[s * N3 + c * N + i + dzp] : cur[s][c];
       T xm[NSUB][3], xp[NSUB][3], ym[NSUB][3], yp[NSUB][3];
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
@@ -555,13 +557,14 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
                 v[c] = acc;
               }
             } else {
+              // several sublattices: the slopes of one sublattice at a
+              // time, all loaded before the first is summed (a load and a
+              // wait per slope cost 3.6 us of dependent trips at stage 6;
+              // holding both sublattices' slopes from the top of the
+              // iteration costs more waves than it hides)
+              stage_sum_n<T>(stage - 1, yn, kin, ca, base, N, v);
 #pragma unroll
-              for (int c = 0; c < 3; ++c) {
-                T acc = yn[base + c * N];
-                for (int j = 0; j < stage - 1; ++j) acc += ca[j] * kin[j][base + c * N];
-                acc += ca[stage - 1] * tau[c];
-                v[c] = acc;
-              }
+              for (int c = 0; c < 3; ++c) v[c] += ca[stage - 1] * tau[c];
             }
             const T inv = T(1) / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
             ynext[base] = v[0] * inv;
@@ -581,11 +584,18 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
                 ev[c] = acc + ew[ns - 1] * (double)tau[c];
               }
             } else {
+              // (a slope of weight zero reads the first one again)
+              T kv[6][3];
+#pragma unroll
+              for (int j = 0; j < 6; ++j)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) kv[j][c] = kslot[j][base + c * N];
 #pragma unroll
               for (int c = 0; c < 3; ++c) {
                 double acc = 0.0;
-                for (int j = 0; j < ns - 1; ++j)
-                  if (ew[j] != 0.0) acc += ew[j] * (double)kin[j][base + c * N];
+#pragma unroll
+                for (int j = 0; j < 6; ++j)
+                  if (j < ns - 1 && ew[j] != 0.0) acc += ew[j] * (double)kv[j][c];
                 ev[c] = acc + ew[ns - 1] * (double)tau[c];
               }
             }
@@ -644,6 +654,19 @@ __global__ __launch_bounds__(256) void k_field(const FieldArgs<T> a) {
   field_block<T, NSUB, EVAL, GDMI, GBX>(a, xcd_remap(blockIdx.x, a.nb_pad), a.stage, a.fuse2);
 }
 
+// The field and the elastic force of one stage in one launch: both read the
+// stage input, strain and stress and write different things, and each alone
+// is a few microseconds of latency on a grid that leaves the chip half
+// empty.  The force's blocks come first (they take longer).
+template <typename T, int NSUB>
+__global__ __launch_bounds__(256) void k_field_force(const FieldArgs<T> a, const ElasticArgs<T> e,
+                                                     int nforce) {
+  if (ctrl_stopped(a.ctrl)) return;
+  const int b = (int)blockIdx.x;
+  if (b < nforce) force_block<T>(e, b);
+  else field_block<T, NSUB, false>(a, xcd_remap(b - nforce, a.nb_pad), a.stage, a.fuse2);
+}
+
 // Many grids in one launch: block b runs block work[b].y of grid work[b].x
 // (the argument blocks live in device memory); a grid whose run is over
 // skips its blocks.
@@ -700,6 +723,23 @@ void launch_field(const FieldArgs<T>& a, bool eval, hipStream_t st, Prof* prof) 
   ProfScope ps(prof, P_FIELD, st);
   if (eval) launch_field_var<T, true>(a, st);
   else launch_field_var<T, false>(a, st);
+}
+
+template <typename T>
+void launch_field_force(const FieldArgs<T>& a, const ElasticArgs<T>& e, hipStream_t st,
+                        Prof* prof) {
+  if (a.gdmi || a.gbx || a.nsub > 2) {
+    launch_field<T>(a, false, st, prof);
+    launch_force<T>(e, st, prof);
+    return;
+  }
+  ProfScope ps(prof, P_FIELD, st);
+  const int nforce = e.nbx * e.nby * e.nz;
+  const dim3 g(a.nb_pad + nforce), b(256);
+  if (a.nsub == 1)
+    hipLaunchKernelGGL((k_field_force<T, 1>), g, b, 0, st, a, e, nforce);
+  else
+    hipLaunchKernelGGL((k_field_force<T, 2>), g, b, 0, st, a, e, nforce);
 }
 
 // --------------------------------------------------------- combine2 ----
@@ -918,6 +958,8 @@ void launch_energy_final(const double* epart, int nblk, double* out, hipStream_t
 
 #define INST(T)                                                                              \
   template void launch_field<T>(const FieldArgs<T>&, bool, hipStream_t, Prof*);             \
+  template void launch_field_force<T>(const FieldArgs<T>&, const ElasticArgs<T>&,           \
+                                      hipStream_t, Prof*);                                  \
   template void launch_combine2<T>(const Table<T>*, const Ctrl*, long, int, hipStream_t,    \
                                    Prof*);                                                   \
   template void launch_control<T>(Ctrl*, Table<T>*, const double*, int, int, hipStream_t,   \

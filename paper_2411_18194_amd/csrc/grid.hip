@@ -159,7 +159,7 @@ template <typename T>
 struct Grid final : GridBase {
   // state and stages
   Buf<T> y[2], sa, sb, k[7];
-  Buf<T> u[2], v[2], usa, usb, vsa, vsb, ku[7], kv[7], eps, epsv, sig;
+  Buf<T> u[2], v[2], usa, usb, vsa, vsb, ku[7], kv[7], eps, sig;
   Buf<T> Bd, gax;
   Buf<uint16_t> gid;
   Buf<double> errpart, epart, eout, spart, samp_t, samp_m, elpart;
@@ -201,7 +201,7 @@ struct Grid final : GridBase {
   void free_all() {
     drop_graphs();
     for (auto* b : {&y[0], &y[1], &sa, &sb, &u[0], &u[1], &v[0], &v[1], &usa, &usb, &vsa, &vsb,
-                    &eps, &epsv, &sig, &Bd, &gax, &K})
+                    &eps, &sig, &Bd, &gax, &K})
       b->release();
     for (int i = 0; i < 7; ++i) { k[i].release(); ku[i].release(); kv[i].release(); }
     gid.release();
@@ -243,14 +243,14 @@ struct Grid final : GridBase {
         const size_t n3 = 3 * (size_t)N;
         for (auto* b : {&u[0], &u[1], &v[0], &v[1], &usa, &usb, &vsa, &vsb}) a.place(*b, n3);
         for (int i = 0; i < 7; ++i) { a.place(ku[i], n3); a.place(kv[i], n3); }
-        for (auto* b : {&eps, &epsv, &sig}) a.place(*b, 6 * (size_t)N);
+        for (auto* b : {&eps, &sig}) a.place(*b, 6 * (size_t)N);
       }
       if (p.demag) a.place(Bd, 3 * (size_t)N);
       a.place(errpart, nb_max);
       a.place(epart, (size_t)nb_max * kNE);
       a.place(eout, kNE);
       a.place(spart, (size_t)nsamp_blk * 9);
-      a.place(elpart, (N + 255) / 256);
+      a.place(elpart, (size_t)nbx * nby * nz);
       a.place(dtbl, 1);
       a.place(dctrl, 1);
     };
@@ -780,7 +780,7 @@ struct Grid final : GridBase {
       e.mel[s] = (p.sub[s].Ms != 0.0 && (p.sub[s].B1 != 0.0 || p.sub[s].B2 != 0.0)) ? 1 : 0;
     }
     e.tbl = dtbl.p; e.ctrl = dctrl.p; e.eps = eps.p; e.sig = sig.p; e.epart = elpart.p;
-    e.epsv = epsv.p; e.beta = (T)p.rayleigh;
+    e.nbx = a.nbx; e.nby = a.nby; e.beta = (T)p.rayleigh;
     e.V = a.V; e.rho = p.rho;
     ea = e;
     drop_graphs();
@@ -896,7 +896,7 @@ struct Grid final : GridBase {
     if (p.elastic) {
       ElasticArgs<T> e = ea;
       e.stage = s;
-      launch_strain(e, stream, &prof);
+      launch_strain(e, false, stream, &prof);
     }
     if (p.demag)
       demag_field<T>(plan, db, dtbl.p, s, dctrl.p, (T)p.sub[0].Ms, ms_of(1), p.nsub, stream,
@@ -904,12 +904,13 @@ struct Grid final : GridBase {
     FieldArgs<T> a = fa;
     a.stage = s;
     a.fuse2 = fuse2 ? 1 : 0;
-    launch_field<T>(a, false, stream, &prof);
     if (p.elastic) {
       ElasticArgs<T> e = ea;
       e.stage = s;
       e.fuse2 = fuse2 ? 1 : 0;
-      launch_elastic_stage<T>(e, false, stream, &prof);
+      launch_field_force<T>(a, e, stream, &prof);
+    } else {
+      launch_field<T>(a, false, stream, &prof);
     }
   }
 
@@ -1194,7 +1195,7 @@ struct Grid final : GridBase {
       ElasticArgs<T> ee = ea;
       ee.stage = 1;
       ee.ctrl = nullptr;
-      launch_strain(ee, stream, &prof);
+      launch_strain(ee, true, stream, &prof);
     }
     if (p.demag)
       demag_field<T>(plan, db, dtbl.p, 1, nullptr, (T)p.sub[0].Ms, ms_of(1), p.nsub, stream,
@@ -1210,12 +1211,6 @@ struct Grid final : GridBase {
     launch_field<T>(a, true, stream, &prof);
     launch_energy_final(epart.p, nblk, eout.p, stream);
     double el = 0.0;
-    if (p.elastic) {
-      ElasticArgs<T> ee = ea;
-      ee.stage = 1;
-      ee.ctrl = nullptr;
-      launch_elastic_stage<T>(ee, true, stream, &prof);
-    }
     MMP_HIP_TRY(hipGetLastError());
     MMP_HIP_TRY(hipStreamSynchronize(stream));
     if (b) {
@@ -1224,7 +1219,7 @@ struct Grid final : GridBase {
     if (e) {
       MMP_HIP_TRY(hipMemcpy(e, eout.p, kNE * sizeof(double), hipMemcpyDeviceToHost));
       if (p.elastic) {
-        const size_t nb = (N + 255) / 256;
+        const size_t nb = elpart.n;
         std::vector<double> part(nb);
         MMP_HIP_TRY(hipMemcpy(part.data(), elpart.p, nb * sizeof(double), hipMemcpyDeviceToHost));
         for (double v : part) el += v;
@@ -1251,7 +1246,7 @@ struct Grid final : GridBase {
       ElasticArgs<T> ee = ea;
       ee.stage = 1;
       ee.ctrl = nullptr;
-      launch_strain(ee, stream, &prof);
+      launch_strain(ee, false, stream, &prof);
     }
     if (p.demag)
       demag_field<T>(plan, db, dtbl.p, 1, nullptr, (T)p.sub[0].Ms, ms_of(1), p.nsub, stream,
