@@ -171,6 +171,7 @@ __device__ __forceinline__ void force_block(const ElasticArgs<T>& a, int w) {
   if (stage < a.tbl->ns) {
     T c[5];
     gcptr<T> pu[5], pv[5];
+#pragma unroll
     for (int j = 0; j < 5; ++j) {
       c[j] = T(0);
       pu[j] = pv[j] = nullptr;

@@ -139,6 +139,26 @@ __device__ void eq6_ghost(const FieldArgs<T>& a, const T (*m)[3], int ax, T side
     for (int c = 0; c < 3; ++c) out[s][c] = m[s][c] + h * g[s][c];
 }
 
+// Accesses of the field kernel: a wave-uniform base and a 32-bit byte offset
+// per lane (grids have at most 2^28 cells, so an array's bytes per component
+// stay below 2^32), which the hardware adds.  64-bit addresses per lane and
+// array took two registers and an addition for every one of the up to 50
+// loads of a cell: FP32 one sublattice 204 -> 123 registers (two -> four
+// waves per SIMD), FP64 298 -> 199 (one -> two); 512x512x16 FP32 90 -> 81 us
+// a stage (4.6 TB/s), FP64 204 -> 170 (4.3 TB/s).
+template <typename T>
+__device__ __forceinline__ T ldo(gcptr<T> base, uint32_t o) {
+  return *(gcptr<T>)((gcptr<char>)base + o);
+}
+template <typename T>
+__device__ __forceinline__ T ldo_nt(gcptr<T> base, uint32_t o) {
+  return __builtin_nontemporal_load((gcptr<T>)((gcptr<char>)base + o));
+}
+template <typename T>
+__device__ __forceinline__ void sto(gptr<T> base, uint32_t o, T v) {
+  *(gptr<T>)((gptr<char>)base + o) = v;
+}
+
 // Block w (tile-major over z chunks) of one grid; stage and fuse2 come from
 // the launch so that one argument block serves every stage.
 // GDMI: general DMI tensors with the Eq. 6 ghosts on every stencil.
@@ -200,29 +220,43 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
 
   if (in) {
     T cur[NSUB][3], zm[NSUB][3], zp[NSUB][3];
-    const long col = (long)y * a.nx + x;
-    const long plane = (long)a.nx * a.ny;
-    const long i0 = (long)z0 * plane + col;
+    constexpr uint32_t S = sizeof(T);
+    const uint32_t col = (uint32_t)(y * a.nx + x);
+    const uint32_t plane = (uint32_t)(a.nx * a.ny);
     // A missing neighbour is the cell itself, so every neighbour load is an
     // unconditional load from a clamped offset: no branches between the
     // loads, which then all go out before the first wait.
     // (on a periodic axis the cell at the opposite end)
-    const long dxm = x > 0 ? -1 : (a.per_x ? a.nx - 1 : 0);
-    const long dxp = x + 1 < a.nx ? 1 : (a.per_x ? 1 - a.nx : 0);
-    const long dym = y > 0 ? -(long)a.nx : (a.per_y ? (long)(a.ny - 1) * a.nx : 0);
-    const long dyp = y + 1 < a.ny ? (long)a.nx : (a.per_y ? -(long)(a.ny - 1) * a.nx : 0);
-    const long dz0 = z0 > 0 ? -plane : 0;
+    const int dxm = x > 0 ? -1 : (a.per_x ? a.nx - 1 : 0);
+    const int dxp = x + 1 < a.nx ? 1 : (a.per_x ? 1 - a.nx : 0);
+    const int dym = y > 0 ? -a.nx : (a.per_y ? (a.ny - 1) * a.nx : 0);
+    const int dyp = y + 1 < a.ny ? a.nx : (a.per_y ? -(a.ny - 1) * a.nx : 0);
+    const bool layers = a.nz > 1;   // a single layer is its own z neighbour
+    {
+      const uint32_t o0 = ((uint32_t)z0 * plane + col) * S;
+      const uint32_t om = z0 > 0 ? o0 - plane * S : o0;
 #pragma unroll
-    for (int s = 0; s < NSUB; ++s)
+      for (int s = 0; s < NSUB; ++s)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        cur[s][c] = m[s * N3 + c * N + i0];
-        // (a single layer has no other: its z neighbour is the cell itself)
-        zm[s][c] = a.nz > 1 ? m[s * N3 + c * N + i0 + dz0] : cur[s][c];
-      }
+        for (int c = 0; c < 3; ++c) {
+          cur[s][c] = ldo<T>(m + s * N3 + c * N, o0);
+          zm[s][c] = layers ? ldo<T>(m + s * N3 + c * N, om) : cur[s][c];
+        }
+    }
     for (int z = z0; z < z1; ++z) {
-      const long i = (long)z * plane + col;
-      const long dzp = z + 1 < a.nz ? plane : 0;
+      const uint32_t i = (uint32_t)z * plane + col, o = i * S;
+      const int dzp = z + 1 < a.nz ? (int)plane : 0;
+      const uint32_t oxm = o + (uint32_t)dxm * S, oxp = o + (uint32_t)dxp * S,
+                     oym = o + (uint32_t)dym * S, oyp = o + (uint32_t)dyp * S,
+                     ozp = o + (uint32_t)dzp * S;
+      // the grain's axis is two loads one behind the other: first
+      T uax[3];
+      if (a.has_anis_u && a.grain) {
+        const int g = a.grain[i];
+        uax[0] = a.gaxes[3 * g];
+        uax[1] = a.gaxes[3 * g + 1];
+        uax[2] = a.gaxes[3 * g + 2];
+      }
       // one sublattice: the stage slopes and y_n of this cell are requested
       // with the stencil loads (they do not depend on the field, and loaded
       // after the k_s stores below they would wait for a second round trip)
@@ -235,43 +269,36 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
 #pragma unroll
           for (int j = 0; j < 6; ++j)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) kv1[j][c] = kslot[j][i + c * N];
+            for (int c = 0; c < 3; ++c) kv1[j][c] = ldo<T>(kslot[j] + c * N, o);
 #pragma unroll
-          for (int c = 0; c < 3; ++c) yv1[c] = yslot[i + c * N];
+          for (int c = 0; c < 3; ++c) yv1[c] = ldo<T>(yslot + c * N, o);
         }
       }
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) zp[s][c] = a.nz > 1 ? m[s * N3 + c * N + i + dzp] : cur[s][c];
+        for (int c = 0; c < 3; ++c)
+          zp[s][c] = layers ? ldo<T>(m + s * N3 + c * N, ozp) : cur[s][c];
       T xm[NSUB][3], xp[NSUB][3], ym[NSUB][3], yp[NSUB][3];
 #pragma unroll
       for (int s = 0; s < NSUB; ++s)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-          const gcptr<T> mc = m + s * N3 + c * N + i;
-          xm[s][c] = mc[dxm];
-          xp[s][c] = mc[dxp];
-          ym[s][c] = mc[dym];
-          yp[s][c] = mc[dyp];
+          const gcptr<T> mc = m + s * N3 + c * N;
+          xm[s][c] = ldo<T>(mc, oxm);
+          xp[s][c] = ldo<T>(mc, oxp);
+          ym[s][c] = ldo<T>(mc, oym);
+          yp[s][c] = ldo<T>(mc, oyp);
         }
       T Bd[3] = {0, 0, 0};
       if (a.has_demag) {
-        Bd[0] = ntload(a.Bd + i);
-        Bd[1] = ntload(a.Bd + N + i);
-        Bd[2] = ntload(a.Bd + 2 * N + i);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) Bd[c] = ldo_nt<T>((gcptr<T>)a.Bd + c * N, o);
       }
       T ep[6] = {0, 0, 0, 0, 0, 0};
       if (a.has_mel) {
 #pragma unroll
-        for (int c = 0; c < 6; ++c) ep[c] = a.eps[c * N + i];
-      }
-      T uax[3];
-      if (a.has_anis_u && a.grain) {
-        const int g = a.grain[i];
-        uax[0] = a.gaxes[3 * g];
-        uax[1] = a.gaxes[3 * g + 1];
-        uax[2] = a.gaxes[3 * g + 2];
+        for (int c = 0; c < 6; ++c) ep[c] = ldo<T>((gcptr<T>)a.eps + c * N, o);
       }
       // link weights x-, x+, y-, y+, z-, z+ of the A11 and A12 stencils: the
       // scale across a grain boundary, 1 inside a grain and towards a
@@ -285,7 +312,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
         wl[1] = gr[dxp] == g0 ? T(1) : f;
         wl[2] = gr[dym] == g0 ? T(1) : f;
         wl[3] = gr[dyp] == g0 ? T(1) : f;
-        wl[4] = gr[z > 0 ? -plane : 0] == g0 ? T(1) : f;
+        wl[4] = gr[z > 0 ? -(int)plane : 0] == g0 ? T(1) : f;
         wl[5] = gr[dzp] == g0 ? T(1) : f;
       }
       auto lk = [&](int k, T v) -> T {
@@ -317,6 +344,20 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
       for (int s = 0; s < NSUB; ++s) {
         const SubC<T>& C = a.sc[s];
         const T* mm = cur[s];
+        // several sublattices: the slopes of one sublattice at a time, asked
+        // for before its field is computed (both at once, with the stencil,
+        // would cost more waves than it hides)
+        T kvs[6][3], yvs[3];
+        if constexpr (NSUB > 1 && !EVAL) {
+          if (stage < ns || !fuse2) {
+#pragma unroll
+            for (int j = 0; j < 6; ++j)
+#pragma unroll
+              for (int c = 0; c < 3; ++c) kvs[j][c] = ldo<T>(kslot[j] + s * N3 + c * N, o);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) yvs[c] = ldo<T>(yslot + s * N3 + c * N, o);
+          }
+        }
         // ghosted in-plane neighbours for exchange/DMI
         T gxm[3], gxp[3], gym[3], gyp[3];
 #pragma unroll
@@ -521,96 +562,54 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
 #pragma unroll
           for (int c = 0; c < 3; ++c) tau[c] -= C.zla * mxmxdm[c] + C.zlb * mxdm[c];
         }
-        const long base = s * N3 + i;
         if (EVAL) {
           if (a.bout) {
-            if (a.out_torque) {
-              a.bout[base] = tau[0];
-              a.bout[base + N] = tau[1];
-              a.bout[base + 2 * N] = tau[2];
-            } else {
-              a.bout[base] = B[0] + Bout[0];
-              a.bout[base + N] = B[1] + Bout[1];
-              a.bout[base + 2 * N] = B[2] + Bout[2];
-            }
+            const gptr<T> bo = (gptr<T>)a.bout + s * N3;
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+              sto<T>(bo + c * N, o, a.out_torque ? tau[c] : B[c] + Bout[c]);
           }
         } else {
           if (!(isfinite(tau[0]) && isfinite(tau[1]) && isfinite(tau[2])))
             atomicOr(&a.ctrl->nonfinite, 1);
-          kout[base] = tau[0];
-          kout[base + N] = tau[1];
-          kout[base + 2 * N] = tau[2];
-          if (stage < ns) {
+#pragma unroll
+          for (int c = 0; c < 3; ++c) sto<T>(kout + s * N3 + c * N, o, tau[c]);
+          // the slopes of this sublattice, loaded above
+          const T(*kv)[3] = NSUB == 1 ? kv1 : kvs;
+          const T* yv = NSUB == 1 ? yv1 : yvs;
+          if (stage < ns || fuse2) {
             T v[3];
-            if constexpr (NSUB == 1) {
-              // the slopes this stage needs, loaded at the top of the
-              // iteration, summed in order.  (Two sublattices would need
-              // twice the registers and lose more waves than the batching
-              // gains.)
+            if (stage < ns) {
 #pragma unroll
               for (int c = 0; c < 3; ++c) {
-                T acc = yv1[c];
+                T acc = yv[c];
 #pragma unroll
                 for (int j = 0; j < 5; ++j)
-                  if (j < stage - 1) acc += ca[j] * kv1[j][c];
+                  if (j < stage - 1) acc += ca[j] * kv[j][c];
                 acc += ca[stage - 1] * tau[c];
                 v[c] = acc;
               }
             } else {
-              // several sublattices: the slopes of one sublattice at a
-              // time, all loaded before the first is summed (a load and a
-              // wait per slope cost 3.6 us of dependent trips at stage 6;
-              // holding both sublattices' slopes from the top of the
-              // iteration costs more waves than it hides)
-              stage_sum_n<T>(stage - 1, yn, kin, ca, base, N, v);
 #pragma unroll
-              for (int c = 0; c < 3; ++c) v[c] += ca[stage - 1] * tau[c];
+              for (int c = 0; c < 3; ++c) v[c] = mm[c] + ca[0] * tau[c];
             }
             const T inv = T(1) / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-            ynext[base] = v[0] * inv;
-            ynext[base + N] = v[1] * inv;
-            ynext[base + 2 * N] = v[2] * inv;
-          } else if (!fuse2) {
-            // error weights: e_j of the earlier slopes (zero weights skip
-            // their loads), then e_ns of this stage's own slope
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sto<T>(ynext + s * N3 + c * N, o, v[c] * inv);
+          } else {
+            // error weights: e_j of the earlier slopes, then e_ns of this
+            // stage's own slope
             double ev[3];
-            if constexpr (NSUB == 1) {
 #pragma unroll
-              for (int c = 0; c < 3; ++c) {
-                double acc = 0.0;
-#pragma unroll
-                for (int j = 0; j < 6; ++j)
-                  if (j < ns - 1 && ew[j] != 0.0) acc += ew[j] * (double)kv1[j][c];
-                ev[c] = acc + ew[ns - 1] * (double)tau[c];
-              }
-            } else {
-              // (a slope of weight zero reads the first one again)
-              T kv[6][3];
+            for (int c = 0; c < 3; ++c) {
+              double acc = 0.0;
 #pragma unroll
               for (int j = 0; j < 6; ++j)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) kv[j][c] = kslot[j][base + c * N];
-#pragma unroll
-              for (int c = 0; c < 3; ++c) {
-                double acc = 0.0;
-#pragma unroll
-                for (int j = 0; j < 6; ++j)
-                  if (j < ns - 1 && ew[j] != 0.0) acc += ew[j] * (double)kv[j][c];
-                ev[c] = acc + ew[ns - 1] * (double)tau[c];
-              }
+                if (j < ns - 1 && ew[j] != 0.0) acc += ew[j] * (double)kv[j][c];
+              ev[c] = acc + ew[ns - 1] * (double)tau[c];
             }
             const double nrm = sqrt(ev[0] * ev[0] + ev[1] * ev[1] + ev[2] * ev[2]);
             emax = nrm > emax ? nrm : emax;
-          } else {
-            {
-              T v[3];
-#pragma unroll
-              for (int c = 0; c < 3; ++c) v[c] = mm[c] + ca[0] * tau[c];
-              const T inv = T(1) / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
-              ynext[base] = v[0] * inv;
-              ynext[base + N] = v[1] * inv;
-              ynext[base + 2 * N] = v[2] * inv;
-            }
           }
         }
       }
