@@ -149,6 +149,8 @@ class DemagMulti {
  private:
   struct Impl;
   Impl* impl = nullptr;
+  char* mem_ = nullptr;   // device tables, cap_ bytes
+  size_t cap_ = 0;
 };
 
 // tables of one axis: line_tw_elems(L) twiddles and L places

@@ -804,7 +804,6 @@ struct DemagMulti<T>::Impl {
   std::vector<ZArgs<T>> z;
   std::vector<YzArgs<T>> yz;
   std::vector<int4> wxf, wxi, wyf, wyi, wz, wyz[2];   // wyz: short, long z columns
-  char* dev = nullptr;
   const XArgs<T>* d_xf = nullptr;
   const XArgs<T>* d_xi = nullptr;
   const YArgs<T>* d_yf = nullptr;
@@ -818,11 +817,12 @@ struct DemagMulti<T>::Impl {
 
 template <typename T>
 void DemagMulti<T>::release() {
-  if (!impl) return;
-  if (impl->dev) {
+  if (mem_) {
     DeviceLock lk(device_mutex());
-    (void)hipFree(impl->dev);
+    (void)hipFree(mem_);
   }
+  mem_ = nullptr;
+  cap_ = 0;
   delete impl;
   impl = nullptr;
 }
@@ -845,7 +845,8 @@ bool demag_multi_fits(const DemagPlan& p) {
 template <typename T>
 int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t st) {
   using V = cpx<T>;
-  release();
+  delete impl;
+  impl = nullptr;
   if (members.empty()) return 0;
   for (const auto& mb : members)
     if (!demag_multi_fits(*mb.plan)) {
@@ -924,19 +925,22 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
   const size_t o_wz = seg(I.wz.size() * sizeof(int4));
   const size_t o_wyz0 = seg(I.wyz[0].size() * sizeof(int4));
   const size_t o_wyz1 = seg(I.wyz[1].size() * sizeof(int4));
-  hipError_t ae;
-  {
+  // the block only grows: freeing it waits for every stream of the device
+  if (off > cap_) {
     DeviceLock lk(device_mutex());
-    ae = hipMalloc(&I.dev, off);
-  }
-  if (ae != hipSuccess) {
-    I.dev = nullptr;
-    release();
-    set_error("device allocation failed (batched demag tables)");
-    return MMP_E_NOMEM;
+    if (mem_) (void)hipFree(mem_);
+    mem_ = nullptr;
+    cap_ = 0;
+    if (hipMalloc(&mem_, 2 * off) != hipSuccess) {
+      mem_ = nullptr;
+      release();
+      set_error("device allocation failed (batched demag tables)");
+      return MMP_E_NOMEM;
+    }
+    cap_ = 2 * off;
   }
   auto put = [&](size_t o, const void* src, size_t bytes) {
-    return bytes ? hipMemcpyAsync(I.dev + o, src, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
+    return bytes ? hipMemcpyAsync(mem_ + o, src, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
   };
   hipError_t e = hipSuccess;
   for (auto r : {put(o_xf, I.xf.data(), I.xf.size() * sizeof(XArgs<T>)),
@@ -959,19 +963,19 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
     return MMP_E_HIP;
   }
   // the x inverse pass reads the same arguments as the forward one
-  I.d_xf = reinterpret_cast<const XArgs<T>*>(I.dev + o_xf);
+  I.d_xf = reinterpret_cast<const XArgs<T>*>(mem_ + o_xf);
   I.d_xi = I.d_xf;
-  I.d_yf = reinterpret_cast<const YArgs<T>*>(I.dev + o_yf);
-  I.d_yi = reinterpret_cast<const YArgs<T>*>(I.dev + o_yi);
-  I.d_z = reinterpret_cast<const ZArgs<T>*>(I.dev + o_z);
-  I.d_yz = reinterpret_cast<const YzArgs<T>*>(I.dev + o_yz);
-  I.d_wxf = reinterpret_cast<const int4*>(I.dev + o_wxf);
-  I.d_wxi = reinterpret_cast<const int4*>(I.dev + o_wxi);
-  I.d_wyf = reinterpret_cast<const int4*>(I.dev + o_wyf);
-  I.d_wyi = reinterpret_cast<const int4*>(I.dev + o_wyi);
-  I.d_wz = reinterpret_cast<const int4*>(I.dev + o_wz);
-  I.d_wyz[0] = reinterpret_cast<const int4*>(I.dev + o_wyz0);
-  I.d_wyz[1] = reinterpret_cast<const int4*>(I.dev + o_wyz1);
+  I.d_yf = reinterpret_cast<const YArgs<T>*>(mem_ + o_yf);
+  I.d_yi = reinterpret_cast<const YArgs<T>*>(mem_ + o_yi);
+  I.d_z = reinterpret_cast<const ZArgs<T>*>(mem_ + o_z);
+  I.d_yz = reinterpret_cast<const YzArgs<T>*>(mem_ + o_yz);
+  I.d_wxf = reinterpret_cast<const int4*>(mem_ + o_wxf);
+  I.d_wxi = reinterpret_cast<const int4*>(mem_ + o_wxi);
+  I.d_wyf = reinterpret_cast<const int4*>(mem_ + o_wyf);
+  I.d_wyi = reinterpret_cast<const int4*>(mem_ + o_wyi);
+  I.d_wz = reinterpret_cast<const int4*>(mem_ + o_wz);
+  I.d_wyz[0] = reinterpret_cast<const int4*>(mem_ + o_wyz0);
+  I.d_wyz[1] = reinterpret_cast<const int4*>(mem_ + o_wyz1);
   return 0;
 }
 

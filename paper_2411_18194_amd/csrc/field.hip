@@ -50,6 +50,14 @@ __device__ __forceinline__ void cross3_acc(const T* a, const T* b, T* o) {
   o[2] = dop(a[0], b[1], a[1], b[0]);
 }
 
+// 1/|v|, with the roundings spelled out: the stage-2 input of a step is formed
+// by different kernels (a stage's own, or the one that continues a run), and
+// has to be the same bits from each
+template <typename T>
+__device__ __forceinline__ T inv_norm(const T* v) {
+  return T(1) / sqrt(fma(v[2], v[2], fma(v[1], v[1], v[0] * v[0])));
+}
+
 template <typename T>
 __device__ __forceinline__ double dot3d(const T* a, const T* b) {
   return (double)a[0] * b[0] + (double)a[1] * b[1] + (double)a[2] * b[2];
@@ -159,6 +167,16 @@ __device__ __forceinline__ void sto(gptr<T> base, uint32_t o, T v) {
   *(gptr<T>)((gptr<char>)base + o) = v;
 }
 
+// a value that is the same in every lane, in a scalar register (loads through
+// the device tables are not known to be uniform)
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename P>
+__device__ __forceinline__ P uni_ptr(P p) {
+  const uint64_t v = (uint64_t)p;
+  const uint64_t lo = (uint32_t)uni((int)(uint32_t)v), hi = (uint32_t)uni((int)(v >> 32));
+  return (P)(lo | hi << 32);
+}
+
 // Block w (tile-major over z chunks) of one grid; stage and fuse2 come from
 // the launch so that one argument block serves every stage.
 // GDMI: general DMI tensors with the Eq. 6 ghosts on every stencil.
@@ -176,7 +194,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
   const bool in = x < a.nx && y < a.ny;
   const long N = a.N;
   const long N3 = 3 * N;
-  const gcptr<T> m = (gcptr<T>)(EVAL ? a.tbl->yn : stage_in(a.tbl, stage));
+  const gcptr<T> m = uni_ptr((gcptr<T>)(EVAL ? a.tbl->yn : stage_in(a.tbl, stage)));
 
   double h = 0.0;
   int ns = 0;
@@ -188,18 +206,18 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
   gcptr<T> yn = nullptr;
   if (!EVAL) {
     h = a.ctrl->h;
-    ns = a.tbl->ns;
+    ns = uni(a.tbl->ns);
     const RKTab& rk = RK::t[a.tbl->rk];
-    kout = (gptr<T>)a.tbl->k[stage - 1];
-    yn = (gcptr<T>)a.tbl->yn;
-    for (int j = 0; j < stage - 1; ++j) kin[j] = (gcptr<T>)a.tbl->k[j];
+    kout = uni_ptr((gptr<T>)a.tbl->k[stage - 1]);
+    yn = uni_ptr((gcptr<T>)a.tbl->yn);
+    for (int j = 0; j < stage - 1; ++j) kin[j] = uni_ptr((gcptr<T>)a.tbl->k[j]);
     if (stage < ns) {
-      ynext = (gptr<T>)stage_out(a.tbl, stage);
+      ynext = uni_ptr((gptr<T>)stage_out(a.tbl, stage));
       for (int j = 0; j < stage; ++j) ca[j] = (T)(rk.a[stage][j] * h);
     } else {
-      if (fuse2) ynext = (gptr<T>)a.tbl->sa;
+      if (fuse2) ynext = uni_ptr((gptr<T>)a.tbl->sa);
       ca[0] = (T)(rk.a[1][0] * h);
-      for (int j = 0; j < ns - 1; ++j) kin[j] = (gcptr<T>)a.tbl->k[j];
+      for (int j = 0; j < ns - 1; ++j) kin[j] = uni_ptr((gcptr<T>)a.tbl->k[j]);
       for (int j = 0; j < ns; ++j) ew[j] = rk.e[j];
     }
   }
@@ -249,6 +267,15 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
       const uint32_t oxm = o + (uint32_t)dxm * S, oxp = o + (uint32_t)dxp * S,
                      oym = o + (uint32_t)dym * S, oyp = o + (uint32_t)dyp * S,
                      ozp = o + (uint32_t)dzp * S;
+      // What a stage does beside its slope is hidden from the compiler within
+      // the iteration: it would make a copy of the loop for every answer, and
+      // contract products and sums into fma differently from copy to copy.
+      // The slope at a state has to be the same bits in every stage (a run
+      // resumed from a saved state evaluates it as k_1, the run it continues
+      // as the last slope).
+      int has_slots = uni(!EVAL && (stage < ns || !fuse2)), has_next = uni(stage < ns || fuse2),
+          is_last = uni(stage >= ns);
+      asm volatile("" : "+s"(has_slots), "+s"(has_next), "+s"(is_last));
       // the grain's axis is two loads one behind the other: first
       T uax[3];
       if (a.has_anis_u && a.grain) {
@@ -265,7 +292,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
       // out before the first wait.
       T kv1[6][3], yv1[3];
       if constexpr (NSUB == 1 && !EVAL) {
-        if (stage < ns || !fuse2) {
+        if (has_slots) {
 #pragma unroll
           for (int j = 0; j < 6; ++j)
 #pragma unroll
@@ -349,7 +376,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
         // would cost more waves than it hides)
         T kvs[6][3], yvs[3];
         if constexpr (NSUB > 1 && !EVAL) {
-          if (stage < ns || !fuse2) {
+          if (has_slots) {
 #pragma unroll
             for (int j = 0; j < 6; ++j)
 #pragma unroll
@@ -577,23 +604,22 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
           // the slopes of this sublattice, loaded above
           const T(*kv)[3] = NSUB == 1 ? kv1 : kvs;
           const T* yv = NSUB == 1 ? yv1 : yvs;
-          if (stage < ns || fuse2) {
+          if (has_next) {
             T v[3];
-            if (stage < ns) {
+            if (!is_last) {
 #pragma unroll
               for (int c = 0; c < 3; ++c) {
                 T acc = yv[c];
 #pragma unroll
                 for (int j = 0; j < 5; ++j)
-                  if (j < stage - 1) acc += ca[j] * kv[j][c];
-                acc += ca[stage - 1] * tau[c];
-                v[c] = acc;
+                  if (j < stage - 1) acc = fma(ca[j], kv[j][c], acc);
+                v[c] = fma(ca[stage - 1], tau[c], acc);
               }
             } else {
 #pragma unroll
-              for (int c = 0; c < 3; ++c) v[c] = mm[c] + ca[0] * tau[c];
+              for (int c = 0; c < 3; ++c) v[c] = fma(ca[0], tau[c], mm[c]);
             }
-            const T inv = T(1) / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+            const T inv = inv_norm(v);
 #pragma unroll
             for (int c = 0; c < 3; ++c) sto<T>(ynext + s * N3 + c * N, o, v[c] * inv);
           } else {
@@ -752,8 +778,8 @@ __device__ __forceinline__ void combine2_cell(const Table<T>* tbl, const Ctrl* c
   const gcptr<T> yn = (gcptr<T>)tbl->yn;
   const gcptr<T> k1 = (gcptr<T>)tbl->k[0];
   T v[3];
-  for (int q = 0; q < 3; ++q) v[q] = yn[base + q * Ncell] + c * k1[base + q * Ncell];
-  const T inv = T(1) / sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]);
+  for (int q = 0; q < 3; ++q) v[q] = fma(c, k1[base + q * Ncell], yn[base + q * Ncell]);
+  const T inv = inv_norm(v);
   const gptr<T> o = (gptr<T>)tbl->sa;
   for (int q = 0; q < 3; ++q) o[base + q * Ncell] = v[q] * inv;
 }

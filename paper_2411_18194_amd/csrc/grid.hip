@@ -175,6 +175,7 @@ struct Grid final : GridBase {
   Buf<int> pos;
   Buf<T> K;
   Buf<char> mem, fft_mem;  // the blocks that hold the buffers above
+  size_t idle_begin = 0, idle_end = 0;  // part of mem unused until a state is set
   bool demag_built = false;
   // layout of the current allocation
   bool allocated = false;
@@ -237,15 +238,6 @@ struct Grid final : GridBase {
     const int nb_max = round_up(nbx * nby * nz, 8);
     nsamp_blk = (int)std::min<long>(256, (N + 255) / 256);
     auto layout = [&](Arena& a) {
-      for (auto* b : {&y[0], &y[1], &sa, &sb}) a.place(*b, nm);
-      for (int i = 0; i < 7; ++i) a.place(k[i], nm);
-      if (p.elastic) {
-        const size_t n3 = 3 * (size_t)N;
-        for (auto* b : {&u[0], &u[1], &v[0], &v[1], &usa, &usb, &vsa, &vsb}) a.place(*b, n3);
-        for (int i = 0; i < 7; ++i) { a.place(ku[i], n3); a.place(kv[i], n3); }
-        for (auto* b : {&eps, &sig}) a.place(*b, 6 * (size_t)N);
-      }
-      if (p.demag) a.place(Bd, 3 * (size_t)N);
       a.place(errpart, nb_max);
       a.place(epart, (size_t)nb_max * kNE);
       a.place(eout, kNE);
@@ -253,6 +245,20 @@ struct Grid final : GridBase {
       a.place(elpart, (size_t)nbx * nby * nz);
       a.place(dtbl, 1);
       a.place(dctrl, 1);
+      a.place(y[0], nm);
+      if (p.elastic) { a.place(u[0], 3 * (size_t)N); a.place(v[0], 3 * (size_t)N); }
+      // from here on: nothing that is kept before the first state is set
+      idle_begin = a.off;
+      for (auto* b : {&y[1], &sa, &sb}) a.place(*b, nm);
+      for (int i = 0; i < 7; ++i) a.place(k[i], nm);
+      if (p.elastic) {
+        const size_t n3 = 3 * (size_t)N;
+        for (auto* b : {&u[1], &v[1], &usa, &usb, &vsa, &vsb}) a.place(*b, n3);
+        for (int i = 0; i < 7; ++i) { a.place(ku[i], n3); a.place(kv[i], n3); }
+        for (auto* b : {&eps, &sig}) a.place(*b, 6 * (size_t)N);
+      }
+      if (p.demag) a.place(Bd, 3 * (size_t)N);
+      idle_end = a.off;
     };
     int rc = 0;
     {
@@ -424,11 +430,20 @@ struct Grid final : GridBase {
   // twiddles and the transformed kernel for the current pads
   int build_demag() {
     DeviceLock lk(device_mutex());
-    double* scratch = nullptr;
-    MMP_HIP_TRY(hipMalloc(&scratch, demag_build_doubles(plan) * sizeof(double)));
+    // a new grid's build works in the stage buffers, which nothing uses yet
+    // (hipFree waits for everything that runs on the device, also for other
+    // grids' steps); later ones, beside a state, in an allocation of their own
+    const size_t need = demag_build_doubles(plan);
+    const bool fresh = !state_set && idle_end - idle_begin >= need * sizeof(double);
+    Buf<double> own;
+    if (!fresh && own.alloc(need)) {
+      set_error("device allocation failed (demag kernel build)");
+      return MMP_E_HIP;
+    }
+    double* scratch = fresh ? reinterpret_cast<double*>(mem.p + idle_begin) : own.p;
     build_all_twiddles(db, plan);
     const int rc = demag_kernel_build<T>(plan, d[0], d[1], d[2], scratch, db.K, stream);
-    (void)hipFree(scratch);
+    own.release();
     if (rc) {
       set_error("demag kernel build failed");
       return MMP_E_HIP;
@@ -1126,14 +1141,22 @@ struct Grid final : GridBase {
     init.max_attempts = o ? o->max_steps : 0;
     if ((rc = begin_segment(init))) return rc;
     const bool sampling = every > 0.0;
-    // enqueue attempts in chunks; the device ignores the ones after done
-    const int chunk = N > 4096 ? 16 : 64;
+    // Attempts are enqueued in chunks; the device skips the ones after the
+    // end, but each skipped one still costs its launches (26 kernels, 50 us on
+    // a 64x16x1 grid), and each chunk's end a host round trip (30 us).  So a
+    // run starts with one graph, and later chunks hold about the attempts that
+    // the controller's present step would need to the end.  (Chunks of 64
+    // left 49 of them idle in a run of 15 attempts: 4.1 -> 2.3 ms.)
+    constexpr int kMostAttempts = 64;
+    int chunk = kGraphAttempts;
     Ctrl c{};
     long long last = -1;
     while (true) {
       if ((rc = enqueue_attempts(false, sampling, chunk))) return rc;
       if ((rc = read_ctrl(&c))) return rc;
       if (c.done || c.status) break;
+      const double left = c.dt > 0.0 ? 1.1 * (t_end - c.t) / c.dt + 1.0 : kMostAttempts;
+      chunk = round_up((int)std::min<double>(left, kMostAttempts), kGraphAttempts);
       const long long made = c.steps + c.rejects;
       if (made == last) {
         set_error("step controller made no progress");
@@ -1591,9 +1614,14 @@ struct Batch final : BatchBase {
                          g->ms_of(2), g->p.nsub});
       if (int rc = dm.build(dms, st)) return rc;
     }
-    d_args.release(); d_work.release(); d_step.release(); d_cptr.release(); d_cgather.release();
-    if (d_args.alloc(n) || d_work.alloc(work.size()) || d_step.alloc(n) || d_cptr.alloc(n) ||
-        d_cgather.alloc(n)) {
+    // the tables only grow: freeing one waits for every stream of the device
+    auto fit = [](auto& b, size_t count) {
+      if (b.p && b.n >= count) return 0;
+      b.release();
+      return b.alloc(count);
+    };
+    if (fit(d_args, n) || fit(d_work, work.size()) || fit(d_step, n) || fit(d_cptr, n) ||
+        fit(d_cgather, n)) {
       set_error("device allocation failed");
       return MMP_E_NOMEM;
     }

@@ -76,12 +76,17 @@ int64_t estimate_bytes(const mmp_request& r, int precision) {
 
 }  // namespace
 
-// Attempts per chunk for `cells` cell-sublattices: about 2^23 / (cells +
-// 2^15), between 8 and 128, i.e. a few ms of device work whether the grid is
-// large (time per attempt grows with its cells) or small (an attempt still
-// costs some tens of us of launches and latency).
-static int chunk_attempts(long long cells) {
-  return (int)std::max<long long>(8, std::min<long long>(128, (1LL << 23) / (cells + (1LL << 15))));
+// Attempts per chunk for `cells` cell-sublattices: about 2 ms of device
+// work, between one graph of 8 attempts and 128.  An attempt takes about
+// 200 us of launches and latency with demag (24 kernels of a batch) and 50
+// without, on top of its cells.  Requests join and leave a batch between
+// chunks, two of which are in flight, so a chunk is how long a new request
+// waits: with chunks up to 128 attempts (28 ms with demag) requests that
+// arrived together ran one after the other instead of in one batch.
+static int chunk_attempts(long long cells, bool demag) {
+  const double us = demag ? 200.0 + (double)cells / 1000.0 : 50.0 + (double)cells / 4000.0;
+  const int n = (int)(2000.0 / us) / 8 * 8;
+  return std::max(8, std::min(128, n));
 }
 
 struct mmp_server_s {
@@ -233,7 +238,7 @@ struct mmp_server_s {
     // cells); two chunks stay in flight so the device never waits for the
     // host
     const int64_t N = (int64_t)q->r.nx * q->r.ny * q->r.nz * q->r.params.nsub;
-    q->chunk = chunk_attempts(N);
+    q->chunk = chunk_attempts(N, q->r.params.demag != 0);
     if (int rc = q->g->impl->run_chunk(q->chunk)) return rc;
     return q->g->impl->run_chunk(q->chunk);
   }
@@ -307,7 +312,9 @@ struct mmp_server_s {
       any = true;
     }
     if (!B.members.empty()) {
-      const int chunk = chunk_attempts(std::max<long long>(1, B.b->cells()));
+      bool demag = false;
+      for (const Req* q : B.members) demag = demag || q->r.params.demag != 0;
+      const int chunk = chunk_attempts(B.b->cells(), demag);
       while (B.b->in_flight() < 2) {
         const int rc = B.b->run_chunk(chunk);
         if (rc) {

@@ -25,6 +25,8 @@
 // indexes into FP64 trig tables), along z a short sum per column; then
 // scaled by -mu0/(Px Py Pz) (and -1 for the odd-odd components, from
 // (-i)^2).
+#include <algorithm>
+
 #include "demag.h"
 
 namespace mmp {
@@ -575,7 +577,8 @@ int stray_kernel_build(int nx, int ny, int nz, double dx, double dy, double dz, 
   return launch_tensor(tensor_args(nx, ny, nz, dx, dy, dz, zt, -dz, k6), st);
 }
 
-// scratch of demag_kernel_build: the tensor, its x and its x-y sums, trig tables
+// scratch of demag_kernel_build: the tensor (and, once its x sums are formed,
+// in its place the x-y sums), the x sums, trig tables
 static void build_sizes(const DemagPlan& p, size_t* n0, size_t* n1, size_t* n2, size_t* nt) {
   *n0 = (size_t)6 * p.nx * p.ny * p.nz;
   *n1 = (size_t)6 * p.nz * p.ny * p.Hx;
@@ -585,7 +588,7 @@ static void build_sizes(const DemagPlan& p, size_t* n0, size_t* n1, size_t* n2, 
 size_t demag_build_doubles(const DemagPlan& p) {
   size_t n0, n1, n2, nt;
   build_sizes(p, &n0, &n1, &n2, &nt);
-  return n0 + n1 + n2 + nt;
+  return std::max(n0, n2) + n1 + nt;
 }
 
 template <typename T>
@@ -594,9 +597,9 @@ int demag_kernel_build(const DemagPlan& p, double dx, double dy, double dz, doub
   size_t n0, n1, n2, nt;
   build_sizes(p, &n0, &n1, &n2, &nt);
   double* n6 = scratch;
-  double* f1 = n6 + n0;
-  double* f2 = f1 + n1;
-  double* tabs = f2 + n2;
+  double* f2 = scratch;
+  double* f1 = scratch + std::max(n0, n2);
+  double* tabs = f1 + n1;
   if (p.rep[0] > 0 || p.rep[1] > 0) {
     if (fill_tensor_images(p.nx, p.ny, p.nz, dx, dy, dz, p.rep[0], p.rep[1], n6, st)) return -1;
   } else if (fill_tensor(p.nx, p.ny, p.nz, dx, dy, dz, n6, st)) {
