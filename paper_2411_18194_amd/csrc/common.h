@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <cmath>
+#include <cstddef>
 #include <mutex>
 #include <string>
 
@@ -110,7 +111,31 @@ struct RKTab {
   double e[7];
 };
 
+// What stage s of a pair needs of its table, passed to the kernels by value:
+// looked up on the device it is two more dependent loads (pair, then
+// coefficient) before a kernel's first data load.
+struct RKStage {
+  int ns;
+  int in, out;   // table slots of the stage's input and of what it writes
+  double a[6];   // weights of the input of stage s + 1
+  double a10;    // weight of k_1 in the input of stage 2
+  double e[7];
+};
+
 enum { RK_DP45 = 0, RK_HEUN = 1, RK_BS23 = 2, RK_CASHKARP = 3, RK_FEHLBERG = 4, RK_COUNT = 5 };
+
+inline int slot_in(int s, int ns);
+inline int slot_out(int s, int ns);
+inline RKStage rk_stage(const RKTab& t, int s) {
+  RKStage o{};
+  o.ns = t.ns;
+  o.in = slot_in(s, t.ns);
+  o.out = slot_out(s, t.ns);
+  o.a10 = t.a[1][0];
+  for (int j = 0; j < 6; ++j) o.a[j] = s < t.ns ? t.a[s][j] : 0.0;
+  for (int j = 0; j < 7; ++j) o.e[j] = t.e[j];
+  return o;
+}
 
 struct RK {
   static constexpr RKTab t[RK_COUNT] = {
@@ -267,23 +292,64 @@ using gptr = __attribute__((address_space(1))) T*;
 template <typename T>
 using gcptr = const __attribute__((address_space(1))) T*;
 
-// Input of RK stage s (1..ns): y_n, then sa/sb alternating, then y_new.
-template <typename T>
-__device__ __forceinline__ const T* stage_in(const Table<T>* tbl, int s) {
-  if (s == 1) return tbl->yn;
-  if (s == tbl->ns) return tbl->ynew;
-  return (s & 1) ? tbl->sb : tbl->sa;
+// A value that is the same in every lane, in a scalar register (loads through
+// the device tables are not known to be uniform).
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename P>
+__device__ __forceinline__ P uni_ptr(P p) {
+  const uint64_t v = (uint64_t)p;
+  const uint64_t lo = (uint32_t)uni((int)(uint32_t)v), hi = (uint32_t)uni((int)(v >> 32));
+  return (P)(lo | hi << 32);
 }
-// Buffer the stage-s kernel writes the next stage's input into.
+// Stage buffers are named by their byte offset in the grid's pointer table
+// (the same for both precisions), chosen on the host: input of stage s of a
+// pair of ns stages is y_n, then sa and sb in turn, then y_new; the kernel of
+// stage s writes stage s + 1's (the last stage of a fixed step: stage 2's).
+inline int slot_in(int s, int ns) {
+  using B = Table<float>;
+  return (int)(s <= 1    ? offsetof(B, yn)
+               : s == ns ? offsetof(B, ynew)
+               : (s & 1) ? offsetof(B, sb)
+                         : offsetof(B, sa));
+}
+inline int slot_out(int s, int ns) { return slot_in(s < ns ? s + 1 : 2, ns < 3 ? 3 : ns); }
+static_assert(offsetof(Table<float>, sb) == offsetof(Table<double>, sb), "");
 template <typename T>
-__device__ __forceinline__ T* stage_out(const Table<T>* tbl, int s) {
-  const int n = s + 1;
-  if (n == tbl->ns) return tbl->ynew;
-  return (n & 1) ? tbl->sb : tbl->sa;
+__device__ __forceinline__ T* table_slot(const Table<T>* tbl, int off) {
+  return uni_ptr(*reinterpret_cast<T* const*>(reinterpret_cast<const char*>(tbl) + off));
 }
 
-__device__ __forceinline__ bool ctrl_stopped(const Ctrl* c) {
-  return c != nullptr && (c->done != 0 || c->status != 0);
+// The run is over or has failed: both flags in one load, not one after the
+// other (every kernel of a step starts with this).
+__device__ __forceinline__ bool ctrl_stopped(const Ctrl* c, int zero = 0) {
+  if (c == nullptr) return false;
+  c = reinterpret_cast<const Ctrl*>(reinterpret_cast<const char*>(c) + zero);
+  return (c->done | c->status) != 0;
+}
+
+// Touches every line of a kernel's arguments at once.  A kernel loads its
+// arguments where it needs them, and the first load of each 64-byte line is
+// a trip to memory: up to five of them one behind the other before the first
+// data load, in kernels that last a few microseconds (with the table slots and
+// the pair's weights passed by value: steps of 1024x256x1 FP32 603 -> 464 us,
+// a 64x16x1 run 2.33 -> 2.05 ms).  Returns a zero that
+// the compiler does not know and that depends on the lines: added to the
+// addresses of the next loads it keeps them behind the touch.  (An asm without
+// outputs would do that too, but counts as a write to memory, after which
+// the compiler no longer uses scalar loads.)
+template <typename P>
+__device__ __forceinline__ int warm_lines(P p, int bytes) {
+  uint32_t x = p[bytes / 4 - 1];
+#pragma unroll
+  for (int i = 0; i < bytes; i += 64) x |= p[i / 4];
+  int zero;
+  asm("s_mov_b32 %0, 0" : "=s"(zero) : "s"(x));
+  return zero;
+}
+template <typename A>
+__device__ __forceinline__ int warm_args() {
+  using P = const __attribute__((address_space(4))) uint32_t*;
+  return warm_lines((P)__builtin_amdgcn_kernarg_segment_ptr(), (int)sizeof(A));
 }
 
 }  // namespace mmp

@@ -63,15 +63,13 @@ struct DemagBufs {
   cpx<T>* twx = nullptr;    // stage twiddles of the line transforms
   cpx<T>* twy = nullptr;
   cpx<T>* twz = nullptr;
-  int* posx = nullptr;      // LDS places of their bins
-  int* posy = nullptr;
-  int* posz = nullptr;
   cpx<T>* tw4x = nullptr;   // four-step tables [k1][t] = exp(-2 pi i t k1/L)
   cpx<T>* tw4y = nullptr;
   T* Bd = nullptr;          // output field [3][N]
+  int ns = 7;               // stages of the pair in use (where stage inputs are)
 };
 
-// B_d for the stage input of `stage` (see stage_in) or, with stage == 0, for
+// B_d for the stage input of `stage` (see stage_src) or, with stage == 0, for
 // the array `src` directly.  M = Ms0 m0 + Ms1 m1 (+ Ms2 m2 for three
 // sublattices).
 template <typename T>
@@ -153,9 +151,9 @@ class DemagMulti {
   size_t cap_ = 0;
 };
 
-// tables of one axis: line_tw_elems(L) twiddles and L places
+// line_tw_elems(L) twiddles of one axis
 template <typename T>
-void build_line_tables(const LineFft& f, cpx<T>* tw, int* pos, hipStream_t st);
+void build_line_tables(const LineFft& f, cpx<T>* tw, hipStream_t st);
 template <typename T>
 void build_twiddles4(cpx<T>* tw, int L, hipStream_t st);
 int split_l2(int L);

@@ -31,11 +31,10 @@ constexpr int yz_max_threads(int real_bytes, int pz) {
 constexpr long kMultiElems = 4096;
 
 // ----------------------------------------------------------------- tables --
-// Stage twiddles of a line transform and the places of its bins in LDS.
+// Stage twiddles of a line transform and the places of its bins.
 template <typename T>
-__global__ void k_line_tables(LineFft f, cpx<T>* tw, int* pos) {
+__global__ void k_line_tables(LineFft f, cpx<T>* tw) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= f.L) return;
   for (int s = 0; s + 1 < f.n; ++s) {
     const LineStage t = f.stage(s);
     const int m = t.r * t.M;   // length of the sub-transform of this stage
@@ -46,34 +45,27 @@ __global__ void k_line_tables(LineFft f, cpx<T>* tw, int* pos) {
       tw[t.tw + i] = cmk<T>((T)cs, (T)sn);
     }
   }
-  int e = 0, k = i;
-  for (int s = 0; s < f.n; ++s) {
-    const LineStage t = f.stage(s);
-    e += (k % t.r) * t.M;
-    k /= t.r;
-  }
-  pos[i] = e + (e / f.rl) * f.pad;
+  if (i < f.L) const_cast<uint16_t*>(line_places(f, tw))[i] = (uint16_t)f.place_of(i);
 }
 
 template <typename T>
-void build_line_tables(const LineFft& f, cpx<T>* tw, int* pos, hipStream_t st) {
-  hipLaunchKernelGGL(k_line_tables<T>, dim3((f.L + 255) / 256), dim3(256), 0, st, f, tw, pos);
+void build_line_tables(const LineFft& f, cpx<T>* tw, hipStream_t st) {
+  hipLaunchKernelGGL(k_line_tables<T>, dim3((f.L + 255) / 256), dim3(256), 0, st, f, tw);
 }
-template void build_line_tables<float>(const LineFft&, cpx<float>*, int*, hipStream_t);
-template void build_line_tables<double>(const LineFft&, cpx<double>*, int*, hipStream_t);
+template void build_line_tables<float>(const LineFft&, cpx<float>*, hipStream_t);
+template void build_line_tables<double>(const LineFft&, cpx<double>*, hipStream_t);
 
 // --------------------------------------------------------------- x pass --
 template <typename T>
 struct XArgs {
   const Table<T>* tbl;
   const Ctrl* ctrl;
-  int stage;
+  int src;    // table slot of the state to transform
   T ms0, ms1, ms2;
   int nsub;
   cpx<T>* S1;
   T* Bd;
   const cpx<T>* tw;
-  const int* pos;
   int nx, ny, nz, Hx, ldy, ty;
   int lnl;    // log2(ty / 2)
   int half;   // the line is at least twice its data (an open axis)
@@ -84,17 +76,17 @@ struct XArgs {
 // arguments: the single-grid kernels pass blockIdx, the batched kernels
 // the entry of their work table.
 template <typename T>
-__device__ __forceinline__ void fftx_fwd_body(const XArgs<T>& a, int stage, int bx, int by,
+__device__ __forceinline__ void fftx_fwd_body(const XArgs<T>& a, int zero, int src, int bx, int by,
                                               int bz) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  const gcptr<T> m = (gcptr<T>)table_slot<T>(a.tbl, src + zero);
+  if (ctrl_stopped(a.ctrl, zero)) return;
   extern __shared__ char smem_raw[];
   V* buf = reinterpret_cast<V*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int c = bz, z = by, y0 = bx * a.ty;
   const int nl = a.ty >> 1;
   const long N = (long)a.nx * a.ny * a.nz;
-  const gcptr<T> m = (gcptr<T>)stage_in(a.tbl, stage);
   const gcptr<T> m0 = m + (long)c * N + (long)z * a.ny * a.nx;
   const gcptr<T> m1 = m0 + 3 * N;
   // rows past ny and cells past nx: a clamped load, zeroed afterwards
@@ -114,14 +106,16 @@ __device__ __forceinline__ void fftx_fwd_body(const XArgs<T>& a, int stage, int 
     const bool in = x < a.nx;
     return cmk<T>(in && ya < a.ny ? re : T(0), in && yb < a.ny ? im : T(0));
   };
-  line_fft_fwd<T>(a.f, buf, a.tw, nl, a.half != 0, tid, nthr, ld);
+  const V* twl = line_stage_tw<T>(a.f, buf, nl, a.tw, tid, nthr);
+  line_fft_fwd<T>(a.f, buf, a.tw, twl, nl, a.half != 0, tid, nthr, ld);
   // unpack the two real spectra and store them transposed
+  const uint16_t* place = line_places(a.f, twl);
   V* out = a.S1 + ((long)(c * a.nz + z) * a.Hx) * a.ldy + y0;
   for (int idx = tid; idx < nl * a.Hx; idx += nthr) {
     const int q = idx & (nl - 1), kx = idx >> a.lnl;
     const int km = kx == 0 ? 0 : a.f.L - kx;
     const V* b = buf + q * a.f.pitch;
-    const V zk = b[a.pos[kx]], zm = b[a.pos[km]];
+    const V zk = b[place[kx]], zm = b[place[km]];
     const T h = T(0.5);
     store2<T>(out + (long)kx * a.ldy + 2 * q,
               cmk<T>(h * (zk.x + zm.x), h * (zk.y - zm.y)),
@@ -131,34 +125,41 @@ __device__ __forceinline__ void fftx_fwd_body(const XArgs<T>& a, int stage, int 
 
 template <typename T>
 __global__ __launch_bounds__(kLineThreads) void k_fftx_fwd(XArgs<T> a) {
-  fftx_fwd_body<T>(a, a.stage, blockIdx.x, blockIdx.y, blockIdx.z);
+  const int zero = warm_args<XArgs<T>>();
+  fftx_fwd_body<T>(a, zero, a.src, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 template <typename T>
-__device__ __forceinline__ void fftx_inv_body(const XArgs<T>& a, int bx, int by, int bz) {
+__device__ __forceinline__ void fftx_inv_body(const XArgs<T>& a, int zero, int bx, int by, int bz) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  // (the spectrum is loaded beside the controller's flags, not behind them)
+  const bool stop = ctrl_stopped(a.ctrl, zero);
   extern __shared__ char smem_raw[];
   V* buf = reinterpret_cast<V*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int c = bz, z = by, y0 = bx * a.ty;
   const int nl = a.ty >> 1;
   const V* in = a.S1 + ((long)(c * a.nz + z) * a.Hx) * a.ldy + y0;
+  const V* twl = line_stage_tw<T>(a.f, buf, nl, a.tw, tid, nthr);
+  const uint16_t* place = line_places(a.f, a.tw);   // (from memory, with the data)
   for (int idx = tid; idx < nl * a.Hx; idx += nthr) {
     const int q = idx & (nl - 1), kx = idx >> a.lnl;
+    const int pk = place[kx], pm = place[kx == 0 ? 0 : a.f.L - kx];
     V xa, xb;
     load2<T>(in + (long)kx * a.ldy + 2 * q, xa, xb);
     // past the last row S1 holds the forward pass's rounding of a zero row,
     // unscaled by the kernel: left in, it would leak into the row before
     if (y0 + 2 * q + 1 >= a.ny) xb = cmk<T>(T(0), T(0));
     V* b = buf + q * a.f.pitch;
-    b[a.pos[kx]] = cmk<T>(xa.x - xb.y, xa.y + xb.x);
-    if (kx > 0 && 2 * kx < a.f.L) b[a.pos[a.f.L - kx]] = cmk<T>(xa.x + xb.y, xb.x - xa.y);
+    b[pk] = cmk<T>(xa.x - xb.y, xa.y + xb.x);
+    if (kx > 0 && 2 * kx < a.f.L) b[pm] = cmk<T>(xa.x + xb.y, xb.x - xa.y);
   }
+  if (stop) return;
+  lds_copies_done();
   __syncthreads();
   const long N = (long)a.nx * a.ny * a.nz;
   T* out = a.Bd + (long)c * N + (long)z * a.ny * a.nx;
-  line_fft_inv<T>(a.f, buf, a.tw, nl, a.half != 0, tid, nthr, [&](int q, int x, V v) {
+  line_fft_inv<T>(a.f, buf, twl, nl, a.half != 0, tid, nthr, [&](int q, int x, V v) {
     const int ya = y0 + 2 * q;
     if (x < a.nx) {
       if (ya < a.ny) out[ya * a.nx + x] = v.x;
@@ -169,7 +170,8 @@ __device__ __forceinline__ void fftx_inv_body(const XArgs<T>& a, int bx, int by,
 
 template <typename T>
 __global__ __launch_bounds__(kLineThreads) void k_fftx_inv(XArgs<T> a) {
-  fftx_inv_body<T>(a, blockIdx.x, blockIdx.y, blockIdx.z);
+  const int zero = warm_args<XArgs<T>>();
+  fftx_inv_body<T>(a, zero, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // --------------------------------------------------------------- y pass --
@@ -179,7 +181,6 @@ struct YArgs {
   const cpx<T>* in;
   cpx<T>* out;
   const cpx<T>* tw;
-  const int* pos;
   int nlines, nvalid_in, ld_in, nvalid_out, ld_out, nl;
   int half;
   FastDiv dL;
@@ -187,32 +188,36 @@ struct YArgs {
 };
 
 template <typename T, bool INV>
-__device__ __forceinline__ void ffty_body(const YArgs<T>& a, int bx) {
+__device__ __forceinline__ void ffty_body(const YArgs<T>& a, int zero, int bx) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  if (ctrl_stopped(a.ctrl, zero)) return;
   extern __shared__ char smem_raw[];
   V* buf = reinterpret_cast<V*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int l0 = bx * a.nl, L = a.f.L;
+  const V* twl = line_stage_tw<T>(a.f, buf, a.nl, a.tw, tid, nthr);
   if constexpr (!INV) {
-    line_fft_fwd<T>(a.f, buf, a.tw, a.nl, a.half != 0, tid, nthr, [&](int l, int n) -> V {
+    line_fft_fwd<T>(a.f, buf, a.tw, twl, a.nl, a.half != 0, tid, nthr, [&](int l, int n) -> V {
       const bool in = l0 + l < a.nlines && n < a.nvalid_in;
       const V v = a.in[in ? (long)(l0 + l) * a.ld_in + n : 0];
       return in ? v : cmk<T>(T(0), T(0));
     });
+    const uint16_t* place = line_places(a.f, twl);
     for (int idx = tid; idx < a.nl * L; idx += nthr) {
       const int l = a.dL.div(idx), k = idx - l * L;
-      if (l0 + l < a.nlines) a.out[(long)(l0 + l) * a.ld_out + k] = buf[l * a.f.pitch + a.pos[k]];
+      if (l0 + l < a.nlines) a.out[(long)(l0 + l) * a.ld_out + k] = buf[l * a.f.pitch + place[k]];
     }
   } else {
+    const uint16_t* place = line_places(a.f, a.tw);
     for (int idx = tid; idx < a.nl * L; idx += nthr) {
       const int l = a.dL.div(idx), k = idx - l * L;
       const bool in = l0 + l < a.nlines;
       const V v = a.in[in ? (long)(l0 + l) * a.ld_in + k : 0];
-      buf[l * a.f.pitch + a.pos[k]] = v;
+      buf[l * a.f.pitch + place[k]] = v;
     }
+    lds_copies_done();
     __syncthreads();
-    line_fft_inv<T>(a.f, buf, a.tw, a.nl, a.half != 0, tid, nthr, [&](int l, int n, V v) {
+    line_fft_inv<T>(a.f, buf, twl, a.nl, a.half != 0, tid, nthr, [&](int l, int n, V v) {
       if (l0 + l < a.nlines && n < a.nvalid_out) a.out[(long)(l0 + l) * a.ld_out + n] = v;
     });
   }
@@ -220,7 +225,8 @@ __device__ __forceinline__ void ffty_body(const YArgs<T>& a, int bx) {
 
 template <typename T, bool INV>
 __global__ __launch_bounds__(kLineThreads) void k_ffty(YArgs<T> a) {
-  ffty_body<T, INV>(a, blockIdx.x);
+  const int zero = warm_args<YArgs<T>>();
+  ffty_body<T, INV>(a, zero, blockIdx.x);
 }
 
 // Symmetric 3x3 multiply with the octant kernel; sy/sz flip the odd parts
@@ -241,76 +247,95 @@ __device__ __forceinline__ void sym3(cpx<T>& mx, cpx<T>& my, cpx<T>& mz, T kxx, 
 // place in S1.  On a 2-D grid the column is the three components alone.
 // Against separate y, z and y passes the padded spectrum never reaches
 // memory (S2 is 2 (Py/ny) times S1, written twice and read twice) and two
-// launches go.  Measured: 183x77x5 FP32 86.1 us in three passes -> 11.4 us;
-// 64x64x4 FP32 15.1 (register kernels) -> 9.8 us; 333x130x1 FP64 57.1 ->
-// 11.8 us.  One kx column per block: few grids have more than a few hundred.
+// launches go.  Measured: 183x77x5 FP32 86.1 us in three passes -> 10.9 us;
+// 64x64x4 FP32 15.1 (register kernels) -> 9.3 us; 333x130x1 FP64 57.1 ->
+// 11.7 us.  One kx column per block: few grids have more than a few hundred.
 template <typename T>
 struct YzArgs {
   const Ctrl* ctrl;
   cpx<T>* S1;     // [3][nz][Hx][ldy]
   const T* K;     // [6][Hz][Hx][Hy]
   const cpx<T>* tw;
-  const int* pos;
   int ny, nz, Pz, Hx, Hy, Hz, ldy, nk, lnk;
   int half;
   FastDiv dL;
   LineFft f;
 };
 
+// The kernel values of one column: 4 of the 2-D kernel, else 6 of each plane
+// kz <= PZ/2.
 template <typename T, int PZ>
-__device__ __forceinline__ void yz_columns(const YzArgs<T>& a, cpx<T>* buf, int kx0, int tid,
-                                           int nthr) {
+struct YzKernel {
+  T v[PZ == 1 ? 1 : PZ / 2 + 1][6];
+};
+// column idx of the block: its kx (columns past the spectrum: the first), ky
+// and octant kernel column
+template <typename T, int PZ>
+__device__ __forceinline__ void yz_load_k(const YzArgs<T>& a, int kx0, int idx,
+                                          YzKernel<T, PZ>& k) {
+  const int L = a.f.L;
+  const int j = a.dL.div(idx), ky = idx - j * L;
+  const int kx = kx0 + j < a.Hx ? kx0 + j : 0, kyo = 2 * ky > L ? L - ky : ky;
+  const long ks = (long)a.Hz * a.Hx * a.Hy, kzs = (long)a.Hx * a.Hy;
+  const T* K = a.K + (long)kx * a.Hy + kyo;
+  if constexpr (PZ == 1) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) k.v[0][c] = K[c * ks];
+  } else {
+#pragma unroll
+    for (int kz = 0; kz <= PZ / 2; ++kz)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) k.v[kz][c] = K[c * ks + kz * kzs];
+  }
+}
+
+template <typename T, int PZ>
+__device__ __forceinline__ void yz_column(const YzArgs<T>& a, cpx<T>* buf,
+                                          const uint16_t* place, int kx0, int idx,
+                                          const YzKernel<T, PZ>& k) {
   using V = cpx<T>;
   const int L = a.f.L;
   const int zl = a.nk * a.f.pitch, cl = a.nz * zl;   // LDS strides of layer, component
-  const long ks = (long)a.Hz * a.Hx * a.Hy, kzs = (long)a.Hx * a.Hy;
-  for (int idx = tid; idx < a.nk * L; idx += nthr) {
-    const int j = a.dL.div(idx), ky = idx - j * L;
-    const int kx = kx0 + j;
-    if (kx >= a.Hx) continue;
-    const bool mir = ky > L / 2;
-    const int kyo = mir ? L - ky : ky;
-    const T sy = mir ? T(-1) : T(1);
-    const T* K = a.K + (long)kx * a.Hy + kyo;
-    V* col = buf + j * a.f.pitch + a.pos[ky];
-    if constexpr (PZ == 1) {
-      V mx = col[0], my = col[cl], mz = col[2 * cl];
-      sym3<T>(mx, my, mz, K[0], K[ks], K[2 * ks], sy * K[3 * ks], T(0), T(0));
-      col[0] = mx;
-      col[cl] = my;
-      col[2 * cl] = mz;
-    } else {
-      V v[3][PZ];
+  const int j = a.dL.div(idx), ky = idx - j * L;
+  if (kx0 + j >= a.Hx) return;
+  const T sy = 2 * ky > L ? T(-1) : T(1);
+  V* col = buf + j * a.f.pitch + place[ky];
+  if constexpr (PZ == 1) {
+    V mx = col[0], my = col[cl], mz = col[2 * cl];
+    sym3<T>(mx, my, mz, k.v[0][0], k.v[0][1], k.v[0][2], sy * k.v[0][3], T(0), T(0));
+    col[0] = mx;
+    col[cl] = my;
+    col[2 * cl] = mz;
+  } else {
+    V v[3][PZ];
 #pragma unroll
-      for (int z = 0; z < PZ / 2; ++z) {
-        const bool in = z < a.nz;
-        const int o = in ? z * zl : 0;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const V x = col[c * cl + o];
-          v[c][z] = in ? x : cmk<T>(T(0), T(0));
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < 3; ++c) dft_hz<T, PZ>(v[c]);
-      // plane kz and its mirror PZ - kz share their kernel values, the
-      // components odd along z with opposite signs
-#pragma unroll
-      for (int kz = 0; kz <= PZ / 2; ++kz) {
-        const T* q = K + kz * kzs;
-        const T kxx = q[0], kyy = q[ks], kzz = q[2 * ks];
-        const T kxy = sy * q[3 * ks], kxz = q[4 * ks], kyz = sy * q[5 * ks];
-        sym3<T>(v[0][kz], v[1][kz], v[2][kz], kxx, kyy, kzz, kxy, kxz, kyz);
-        if (kz > 0 && 2 * kz < PZ)
-          sym3<T>(v[0][PZ - kz], v[1][PZ - kz], v[2][PZ - kz], kxx, kyy, kzz, kxy, -kxz, -kyz);
-      }
+    for (int z = 0; z < PZ / 2; ++z) {
+      const bool in = z < a.nz;
+      const int o = in ? z * zl : 0;
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        dft<T, PZ, true>(v[c]);
-#pragma unroll
-        for (int z = 0; z < PZ / 2; ++z)
-          if (z < a.nz) col[c * cl + z * zl] = v[c][z];
+        const V x = col[c * cl + o];
+        v[c][z] = in ? x : cmk<T>(T(0), T(0));
       }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) dft_hz<T, PZ>(v[c]);
+    // plane kz and its mirror PZ - kz share their kernel values, the
+    // components odd along z with opposite signs
+#pragma unroll
+    for (int kz = 0; kz <= PZ / 2; ++kz) {
+      const T* q = k.v[kz];
+      const T kxy = sy * q[3], kyz = sy * q[5];
+      sym3<T>(v[0][kz], v[1][kz], v[2][kz], q[0], q[1], q[2], kxy, q[4], kyz);
+      if (kz > 0 && 2 * kz < PZ)
+        sym3<T>(v[0][PZ - kz], v[1][PZ - kz], v[2][PZ - kz], q[0], q[1], q[2], kxy, -q[4], -kyz);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      dft<T, PZ, true>(v[c]);
+#pragma unroll
+      for (int z = 0; z < PZ / 2; ++z)
+        if (z < a.nz) col[c * cl + z * zl] = v[c][z];
     }
   }
 }
@@ -320,25 +345,38 @@ __device__ __forceinline__ void yz_columns(const YzArgs<T>& a, cpx<T>* buf, int 
 // enough waves)
 #define MMP_YZ_SMALL(X) X(1) X(4) X(6) X(8)
 #define MMP_YZ_LARGE(X) X(10) X(12) X(14) X(16)
+#define MMP_YZ_LENGTHS(X) MMP_YZ_SMALL(X) MMP_YZ_LARGE(X)
+constexpr int kYzClasses = 2;   // launches of a batch: short, long columns
 
-template <typename T, typename COL>
-__device__ __forceinline__ void yz_body(const YzArgs<T>& a, int bx, COL&& columns) {
+// The first column's kernel values are asked for with the lines, two
+// transforms before their use; blocks whose lines are longer than their
+// threads load the later columns' at their turn.  The controller's flags come
+// beside the lines, too, not before them.
+template <typename T, int PZ>
+__device__ __forceinline__ void yz_body(const YzArgs<T>& a, int zero, int bx) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  const bool stop = ctrl_stopped(a.ctrl, zero);
   extern __shared__ char smem_raw[];
   V* buf = reinterpret_cast<V*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int kx0 = bx * a.nk;
-  const int lines = 3 * a.nz * a.nk;
-  line_fft_fwd<T>(a.f, buf, a.tw, lines, a.half != 0, tid, nthr, [&](int l, int n) -> V {
+  const int lines = 3 * a.nz * a.nk, ncol = a.nk * a.f.L;
+  const V* twl = line_stage_tw<T>(a.f, buf, lines, a.tw, tid, nthr);
+  YzKernel<T, PZ> k;
+  yz_load_k<T, PZ>(a, kx0, tid < ncol ? tid : 0, k);
+  line_fft_fwd<T>(a.f, buf, a.tw, twl, lines, a.half != 0, tid, nthr, [&](int l, int n) -> V {
     const int kx = kx0 + (l & (a.nk - 1));
     const bool in = kx < a.Hx && n < a.ny;
     const V v = a.S1[in ? ((long)(l >> a.lnk) * a.Hx + kx) * a.ldy + n : 0];
     return in ? v : cmk<T>(T(0), T(0));
   });
-  columns(buf, kx0, tid, nthr);
+  if (stop) return;
+  for (int idx = tid; idx < ncol; idx += nthr) {
+    if (idx != tid) yz_load_k<T, PZ>(a, kx0, idx, k);
+    yz_column<T, PZ>(a, buf, line_places(a.f, twl), kx0, idx, k);
+  }
   __syncthreads();
-  line_fft_inv<T>(a.f, buf, a.tw, lines, a.half != 0, tid, nthr, [&](int l, int n, V v) {
+  line_fft_inv<T>(a.f, buf, twl, lines, a.half != 0, tid, nthr, [&](int l, int n, V v) {
     const int kx = kx0 + (l & (a.nk - 1));
     if (kx < a.Hx && n < a.ny) a.S1[((long)(l >> a.lnk) * a.Hx + kx) * a.ldy + n] = v;
   });
@@ -346,9 +384,8 @@ __device__ __forceinline__ void yz_body(const YzArgs<T>& a, int bx, COL&& column
 
 template <typename T, int PZ>
 __global__ __launch_bounds__(yz_max_threads((int)sizeof(T), PZ)) void k_yz(YzArgs<T> a) {
-  yz_body<T>(a, blockIdx.x, [&](cpx<T>* buf, int kx0, int tid, int nthr) {
-    yz_columns<T, PZ>(a, buf, kx0, tid, nthr);
-  });
+  const int zero = warm_args<YzArgs<T>>();
+  yz_body<T, PZ>(a, zero, blockIdx.x);
 }
 
 // ---------------------------------------------------------------- z pass --
@@ -360,15 +397,14 @@ struct ZArgs {
   cpx<T>* S2;     // [3][nz][Hx][Py]
   const T* K;     // [6][Hz][Hx][Hy]
   const cpx<T>* tw;
-  const int* pos;
   int nz, Hx, Py, Hy, Hz, tk, ltk;
   LineFft f;
 };
 
 template <typename T>
-__device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int bx, int by) {
+__device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int zero, int bx, int by) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  if (ctrl_stopped(a.ctrl, zero)) return;
   extern __shared__ char smem_raw[];
   V* buf = reinterpret_cast<V*>(smem_raw);
   const int tid = threadIdx.x, nthr = blockDim.x;
@@ -377,6 +413,7 @@ __device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int bx, int by)
   const long zstride = (long)a.Hx * a.Py;
   const long cstride = (long)a.nz * zstride;
   V* base = a.S2 + (long)kx * a.Py + ky0;
+  const V* twl = line_stage_tw<T>(a.f, buf, 3 * tk, a.tw, tid, nthr);
   // planes in natural order, columns fastest (coalesced along ky)
   for (int c = 0; c < 3; ++c)
     for (int idx = tid; idx < tk * L; idx += nthr) {
@@ -385,8 +422,9 @@ __device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int bx, int by)
       const V v = base[in ? c * cstride + z * zstride + j : 0];
       buf[(c * tk + j) * pitch + z + a.f.drl.div(z) * a.f.pad] = in ? v : cmk<T>(T(0), T(0));
     }
+  lds_copies_done();
   __syncthreads();
-  line_fft_fwd_lds<T>(a.f, buf, a.tw, 3 * tk, tid, nthr);
+  line_fft_fwd_lds<T>(a.f, buf, twl, 3 * tk, tid, nthr);
   const long ks = (long)a.Hz * a.Hx * a.Hy;
   for (int idx = tid; idx < tk * L; idx += nthr) {
     const int j = idx & (tk - 1), kz = idx >> a.ltk;
@@ -396,7 +434,7 @@ __device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int bx, int by)
     const T sy = ky <= a.Py / 2 ? T(1) : T(-1);
     const int kzo = kz <= L / 2 ? kz : L - kz;
     const T sz = kz <= L / 2 ? T(1) : T(-1);
-    V* p = buf + j * pitch + a.pos[kz];
+    V* p = buf + j * pitch + line_places(a.f, twl)[kz];
     const int cl = tk * pitch;
     const T* K = a.K + ((long)kzo * a.Hx + kx) * a.Hy + kyo;
     V mx = p[0], my = p[cl], mz = p[2 * cl];
@@ -407,7 +445,7 @@ __device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int bx, int by)
     p[2 * cl] = mz;
   }
   __syncthreads();
-  line_fft_inv_lds<T>(a.f, buf, a.tw, 3 * tk, tid, nthr);
+  line_fft_inv_lds<T>(a.f, buf, twl, 3 * tk, tid, nthr);
   for (int c = 0; c < 3; ++c)
     for (int idx = tid; idx < tk * a.nz; idx += nthr) {
       const int j = idx & (tk - 1), z = idx >> a.ltk;
@@ -419,7 +457,8 @@ __device__ __forceinline__ void fftz_mul_body(const ZArgs<T>& a, int bx, int by)
 
 template <typename T>
 __global__ __launch_bounds__(kLineThreads) void k_fftz_mul(ZArgs<T> a) {
-  fftz_mul_body<T>(a, blockIdx.x, blockIdx.y);
+  const int zero = warm_args<ZArgs<T>>();
+  fftz_mul_body<T>(a, zero, blockIdx.x, blockIdx.y);
 }
 
 // --------------------------------------------------------- batched passes --
@@ -431,30 +470,30 @@ constexpr int kMultiThreads = 256;
 
 template <typename T>
 __global__ __launch_bounds__(kMultiThreads) void k_fftx_fwd_multi(
-    const XArgs<T>* __restrict__ args, const int4* __restrict__ work, int stage) {
+    const XArgs<T>* __restrict__ args, const int4* __restrict__ work, int src) {
   const int4 w = work[blockIdx.x];
-  fftx_fwd_body<T>(args[w.x], stage, w.y, w.z, w.w);
+  fftx_fwd_body<T>(args[w.x], warm_lines((const uint32_t*)&args[w.x], (int)sizeof(XArgs<T>)), src, w.y, w.z, w.w);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kMultiThreads) void k_fftx_inv_multi(
     const XArgs<T>* __restrict__ args, const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
-  fftx_inv_body<T>(args[w.x], w.y, w.z, w.w);
+  fftx_inv_body<T>(args[w.x], warm_lines((const uint32_t*)&args[w.x], (int)sizeof(XArgs<T>)), w.y, w.z, w.w);
 }
 
 template <typename T, bool INV>
 __global__ __launch_bounds__(kMultiThreads) void k_ffty_multi(const YArgs<T>* __restrict__ args,
                                                               const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
-  ffty_body<T, INV>(args[w.x], w.y);
+  ffty_body<T, INV>(args[w.x], 0, w.y);
 }
 
 template <typename T>
 __global__ __launch_bounds__(kMultiThreads) void k_fftz_mul_multi(
     const ZArgs<T>* __restrict__ args, const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
-  fftz_mul_body<T>(args[w.x], w.y, w.z);
+  fftz_mul_body<T>(args[w.x], 0, w.y, w.z);
 }
 
 // LARGE: the members with z pads of 10..16 (one launch for them and one for
@@ -464,15 +503,14 @@ __global__ __launch_bounds__(kMultiThreads) void k_yz_multi(const YzArgs<T>* __r
                                                             const int4* __restrict__ work) {
   const int4 w = work[blockIdx.x];
   const YzArgs<T>& a = args[w.x];
-  yz_body<T>(a, w.y, [&](cpx<T>* buf, int kx0, int tid, int nthr) {
-#define X(P) case P: yz_columns<T, P>(a, buf, kx0, tid, nthr); break;
-    if constexpr (LARGE) {
-      switch (a.Pz) { MMP_YZ_LARGE(X) }
-    } else {
-      switch (a.Pz) { MMP_YZ_SMALL(X) }
-    }
+  const int zero = warm_lines((const uint32_t*)&a, (int)sizeof(YzArgs<T>));
+#define X(P) case P: yz_body<T, P>(a, zero, w.y); break;
+  if constexpr (LARGE) {
+    switch (a.Pz) { MMP_YZ_LARGE(X) }
+  } else {
+    switch (a.Pz) { MMP_YZ_SMALL(X) }
+  }
 #undef X
-  });
 }
 
 // ------------------------------------------------------------------ plan --
@@ -497,12 +535,16 @@ static int line_threads(const LineFft& f, long lines, int most) {
 // 160 KiB of a CU; a block that size still moves a quarter of what the
 // separate passes move through memory).
 static constexpr long kYzLds = 131072;
-static bool yz_fits(int nz, int Pz, const LineFft& fy, int real_bytes) {
-  bool built = false;
-#define X(P) built = built || (P > 1 && Pz == P);
-  MMP_YZ_SMALL(X) MMP_YZ_LARGE(X)
+static bool yz_built(int Pz) {
+  switch (Pz) {
+#define X(P) case P: return true;
+    MMP_YZ_LENGTHS(X)
 #undef X
-  return nz > 1 && built && 3L * nz * fy.pitch * 2 * real_bytes <= kYzLds;
+  }
+  return false;
+}
+static bool yz_fits(int nz, int Pz, const LineFft& fy, int real_bytes) {
+  return nz > 1 && Pz > 1 && yz_built(Pz) && (long)line_lds_elems(fy, 3L * nz, 2 * real_bytes) * 2 * real_bytes <= kYzLds;
 }
 
 // An open axis is zero-padded to P >= 2n - 1; a periodic one is cyclic
@@ -664,9 +706,9 @@ template <typename T>
 static XArgs<T> x_args(const DemagPlan& p, const DemagBufs<T>& b, const Table<T>* tbl, int stage,
                        const Ctrl* ctrl, T ms0, T ms1, T ms2, int nsub, int ty) {
   XArgs<T> a{};
-  a.tbl = tbl; a.ctrl = ctrl; a.stage = stage;
+  a.tbl = tbl; a.ctrl = ctrl; a.src = slot_in(stage, b.ns);
   a.ms0 = ms0; a.ms1 = ms1; a.ms2 = ms2; a.nsub = nsub;
-  a.S1 = b.S1; a.Bd = b.Bd; a.tw = b.twx; a.pos = b.posx;
+  a.S1 = b.S1; a.Bd = b.Bd; a.tw = b.twx;
   a.nx = p.nx; a.ny = p.ny; a.nz = p.nz; a.Hx = p.Hx; a.ldy = p.ldy;
   a.ty = ty; a.lnl = log2i(ty / 2); a.half = p.rep[0] > 0 || p.Px == 1 ? 0 : 1; a.f = p.fx;
   return a;
@@ -675,7 +717,7 @@ static XArgs<T> x_args(const DemagPlan& p, const DemagBufs<T>& b, const Table<T>
 template <typename T>
 static YzArgs<T> yz_args(const DemagPlan& p, const DemagBufs<T>& b, const Ctrl* ctrl, int nk) {
   YzArgs<T> a{};
-  a.ctrl = ctrl; a.S1 = b.S1; a.K = b.K; a.tw = b.twy; a.pos = b.posy;
+  a.ctrl = ctrl; a.S1 = b.S1; a.K = b.K; a.tw = b.twy;
   a.ny = p.ny; a.nz = p.nz; a.Pz = p.Pz; a.Hx = p.Hx; a.Hy = p.Hy; a.Hz = p.Hz; a.ldy = p.ldy;
   a.nk = nk; a.lnk = log2i(nk); a.half = p.rep[1] > 0 || p.Py == 1 ? 0 : 1;
   a.dL = make_div(p.Py); a.f = p.fy;
@@ -685,7 +727,7 @@ static YzArgs<T> yz_args(const DemagPlan& p, const DemagBufs<T>& b, const Ctrl* 
 template <typename T>
 static ZArgs<T> z_args(const DemagPlan& p, const DemagBufs<T>& b, const Ctrl* ctrl, int tk) {
   ZArgs<T> a{};
-  a.ctrl = ctrl; a.S2 = b.S2; a.K = b.K; a.tw = b.twz; a.pos = b.posz;
+  a.ctrl = ctrl; a.S2 = b.S2; a.K = b.K; a.tw = b.twz;
   a.nz = p.nz; a.Hx = p.Hx; a.Py = p.Py; a.Hy = p.Hy; a.Hz = p.Hz;
   a.tk = tk; a.ltk = log2i(tk); a.f = p.fz;
   return a;
@@ -704,7 +746,7 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
       if (p.p2x) {
         const size_t lds4 = x4_lds_bytes(p.Px, ty / 2, inv, (int)sizeof(V));
         X4Args<T> a;
-        a.tbl = tbl; a.ctrl = ctrl; a.stage = stage; a.ms0 = ms0; a.ms1 = ms1; a.nsub = nsub;
+        a.tbl = tbl; a.ctrl = ctrl; a.src = slot_in(stage, b.ns); a.ms0 = ms0; a.ms1 = ms1; a.nsub = nsub;
         a.ms2 = ms2;
         a.S1 = b.S1; a.Bd = b.Bd; a.tw4 = b.tw4x;
         a.nx = p.nx; a.ny = p.ny; a.nz = p.nz; a.Hx = p.Hx; a.ldy = p.ldy; a.ty = ty;
@@ -714,7 +756,7 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
       } else {
         const XArgs<T> a = x_args<T>(p, b, tbl, stage, ctrl, ms0, ms1, ms2, nsub, ty);
         const dim3 blk(x_threads(p, ty));
-        const size_t lds = (size_t)(ty / 2) * p.fx.pitch * sizeof(V);
+        const size_t lds = line_lds_elems(p.fx, ty / 2, sizeof(V)) * sizeof(V);
         if (inv) hipLaunchKernelGGL((k_fftx_inv<T>), g, blk, lds, st, a);
         else hipLaunchKernelGGL((k_fftx_fwd<T>), g, blk, lds, st, a);
       }
@@ -730,7 +772,7 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
         launch_m4<T>(p.Py, p.rep[1] > 0, g, m2_threads(p, (int)sizeof(T)), lds, st, a);
       } else {
         hipLaunchKernelGGL((k_yz<T, 1>), g, dim3(m2_threads(p, (int)sizeof(T))),
-                           (size_t)3 * p.nk * p.fy.pitch * sizeof(V), st,
+                           line_lds_elems(p.fy, 3L * p.nk, sizeof(V)) * sizeof(V), st,
                            yz_args<T>(p, b, ctrl, p.nk));
       }
       break;
@@ -738,11 +780,11 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
     case DP_YZ: {
       const dim3 g(p.Hx);
       const dim3 blk(line_threads(p.fy, 3L * p.nz, yz_max_threads((int)sizeof(T), p.Pz)));
-      const size_t lds = (size_t)3 * p.nz * p.fy.pitch * sizeof(V);
+      const size_t lds = line_lds_elems(p.fy, 3L * p.nz, sizeof(V)) * sizeof(V);
       const YzArgs<T> a = yz_args<T>(p, b, ctrl, 1);
       switch (p.Pz) {
 #define X(P) case P: hipLaunchKernelGGL((k_yz<T, P>), g, blk, lds, st, a); break;
-        MMP_YZ_SMALL(X) MMP_YZ_LARGE(X)
+        MMP_YZ_LENGTHS(X)
 #undef X
       }
       break;
@@ -766,11 +808,11 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
         launch_y4<T>(p.Py, inv, p.rep[1] > 0, g, y_threads(p, nl), lds, st, a);
       } else {
         YArgs<T> a{};
-        a.ctrl = ctrl; a.in = in; a.out = out; a.tw = b.twy; a.pos = b.posy;
+        a.ctrl = ctrl; a.in = in; a.out = out; a.tw = b.twy;
         a.nlines = nlines; a.nvalid_in = nvi; a.ld_in = ldi; a.nvalid_out = nvo; a.ld_out = ldo;
         a.nl = nl; a.half = p.rep[1] > 0 || p.Py == 1 ? 0 : 1; a.dL = make_div(p.Py); a.f = p.fy;
         const dim3 blk(y_threads(p, nl));
-        const size_t ldm = (size_t)nl * p.fy.pitch * sizeof(V);
+        const size_t ldm = line_lds_elems(p.fy, nl, sizeof(V)) * sizeof(V);
         if (inv) hipLaunchKernelGGL((k_ffty<T, true>), g, blk, ldm, st, a);
         else hipLaunchKernelGGL((k_ffty<T, false>), g, blk, ldm, st, a);
       }
@@ -787,7 +829,7 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
         launch_z4<T>(p.Pz, p.zq, p.zw, p.zmode, dim3(a.nb_pad), p.zt, st, a);
       } else {
         const dim3 g((p.Py + p.tk - 1) / p.tk, p.Hx), blk(z_threads(p));
-        hipLaunchKernelGGL((k_fftz_mul<T>), g, blk, (size_t)3 * p.tk * p.fz.pitch * sizeof(V), st,
+        hipLaunchKernelGGL((k_fftz_mul<T>), g, blk, line_lds_elems(p.fz, 3L * p.tk, sizeof(V)) * sizeof(V), st,
                            z_args<T>(p, b, ctrl, p.tk));
       }
       break;
@@ -803,7 +845,7 @@ struct DemagMulti<T>::Impl {
   std::vector<YArgs<T>> yf, yi;
   std::vector<ZArgs<T>> z;
   std::vector<YzArgs<T>> yz;
-  std::vector<int4> wxf, wxi, wyf, wyi, wz, wyz[2];   // wyz: short, long z columns
+  std::vector<int4> wxf, wxi, wyf, wyi, wz, wyz[kYzClasses];
   const XArgs<T>* d_xf = nullptr;
   const XArgs<T>* d_xi = nullptr;
   const YArgs<T>* d_yf = nullptr;
@@ -811,8 +853,8 @@ struct DemagMulti<T>::Impl {
   const ZArgs<T>* d_z = nullptr;
   const YzArgs<T>* d_yz = nullptr;
   const int4 *d_wxf = nullptr, *d_wxi = nullptr, *d_wyf = nullptr, *d_wyi = nullptr,
-             *d_wz = nullptr, *d_wyz[2] = {nullptr, nullptr};
-  size_t lds_x = 0, lds_y = 0, lds_z = 0, lds_yz[2] = {0, 0};
+             *d_wz = nullptr, *d_wyz[kYzClasses] = {};
+  size_t lds_x = 0, lds_y = 0, lds_z = 0, lds_yz[kYzClasses] = {};
 };
 
 template <typename T>
@@ -870,7 +912,7 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
           I.wxf.push_back(make_int4(gi, b, z, c));
           I.wxi.push_back(make_int4(gi, b, z, c));
         }
-    I.lds_x = std::max(I.lds_x, (size_t)(ty / 2) * p.fx.pitch * sizeof(V));
+    I.lds_x = std::max(I.lds_x, line_lds_elems(p.fx, ty / 2, sizeof(V)) * sizeof(V));
     if (p.nz == 1 || p.fuse) {
       const int nk = p.fuse ? 1 : pow2_floor(cap / (3L * p.Py), 64);
       I.yz.push_back(yz_args<T>(p, mb.bufs, mb.ctrl, nk));
@@ -878,12 +920,12 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
       for (int b = 0; b < (p.Hx + nk - 1) / nk; ++b)
         I.wyz[cls].push_back(make_int4(idx, b, 0, 0));
       I.lds_yz[cls] =
-          std::max(I.lds_yz[cls], (size_t)3 * p.nz * nk * p.fy.pitch * sizeof(V));
+          std::max(I.lds_yz[cls], line_lds_elems(p.fy, 3L * p.nz * nk, sizeof(V)) * sizeof(V));
     } else {
       const int nl = pow2_floor(cap / p.Py, 64);
       const int nlines = 3 * p.nz * p.Hx;
       YArgs<T> a{};
-      a.ctrl = mb.ctrl; a.tw = mb.bufs.twy; a.pos = mb.bufs.posy; a.nlines = nlines; a.nl = nl;
+      a.ctrl = mb.ctrl; a.tw = mb.bufs.twy; a.nlines = nlines; a.nl = nl;
       a.half = p.rep[1] > 0 || p.Py == 1 ? 0 : 1; a.dL = make_div(p.Py); a.f = p.fy;
       YArgs<T> f = a, i = a;
       f.in = mb.bufs.S1; f.out = mb.bufs.S2;
@@ -897,13 +939,13 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
         I.wyf.push_back(make_int4(idx, b, 0, 0));
         I.wyi.push_back(make_int4(idx, b, 0, 0));
       }
-      I.lds_y = std::max(I.lds_y, (size_t)nl * p.fy.pitch * sizeof(V));
+      I.lds_y = std::max(I.lds_y, line_lds_elems(p.fy, nl, sizeof(V)) * sizeof(V));
       const int tk = pow2_floor(cap / (3L * p.Pz), 64);
       I.z.push_back(z_args<T>(p, mb.bufs, mb.ctrl, tk));
       const int zi = (int)I.z.size() - 1;
       for (int kx = 0; kx < p.Hx; ++kx)
         for (int b = 0; b < (p.Py + tk - 1) / tk; ++b) I.wz.push_back(make_int4(zi, b, kx, 0));
-      I.lds_z = std::max(I.lds_z, (size_t)3 * tk * p.fz.pitch * sizeof(V));
+      I.lds_z = std::max(I.lds_z, line_lds_elems(p.fz, 3L * tk, sizeof(V)) * sizeof(V));
     }
   }
   // one device allocation, 256-byte aligned segments
@@ -923,8 +965,8 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
   const size_t o_wyf = seg(I.wyf.size() * sizeof(int4));
   const size_t o_wyi = seg(I.wyi.size() * sizeof(int4));
   const size_t o_wz = seg(I.wz.size() * sizeof(int4));
-  const size_t o_wyz0 = seg(I.wyz[0].size() * sizeof(int4));
-  const size_t o_wyz1 = seg(I.wyz[1].size() * sizeof(int4));
+  size_t o_wyz[kYzClasses];
+  for (int i = 0; i < kYzClasses; ++i) o_wyz[i] = seg(I.wyz[i].size() * sizeof(int4));
   // the block only grows: freeing it waits for every stream of the device
   if (off > cap_) {
     DeviceLock lk(device_mutex());
@@ -952,10 +994,12 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
                  put(o_wxi, I.wxi.data(), I.wxi.size() * sizeof(int4)),
                  put(o_wyf, I.wyf.data(), I.wyf.size() * sizeof(int4)),
                  put(o_wyi, I.wyi.data(), I.wyi.size() * sizeof(int4)),
-                 put(o_wz, I.wz.data(), I.wz.size() * sizeof(int4)),
-                 put(o_wyz0, I.wyz[0].data(), I.wyz[0].size() * sizeof(int4)),
-                 put(o_wyz1, I.wyz[1].data(), I.wyz[1].size() * sizeof(int4))})
+                 put(o_wz, I.wz.data(), I.wz.size() * sizeof(int4))})
     if (r != hipSuccess) e = r;
+  for (int i = 0; i < kYzClasses; ++i) {
+    const hipError_t r = put(o_wyz[i], I.wyz[i].data(), I.wyz[i].size() * sizeof(int4));
+    if (r != hipSuccess) e = r;
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     release();
@@ -974,8 +1018,8 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
   I.d_wyf = reinterpret_cast<const int4*>(mem_ + o_wyf);
   I.d_wyi = reinterpret_cast<const int4*>(mem_ + o_wyi);
   I.d_wz = reinterpret_cast<const int4*>(mem_ + o_wz);
-  I.d_wyz[0] = reinterpret_cast<const int4*>(mem_ + o_wyz0);
-  I.d_wyz[1] = reinterpret_cast<const int4*>(mem_ + o_wyz1);
+  for (int i = 0; i < kYzClasses; ++i)
+    I.d_wyz[i] = reinterpret_cast<const int4*>(mem_ + o_wyz[i]);
   return 0;
 }
 
@@ -985,7 +1029,7 @@ void DemagMulti<T>::launch(int stage, hipStream_t st) const {
   const Impl& I = *impl;
   const dim3 b(kMultiThreads);
   hipLaunchKernelGGL((k_fftx_fwd_multi<T>), dim3((unsigned)I.wxf.size()), b, I.lds_x, st, I.d_xf,
-                     I.d_wxf, stage);
+                     I.d_wxf, slot_in(stage, RK::t[RK_DP45].ns));
   if (!I.wyz[0].empty())
     hipLaunchKernelGGL((k_yz_multi<T, false>), dim3((unsigned)I.wyz[0].size()), b, I.lds_yz[0], st,
                        I.d_yz, I.d_wyz[0]);

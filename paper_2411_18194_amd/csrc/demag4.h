@@ -10,7 +10,7 @@ template <typename T>
 struct X4Args {
   const Table<T>* tbl;
   const Ctrl* ctrl;
-  int stage;
+  int src;    // table slot of the state to transform
   T ms0, ms1, ms2;
   int nsub;
   cpx<T>* S1;

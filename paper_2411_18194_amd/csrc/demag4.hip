@@ -75,7 +75,8 @@ __device__ __forceinline__ void fs_step3(cpx<T> (*u)[L2], const cpx<T>* line, in
 template <typename T, int L1, int L2, bool INV, bool FULL>
 __global__ __launch_bounds__(256) void k4_ffty(Y4Args<T> a) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  const int zero = warm_args<Y4Args<T>>();
+  if (ctrl_stopped(a.ctrl, zero)) return;
   constexpr int L = L1 * L2;
   extern __shared__ char smem_raw[];
   V* lds = reinterpret_cast<V*>(smem_raw);
@@ -236,7 +237,9 @@ constexpr int xhalf_stride() { return L / 2 + 32; }
 template <typename T, int L1, int L2, bool FULL, bool HALF = false>
 __global__ __launch_bounds__(256) void k4_fftx_fwd(X4Args<T> a) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  const int zero = warm_args<X4Args<T>>();
+  const gcptr<T> m = (gcptr<T>)table_slot<T>(a.tbl, a.src + zero);
+  if (ctrl_stopped(a.ctrl, zero)) return;
   constexpr int L = L1 * L2;
   extern __shared__ char smem_raw[];
   V* lds = reinterpret_cast<V*>(smem_raw);
@@ -245,7 +248,6 @@ __global__ __launch_bounds__(256) void k4_fftx_fwd(X4Args<T> a) {
   const int c = blockIdx.z, z = blockIdx.y, y0 = blockIdx.x * a.ty;
   const int nl = a.ty >> 1;
   const long N = (long)a.nx * a.ny * a.nz;
-  const gcptr<T> m = (gcptr<T>)stage_in(a.tbl, a.stage);
   const gcptr<T> m0 = m + (long)c * N + (long)z * a.ny * a.nx;
   const gcptr<T> m1 = m0 + 3 * N;
   const int ya = y0 + 2 * q, yb = ya + 1;
@@ -326,7 +328,8 @@ __global__ __launch_bounds__(256) void k4_fftx_fwd(X4Args<T> a) {
 template <typename T, int L1, int L2>
 __global__ __launch_bounds__(256) void k4_fftx_inv(X4Args<T> a) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  const int zero = warm_args<X4Args<T>>();
+  if (ctrl_stopped(a.ctrl, zero)) return;
   constexpr int L = L1 * L2;
   extern __shared__ char smem_raw[];
   V* lds = reinterpret_cast<V*>(smem_raw);
@@ -397,7 +400,8 @@ __global__ __launch_bounds__(256) void k4_fftx_inv(X4Args<T> a) {
 template <typename T, int L1, int L2, bool FULL>
 __global__ __launch_bounds__(256) void k4_ffty_mul2d(M4Args<T> a) {
   using V = cpx<T>;
-  if (ctrl_stopped(a.ctrl)) return;
+  const int zero = warm_args<M4Args<T>>();
+  if (ctrl_stopped(a.ctrl, zero)) return;
   constexpr int L = L1 * L2;
   extern __shared__ char smem_raw[];
   V* lds = reinterpret_cast<V*>(smem_raw);

@@ -19,6 +19,7 @@ struct ElasticArgs {
   int mel[2];                    // sublattice contributes a force
   const Table<T>* tbl;
   Ctrl* ctrl;
+  int rk;                        // the pair (RK::t), host side
   int stage;                     // 1..7, or 0 = evaluate at (un, vn)
   int fuse2;
   T* eps;                        // [6][N] strain of the stage input

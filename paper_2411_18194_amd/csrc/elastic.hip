@@ -62,7 +62,8 @@ __device__ __forceinline__ void cubic_stress(const ElasticArgs<T>& a, const T* e
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int eval) {
+__global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int ns, double cs, int eval) {
+  const gcptr<T> u0 = u_in<T>(a.tbl, a.stage, ns), v0 = v_in<T>(a.tbl, a.stage, ns);
   if (ctrl_stopped(a.ctrl)) return;
   int x, y, z;
   const bool in = tile_cell((int)blockIdx.x, a.nbx, a.nby, a.nx, a.ny, &x, &y, &z);
@@ -74,11 +75,11 @@ __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int eval) {
                   dz = diff_at<T>(z, a.nz, a.nx * a.ny, a.dz);
     const bool flat = a.nz == 1;
     T e[6], s[6];
-    sym_grad<T>((gcptr<T>)u_in(a.tbl, a.stage) + i, N, dx, dy, dz, flat, e);
+    sym_grad<T>(u0 + i, N, dx, dy, dz, flat, e);
     cubic_stress<T>(a, e, s);
 #pragma unroll
     for (int c = 0; c < 6; ++c) a.eps[c * N + i] = e[c];
-    const gcptr<T> v = (gcptr<T>)v_in(a.tbl, a.stage) + i;
+    const gcptr<T> v = v0 + i;
     if (eval) {
       double w = 0.0;
       for (int c = 0; c < 3; ++c) w += (double)s[c] * e[c];
@@ -104,8 +105,7 @@ __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int eval) {
       for (int j = 0; j < 3; ++j) s[voigt(k, j)] = face ? T(0) : s[voigt(k, j)];
     }
     if (a.trac_amp != 0.0 && a.nx >= 2 && x == 0) {
-      const double ts = a.ctrl ? a.ctrl->t + (a.stage > 0 ? RK::t[a.tbl->rk].c[a.stage - 1] * a.ctrl->h : 0.0)
-                               : 0.0;
+      const double ts = a.ctrl ? a.ctrl->t + cs * a.ctrl->h : 0.0;
       s[4] = (T)(a.trac_amp * sin(a.trac_omega * ts));
     }
 #pragma unroll
@@ -124,9 +124,8 @@ __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int eval) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_force(ElasticArgs<T> a) {
-  if (ctrl_stopped(a.ctrl)) return;
-  force_block<T>(a, (int)blockIdx.x);
+__global__ __launch_bounds__(256) void k_force(ElasticArgs<T> a, const RKStage rk) {
+  force_block<T>(a, rk, (int)blockIdx.x);
 }
 
 template <typename T>
@@ -147,13 +146,16 @@ static dim3 elastic_grid(const ElasticArgs<T>& a) {
 template <typename T>
 void launch_strain(const ElasticArgs<T>& a, bool eval, hipStream_t st, Prof* prof) {
   ProfScope ps(prof, P_ELASTIC, st);
-  hipLaunchKernelGGL(k_strain<T>, elastic_grid(a), dim3(256), 0, st, a, eval ? 1 : 0);
+  const RKTab& t = RK::t[a.rk];
+  hipLaunchKernelGGL(k_strain<T>, elastic_grid(a), dim3(256), 0, st, a, t.ns,
+                     a.stage > 0 ? t.c[a.stage - 1] : 0.0, eval ? 1 : 0);
 }
 
 template <typename T>
 void launch_force(const ElasticArgs<T>& a, hipStream_t st, Prof* prof) {
   ProfScope ps(prof, P_ELASTIC, st);
-  hipLaunchKernelGGL(k_force<T>, elastic_grid(a), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_force<T>, elastic_grid(a), dim3(256), 0, st, a,
+                     rk_stage(RK::t[a.rk], a.stage));
 }
 
 template <typename T>

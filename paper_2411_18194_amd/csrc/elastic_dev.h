@@ -41,29 +41,18 @@ __device__ __forceinline__ T deriv(gcptr<T> f, const Diff<T>& d) {
   return d.w1 * (f[d.p1] - f[d.m1]) + d.w2 * (f[d.p2] - f[d.m2]);
 }
 
+// input of stage s (0 or 1: the accepted state) among four buffers of u or v
 template <typename T>
-__device__ __forceinline__ const T* u_in(const Table<T>* t, int s) {
-  if (s == 0 || s == 1) return t->un;
-  if (s == t->ns) return t->unew;
-  return (s & 1) ? t->usb : t->usa;
+__device__ __forceinline__ gcptr<T> stage_pick(T* n, T* nw, T* a, T* b, int s, int ns) {
+  return uni_ptr((gcptr<T>)(s <= 1 ? n : s == ns ? nw : (s & 1) ? b : a));
 }
 template <typename T>
-__device__ __forceinline__ const T* v_in(const Table<T>* t, int s) {
-  if (s == 0 || s == 1) return t->vn;
-  if (s == t->ns) return t->vnew;
-  return (s & 1) ? t->vsb : t->vsa;
+__device__ __forceinline__ gcptr<T> u_in(const Table<T>* t, int s, int ns) {
+  return stage_pick<T>(t->un, t->unew, t->usa, t->usb, s, ns);
 }
 template <typename T>
-__device__ __forceinline__ T* u_out(const Table<T>* t, int s) {
-  const int n = s + 1;
-  if (n == t->ns) return t->unew;
-  return (n & 1) ? t->usb : t->usa;
-}
-template <typename T>
-__device__ __forceinline__ T* v_out(const Table<T>* t, int s) {
-  const int n = s + 1;
-  if (n == t->ns) return t->vnew;
-  return (n & 1) ? t->vsb : t->vsa;
+__device__ __forceinline__ gcptr<T> v_in(const Table<T>* t, int s, int ns) {
+  return stage_pick<T>(t->vn, t->vnew, t->vsa, t->vsb, s, ns);
 }
 
 // cell of thread t in 64x4 tile w of the plane-major tiles
@@ -108,12 +97,33 @@ __device__ __forceinline__ void stage_sum_n(int nj, const gcptr<T> yn, const gcp
 // Tile w of the force: divergence of the stress, magnetoelastic force of Eq.
 // 8 per sublattice, k_u and k_v, and the next stage's u and v.
 template <typename T>
-__device__ __forceinline__ void force_block(const ElasticArgs<T>& a, int w) {
+__device__ __forceinline__ void force_block(const ElasticArgs<T>& a, const RKStage& rk, int w) {
+  const int stage = a.stage, ns = rk.ns, nj = stage - 1;
+  // pointers and step size first, in one trip with the controller's flags
+  const gcptr<T> m0 = (gcptr<T>)table_slot<T>(a.tbl, rk.in), u0 = u_in<T>(a.tbl, stage, ns),
+                 v0 = v_in<T>(a.tbl, stage, ns);
+  const gptr<T> KU0 = uni_ptr((gptr<T>)a.tbl->ku[nj]), KV0 = uni_ptr((gptr<T>)a.tbl->kv[nj]);
+  const gcptr<T> un = uni_ptr((gcptr<T>)a.tbl->un), vn = uni_ptr((gcptr<T>)a.tbl->vn);
+  gcptr<T> pu[5], pv[5];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    pu[j] = pv[j] = nullptr;
+    if (j < nj) {
+      pu[j] = uni_ptr((gcptr<T>)a.tbl->ku[j]);
+      pv[j] = uni_ptr((gcptr<T>)a.tbl->kv[j]);
+    }
+  }
+  // the next stage's input (the last stage of a fixed step: stage 2's)
+  const bool nxt = stage < ns && stage + 1 == ns;
+  const bool tosa = stage >= ns || (stage & 1) != 0;
+  const gptr<T> uo0 = uni_ptr((gptr<T>)(nxt ? a.tbl->unew : tosa ? a.tbl->usa : a.tbl->usb));
+  const gptr<T> vo0 = uni_ptr((gptr<T>)(nxt ? a.tbl->vnew : tosa ? a.tbl->vsa : a.tbl->vsb));
+  const double h = a.ctrl->h;
+  if (ctrl_stopped(a.ctrl)) return;
   int x, y, z;
   if (!tile_cell(w, a.nbx, a.nby, a.nx, a.ny, &x, &y, &z)) return;
   const long N = a.N;
   const long i = ((long)z * a.ny + y) * a.nx + x;
-  const int stage = a.stage;
   const Diff<T> dx = diff_at<T>(x, a.nx, 1, a.dx), dy = diff_at<T>(y, a.ny, a.nx, a.dy),
                 dz = diff_at<T>(z, a.nz, a.nx * a.ny, a.dz);
   const bool flat = a.nz == 1;   // no derivative along z
@@ -127,7 +137,7 @@ __device__ __forceinline__ void force_block(const ElasticArgs<T>& a, int w) {
     f[1] += deriv<T>(sg + 5 * N, dz);
     f[2] += deriv<T>(sg + 2 * N, dz);
   }
-  const gcptr<T> m = (gcptr<T>)stage_in(a.tbl, stage) + i;
+  const gcptr<T> m = m0 + i;
   for (int s = 0; s < a.nsub; ++s) {
     if (!a.mel[s]) continue;
     const gcptr<T> ms = m + (long)s * 3 * N;
@@ -152,52 +162,39 @@ __device__ __forceinline__ void force_block(const ElasticArgs<T>& a, int w) {
       f[r] += acc;
     }
   }
-  const gcptr<T> v = (gcptr<T>)v_in(a.tbl, stage) + i;
+  const gcptr<T> v = v0 + i;
   T ku[3], kv[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     ku[c] = v[c * N];
     kv[c] = (f[c] - a.eta * ku[c]) * a.inv_rho;
   }
-  const gptr<T> KU = (gptr<T>)a.tbl->ku[stage - 1] + i, KV = (gptr<T>)a.tbl->kv[stage - 1] + i;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    KU[c * N] = ku[c];
-    KV[c * N] = kv[c];
+    KU0[i + c * N] = ku[c];
+    KV0[i + c * N] = kv[c];
   }
-  const double h = a.ctrl->h;
-  const RKTab& rk = RK::t[a.tbl->rk];
-  const int nj = stage - 1;
-  if (stage < a.tbl->ns) {
+  if (stage < ns) {
     T c[5];
-    gcptr<T> pu[5], pv[5];
 #pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      c[j] = T(0);
-      pu[j] = pv[j] = nullptr;
-      if (j < nj) {
-        c[j] = (T)(rk.a[stage][j] * h);
-        pu[j] = (gcptr<T>)a.tbl->ku[j];
-        pv[j] = (gcptr<T>)a.tbl->kv[j];
-      }
-    }
+    for (int j = 0; j < 5; ++j) c[j] = (T)(rk.a[j] * h);
     T au[3], av[3];
-    stage_sum_n<T>(nj, (gcptr<T>)a.tbl->un, pu, c, i, N, au);
-    stage_sum_n<T>(nj, (gcptr<T>)a.tbl->vn, pv, c, i, N, av);
-    const gptr<T> uo = (gptr<T>)u_out(a.tbl, stage) + i, vo = (gptr<T>)v_out(a.tbl, stage) + i;
-    const T cs = (T)(rk.a[stage][nj] * h);
+    stage_sum_n<T>(nj, un, pu, c, i, N, au);
+    stage_sum_n<T>(nj, vn, pv, c, i, N, av);
+    T cs = T(0);   // weight of this stage's own slope
+#pragma unroll
+    for (int j = 0; j < 6; ++j) cs = j == nj ? (T)(rk.a[j] * h) : cs;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      uo[q * N] = au[q] + cs * ku[q];
-      vo[q * N] = av[q] + cs * kv[q];
+      uo0[i + q * N] = au[q] + cs * ku[q];
+      vo0[i + q * N] = av[q] + cs * kv[q];
     }
   } else if (a.fuse2) {
-    const gcptr<T> u = (gcptr<T>)u_in(a.tbl, stage) + i;
-    const T c21 = (T)(rk.a[1][0] * h);
+    const T c21 = (T)(rk.a10 * h);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      ((gptr<T>)a.tbl->usa)[i + c * N] = u[c * N] + c21 * ku[c];
-      ((gptr<T>)a.tbl->vsa)[i + c * N] = ku[c] + c21 * kv[c];
+      uo0[i + c * N] = u0[i + c * N] + c21 * ku[c];
+      vo0[i + c * N] = ku[c] + c21 * kv[c];
     }
   }
 }

@@ -7,7 +7,7 @@
 // butterfly at inner index lo by exp(-2 pi i q lo / (r_s M_s)), M_s the
 // length below digit s.  Digit s then holds frequency digit s, so the
 // spectrum sits at permuted places: bin k = d0 + r0 d1 + r0 r1 d2 + ... at
-// LDS element pos[k].  The inverse runs the stages backwards from there to
+// a place of its own (place_of).  The inverse runs the stages backwards from there to
 // natural order.  Nothing is reordered in between: what works on the
 // spectrum (the unpacking of two real lines, the kernel products, the z
 // transforms) looks its places up.
@@ -21,8 +21,8 @@
 // are padded to an odd pitch, so that the last pass (each thread on its own
 // row) spreads over the LDS banks.
 // Measured (MI355X, one launch): x forward / inverse of 183x77x5 FP32 cells
-// (lines of 378) 28.4 / 21.8 -> 7.5 / 7.2 us, of 333x130x1 FP64 (lines of
-// 672) 24.2 / 22.3 -> 9.8 / 9.6 us against passes of radix 2-8 with
+// (lines of 378) 28.4 / 21.8 -> 6.9 / 7.0 us, of 333x130x1 FP64 (lines of
+// 672) 24.2 / 22.3 -> 9.5 / 9.0 us against passes of radix 2-8 with
 // autosorting stages, two barriers each and integer divisions.
 #pragma once
 
@@ -285,6 +285,7 @@ struct LineStage {
 // memory.
 struct LineFft {
   int L, n, pitch;   // points, stages, padded elements per line
+  int ntw, nst;      // twiddles of all stages but the last; with the bins' places
   int rl, pad;       // last radix, padding per row of rl elements
   FastDiv drl;
   LineStage s0, s1, s2, s3;
@@ -300,6 +301,17 @@ struct LineFft {
     o.dM.m = (uint32_t)pick((int)s0.dM.m, (int)s1.dM.m, (int)s2.dM.m, (int)s3.dM.m);
     o.dnb.m = (uint32_t)pick((int)s0.dnb.m, (int)s1.dnb.m, (int)s2.dnb.m, (int)s3.dnb.m);
     return o;
+  }
+  // LDS place of bin k: its digits, least significant first, are the digits
+  // of the element index, most significant first
+  __host__ __device__ int place_of(int k) const {
+    int e = 0;
+    const LineStage* st[kMaxStages] = {&s0, &s1, &s2, &s3};
+    for (int s = 0; s < n; ++s) {
+      e += (k % st[s]->r) * st[s]->M;
+      k /= st[s]->r;
+    }
+    return e + e / rl * pad;
   }
 };
 
@@ -378,20 +390,28 @@ inline bool make_line_fft(int L, LineFft* f) {
     t.dnb = make_div(t.nb);
     if (!last) tw += r[s] * M;
   }
+  o.ntw = tw;
+  o.nst = (tw + 1) / 2 * 2 + (L + 3) / 4;
   *f = o;
   return true;
 }
 
-// twiddles of all stages but the last (fewer than 2 L), LDS place of bin k
-__host__ __device__ inline int line_tw_elems(int L) { return 2 * L; }
-inline int line_pos(const LineFft& f, int k) {
-  const LineStage* st[kMaxStages] = {&f.s0, &f.s1, &f.s2, &f.s3};
-  int e = 0;
-  for (int s = 0; s < f.n; ++s) {
-    e += (k % st[s]->r) * st[s]->M;
-    k /= st[s]->r;
-  }
-  return e + (e / f.rl) * f.pad;
+// Table of one axis, in complex elements: the twiddles of all stages but the
+// last (fewer than 1.6 L), then, from an even element on, the places of the
+// bins as 16-bit values (four or eight to an element; nst counts four).
+inline int line_tw_elems(int L) { return 2 * L + 256; }
+template <typename V>
+__host__ __device__ inline const uint16_t* line_places(const LineFft& f, const V* tw) {
+  return reinterpret_cast<const uint16_t*>(tw + (f.ntw + 1) / 2 * 2);
+}
+// LDS elements of `lines` lines (to an even number of elements) and, behind
+// them, the axis' table in whole kilobytes (line_stage_tw)
+__host__ __device__ inline int line_tw_at(const LineFft& f, int lines) {
+  return (lines * f.pitch + 1) & ~1;
+}
+inline size_t line_lds_elems(const LineFft& f, long lines, size_t elem_bytes) {
+  const size_t kb = 1024 / elem_bytes;
+  return line_tw_at(f, (int)lines) + (f.nst + kb - 1) / kb * kb;
 }
 
 // --------------------------------------------------------------- passes --
@@ -406,6 +426,30 @@ __device__ __forceinline__ int line_place(const LineFft& f, const LineStage& t, 
   *lo = l;
   return hi * t.HP + l + f.drl.div(l) * f.pad;
 }
+
+// Copies the axis' table behind the lines in LDS: every stage but the first
+// forward one reads its twiddles there, and whatever works on the spectrum
+// the places (a trip to L2 per stage is longer than the stage).  The copy goes to LDS without registers, 16 bytes per lane and 1 KiB
+// per wave, and nothing waits for it before lds_copies_done() and a barrier;
+// a copy through registers would hold up the data loads behind it.
+template <typename T>
+__device__ __forceinline__ const cpx<T>* line_stage_tw(const LineFft& f, cpx<T>* buf, int lines,
+                                                       const cpx<T>* __restrict__ tw, int tid,
+                                                       int nthr) {
+  constexpr int PER = 16 / (int)sizeof(cpx<T>), CH = 64 * PER;
+  cpx<T>* d = buf + line_tw_at(f, lines);
+  const int wave = uni(tid >> 6), lane = tid & 63, last = (f.nst - 1) / PER * PER;
+  for (int i = wave * CH; i < f.nst; i += (nthr >> 6) * CH) {
+    const int e = i + lane * PER;
+    // (the table has room behind nst: its last 16 bytes may reach past it)
+    const cpx<T>* src = tw + (e < f.nst ? e : last);
+    __builtin_amdgcn_global_load_lds(
+        (__attribute__((address_space(1))) void*)const_cast<cpx<T>*>(src),
+        (__attribute__((address_space(3))) void*)(d + i), 16, 0, 0);
+  }
+  return d;
+}
+__device__ __forceinline__ void lds_copies_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // First forward stage of `lines` lines: element n of line l comes from
 // ld(l, n) (which loads a clamped address where it must return zero), goes
@@ -433,12 +477,16 @@ __device__ __forceinline__ void line_fwd_first_r(const LineFft& f, cpx<T>* buf,
         for (int q = RH; q < R; ++q) v[q] = ld(l, q * t.M + b);
       }
     }
-    dft<T, R, false>(v);
+    // (the stage's twiddles come with the data, from memory)
     int lo;
     V* p = buf + l * f.pitch + line_place(f, t, b, &lo);
+    V t1[R];
+#pragma unroll
+    for (int q = 1; q < R; ++q) t1[q] = tw[f.n > 1 ? t.tw + q * t.M + lo : 0];
+    dft<T, R, false>(v);
     if (f.n > 1) {
 #pragma unroll
-      for (int q = 1; q < R; ++q) v[q] = cmul(v[q], tw[t.tw + q * t.M + lo]);
+      for (int q = 1; q < R; ++q) v[q] = cmul(v[q], t1[q]);
     }
 #pragma unroll
     for (int q = 0; q < R; ++q) p[q * t.PM] = v[q];
@@ -447,7 +495,7 @@ __device__ __forceinline__ void line_fwd_first_r(const LineFft& f, cpx<T>* buf,
 
 template <typename T, int R, bool INV>
 __device__ __forceinline__ void line_inner_r(const LineFft& f, const LineStage& t, bool twid,
-                                             cpx<T>* buf, const cpx<T>* __restrict__ tw,
+                                             cpx<T>* buf, const cpx<T>* tw,
                                              int lines, int tid, int nthr) {
   using V = cpx<T>;
   const int total = lines * t.nb;
@@ -476,7 +524,7 @@ __device__ __forceinline__ void line_inner_r(const LineFft& f, const LineStage& 
 // elements n >= L/2 are not wanted (radix even).
 template <typename T, int R, typename ST>
 __device__ __forceinline__ void line_inv_last_r(const LineFft& f, const cpx<T>* buf,
-                                                const cpx<T>* __restrict__ tw, int lines,
+                                                const cpx<T>* tw, int lines,
                                                 bool half, int tid, int nthr, ST&& st) {
   using V = cpx<T>;
   const LineStage t = f.s0;
@@ -505,23 +553,25 @@ __device__ __forceinline__ void line_inv_last_r(const LineFft& f, const cpx<T>* 
   }
 }
 
-// Forward transform of `lines` lines into LDS (spectrum at pos[k] of each
-// line).  Ends with a barrier.
+// Forward transform of `lines` lines into LDS (bin k at line_places()[k] of
+// each line); tw: the table in memory, twl: in LDS (line_stage_tw, no barrier
+// needed in between).  Ends with a barrier.
 template <typename T, typename LD>
 __device__ __forceinline__ void line_fft_fwd(const LineFft& f, cpx<T>* buf,
-                                             const cpx<T>* __restrict__ tw, int lines, bool half,
-                                             int tid, int nthr, LD&& ld) {
+                                             const cpx<T>* __restrict__ tw, const cpx<T>* twl,
+                                             int lines, bool half, int tid, int nthr, LD&& ld) {
   switch (f.s0.r) {
 #define X(R) case R: line_fwd_first_r<T, R>(f, buf, tw, lines, half, tid, nthr, ld); break;
     MMP_RADICES(X)
 #undef X
   }
+  lds_copies_done();
   __syncthreads();
   for (int s = 1; s < f.n; ++s) {
     const LineStage t = f.stage(s);
     const bool twid = s < f.n - 1;
     switch (t.r) {
-#define X(R) case R: line_inner_r<T, R, false>(f, t, twid, buf, tw, lines, tid, nthr); break;
+#define X(R) case R: line_inner_r<T, R, false>(f, t, twid, buf, twl, lines, tid, nthr); break;
       MMP_RADICES(X)
 #undef X
     }
@@ -529,24 +579,23 @@ __device__ __forceinline__ void line_fft_fwd(const LineFft& f, cpx<T>* buf,
   }
 }
 
-// Inverse transform (unnormalised) of `lines` spectra in LDS; the caller's
-// writes to LDS are behind a barrier.
+// Inverse transform (unnormalised) of `lines` spectra in LDS, twiddles in
+// LDS; the caller's writes to both are behind a barrier.
 template <typename T, typename ST>
-__device__ __forceinline__ void line_fft_inv(const LineFft& f, cpx<T>* buf,
-                                             const cpx<T>* __restrict__ tw, int lines, bool half,
-                                             int tid, int nthr, ST&& st) {
+__device__ __forceinline__ void line_fft_inv(const LineFft& f, cpx<T>* buf, const cpx<T>* twl,
+                                             int lines, bool half, int tid, int nthr, ST&& st) {
   for (int s = f.n - 1; s > 0; --s) {
     const LineStage t = f.stage(s);
     const bool twid = s < f.n - 1;
     switch (t.r) {
-#define X(R) case R: line_inner_r<T, R, true>(f, t, twid, buf, tw, lines, tid, nthr); break;
+#define X(R) case R: line_inner_r<T, R, true>(f, t, twid, buf, twl, lines, tid, nthr); break;
       MMP_RADICES(X)
 #undef X
     }
     __syncthreads();
   }
   switch (f.s0.r) {
-#define X(R) case R: line_inv_last_r<T, R>(f, buf, tw, lines, half, tid, nthr, st); break;
+#define X(R) case R: line_inv_last_r<T, R>(f, buf, twl, lines, half, tid, nthr, st); break;
     MMP_RADICES(X)
 #undef X
   }
@@ -556,7 +605,7 @@ __device__ __forceinline__ void line_fft_inv(const LineFft& f, cpx<T>* buf,
 // each ending with a barrier.
 template <typename T, bool INV>
 __device__ __forceinline__ void line_stage_lds(const LineFft& f, int s, cpx<T>* buf,
-                                               const cpx<T>* __restrict__ tw, int lines, int tid,
+                                               const cpx<T>* tw, int lines, int tid,
                                                int nthr) {
   const LineStage t = f.stage(s);
   const bool twid = s < f.n - 1;

@@ -53,6 +53,7 @@ struct FieldArgs {
   const T* eps;
   const Table<T>* tbl;
   Ctrl* ctrl;
+  int rk;                     // the pair (RK::t), host side
   int stage;
   int fuse2;
   double* errpart;
@@ -98,8 +99,8 @@ template <typename T>
 void launch_step_multi(const StepWork<T>* w, int ngrids, long max_cells, hipStream_t st);
 
 template <typename T>
-void launch_combine2(const Table<T>* tbl, const Ctrl* ctrl, long Ncell, int nsub, hipStream_t st,
-                     Prof* prof);
+void launch_combine2(const Table<T>* tbl, const Ctrl* ctrl, int rk, long Ncell, int nsub,
+                     hipStream_t st, Prof* prof);
 
 template <typename T>
 void launch_control(Ctrl* ctrl, Table<T>* tbl, const double* errpart, int nerr, int elastic,

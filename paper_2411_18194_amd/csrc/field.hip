@@ -167,23 +167,13 @@ __device__ __forceinline__ void sto(gptr<T> base, uint32_t o, T v) {
   *(gptr<T>)((gptr<char>)base + o) = v;
 }
 
-// a value that is the same in every lane, in a scalar register (loads through
-// the device tables are not known to be uniform)
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-template <typename P>
-__device__ __forceinline__ P uni_ptr(P p) {
-  const uint64_t v = (uint64_t)p;
-  const uint64_t lo = (uint32_t)uni((int)(uint32_t)v), hi = (uint32_t)uni((int)(v >> 32));
-  return (P)(lo | hi << 32);
-}
-
 // Block w (tile-major over z chunks) of one grid; stage and fuse2 come from
 // the launch so that one argument block serves every stage.
 // GDMI: general DMI tensors with the Eq. 6 ghosts on every stencil.
 // GBX: exchange links between different grains scaled by gbx_scale.
 template <typename T, int NSUB, bool EVAL, bool GDMI = false, bool GBX = false>
-__device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, const int stage,
-                                            const int fuse2) {
+__device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage& rk, const int zero, const int w,
+                                            const int stage, const int fuse2) {
   const int ntile = a.nbx * a.nby;
   if (w >= ntile * a.nzc) return;
   const int tile = w % ntile;
@@ -194,38 +184,37 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
   const bool in = x < a.nx && y < a.ny;
   const long N = a.N;
   const long N3 = 3 * N;
-  const gcptr<T> m = uni_ptr((gcptr<T>)(EVAL ? a.tbl->yn : stage_in(a.tbl, stage)));
-
+  // every pointer and the step size first: their loads and the controller's
+  // flags make one trip, the data the second
+  const gcptr<T> m = (gcptr<T>)table_slot<T>(a.tbl, rk.in + zero);
   double h = 0.0;
-  int ns = 0;
+  const int ns = rk.ns;
   T ca[6] = {0, 0, 0, 0, 0, 0};
-  double ew[7] = {0, 0, 0, 0, 0, 0, 0};
   gcptr<T> kin[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   gptr<T> kout = nullptr;
   gptr<T> ynext = nullptr;
   gcptr<T> yn = nullptr;
   if (!EVAL) {
     h = a.ctrl->h;
-    ns = uni(a.tbl->ns);
-    const RKTab& rk = RK::t[a.tbl->rk];
     kout = uni_ptr((gptr<T>)a.tbl->k[stage - 1]);
     yn = uni_ptr((gcptr<T>)a.tbl->yn);
-    for (int j = 0; j < stage - 1; ++j) kin[j] = uni_ptr((gcptr<T>)a.tbl->k[j]);
-    if (stage < ns) {
-      ynext = uni_ptr((gptr<T>)stage_out(a.tbl, stage));
-      for (int j = 0; j < stage; ++j) ca[j] = (T)(rk.a[stage][j] * h);
-    } else {
-      if (fuse2) ynext = uni_ptr((gptr<T>)a.tbl->sa);
-      ca[0] = (T)(rk.a[1][0] * h);
-      for (int j = 0; j < ns - 1; ++j) kin[j] = uni_ptr((gcptr<T>)a.tbl->k[j]);
-      for (int j = 0; j < ns; ++j) ew[j] = rk.e[j];
-    }
+#pragma unroll
+    for (int j = 0; j < 6; ++j)
+      if (j < stage - 1) kin[j] = uni_ptr((gcptr<T>)a.tbl->k[j]);
+    ynext = (gptr<T>)table_slot<T>(a.tbl, rk.out + zero);
   }
+  if (ctrl_stopped(a.ctrl, zero)) return;
+  if (!EVAL) {
+#pragma unroll
+    for (int j = 0; j < 6; ++j) ca[j] = (T)((stage < ns ? rk.a[j] : (j == 0 ? rk.a10 : 0.0)) * h);
+  }
+  const double* ew = rk.e;
   // slopes the one-sublattice march loads up front (see below): the ones
   // this stage sums, and in the other slots a buffer read anyway (k_1, or
   // y_n at stage 1, which has no earlier slope; never a null table entry)
   const gcptr<T> spare = stage >= 2 ? kin[0] : yn;
   gcptr<T> kslot[6];
+#pragma unroll
   for (int j = 0; j < 6; ++j) {
     const bool used = !EVAL && (stage < ns ? j < stage - 1 : (j < ns - 1 && ew[j] != 0.0));
     kslot[j] = used ? kin[j] : spare;
@@ -674,9 +663,9 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const int w, 
 }
 
 template <typename T, int NSUB, bool EVAL, bool GDMI = false, bool GBX = false>
-__global__ __launch_bounds__(256) void k_field(const FieldArgs<T> a) {
-  if (ctrl_stopped(a.ctrl)) return;
-  field_block<T, NSUB, EVAL, GDMI, GBX>(a, xcd_remap(blockIdx.x, a.nb_pad), a.stage, a.fuse2);
+__global__ __launch_bounds__(256) void k_field(const FieldArgs<T> a, const RKStage rk) {
+  const int zero = warm_args<FieldArgs<T>>();
+  field_block<T, NSUB, EVAL, GDMI, GBX>(a, rk, zero, xcd_remap(blockIdx.x, a.nb_pad), a.stage, a.fuse2);
 }
 
 // The field and the elastic force of one stage in one launch: both read the
@@ -684,12 +673,12 @@ __global__ __launch_bounds__(256) void k_field(const FieldArgs<T> a) {
 // is a few microseconds of latency on a grid that leaves the chip half
 // empty.  The force's blocks come first (they take longer).
 template <typename T, int NSUB>
-__global__ __launch_bounds__(256) void k_field_force(const FieldArgs<T> a, const ElasticArgs<T> e,
-                                                     int nforce) {
-  if (ctrl_stopped(a.ctrl)) return;
+__global__ __launch_bounds__(256) void k_field_force(const FieldArgs<T> a, const RKStage rk,
+                                                     const ElasticArgs<T> e, int nforce) {
   const int b = (int)blockIdx.x;
-  if (b < nforce) force_block<T>(e, b);
-  else field_block<T, NSUB, false>(a, xcd_remap(b - nforce, a.nb_pad), a.stage, a.fuse2);
+  const int zero = warm_args<FieldArgs<T>>();
+  if (b < nforce) force_block<T>(e, rk, b);
+  else field_block<T, NSUB, false>(a, rk, zero, xcd_remap(b - nforce, a.nb_pad), a.stage, a.fuse2);
 }
 
 // Many grids in one launch: block b runs block work[b].y of grid work[b].x
@@ -698,37 +687,41 @@ __global__ __launch_bounds__(256) void k_field_force(const FieldArgs<T> a, const
 template <typename T, int NSUB>
 __global__ __launch_bounds__(256) void k_field_multi(const FieldArgs<T>* __restrict__ args,
                                                      const int2* __restrict__ work, int nwork,
-                                                     int nb_pad, int stage, int fuse2) {
+                                                     int nb_pad, int stage, int fuse2,
+                                                     const RKStage rk) {
   const int b = xcd_remap(blockIdx.x, nb_pad);
   if (b >= nwork) return;
   const int2 wk = work[b];
   const FieldArgs<T>& a = args[wk.x];
-  if (ctrl_stopped(a.ctrl)) return;
-  field_block<T, NSUB, false>(a, wk.y, stage, fuse2);
+  const int zero = warm_lines((const uint32_t*)&a, (int)sizeof(FieldArgs<T>));
+  field_block<T, NSUB, false>(a, rk, zero, wk.y, stage, fuse2);
 }
 
 template <typename T>
 void launch_field_multi(const FieldArgs<T>* args, const int2* work, int nwork, int nsub, int stage,
                         int fuse2, hipStream_t st) {
   const int nb_pad = round_up(nwork, 8);
+  // a batch steps the Dormand-Prince pair
+  const RKStage rk = rk_stage(RK::t[RK_DP45], stage);
   if (nsub == 1)
     hipLaunchKernelGGL((k_field_multi<T, 1>), dim3(nb_pad), dim3(256), 0, st, args, work, nwork,
-                       nb_pad, stage, fuse2);
+                       nb_pad, stage, fuse2, rk);
   else
     hipLaunchKernelGGL((k_field_multi<T, 2>), dim3(nb_pad), dim3(256), 0, st, args, work, nwork,
-                       nb_pad, stage, fuse2);
+                       nb_pad, stage, fuse2, rk);
 }
 
 // The Eq. 6 ghosts (GDMI) exist for one and two sublattices only.
 template <typename T, bool EVAL, bool GDMI, bool GBX>
 void launch_field_nsub(const FieldArgs<T>& a, hipStream_t st) {
   const dim3 g(a.nb_pad), b(256);
+  const RKStage rk = rk_stage(RK::t[a.rk], a.stage);
   if (a.nsub == 1) {
-    hipLaunchKernelGGL((k_field<T, 1, EVAL, GDMI, GBX>), g, b, 0, st, a);
+    hipLaunchKernelGGL((k_field<T, 1, EVAL, GDMI, GBX>), g, b, 0, st, a, rk);
   } else if (a.nsub == 2) {
-    hipLaunchKernelGGL((k_field<T, 2, EVAL, GDMI, GBX>), g, b, 0, st, a);
+    hipLaunchKernelGGL((k_field<T, 2, EVAL, GDMI, GBX>), g, b, 0, st, a, rk);
   } else if constexpr (!GDMI) {
-    hipLaunchKernelGGL((k_field<T, 3, EVAL, GDMI, GBX>), g, b, 0, st, a);
+    hipLaunchKernelGGL((k_field<T, 3, EVAL, GDMI, GBX>), g, b, 0, st, a, rk);
   }
 }
 
@@ -761,20 +754,21 @@ void launch_field_force(const FieldArgs<T>& a, const ElasticArgs<T>& e, hipStrea
   ProfScope ps(prof, P_FIELD, st);
   const int nforce = e.nbx * e.nby * e.nz;
   const dim3 g(a.nb_pad + nforce), b(256);
+  const RKStage rk = rk_stage(RK::t[a.rk], a.stage);
   if (a.nsub == 1)
-    hipLaunchKernelGGL((k_field_force<T, 1>), g, b, 0, st, a, e, nforce);
+    hipLaunchKernelGGL((k_field_force<T, 1>), g, b, 0, st, a, rk, e, nforce);
   else
-    hipLaunchKernelGGL((k_field_force<T, 2>), g, b, 0, st, a, e, nforce);
+    hipLaunchKernelGGL((k_field_force<T, 2>), g, b, 0, st, a, rk, e, nforce);
 }
 
 // --------------------------------------------------------- combine2 ----
 // Stage-2 input for a new attempt: normalise(y_n + h a21 k1).
 template <typename T>
-__device__ __forceinline__ void combine2_cell(const Table<T>* tbl, const Ctrl* ctrl, long Ncell,
-                                              long i) {
+__device__ __forceinline__ void combine2_cell(const Table<T>* tbl, const Ctrl* ctrl, double a10,
+                                              long Ncell, long i) {
   const long s = i / Ncell, cell = i - s * Ncell;
   const long base = s * 3 * Ncell + cell;
-  const T c = (T)(RK::t[tbl->rk].a[1][0] * ctrl->h);
+  const T c = (T)(a10 * ctrl->h);
   const gcptr<T> yn = (gcptr<T>)tbl->yn;
   const gcptr<T> k1 = (gcptr<T>)tbl->k[0];
   T v[3];
@@ -785,20 +779,21 @@ __device__ __forceinline__ void combine2_cell(const Table<T>* tbl, const Ctrl* c
 }
 
 template <typename T>
-__global__ void k_combine2_cells(const Table<T>* tbl, const Ctrl* ctrl, long Ncell, int nsub) {
+__global__ void k_combine2_cells(const Table<T>* tbl, const Ctrl* ctrl, double a10, long Ncell,
+                                 int nsub) {
   if (ctrl_stopped(ctrl)) return;
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= Ncell * nsub) return;
-  combine2_cell<T>(tbl, ctrl, Ncell, i);
+  combine2_cell<T>(tbl, ctrl, a10, Ncell, i);
 }
 
 template <typename T>
-void launch_combine2(const Table<T>* tbl, const Ctrl* ctrl, long Ncell, int nsub, hipStream_t st,
-                     Prof* prof) {
+void launch_combine2(const Table<T>* tbl, const Ctrl* ctrl, int rk, long Ncell, int nsub,
+                     hipStream_t st, Prof* prof) {
   ProfScope ps(prof, P_COMBINE, st);
   const long n = Ncell * nsub;
   hipLaunchKernelGGL((k_combine2_cells<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                     tbl, ctrl, Ncell, nsub);
+                     tbl, ctrl, RK::t[rk].a[1][0], Ncell, nsub);
 }
 
 // ---------------------------------------------------------- control ----
@@ -894,7 +889,7 @@ __global__ void k_combine2_multi(const StepWork<T>* __restrict__ w) {
   if (ctrl_stopped(g.ctrl)) return;
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= g.N * g.nsub) return;
-  combine2_cell<T>(g.tbl, g.ctrl, g.N, i);
+  combine2_cell<T>(g.tbl, g.ctrl, RK::t[RK_DP45].a[1][0], g.N, i);
 }
 
 template <typename T>
@@ -985,8 +980,8 @@ void launch_energy_final(const double* epart, int nblk, double* out, hipStream_t
   template void launch_field<T>(const FieldArgs<T>&, bool, hipStream_t, Prof*);             \
   template void launch_field_force<T>(const FieldArgs<T>&, const ElasticArgs<T>&,           \
                                       hipStream_t, Prof*);                                  \
-  template void launch_combine2<T>(const Table<T>*, const Ctrl*, long, int, hipStream_t,    \
-                                   Prof*);                                                   \
+  template void launch_combine2<T>(const Table<T>*, const Ctrl*, int, long, int,            \
+                                   hipStream_t, Prof*);                                                   \
   template void launch_control<T>(Ctrl*, Table<T>*, const double*, int, int, hipStream_t,   \
                                   Prof*);                                                    \
   template void launch_sample<T>(Ctrl*, const Table<T>*, int, long, double*, int, double*,  \

@@ -172,7 +172,6 @@ struct Grid final : GridBase {
   DemagPlan plan{};
   DemagBufs<T> db{};
   Buf<cpx<T>> S1, S2, tw;
-  Buf<int> pos;
   Buf<T> K;
   Buf<char> mem, fft_mem;  // the blocks that hold the buffers above
   size_t idle_begin = 0, idle_end = 0;  // part of mem unused until a state is set
@@ -211,7 +210,7 @@ struct Grid final : GridBase {
     dctrl.release();
     sctrl.release();
     sres.release();
-    S1.release(); S2.release(); tw.release(); pos.release();
+    S1.release(); S2.release(); tw.release();
     mem.release();
     fft_mem.release();
     plan = DemagPlan{};
@@ -381,14 +380,13 @@ struct Grid final : GridBase {
         a.place(S2, np.s2_elems);
         a.place(K, np.k_elems);
         a.place(tw, demag_tw_elems(np));
-        a.place(pos, (size_t)np.Px + np.Py + np.Pz);
       };
       Arena a;
       layout(a);
       const int rc = a.alloc(fft_mem);
       if (!rc) layout(a);
       if (rc) {
-        S1.release(); S2.release(); K.release(); tw.release(); pos.release();
+        S1.release(); S2.release(); K.release(); tw.release();
         plan = DemagPlan{};
         set_error("device allocation failed");
         return MMP_E_NOMEM;
@@ -397,7 +395,7 @@ struct Grid final : GridBase {
       k1_valid = false;
     }
     plan = np;
-    set_demag_ptrs(db, S1.p, S2.p, K.p, tw.p, pos.p, plan);
+    set_demag_ptrs(db, S1.p, S2.p, K.p, tw.p, plan);
     return 0;
   }
 
@@ -408,7 +406,7 @@ struct Grid final : GridBase {
            pl.Py;
   }
 
-  static void set_demag_ptrs(DemagBufs<T>& b, cpx<T>* s1, cpx<T>* s2, T* k, cpx<T>* t, int* pos,
+  static void set_demag_ptrs(DemagBufs<T>& b, cpx<T>* s1, cpx<T>* s2, T* k, cpx<T>* t,
                              const DemagPlan& pl) {
     b.S1 = s1; b.S2 = s2; b.K = k;
     b.twx = t;
@@ -416,13 +414,12 @@ struct Grid final : GridBase {
     b.twz = b.twy + line_tw_elems(pl.Py);
     b.tw4x = b.twz + line_tw_elems(pl.Pz);
     b.tw4y = b.tw4x + pl.Px;
-    b.posx = pos; b.posy = pos + pl.Px; b.posz = b.posy + pl.Py;
   }
 
   void build_all_twiddles(const DemagBufs<T>& b, const DemagPlan& pl) {
-    build_line_tables<T>(pl.fx, b.twx, b.posx, stream);
-    build_line_tables<T>(pl.fy, b.twy, b.posy, stream);
-    build_line_tables<T>(pl.fz, b.twz, b.posz, stream);
+    build_line_tables<T>(pl.fx, b.twx, stream);
+    build_line_tables<T>(pl.fy, b.twy, stream);
+    build_line_tables<T>(pl.fz, b.twz, stream);
     build_twiddles4<T>(b.tw4x, pl.Px, stream);
     build_twiddles4<T>(b.tw4y, pl.Py, stream);
   }
@@ -645,10 +642,9 @@ struct Grid final : GridBase {
           const bool cur = c.Px == plan.Px && c.Py == plan.Py && c.Pz == plan.Pz;
           DemagBufs<T> tb = db;
           Buf<cpx<T>> s1, s2, twb;
-          Buf<int> pb;
           Buf<T> kb;
           auto drop = [&] {
-            s1.release(); s2.release(); kb.release(); twb.release(); pb.release();
+            s1.release(); s2.release(); kb.release(); twb.release();
           };
           if (cur) {
             c.tyf = plan.tyf; c.tyi = plan.tyi; c.nlyf = plan.nlyf; c.nlyi = plan.nlyi;
@@ -657,11 +653,11 @@ struct Grid final : GridBase {
             if (demag_plan_check(c, (int)sizeof(T)) != 0) c = plan;
           } else {
             if (s1.alloc(c.s1_elems) || s2.alloc(c.s2_elems) || kb.alloc(c.k_elems) ||
-                twb.alloc(demag_tw_elems(c)) || pb.alloc((size_t)c.Px + c.Py + c.Pz)) {
+                twb.alloc(demag_tw_elems(c))) {
               drop();
               continue;  // this pad set does not fit next to the grid
             }
-            set_demag_ptrs(tb, s1.p, s2.p, kb.p, twb.p, pb.p, c);
+            set_demag_ptrs(tb, s1.p, s2.p, kb.p, twb.p, c);
             MMP_HIP_TRY(hipMemsetAsync(kb.p, 0, c.k_elems * sizeof(T), stream));
             build_all_twiddles(tb, c);
           }
@@ -770,9 +766,11 @@ struct Grid final : GridBase {
               (T)(on && Ms != 0.0 && p.nsub == 2 ? -2.0 * p.dmi_W12[i][c] / Ms : 0.0);
         }
     }
+    a.rk = p.solver;
     a.per_x = p.pbc[0] > 0 ? 1 : 0;
     a.per_y = p.pbc[1] > 0 ? 1 : 0;
     fa = a;
+    db.ns = RK::t[p.solver].ns;
     set_field_zc(field_zc > 0 ? field_zc : default_field_zc());
     // the pair in use: its stage count and index, read by every stage kernel
     if (a_rk != p.solver) {
@@ -795,6 +793,7 @@ struct Grid final : GridBase {
       e.mel[s] = (p.sub[s].Ms != 0.0 && (p.sub[s].B1 != 0.0 || p.sub[s].B2 != 0.0)) ? 1 : 0;
     }
     e.tbl = dtbl.p; e.ctrl = dctrl.p; e.eps = eps.p; e.sig = sig.p; e.epart = elpart.p;
+    e.rk = p.solver;
     e.nbx = a.nbx; e.nby = a.nby; e.beta = (T)p.rayleigh;
     e.V = a.V; e.rho = p.rho;
     ea = e;
@@ -930,7 +929,7 @@ struct Grid final : GridBase {
   }
 
   void combine2() {
-    launch_combine2<T>(dtbl.p, dctrl.p, N, p.nsub, stream, &prof);
+    launch_combine2<T>(dtbl.p, dctrl.p, p.solver, N, p.nsub, stream, &prof);
     if (p.elastic) launch_elastic_combine2<T>(dtbl.p, dctrl.p, N, stream, &prof);
   }
 
