@@ -52,7 +52,8 @@ METRIC = ("cell-field-evals/s 512x512x16 FP32 vs FP64; batched solves/s with p50
           "latency")
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = tuple("paper_2411_18194_amd/csrc/" + f for f in (
-    "demag.hip", "demag4.hip", "fft4.h", "fft_engine.h", "field.hip", "field.h", "common.h"))
+    "demag.hip", "demag4.hip", "fft4.h", "fft_lines.h", "field.hip", "field.h", "elastic_dev.h",
+    "common.h"))
 COUNTERS = os.path.join(ROOT, "profiles", "counters_c2_fp32.json")
 
 

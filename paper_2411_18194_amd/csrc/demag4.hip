@@ -233,9 +233,13 @@ constexpr int xhalf_stride() { return L / 2 + 32; }
 // HALF (lines of 64 points or more): the step-1/step-3 transpose and the
 // unpack each go through LDS in two halves of a line (rows k1 < L1/2, then
 // the rest; spectrum bins k in [0, L/4) and (3L/4, L), then [L/4, 3L/4]),
-// so a block holds half the LDS and twice as many blocks fit on a CU.
+// so a block holds half the LDS and twice as many blocks fit on a CU.  64-bit
+// lines of 32-point rows are held to the 256 registers that let the second
+// block's waves in (1 to 12 values spill): x forward of a 512x512x16 FP64
+// film, bound by those waves in flight, 113 -> 83 us (2.7 -> 3.6 TB/s).
 template <typename T, int L1, int L2, bool FULL, bool HALF = false>
-__global__ __launch_bounds__(256) void k4_fftx_fwd(X4Args<T> a) {
+__global__ __launch_bounds__(256, HALF && sizeof(T) == 8 && L1 == 32 ? 2 : 1)
+void k4_fftx_fwd(X4Args<T> a) {
   using V = cpx<T>;
   const int zero = warm_args<X4Args<T>>();
   const gcptr<T> m = (gcptr<T>)table_slot<T>(a.tbl, a.src + zero);
@@ -862,9 +866,9 @@ template <typename T, int L>
 static void lx(bool inv, bool full, dim3 g, int thr, size_t lds, hipStream_t st,
                const X4Args<T>& a) {
   constexpr int L1 = Split<L>::L1, L2 = Split<L>::L2;
-  // half-LDS forward pass for 32-bit values (x4_lds_bytes); 64-bit lines
-  // would hold more registers than the LDS saving gains
-  constexpr bool H = L >= 64 && sizeof(T) == 4;
+  // half-LDS forward pass (x4_lds_bytes), but for 64-bit lines of 2048
+  // points, which hold twice the registers that two waves per SIMD leave
+  constexpr bool H = L >= 64 && (sizeof(T) == 4 || L <= 1024);
   if (inv) hipLaunchKernelGGL((k4_fftx_inv<T, L1, L2>), g, dim3(thr), lds, st, a);
   else if (full) hipLaunchKernelGGL((k4_fftx_fwd<T, L1, L2, true, H>), g, dim3(thr), lds, st, a);
   else hipLaunchKernelGGL((k4_fftx_fwd<T, L1, L2, false, H>), g, dim3(thr), lds, st, a);
