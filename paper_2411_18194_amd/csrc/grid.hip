@@ -555,9 +555,6 @@ struct Grid final : GridBase {
   // the demag passes included, per stage. Marches are ranked by attempts: a
   // stage's slopes are written once and read by every later one, and the
   // passes between two field launches fill the caches with their own lines.
-  // Stage 2 alone, its inputs warm in the last-level cache, was fastest with
-  // a march of 1 on a 512x512x16 FP32 film; that march then took 110 us per
-  // stage of a step, 16 planes 87 us.
   double time_field(int zc, bool step, Ctrl* tctrl, int reps) {
     set_field_zc(zc);
     FieldArgs<T> a = fa;
@@ -596,6 +593,25 @@ struct Grid final : GridBase {
     Ctrl c{};
     c.h = 1e-15;
     MMP_HIP_TRY(hipMemcpy(tc.p, &c, sizeof(c), hipMemcpyHostToDevice));
+    // Finite slopes and stage inputs to time on: the first stage writes k_1
+    // and stage 2's input, from any finite vectors before a state is set (a
+    // k_1 that a run left is kept). On what a fresh allocation holds every
+    // cell reports a non-finite torque with an atomic, and the march is
+    // picked by those (a 512x512x16 FP32 film: 750 us a launch, not 90).
+    if (k1_valid) {
+      launch_combine2<T>(dtbl.p, tc.p, p.solver, N, p.nsub, stream, nullptr);
+    } else {
+      if (!state_set)
+        MMP_HIP_TRY(hipMemsetAsync(y[0].p, 0x3c, y[0].n * sizeof(T), stream));
+      if (p.demag)
+        demag_field<T>(plan, db, dtbl.p, 1, nullptr, (T)p.sub[0].Ms, ms_of(1), p.nsub, stream,
+                       nullptr, ms_of(2));
+      FieldArgs<T> first = fa;
+      first.stage = 1;
+      first.fuse2 = 0;
+      first.ctrl = tc.p;
+      launch_field<T>(first, false, stream, nullptr);
+    }
     const int reps = N >= (1L << 22) ? 5 : N >= (1L << 16) ? 20 : 50;
     const int steps = (reps + 4) / 5;
     int best = field_zc;
