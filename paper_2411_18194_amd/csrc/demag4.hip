@@ -520,85 +520,100 @@ __device__ __forceinline__ cpx<T> lane_root(int q) {
   return w;
 }
 
-// exp(-2 pi i n t / P) with n = N0 + q and t = q ^ D, for the lane index q < Q
-template <typename T, int P, int Q, int D, int N0>
+// Forward input of the four lanes of a column, the reverse of their inverse
+// (zcol_inverse_store): lane q loads planes n = q R/2 ... and the lanes swap
+// them so that each has every x(r) and x(r + R), of which
+//   y_q(r) = w^(r q) (x(r) + (-i)^q x(r + R)), R = PZ/4,
+// is its twisted, folded column.  (Twisting all PZ/2 planes for each lane, as
+// two lanes do, is twice the multiplications and three times the registers in
+// flight: with this and the inverse's 4-point sum 219 -> 168 registers, so
+// three waves per SIMD instead of two, and a tenth fewer instructions;
+// 512x512x16 FP64, bound by both, 264 -> 247 us, 4.1 TB/s.)
+template <typename T, int PZ>
+__device__ __forceinline__ void zcol_load_quad(const cpx<T>* col, long zs, long cs, int nz, int q,
+                                               cpx<T>* vx, cpx<T>* vy, cpx<T>* vz) {
+  using V = cpx<T>;
+  constexpr int R = PZ / 4;
+  V l[3][R / 2];
+#pragma unroll
+  for (int j = 0; j < R / 2; ++j) {
+    const int n = q * (R / 2) + j;
+    const long off = (long)(n < nz ? n : 0) * zs;
+    l[0][j] = ntload(col + off);
+    l[1][j] = ntload(col + cs + off);
+    l[2][j] = ntload(col + 2 * cs + off);
+  }
+#pragma unroll
+  for (int j = 0; j < R / 2; ++j)
+    if (q * (R / 2) + j >= nz) l[0][j] = l[1][j] = l[2][j] = cmk<T>(0, 0);
+  const bool up = (q & 2) != 0, odd = (q & 1) != 0;
+  const T sg = up ? T(-1) : T(1);
+  auto column = [&](const V* x, V* v) {
+    // lanes 0 and 1: x(r); lane 2: x(r + R); lane 3: -i x(r + R), which lane 1
+    // adds and lane 3 subtracts
+#pragma unroll
+    for (int j = 0; j < R / 2; ++j) {
+      const V got = quad_xor_c<1, T>(x[j]);
+      v[j] = odd ? got : x[j];
+      v[j + R / 2] = odd ? x[j] : got;
+    }
+    static_for<0, R>([&](auto rc) {
+      constexpr int r = decltype(rc)::value;
+      const V s = up && odd ? cmk<T>(v[r].y, -v[r].x) : v[r];
+      const V o = quad_xor_c<2, T>(s);
+      v[r] = cmk<T>(fma(sg, s.x, o.x), fma(sg, s.y, o.y));
+      if constexpr (r > 0) v[r] = cmul(v[r], lane_root<T, r, PZ, 4, false>(q));
+    });
+  };
+  column(l[0], vx);
+  column(l[1], vy);
+  column(l[2], vz);
+}
+
+// exp(-2 pi i n t / P) with n = N0 + q and t = q ^ D, for the lane index q < 2
+template <typename T, int P, int D, int N0>
 __device__ __forceinline__ cpx<T> split_root(int q) {
   cpx<T> w = root<T, (N0 * D) % P, P, false>();
-  if constexpr (Q >= 2)
-    if (q == 1) w = root<T, ((N0 + 1) * (1 ^ D)) % P, P, false>();
-  if constexpr (Q >= 4) {
-    if (q == 2) w = root<T, ((N0 + 2) * (2 ^ D)) % P, P, false>();
-    if (q == 3) w = root<T, ((N0 + 3) * (3 ^ D)) % P, P, false>();
-  }
+  if (q == 1) w = root<T, ((N0 + 1) * (1 ^ D)) % P, P, false>();
   return w;
 }
 
-// Forward input of the Q lanes of a column with the loads shared: lane t
-// needs its twisted, folded column y_t(r) = sum over n = r (mod R) of
-// x(n) w^(n t), R = PZ/Q.  When Q divides R every plane n of a residue r
-// lies in lane r mod Q, so lane q loads only the planes n = Q i + q, forms
-// for each lane t = q ^ D of the quad the terms of t's residues r = q + Q j
-// that its planes carry, and the terms reach t by the quad permutation ^D.
-// The sums and twiddles are those of loading every plane in every lane, at
-// 1/Q of the loads and of the registers they occupy.
-template <typename T, int PZ, int Q>
+// Forward input of the two lanes of a column with the loads shared: lane t
+// needs its twisted, folded column y_t(r) = x(r) w^(r t), r < R = PZ/2.  Lane
+// q loads only the planes n = 2 i + q, forms their terms for both lanes, and
+// the other lane's reach it by the quad permutation ^1.  The twiddles are
+// those of loading every plane in every lane, at half the loads and the
+// registers they occupy.
+template <typename T, int PZ>
 __device__ __forceinline__ void zcol_load_split(const cpx<T>* col, long zs, long cs, int nz,
                                                 int q, cpx<T>* vx, cpx<T>* vy, cpx<T>* vz) {
   using V = cpx<T>;
-  constexpr int R = PZ / Q, NH = PZ / 2, NL = NH / Q, J = R / Q, K = NH / R;
-  static_assert(Q > 1 && R % Q == 0 && NL >= 1 && K >= 1, "shared column loads");
-  V l[3][NL];
+  constexpr int R = PZ / 2, J = R / 2;
+  static_assert(J >= 1, "shared column loads");
+  V l[3][J];
 #pragma unroll
-  for (int i = 0; i < NL; ++i) {
-    const int n = Q * i + q;
+  for (int i = 0; i < J; ++i) {
+    const int n = 2 * i + q;
     const long off = (long)(n < nz ? n : 0) * zs;
     l[0][i] = ntload(col + off);
     l[1][i] = ntload(col + cs + off);
     l[2][i] = ntload(col + 2 * cs + off);
   }
 #pragma unroll
-  for (int i = 0; i < NL; ++i)
-    if (Q * i + q >= nz) l[0][i] = l[1][i] = l[2][i] = cmk<T>(0, 0);
-  V in[3][Q][J];
-  static_for<0, Q>([&](auto dc) {
-    constexpr int D = decltype(dc)::value;
+  for (int i = 0; i < J; ++i)
+    if (2 * i + q >= nz) l[0][i] = l[1][i] = l[2][i] = cmk<T>(0, 0);
+  auto column = [&](const V* x, V* v) {
     static_for<0, J>([&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      V acc[3] = {cmk<T>(0, 0), cmk<T>(0, 0), cmk<T>(0, 0)};
-      static_for<0, K>([&](auto kc) {
-        constexpr int k = decltype(kc)::value;
-        const V w = split_root<T, PZ, Q, D, Q * j + R * k>(q);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[c] = cadd(acc[c], cmul(l[c][j + J * k], w));
-      });
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        if constexpr (D == 0) in[c][D][j] = acc[c];
-        else in[c][D][j] = quad_xor_c<D, T>(acc[c]);
-      }
+      const V own = cmul(x[j], split_root<T, PZ, 0, 2 * j>(q));
+      const V got = quad_xor_c<1, T>(cmul(x[j], split_root<T, PZ, 1, 2 * j>(q)));
+      v[2 * j] = q == 0 ? own : got;
+      v[2 * j + 1] = q == 0 ? got : own;
     });
-  });
-  // residue r = p + Q j came from lane p through the permutation ^(p ^ q)
-#pragma unroll
-  for (int p = 0; p < Q; ++p) {
-    const int D = p ^ q;
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      V o[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        o[c] = in[c][0][j];
-        if (D == 1) o[c] = in[c][1][j];
-        if constexpr (Q >= 4) {
-          if (D == 2) o[c] = in[c][2][j];
-          if (D == 3) o[c] = in[c][3][j];
-        }
-      }
-      vx[p + Q * j] = o[0];
-      vy[p + Q * j] = o[1];
-      vz[p + Q * j] = o[2];
-    }
-  }
+  };
+  column(l[0], vx);
+  column(l[1], vy);
+  column(l[2], vz);
 }
 
 // one complex value through a global-typed pointer (a global, not flat,
@@ -615,8 +630,8 @@ __device__ __forceinline__ void gstore(gptr<cpx<T>> p, cpx<T> v) {
 // store of the first nz planes.  Lane q holds B(kz = Q j + q) at register
 // bitrev<R>(j); with R = PZ/Q,
 //   b(n) = sum_q w^(-n q) IFFT_R(B(Q j + q))(n mod R),
-// so each lane forms its term for n < PZ/2 and the Q lanes sum them with a
-// recursive-halving exchange that leaves lane q owning PZ/(2Q) planes.
+// so each lane forms its term for n < PZ/2 and the Q lanes sum them with an
+// exchange that leaves lane q owning the PZ/(2Q) planes from q PZ/(2Q).
 // Plain stores: the y inverse pass reads these planes next, and part of
 // them is still in the Infinity Cache when it does.
 template <typename T, int PZ, int Q>
@@ -632,6 +647,33 @@ __device__ __forceinline__ void zcol_inverse_store(cpx<T>* v, gptr<cpx<T>> col, 
 #pragma unroll
     for (int z = 0; z < NH; ++z)
       if (z < nz) gstore<T>(col + z * zs, t[bitrev<PZ>(z)]);
+  } else if constexpr (Q == 4 && R >= 4) {
+    // n = r + R k: the lane's term at r = n mod R is the same for k = 0 and
+    // 1 but for a power of i, so the lanes' sum is a 4-point transform of
+    // which the lower lane pair forms k = 0, the upper k = 1
+#pragma unroll
+    for (int k = 0; k < R; ++k) v[k] = t[bitrev<R>(k)];
+    static_for<1, R>([&](auto rc) {
+      constexpr int r = decltype(rc)::value;
+      v[r] = cmul(v[r], lane_root<T, r, PZ, Q, true>(q));
+    });
+    const bool up = (q & 2) != 0, odd = (q & 1) != 0;
+    const T sg = up ? T(-1) : T(1);
+    // lanes 0 and 1: t0 + t2, t1 + t3; lanes 2 and 3: t0 - t2, i (t1 - t3)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const V o = quad_xor_c<2, T>(v[r]);
+      const V d = cmk<T>(fma(sg, v[r].x, o.x), fma(sg, v[r].y, o.y));
+      v[r] = up && odd ? cmk<T>(-d.y, d.x) : d;
+    }
+    // the two lanes of a pair add theirs for half of the r each
+    const gptr<V> own = col + (q * (R / 2)) * zs;
+#pragma unroll
+    for (int j = 0; j < R / 2; ++j) {
+      const V got = quad_xor_c<1, T>(odd ? v[j] : v[j + R / 2]);
+      const V x = cadd(odd ? v[j + R / 2] : v[j], got);
+      if (q * (R / 2) + j < nz) gstore<T>(own + j * zs, x);
+    }
   } else {
     V c[NH];
     static_for<0, NH>([&](auto nc) {
@@ -740,8 +782,10 @@ __device__ __forceinline__ void fftz_mul_body(const Z4Args<T>& a) {
   V* col = a.S2 + (long)kx * a.Py + ky;
   V vx[R], vy[R], vz[R];
   // nz <= PZ/2 for every power-of-two pad, so the upper half is zero
-  if constexpr (Q > 1 && (PZ / Q) % Q == 0) {
-    zcol_load_split<T, PZ, Q>(col, zs, cs, a.nz, q, vx, vy, vz);
+  if constexpr (Q == 4 && R >= 4) {
+    zcol_load_quad<T, PZ>(col, zs, cs, a.nz, q, vx, vy, vz);
+  } else if constexpr (Q == 2 && R >= 2) {
+    zcol_load_split<T, PZ>(col, zs, cs, a.nz, q, vx, vy, vz);
   } else {
     // all planes are loaded first (a plain unrolled loop keeps the loads
     // back to back), then lane q twists them by w^(n q) and folds mod R

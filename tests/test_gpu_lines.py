@@ -104,3 +104,19 @@ def test_single_cell_axes(n, prec):
     g.set_plan(lds_axes=7)
     assert _err(g, ref) <= TOL[prec]
     g.close()
+
+
+# Several lanes per column in the z pass of power-of-two pads: the lanes' own
+# planes all, partly or not there, on pads of 16 (too long in y for the fused
+# pass), 32 and 64.
+@pytest.mark.parametrize("prec", [mmp.FP64, mmp.FP32])
+@pytest.mark.parametrize("n,lanes", [((6, 256, 8), 4), ((6, 250, 5), 4), ((6, 250, 7), 2),
+                                     ((17, 24, 9), 4), ((9, 33, 13), 2), ((16, 20, 16), 4),
+                                     ((7, 12, 17), 4), ((5, 9, 32), 4)])
+def test_z_column_lanes(n, lanes, prec):
+    g, ref = _case(n, prec, 93)
+    pads = [1 << (2 * k - 2).bit_length() for k in n]
+    pl = g.set_plan(pad=pads, z_lanes=lanes, z_waves=1)
+    assert pl["z_lanes"] == lanes and pl["kinds"] & 4
+    assert _err(g, ref) <= TOL[prec]
+    g.close()
