@@ -1089,9 +1089,9 @@ void demag_field(const DemagPlan& p, const DemagBufs<T>& b, const Table<T>* tbl,
 // ------------------------------------------------------------ autotuner --
 // Mean time of `reps` launches of the passes in seq[0..ns) after one warm-up
 // launch of the last; negative when a launch fails. The tuner times each
-// candidate of a pass right after the pass before it in an evaluation (the
-// first pass after the last one), so the candidate meets the caches as it
-// does there (the pair's time ranks the candidates as their own would).
+// candidate of a pass right after the pass before it in an evaluation, so the
+// candidate meets the caches as it does there (the pair's time ranks the
+// candidates as their own would), and the first pass's in whole evaluations.
 template <typename T>
 static double time_passes(const int* seq, int ns, const DemagPlan& p, const DemagBufs<T>& b,
                           const Table<T>* tbl, T ms0, T ms1, int nsub, hipStream_t st, int reps,
@@ -1182,10 +1182,15 @@ double demag_tune(DemagPlan* pp, const DemagBufs<T>& b, const Table<T>* tbl, T m
     }
     double bt = -1.0;
     for (const DemagPlan& c : cand) {
-      // the first pass follows the last one of the previous evaluation
+      // the x forward pass by whole evaluations: what its narrower stores (8
+      // rows are half a line of S1 in FP32) cost shows under the y and z
+      // passes' traffic only (512x512x16 FP32: 8 and 16 rows tie after the x
+      // inverse pass, and take 47 and 36 us in a step)
       const int pair[2] = {passes[i > 0 ? i - 1 : n - 1], pass};
-      const double t = time_passes<T>(pair, n > 1 ? 2 : 1, c, b, tbl, ms0, ms1, nsub, st, reps,
-                                      ms2);
+      const double t = pass == DP_XF
+                           ? time_passes<T>(passes, n, c, b, tbl, ms0, ms1, nsub, st, reps, ms2)
+                           : time_passes<T>(pair, n > 1 ? 2 : 1, c, b, tbl, ms0, ms1, nsub, st,
+                                            reps, ms2);
       if (t < 0.0) continue;
       if (bt < 0.0 || t < bt) {
         bt = t;
