@@ -259,8 +259,7 @@ mmp_status mmp_eval_heff(mmp_grid g, uint32_t term_mask, double* b_out,
  *   receives t and the next step size.
  * mmp_eval_heff_device: b_dev (nsub*3*N) receives what mmp_eval_heff's
  *   b_out does for term_mask (B in tesla, or dm/dt with MMP_OUT_TORQUE);
- *   no energies.  An FP32 grid keeps an FP32 buffer of that size from its
- *   first call. */
+ *   no energies. */
 mmp_status mmp_set_state_device(mmp_grid g, const double* m_dev, const double* u_dev,
                                 const double* v_dev, double t);
 mmp_status mmp_get_state_device(mmp_grid g, double* m_dev, double* u_dev, double* v_dev,

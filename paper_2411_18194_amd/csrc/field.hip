@@ -151,9 +151,10 @@ __device__ void eq6_ghost(const FieldArgs<T>& a, const T (*m)[3], int ax, T side
 // per lane (grids have at most 2^28 cells, so an array's bytes per component
 // stay below 2^32), which the hardware adds.  64-bit addresses per lane and
 // array took two registers and an addition for every one of the up to 50
-// loads of a cell: FP32 one sublattice 204 -> 123 registers (two -> four
-// waves per SIMD), FP64 298 -> 199 (one -> two); 512x512x16 FP32 90 -> 81 us
-// a stage (4.6 TB/s), FP64 204 -> 170 (4.3 TB/s).
+// loads of a cell: FP32 one sublattice 204 -> 97 registers (two -> four
+// waves per SIMD), FP64 298 -> 172 (one -> two); 512x512x16 FP32 90 -> 87 us
+// a stage (4.3 TB/s), FP64 204 -> 174 (4.2 TB/s; held to the 168 registers of
+// three waves 176).
 template <typename T>
 __device__ __forceinline__ T ldo(gcptr<T> base, uint32_t o) {
   return *(gcptr<T>)((gcptr<char>)base + o);

@@ -52,11 +52,13 @@ struct Req {
   std::string err;   // message of the call that failed the request
 };
 
-// Device footprint of a request: the buffers Grid<T>::alloc_layout makes
-// for its parameters (state pair, stage pair, 7 slopes; with elasticity u
-// and v pairs, their stage pairs, 14 slopes and the strain, strain-rate and
-// stress tensors; grain ids and axes; the demag spectra, kernel and field),
-// the transient FP64 tensor of the demag build, and 1 MiB of small buffers.
+// Device footprint of a request, an upper bound: the buffers
+// Grid<T>::alloc_layout makes for its parameters (state pair, stage pair, 7
+// slopes; with elasticity u and v pairs, their stage pairs, 14 slopes and
+// room for three symmetric tensors, of which it keeps strain and stress; grain
+// ids and axes; the demag spectra, kernel and field), the FP64 tensor of the
+// demag build (which lies in the stage buffers where it fits), and 1 MiB of
+// small buffers.
 int64_t estimate_bytes(const mmp_request& r, int precision) {
   const int64_t N = (int64_t)r.nx * r.ny * r.nz;
   const int64_t rb = precision == MMP_FP64 ? 8 : 4;
