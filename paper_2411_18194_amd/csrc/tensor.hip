@@ -97,11 +97,21 @@ struct TensorArgs {
   double dx, dy, dz, dmax;
   double z0, zs;
   double* n6;          // [6][nz][ny][nx]
-  int bx, by, bz;      // box of offsets this launch covers
+  int bx, by, bz;      // box of offsets the launches cover
+  long i0;             // first offset of this launch (near, middle regime)
   int nq;              // quadrature points per axis (2n)
   double qt[24], qw[24];
   int rx, ry;          // image repetitions along x and y (0: open axis)
 };
+
+// offset of this block in the box
+__device__ __forceinline__ void box_offset(const TensorArgs& a, int* X, int* Y, int* Z) {
+  const long i = a.i0 + blockIdx.x;
+  const int r = (int)(i / a.bx);
+  *X = (int)(i - (long)r * a.bx);
+  *Y = r % a.by;
+  *Z = r / a.by;
+}
 
 // Newell's formula: one block per offset of the box.  Each of the 6 x 27
 // terms has its own thread (an evaluation takes microseconds of dependent
@@ -109,8 +119,8 @@ struct TensorArgs {
 // back to back: 302 us for any grid, 10 now), summed in order by six threads.
 constexpr int kNearThreads = 192;
 __global__ __launch_bounds__(kNearThreads) void k_tensor_near(TensorArgs a) {
-  const int i = blockIdx.x;
-  const int X = i % a.bx, Y = (i / a.bx) % a.by, Z = i / (a.bx * a.by);
+  int X, Y, Z;
+  box_offset(a, &X, &Y, &Z);
   const double x = X * a.dx, y = Y * a.dy, z = a.z0 + Z * a.zs;
   const double r = sqrt(x * x + y * y + z * z) / a.dmax;
   if (r >= kRNear) return;
@@ -146,8 +156,8 @@ __global__ __launch_bounds__(kNearThreads) void k_tensor_near(TensorArgs a) {
 // offsets with a division and six sums per point, 31 now).
 constexpr int kQuadThreads = 256;
 __global__ __launch_bounds__(kQuadThreads) void k_tensor_quad(TensorArgs a) {
-  const int i = blockIdx.x;
-  const int X = i % a.bx, Y = (i / a.bx) % a.by, Z = i / (a.bx * a.by);
+  int X, Y, Z;
+  box_offset(a, &X, &Y, &Z);
   const double x = X * a.dx, y = Y * a.dy, z = a.z0 + Z * a.zs;
   const double r = sqrt(x * x + y * y + z * z) / a.dmax;
   if (r < kRNear || r >= kRFar) return;
@@ -533,14 +543,21 @@ static int launch_tensor(TensorArgs a, hipStream_t st) {
   // layers of the box: from the offset nearest to zero upwards on the grid's
   // own offsets; a layer above the grid is nearest to the last one
   const bool own = a.z0 == 0.0;
+  // a launch holds fewer than 2^32 threads, which the boxes of flat or tall
+  // cells on a large grid exceed (40 dmax/d offsets per axis): in pieces
+  constexpr long kPiece = 1L << 22;
+  auto pieces = [&](auto kernel, int threads) {
+    const long nb = (long)a.bx * a.by * a.bz;
+    for (a.i0 = 0; a.i0 < nb; a.i0 += kPiece)
+      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(kPiece, nb - a.i0)), dim3(threads), 0, st,
+                         a);
+  };
   a.bx = box(kRNear, a.nx, a.dx); a.by = box(kRNear, a.ny, a.dy);
   a.bz = own ? box(kRNear, a.nz, a.dz) : a.nz;
-  hipLaunchKernelGGL(k_tensor_near, dim3((unsigned)(a.bx * a.by * a.bz)), dim3(kNearThreads), 0,
-                     st, a);
+  pieces(k_tensor_near, kNearThreads);
   a.bx = box(kRFar, a.nx, a.dx); a.by = box(kRFar, a.ny, a.dy);
   a.bz = own ? box(kRFar, a.nz, a.dz) : a.nz;
-  hipLaunchKernelGGL(k_tensor_quad, dim3((unsigned)((long)a.bx * a.by * a.bz)),
-                     dim3(kQuadThreads), 0, st, a);
+  pieces(k_tensor_quad, kQuadThreads);
   const long N = (long)a.nx * a.ny * a.nz;
   hipLaunchKernelGGL(k_tensor_far, dim3((unsigned)((N + 127) / 128)), dim3(128), 0, st, a);
   return hipGetLastError() == hipSuccess ? 0 : -1;

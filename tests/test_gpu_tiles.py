@@ -46,3 +46,24 @@ def test_spectrum_tiles(n, pbc):
     b, _ = g.eval_heff(mmp.T_DEMAG)
     g.close()
     assert np.abs(b - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+def test_stray_tensor_in_pieces():
+    """A tensor whose offsets need more threads than one launch holds: 64x64
+    offsets within reach of tall cells, 4097 layers, of which the top ones are
+    magnetised.  The same layers on a grid of their own give the same field."""
+    torch = pytest.importorskip("torch")
+    cell, top, height = (1e-9, 1e-9, 2e-9), 8, 3e-9
+    m = inputs.smoothed_random_unit(inputs.rng(95), 1, (64, 64, top), sigma=1.5)
+    out = []
+    for nz in (4097, top):
+        p = inputs.base_params((64, 64, nz), cell)
+        p.update(Ms=[9e5], A11=[1.3e-11], alpha=[0.1])
+        full = torch.zeros((1, 3, nz, 64, 64), dtype=torch.float64, device="cuda")
+        full[:, :, nz - top:] = torch.from_numpy(m).to("cuda")
+        torch.cuda.synchronize()
+        g = mmp.Grid(p, mmp.FP64)
+        g.set_state_device(full)
+        out.append(g.stray_field(height))
+        g.close()
+    assert np.abs(out[0] - out[1]).max() <= 1e-12 * np.abs(out[1]).max()
