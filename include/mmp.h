@@ -360,7 +360,14 @@ typedef struct {
   int32_t y_lines[2];     /* lines per block, forward / inverse y pass:
                              1..64 (3-D grids)                             */
   int32_t xy_cols;        /* kx columns per block of the fused y pass of
-                             2-D grids: 1..64                              */
+                             2-D grids: 1..64.  A 3-D grid of up to 8 layers
+                             whose padded y lines of all layers fit a
+                             block's LDS runs y and z as one pass: 0 here
+                             asks for separate passes instead.  So do
+                             y_lines, z_cols or z_ values that are neither
+                             the grid's present ones nor the defaults of the
+                             pads, while bits 1 and 2 of lds_axes are clear
+                             (the plan then reads 0 here)                  */
   int32_t z_cols;         /* ky columns per block, mixed-radix z pass      */
   int32_t z_lanes;        /* lanes per (kx, ky) column, register z pass
                              (power-of-two Pz <= 64): 1, 2 or 4            */
@@ -374,11 +381,9 @@ typedef struct {
                              else Pz/z_lanes).  Same arithmetic per column */
   int32_t field_zplanes;  /* z cells per thread of the field kernel        */
   uint32_t kinds;         /* out: bits 0/1/2 set when the x/y/z passes use
-                             the power-of-two register kernels (a 3-D grid
-                             of up to 8 layers whose padded y lines of all
-                             layers fit a block's LDS runs y and z as one
-                             pass, whatever bits 1 and 2 and the y and z
-                             launch shapes say)                            */
+                             the power-of-two register kernels (bits 1 and
+                             2: where y and z are separate passes, see
+                             xy_cols)                                      */
   int32_t lds_axes;       /* bits 0/1/2: run the x/y/z passes through the
                              mixed-radix LDS kernels even where the pad is
                              a power of two (0 = the register kernels
@@ -400,7 +405,8 @@ mmp_status mmp_set_plan(mmp_grid g, const mmp_plan* p);
 /* Autotuner.  For every pad set built from the smallest even 7-smooth pad
  * and the smallest power-of-two pad of each axis, times the candidate
  * launch shapes of each demag pass on the grid's stream (HIP events, real
- * buffers; pad sets that do not fit in free device memory are skipped),
+ * buffers; pad sets that do not fit in free device memory are skipped), with
+ * y and z as one pass and as two where they can be one,
  * then the field kernel's z march lengths; installs the fastest plan and
  * keeps it for grids of the same (nx, ny, nz, precision, demag on/off) on
  * this device that later calls of mmp_set_params set up in this process.

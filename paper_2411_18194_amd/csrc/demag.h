@@ -25,14 +25,15 @@ struct DemagPlan {
   int ldy = 0;                      // multiple of 16, so any x block shape fits
   LineFft fx{}, fy{}, fz{};         // mixed-radix line transforms of the axes
   // 3-D grids: y, z and multiply as one pass over the layers of a kx column
-  // in LDS (see yz_fits); S2 is then not used
+  // in LDS (see yz_fits); S2 is then not used.  The default wherever it fits;
+  // nk = 0 stands for the separate passes there (demag_plan_separate)
   bool fuse = false;
   // power-of-two axes use the register four-step kernels
   bool p2x = false, p2y = false, p2z = false;
   // launch shapes
   int tyf = 0, tyi = 0;             // x passes: rows (even, <= 16) per block, fwd / inv
   int nlyf = 0, nlyi = 0;           // y passes: lines per block, fwd / inv
-  int nk = 0;                       // 2-D fused y pass: kx columns per block
+  int nk = 0;                       // 2-D fused y pass: kx columns per block (3-D: see fuse)
   int tk = 0;                       // mixed-radix z pass: ky columns per block
   int zq = 1, zw = 1, zt = 0;       // register z pass: lanes per column, waves hint, threads
   int zmode = 0;                    // register z pass: 1 = kernel values staged through LDS
@@ -50,6 +51,8 @@ struct DemagPlan {
 // rep (nullptr: open boundaries).  Returns 0, or -1 for an unsupported pad.
 int demag_plan(int nx, int ny, int nz, int real_bytes, const int* pads, DemagPlan* p,
                const int* rep = nullptr);
+// The same pads with y and z as separate passes.
+void demag_plan_separate(DemagPlan* p);
 // 0 if every launch shape of p is within the kernels' limits.
 int demag_plan_check(const DemagPlan& p, int real_bytes);
 

@@ -698,6 +698,12 @@ int demag_plan(int nx, int ny, int nz, int real_bytes, const int* pads, DemagPla
   return 0;
 }
 
+void demag_plan_separate(DemagPlan* p) {
+  p->fuse = false;
+  p->nk = 0;
+  p->s2_elems = (size_t)3 * p->nz * p->Hx * p->Py;
+}
+
 // --------------------------------------------------------------- passes --
 static int log2i(int v) {
   int l = 0;

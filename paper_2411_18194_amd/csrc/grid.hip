@@ -504,6 +504,16 @@ struct Grid final : GridBase {
     return 0;
   }
 
+  // launch shapes of the separate y and z passes
+  static bool same_yz_shapes(const DemagPlan& a, const DemagPlan& b) {
+    return a.nlyf == b.nlyf && a.nlyi == b.nlyi && a.tk == b.tk && a.zq == b.zq && a.zw == b.zw &&
+           a.zt == b.zt && a.zmode == b.zmode;
+  }
+  static void copy_yz_shapes(const DemagPlan& from, DemagPlan* to) {
+    to->nlyf = from.nlyf; to->nlyi = from.nlyi; to->tk = from.tk;
+    to->zq = from.zq; to->zw = from.zw; to->zt = from.zt; to->zmode = from.zmode;
+  }
+
   int set_plan(const mmp_plan* in) override {
     if (!params_set) {
       set_error("no plan: set parameters first");
@@ -524,6 +534,7 @@ struct Grid final : GridBase {
         set_error("lds_axes: bits 0..2 only");
         return MMP_E_ARG;
       }
+      const DemagPlan def = np;
       np.force_lds = in->lds_axes;
       if (np.force_lds & 1) np.p2x = false;
       if (np.force_lds & 2) np.p2y = false;
@@ -538,6 +549,21 @@ struct Grid final : GridBase {
       if (demag_plan_check(np, (int)sizeof(T)) != 0) {
         set_error("plan launch shape outside the kernels' limits");
         return MMP_E_ARG;
+      }
+      if (np.fuse) {
+        // One pass over y and z, unless the caller wants two: by xy_cols = 0,
+        // or by shapes that only those have and that are neither the ones the
+        // grid holds nor the defaults of these pads (with the LDS kernels
+        // asked for, of which the fused pass is one, by xy_cols alone)
+        const bool lds = (np.force_lds & 6) != 0;
+        const bool asked = !lds && !same_yz_shapes(np, plan) && !same_yz_shapes(np, def);
+        if (np.nk == 0 || asked) {
+          demag_plan_separate(&np);
+        } else if (!lds) {
+          // a fused plan holds its pads' defaults, so that it says the same
+          // to any grid it is given to later
+          copy_yz_shapes(def, &np);
+        }
       }
       int rc = install_plan(np);
       if (!rc && !demag_built) rc = build_demag();
@@ -667,44 +693,66 @@ struct Grid final : GridBase {
     MMP_HIP_TRY(hipStreamSynchronize(stream));
     DemagPlan best{};
     double best_ms = -1.0;
+    // y and z as one pass, where it fits, and as two: near the limit of the
+    // LDS, where a block fills a CU alone, either may win (steps of a 256x128x8
+    // FP64 film take 502 us in one pass and 408 with the best two, of a
+    // 200x240x8 FP32 one 357 and 423)
+    auto tune = [&](DemagPlan c) -> int {
+      const bool cur =
+          c.Px == plan.Px && c.Py == plan.Py && c.Pz == plan.Pz && c.fuse == plan.fuse;
+      DemagBufs<T> tb = db;
+      Buf<cpx<T>> s1, s2, twb;
+      Buf<T> kb;
+      auto drop = [&] {
+        s1.release(); s2.release(); kb.release(); twb.release();
+      };
+      if (cur) {
+        c.tyf = plan.tyf; c.tyi = plan.tyi;
+        if (nz == 1) c.nk = plan.nk;
+        if (!c.fuse) {
+          c.nlyf = plan.nlyf; c.nlyi = plan.nlyi;
+          c.tk = plan.tk;
+          if (c.p2z == plan.p2z) { c.zq = plan.zq; c.zw = plan.zw; c.zt = plan.zt; }
+        }
+        if (demag_plan_check(c, (int)sizeof(T)) != 0) c = plan;
+      } else {
+        if (s1.alloc(c.s1_elems) || s2.alloc(c.s2_elems) || kb.alloc(c.k_elems) ||
+            twb.alloc(demag_tw_elems(c))) {
+          drop();
+          return 0;  // this pad set does not fit next to the grid
+        }
+        set_demag_ptrs(tb, s1.p, s2.p, kb.p, twb.p, c);
+        const hipError_t e = hipMemsetAsync(kb.p, 0, c.k_elems * sizeof(T), stream);
+        if (e != hipSuccess) {
+          drop();
+          set_error(std::string("autotune: ") + hipGetErrorString(e));
+          return MMP_E_HIP;
+        }
+        build_all_twiddles(tb, c);
+      }
+      const double ms = demag_tune<T>(&c, tb, dtbl.p, ms0, ms1, p.nsub, stream, ms2);
+      const hipError_t e = hipStreamSynchronize(stream);
+      drop();
+      if (e != hipSuccess) {
+        set_error(std::string("autotune: ") + hipGetErrorString(e));
+        return MMP_E_HIP;
+      }
+      if (ms > 0.0 && (best_ms < 0.0 || ms < best_ms)) {
+        best_ms = ms;
+        best = c;
+      }
+      return 0;
+    };
     for (int i = 0; i < nxc; ++i)
       for (int j = 0; j < nyc; ++j)
         for (int k = 0; k < nzc; ++k) {
           const int pads[3] = {cx[i], cy[j], cz[k]};
           DemagPlan c;
           if (demag_plan(nx, ny, nz, (int)sizeof(T), pads, &c, p.pbc) != 0) continue;
-          const bool cur = c.Px == plan.Px && c.Py == plan.Py && c.Pz == plan.Pz;
-          DemagBufs<T> tb = db;
-          Buf<cpx<T>> s1, s2, twb;
-          Buf<T> kb;
-          auto drop = [&] {
-            s1.release(); s2.release(); kb.release(); twb.release();
-          };
-          if (cur) {
-            c.tyf = plan.tyf; c.tyi = plan.tyi; c.nlyf = plan.nlyf; c.nlyi = plan.nlyi;
-            c.nk = plan.nk; c.tk = plan.tk;
-            if (c.p2z == plan.p2z) { c.zq = plan.zq; c.zw = plan.zw; c.zt = plan.zt; }
-            if (demag_plan_check(c, (int)sizeof(T)) != 0) c = plan;
-          } else {
-            if (s1.alloc(c.s1_elems) || s2.alloc(c.s2_elems) || kb.alloc(c.k_elems) ||
-                twb.alloc(demag_tw_elems(c))) {
-              drop();
-              continue;  // this pad set does not fit next to the grid
-            }
-            set_demag_ptrs(tb, s1.p, s2.p, kb.p, twb.p, c);
-            MMP_HIP_TRY(hipMemsetAsync(kb.p, 0, c.k_elems * sizeof(T), stream));
-            build_all_twiddles(tb, c);
-          }
-          const double ms = demag_tune<T>(&c, tb, dtbl.p, ms0, ms1, p.nsub, stream, ms2);
-          const hipError_t e = hipStreamSynchronize(stream);
-          drop();
-          if (e != hipSuccess) {
-            set_error(std::string("autotune: ") + hipGetErrorString(e));
-            return MMP_E_HIP;
-          }
-          if (ms > 0.0 && (best_ms < 0.0 || ms < best_ms)) {
-            best_ms = ms;
-            best = c;
+          if (int rc = tune(c)) return rc;
+          if (c.fuse) {
+            demag_plan_separate(&c);
+            if (int rc = tune(c)) return rc;
           }
         }
     if (best_ms < 0.0) {
