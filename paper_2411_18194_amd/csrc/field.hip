@@ -172,7 +172,9 @@ __device__ __forceinline__ void sto(gptr<T> base, uint32_t o, T v) {
 // the launch so that one argument block serves every stage.
 // GDMI: general DMI tensors with the Eq. 6 ghosts on every stencil.
 // GBX: exchange links between different grains scaled by gbx_scale.
-template <typename T, int NSUB, bool EVAL, bool GDMI = false, bool GBX = false>
+// NK: slopes a cell's sum may hold (the pair's stages less one); 6 serves every
+// pair, the pairs of two and three run their own with several sublattices.
+template <typename T, int NSUB, bool EVAL, bool GDMI = false, bool GBX = false, int NK = 6>
 __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage& rk, const int zero, const int w,
                                             const int stage, const int fuse2) {
   const int ntile = a.nbx * a.nby;
@@ -183,8 +185,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
   const int x = (tile % a.nbx) * kTileX + (int)(threadIdx.x % kTileX);
   const int y = (tile / a.nbx) * kTileY + (int)(threadIdx.x / kTileX);
   const bool in = x < a.nx && y < a.ny;
-  const long N = a.N;
-  const long N3 = 3 * N;
+  const long N0 = a.N;
   // every pointer and the step size first: their loads and the controller's
   // flags make one trip, the data the second
   const gcptr<T> m = (gcptr<T>)table_slot<T>(a.tbl, rk.in + zero);
@@ -228,6 +229,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
 
   if (in) {
     T cur[NSUB][3], zm[NSUB][3], zp[NSUB][3];
+    const long N = N0, N3 = 3 * N0;
     constexpr uint32_t S = sizeof(T);
     const uint32_t col = (uint32_t)(y * a.nx + x);
     const uint32_t plane = (uint32_t)(a.nx * a.ny);
@@ -252,6 +254,13 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
         }
     }
     for (int z = z0; z < z1; ++z) {
+      // The component stride of the short pairs is hidden too: the bases of
+      // every array and component, kept from one iteration to the next, are
+      // more than the scalar registers hold, and to fetch them back from
+      // vector lanes takes longer than to add the stride anew.
+      long N = N0;
+      if constexpr (NSUB > 1 && NK < 6) asm volatile("" : "+s"(N));
+      const long N3 = 3 * N;
       const uint32_t i = (uint32_t)z * plane + col, o = i * S;
       const int dzp = z + 1 < a.nz ? (int)plane : 0;
       const uint32_t oxm = o + (uint32_t)dxm * S, oxp = o + (uint32_t)dxp * S,
@@ -263,7 +272,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
       // The slope at a state has to be the same bits in every stage (a run
       // resumed from a saved state evaluates it as k_1, the run it continues
       // as the last slope).
-      int has_slots = uni(!EVAL && (stage < ns || !fuse2)), has_next = uni(stage < ns || fuse2),
+      int has_slots = uni(EVAL ? 0 : stage < ns ? max(stage - 1, 1) : fuse2 ? 0 : ns - 1), has_next = uni(stage < ns || fuse2),
           is_last = uni(stage >= ns);
       asm volatile("" : "+s"(has_slots), "+s"(has_next), "+s"(is_last));
       // the grain's axis is two loads one behind the other: first
@@ -280,11 +289,11 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
       // Every slot is loaded (a slot this stage does not use reads k_1
       // again, a cache hit): no branch between the loads, which then all go
       // out before the first wait.
-      T kv1[6][3], yv1[3];
+      T kv1[NK][3], yv1[3];
       if constexpr (NSUB == 1 && !EVAL) {
         if (has_slots) {
 #pragma unroll
-          for (int j = 0; j < 6; ++j)
+          for (int j = 0; j < NK; ++j)
 #pragma unroll
             for (int c = 0; c < 3; ++c) kv1[j][c] = ldo<T>(kslot[j] + c * N, o);
 #pragma unroll
@@ -363,14 +372,24 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
         const T* mm = cur[s];
         // several sublattices: the slopes of one sublattice at a time, asked
         // for before its field is computed (both at once, with the stencil,
-        // would cost more waves than it hides)
-        T kvs[6][3], yvs[3];
+        // would cost more waves than it hides).  The short pairs ask for the
+        // ones a stage sums and no more: with six slots per stage, as one load
+        // without branches, Heun and Bogacki-Shampine steps of 512x512x2 FP64
+        // took 88 and 132 us with two sublattices, 172 and 262 with three, and
+        // take 79 and 119, 103 and 164.  (Dormand-Prince steps, 278 and 564,
+        // are as fast with all six.)
+        T kvs[NK][3], yvs[3];
         if constexpr (NSUB > 1 && !EVAL) {
           if (has_slots) {
 #pragma unroll
-            for (int j = 0; j < 6; ++j)
+            for (int j = 0; j < NK; ++j) {
+              if (NK == 6 || j == 0 || has_slots > j) {
 #pragma unroll
-              for (int c = 0; c < 3; ++c) kvs[j][c] = ldo<T>(kslot[j] + s * N3 + c * N, o);
+                for (int c = 0; c < 3; ++c) kvs[j][c] = ldo<T>(kslot[j] + s * N3 + c * N, o);
+              } else {
+                kvs[j][0] = kvs[j][1] = kvs[j][2] = T(0);
+              }
+            }
 #pragma unroll
             for (int c = 0; c < 3; ++c) yvs[c] = ldo<T>(yslot + s * N3 + c * N, o);
           }
@@ -601,7 +620,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
               for (int c = 0; c < 3; ++c) {
                 T acc = yv[c];
 #pragma unroll
-                for (int j = 0; j < 5; ++j)
+                for (int j = 0; j < (NK < 5 ? NK : 5); ++j)
                   if (j < stage - 1) acc = fma(ca[j], kv[j][c], acc);
                 v[c] = fma(ca[stage - 1], tau[c], acc);
               }
@@ -620,7 +639,7 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
             for (int c = 0; c < 3; ++c) {
               double acc = 0.0;
 #pragma unroll
-              for (int j = 0; j < 6; ++j)
+              for (int j = 0; j < NK; ++j)
                 if (j < ns - 1 && ew[j] != 0.0) acc += ew[j] * (double)kv[j][c];
               ev[c] = acc + ew[ns - 1] * (double)tau[c];
             }
@@ -663,10 +682,10 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
   }
 }
 
-template <typename T, int NSUB, bool EVAL, bool GDMI = false, bool GBX = false>
+template <typename T, int NSUB, bool EVAL, bool GDMI = false, bool GBX = false, int NK = 6>
 __global__ __launch_bounds__(256) void k_field(const FieldArgs<T> a, const RKStage rk) {
   const int zero = warm_args<FieldArgs<T>>();
-  field_block<T, NSUB, EVAL, GDMI, GBX>(a, rk, zero, xcd_remap(blockIdx.x, a.nb_pad), a.stage, a.fuse2);
+  field_block<T, NSUB, EVAL, GDMI, GBX, NK>(a, rk, zero, xcd_remap(blockIdx.x, a.nb_pad), a.stage, a.fuse2);
 }
 
 // The field and the elastic force of one stage in one launch: both read the
@@ -717,12 +736,22 @@ template <typename T, bool EVAL, bool GDMI, bool GBX>
 void launch_field_nsub(const FieldArgs<T>& a, hipStream_t st) {
   const dim3 g(a.nb_pad), b(256);
   const RKStage rk = rk_stage(RK::t[a.rk], a.stage);
+  auto go = [&](auto nk) {
+    constexpr int NK = decltype(nk)::value;
+    if (a.nsub == 2) {
+      hipLaunchKernelGGL((k_field<T, 2, EVAL, GDMI, GBX, NK>), g, b, 0, st, a, rk);
+    } else if constexpr (!GDMI) {
+      hipLaunchKernelGGL((k_field<T, 3, EVAL, GDMI, GBX, NK>), g, b, 0, st, a, rk);
+    }
+  };
   if (a.nsub == 1) {
     hipLaunchKernelGGL((k_field<T, 1, EVAL, GDMI, GBX>), g, b, 0, st, a, rk);
-  } else if (a.nsub == 2) {
-    hipLaunchKernelGGL((k_field<T, 2, EVAL, GDMI, GBX>), g, b, 0, st, a, rk);
-  } else if constexpr (!GDMI) {
-    hipLaunchKernelGGL((k_field<T, 3, EVAL, GDMI, GBX>), g, b, 0, st, a, rk);
+  } else if constexpr (EVAL) {
+    go(std::integral_constant<int, 6>{});
+  } else {
+    if (rk.ns == 3) go(std::integral_constant<int, 2>{});
+    else if (rk.ns == 4) go(std::integral_constant<int, 3>{});
+    else go(std::integral_constant<int, 6>{});
   }
 }
 
