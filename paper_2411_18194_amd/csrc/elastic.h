@@ -7,11 +7,29 @@
 
 namespace mmp {
 
+// Blocks of the strain and force kernels over nz planes of nbx x nby tiles of
+// 64x4 cells: the tiles, whose rows share their y neighbours, or 256
+// consecutive cells each where more than a tenth of the tiles' lanes would lie
+// past the grid.  Steps in tiles / linear (FP64): 16x8192 514 / 339 us, 1x65536
+// 3520 / 1560, 65x4096 577 / 453, 160x1600 372 / 358, 300x200x4 396 / 403,
+// 128x2048 336 / 340.  While every tile has a CU to itself idle lanes cost
+// nothing (2048x1: 66 / 71).
+// (The kernels are built for each: with a branch on it steps of 2048x64 FP32
+// in tiles took 138 us instead of 137, linear ones of 16x8192 208 instead of 180.)
+inline bool elastic_linear(long N, int nbx, int nby, int nz) {
+  const long tiles = (long)nbx * nby * nz, lines = (N + 255) / 256;
+  return tiles > 256 && 10 * tiles > 11 * lines;
+}
+inline int elastic_blocks(long N, int nbx, int nby, int nz) {
+  return (int)(nbx == 0 || elastic_linear(N, nbx, nby, nz) ? (N + 255) / 256
+                                                           : (long)nbx * nby * nz);
+}
+
 template <typename T>
 struct ElasticArgs {
   int nx, ny, nz, nsub;
   long N;
-  int nbx, nby;                  // 64x4 tiles (blocks: nbx nby nz)
+  int nbx, nby;                  // 64x4 tiles; nbx 0: 256 consecutive cells a block
   T dx, dy, dz;
   T C11, C12, C44, eta, inv_rho;
   double trac_amp, trac_omega;   // sigma_xz(t) = amp sin(omega t) on x = 0

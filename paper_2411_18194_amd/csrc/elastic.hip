@@ -61,12 +61,12 @@ __device__ __forceinline__ void cubic_stress(const ElasticArgs<T>& a, const T* e
   s[5] = T(2) * a.C44 * e[5];
 }
 
-template <typename T>
+template <typename T, bool LIN>
 __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int ns, double cs, int eval) {
   const gcptr<T> u0 = u_in<T>(a.tbl, a.stage, ns), v0 = v_in<T>(a.tbl, a.stage, ns);
   if (ctrl_stopped(a.ctrl)) return;
   int x, y, z;
-  const bool in = tile_cell((int)blockIdx.x, a.nbx, a.nby, a.nx, a.ny, &x, &y, &z);
+  const bool in = tile_cell<T, LIN>(a, (int)blockIdx.x, &x, &y, &z);
   double e_el = 0.0;
   if (in) {
     const long N = a.N;
@@ -123,9 +123,9 @@ __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int ns, double
   }
 }
 
-template <typename T>
+template <typename T, bool LIN>
 __global__ __launch_bounds__(256) void k_force(ElasticArgs<T> a, const RKStage rk) {
-  force_block<T>(a, rk, (int)blockIdx.x);
+  force_block<T, LIN>(a, rk, (int)blockIdx.x);
 }
 
 template <typename T>
@@ -140,22 +140,27 @@ __global__ void k_elastic_combine2(const Table<T>* tbl, const Ctrl* ctrl, long n
 
 template <typename T>
 static dim3 elastic_grid(const ElasticArgs<T>& a) {
-  return dim3((unsigned)(a.nbx * a.nby * a.nz));
+  return dim3((unsigned)elastic_blocks(a.N, a.nbx, a.nby, a.nz));
 }
 
 template <typename T>
 void launch_strain(const ElasticArgs<T>& a, bool eval, hipStream_t st, Prof* prof) {
   ProfScope ps(prof, P_ELASTIC, st);
   const RKTab& t = RK::t[a.rk];
-  hipLaunchKernelGGL(k_strain<T>, elastic_grid(a), dim3(256), 0, st, a, t.ns,
-                     a.stage > 0 ? t.c[a.stage - 1] : 0.0, eval ? 1 : 0);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, elastic_grid(a), dim3(256), 0, st, a, t.ns,
+                       a.stage > 0 ? t.c[a.stage - 1] : 0.0, eval ? 1 : 0);
+  };
+  if (a.nbx == 0) go(k_strain<T, true>);
+  else go(k_strain<T, false>);
 }
 
 template <typename T>
 void launch_force(const ElasticArgs<T>& a, hipStream_t st, Prof* prof) {
   ProfScope ps(prof, P_ELASTIC, st);
-  hipLaunchKernelGGL(k_force<T>, elastic_grid(a), dim3(256), 0, st, a,
-                     rk_stage(RK::t[a.rk], a.stage));
+  const RKStage rk = rk_stage(RK::t[a.rk], a.stage);
+  if (a.nbx == 0) hipLaunchKernelGGL((k_force<T, true>), elastic_grid(a), dim3(256), 0, st, a, rk);
+  else hipLaunchKernelGGL((k_force<T, false>), elastic_grid(a), dim3(256), 0, st, a, rk);
 }
 
 template <typename T>

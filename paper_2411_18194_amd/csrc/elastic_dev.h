@@ -55,14 +55,23 @@ __device__ __forceinline__ gcptr<T> v_in(const Table<T>* t, int s, int ns) {
   return stage_pick<T>(t->vn, t->vnew, t->vsa, t->vsb, s, ns);
 }
 
-// cell of thread t in 64x4 tile w of the plane-major tiles
-__device__ __forceinline__ bool tile_cell(int w, int nbx, int nby, int nx, int ny, int* x, int* y,
-                                          int* z) {
-  const int tx = w % nbx, r = w / nbx;
-  *x = tx * 64 + (int)(threadIdx.x & 63);
-  *y = (r % nby) * 4 + (int)(threadIdx.x >> 6);
-  *z = r / nby;
-  return *x < nx && *y < ny;
+// cell of this thread in block w: 64x4 tile w of the plane-major tiles, or
+// (LIN, see elastic_linear) the w-th 256 cells
+template <typename T, bool LIN>
+__device__ __forceinline__ bool tile_cell(const ElasticArgs<T>& a, int w, int* x, int* y, int* z) {
+  if constexpr (LIN) {
+    const int i = w * 256 + (int)threadIdx.x, r = i / a.nx;
+    *x = i - r * a.nx;
+    *y = r % a.ny;
+    *z = r / a.ny;
+    return i < a.N;
+  } else {
+    const int tx = w % a.nbx, r = w / a.nbx;
+    *x = tx * 64 + (int)(threadIdx.x & 63);
+    *y = (r % a.nby) * 4 + (int)(threadIdx.x >> 6);
+    *z = r / a.nby;
+    return *x < a.nx && *y < a.ny;
+  }
 }
 
 // y_n + sum_{j<NJ} c_j k_j at one cell, every load issued before the first sum
@@ -96,7 +105,7 @@ __device__ __forceinline__ void stage_sum_n(int nj, const gcptr<T> yn, const gcp
 
 // Tile w of the force: divergence of the stress, magnetoelastic force of Eq.
 // 8 per sublattice, k_u and k_v, and the next stage's u and v.
-template <typename T>
+template <typename T, bool LIN>
 __device__ __forceinline__ void force_block(const ElasticArgs<T>& a, const RKStage& rk, int w) {
   const int stage = a.stage, ns = rk.ns, nj = stage - 1;
   // pointers and step size first, in one trip with the controller's flags
@@ -121,7 +130,7 @@ __device__ __forceinline__ void force_block(const ElasticArgs<T>& a, const RKSta
   const double h = a.ctrl->h;
   if (ctrl_stopped(a.ctrl)) return;
   int x, y, z;
-  if (!tile_cell(w, a.nbx, a.nby, a.nx, a.ny, &x, &y, &z)) return;
+  if (!tile_cell<T, LIN>(a, w, &x, &y, &z)) return;
   const long N = a.N;
   const long i = ((long)z * a.ny + y) * a.nx + x;
   const Diff<T> dx = diff_at<T>(x, a.nx, 1, a.dx), dy = diff_at<T>(y, a.ny, a.nx, a.dy),

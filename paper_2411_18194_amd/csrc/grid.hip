@@ -241,7 +241,7 @@ struct Grid final : GridBase {
       a.place(epart, (size_t)nb_max * kNE);
       a.place(eout, kNE);
       a.place(spart, (size_t)nsamp_blk * 9);
-      a.place(elpart, (size_t)nbx * nby * nz);
+      a.place(elpart, (size_t)elastic_blocks(N, nbx, nby, nz));
       a.place(dtbl, 1);
       a.place(dctrl, 1);
       a.place(y[0], nm);
@@ -877,6 +877,7 @@ struct Grid final : GridBase {
     e.tbl = dtbl.p; e.ctrl = dctrl.p; e.eps = eps.p; e.sig = sig.p; e.epart = elpart.p;
     e.rk = p.solver;
     e.nbx = a.nbx; e.nby = a.nby; e.beta = (T)p.rayleigh;
+    if (elastic_linear(N, e.nbx, e.nby, nz)) e.nbx = 0;
     e.V = a.V; e.rho = p.rho;
     ea = e;
     drop_graphs();
