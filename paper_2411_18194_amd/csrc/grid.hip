@@ -584,17 +584,16 @@ struct Grid final : GridBase {
   double time_field(int zc, bool step, Ctrl* tctrl, int reps) {
     set_field_zc(zc);
     FieldArgs<T> a = fa;
+    a.stage = 2;
     a.fuse2 = 0;
     a.ctrl = tctrl;
-    const T ms0 = (T)p.sub[0].Ms, ms1 = ms_of(1), ms2 = ms_of(2);
     const int last = step ? RK::t[p.solver].ns : 2;
     auto stages = [&] {
-      for (a.stage = 2; a.stage <= last; ++a.stage) {
-        if (step && p.demag)
-          demag_field<T>(plan, db, dtbl.p, a.stage, nullptr, ms0, ms1, p.nsub, stream, nullptr,
-                         ms2);
+      if (!step) {
         launch_field<T>(a, false, stream, nullptr);
+        return;
       }
+      for (int s = 2; s <= last; ++s) enqueue_stage(s, false, tctrl, nullptr);
     };
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess) return -1.0;
@@ -624,19 +623,14 @@ struct Grid final : GridBase {
     // k_1 that a run left is kept). On what a fresh allocation holds every
     // cell reports a non-finite torque with an atomic, and the march is
     // picked by those (a 512x512x16 FP32 film: 750 us a launch, not 90).
+    // (u and v are zero until a state is set.)
     if (k1_valid) {
       launch_combine2<T>(dtbl.p, tc.p, p.solver, N, p.nsub, stream, nullptr);
+      if (p.elastic) launch_elastic_combine2<T>(dtbl.p, tc.p, N, stream, nullptr);
     } else {
       if (!state_set)
         MMP_HIP_TRY(hipMemsetAsync(y[0].p, 0x3c, y[0].n * sizeof(T), stream));
-      if (p.demag)
-        demag_field<T>(plan, db, dtbl.p, 1, nullptr, (T)p.sub[0].Ms, ms_of(1), p.nsub, stream,
-                       nullptr, ms_of(2));
-      FieldArgs<T> first = fa;
-      first.stage = 1;
-      first.fuse2 = 0;
-      first.ctrl = tc.p;
-      launch_field<T>(first, false, stream, nullptr);
+      enqueue_stage(1, false, tc.p, nullptr);
     }
     const int reps = N >= (1L << 22) ? 5 : N >= (1L << 16) ? 20 : 50;
     const int steps = (reps + 4) / 5;
@@ -989,25 +983,30 @@ struct Grid final : GridBase {
   }
 
   // ---------------------------------------------------------- stages --
-  void stage(int s, bool fuse2) {
+  void stage(int s, bool fuse2) { enqueue_stage(s, fuse2, dctrl.p, &prof); }
+
+  void enqueue_stage(int s, bool fuse2, Ctrl* ctrl, Prof* pr) {
     if (p.elastic) {
       ElasticArgs<T> e = ea;
       e.stage = s;
-      launch_strain(e, false, stream, &prof);
+      e.ctrl = ctrl;
+      launch_strain(e, false, stream, pr);
     }
     if (p.demag)
-      demag_field<T>(plan, db, dtbl.p, s, dctrl.p, (T)p.sub[0].Ms, ms_of(1), p.nsub, stream,
-                     &prof, ms_of(2));
+      demag_field<T>(plan, db, dtbl.p, s, ctrl, (T)p.sub[0].Ms, ms_of(1), p.nsub, stream, pr,
+                     ms_of(2));
     FieldArgs<T> a = fa;
     a.stage = s;
     a.fuse2 = fuse2 ? 1 : 0;
+    a.ctrl = ctrl;
     if (p.elastic) {
       ElasticArgs<T> e = ea;
       e.stage = s;
       e.fuse2 = fuse2 ? 1 : 0;
-      launch_field_force<T>(a, e, stream, &prof);
+      e.ctrl = ctrl;
+      launch_field_force<T>(a, e, stream, pr);
     } else {
-      launch_field<T>(a, false, stream, &prof);
+      launch_field<T>(a, false, stream, pr);
     }
   }
 

@@ -42,3 +42,68 @@ def test_tuning_leaves_runs_alone(n, nsub, prec):
     c.set_plan(**pl)
     c.run_fixed(dt, 4)
     assert np.array_equal(end(c), ref)
+
+
+def _track(n, seed=96):
+    p, _ = inputs.config_c4_crop()
+    p = dict(p, n=n)
+    nx, ny, nz = n
+    r = inputs.rng(seed)
+    m = inputs.smoothed_random_unit(r, 1, n, sigma=1.5)
+    u = 1e-12 * r.standard_normal((3, nz, ny, nx))
+    v = 1e-3 * r.standard_normal((3, nz, ny, nx))
+    return p, np.concatenate([m, -m]), u, v
+
+
+@pytest.mark.parametrize("prec", [mmp.FP64, mmp.FP32])
+@pytest.mark.parametrize("n", [(40, 10, 1), (12, 9, 6)])
+def test_tuning_leaves_elastic_runs_alone(n, prec):
+    """m, u and v: before a state, and between two halves of a run."""
+    p, m, u, v = _track(n)
+    dt = 1e-15
+
+    def end(g):
+        out = g.get_state()[:3]
+        g.close()
+        return out
+
+    def same(a, b):
+        return all(np.array_equal(x, y) for x, y in zip(a, b))
+
+    a = mmp.Grid(p, prec)
+    pl = a.plan()
+    a.set_state(m, u, v)
+    a.run_fixed(dt, 8)
+    ref = end(a)
+    assert all(np.isfinite(x).all() for x in ref)
+    b = mmp.Grid(p, prec)
+    b.autotune()
+    b.set_plan(**pl)
+    b.set_state(m, u, v)
+    b.run_fixed(dt, 8)
+    assert same(end(b), ref)
+    c = mmp.Grid(p, prec)
+    c.set_plan(**pl)
+    c.set_state(m, u, v)
+    c.run_fixed(dt, 4)
+    c.autotune()
+    c.set_plan(**pl)
+    c.run_fixed(dt, 4)
+    assert same(end(c), ref)
+
+
+def test_march_is_not_tuned_on_a_stale_strain():
+    """The strain that the timed kernels read is of the state at hand, not what
+    an earlier evaluation left (here NaN, which every cell would report with an
+    atomic on one flag: many times the kernel's time)."""
+    p, m, u, v = _track((256, 256, 8))
+    m = np.broadcast_to(m[:, :, :1, :1, :1], m.shape).copy()
+    ms = []
+    for bad in (False, True):
+        g = mmp.Grid(p, mmp.FP32)
+        g.set_state(m, np.full_like(u, np.nan) if bad else u, v)
+        g.eval_heff(mmp.T_ALL, want_b=False)
+        g.set_state(m, u, v)
+        ms.append(min(g.autotune()["field_ms"] for _ in range(3)))
+        g.close()
+    assert ms[1] < 2.0 * ms[0], ms
