@@ -392,7 +392,9 @@ typedef struct {
   double demag_ms;        /* out: time of one demag evaluation measured by
                              mmp_autotune for this plan, 0 if not tuned    */
   double field_ms;        /* out: time of one field-kernel stage measured
-                             by mmp_autotune, 0 if not tuned               */
+                             by mmp_autotune with this march on a grid of
+                             the same sublattices, elasticity, solver,
+                             boundary condition and grain links, 0 if none  */
 } mmp_plan;
 
 /* The grid's current plan.  MMP_E_STATE before mmp_set_params. */

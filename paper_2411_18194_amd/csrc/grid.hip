@@ -24,10 +24,18 @@ struct TunedPlan {
   DemagPlan demag;
   double demag_ms;
   int field_zc;
-  double field_ms;
+};
+// The march is also kept per field kernel (sublattices, elastic, pair, Eq. 6
+// ghosts, grain links) with its time: a grid of a tuned shape that runs another
+// kernel starts from the shape's march, whose time is not its own.
+using MarchKey = std::tuple<PlanKey, int, int, int, int, int>;
+struct TunedMarch {
+  int zc;
+  double ms;
 };
 static std::mutex g_plan_mu;
 static std::map<PlanKey, TunedPlan> g_plans;
+static std::map<MarchKey, TunedMarch> g_marches;
 
 static int current_device() {
   int dev = 0;
@@ -280,7 +288,6 @@ struct Grid final : GridBase {
         np = it->second.demag;
         tuned_ms = it->second.demag_ms;
         field_zc = it->second.field_zc;
-        field_ms = it->second.field_ms;
         cached = true;
       }
     }
@@ -324,6 +331,7 @@ struct Grid final : GridBase {
     MMP_HIP_TRY(hipMemcpyAsync(dctrl.p, &c, sizeof(c), hipMemcpyHostToDevice, stream));
     MMP_HIP_TRY(hipStreamSynchronize(stream));
     allocated = true;
+    march_of = MarchKey{};
     a_nsub = p.nsub; a_elastic = p.elastic; a_demag = p.demag;
     a_pbc[0] = p.pbc[0]; a_pbc[1] = p.pbc[1];
     state_set = false;
@@ -456,6 +464,25 @@ struct Grid final : GridBase {
   PlanKey plan_key() const {
     return PlanKey(nx, ny, nz, (int)sizeof(T), p.demag ? 1 : 0, current_device(), p.pbc[0],
                    p.pbc[1]);
+  }
+
+  MarchKey march_key() const {
+    return MarchKey(plan_key(), p.nsub, p.elastic ? 1 : 0, p.solver, p.bc_eq6 ? 1 : 0, fa.gbx);
+  }
+  MarchKey march_of{};   // the kernel that field_ms is of
+
+  // after a change of the field kernel: the march that was tuned for it (for a
+  // new layout; else the grid keeps the one it has) and that march's time
+  void find_march(bool fresh) {
+    const MarchKey key = march_key();
+    if (key == march_of) return;
+    march_of = key;
+    field_ms = 0.0;
+    std::lock_guard<std::mutex> lk(g_plan_mu);
+    auto it = g_marches.find(key);
+    if (it == g_marches.end()) return;
+    if (fresh) field_zc = it->second.zc;
+    if (field_zc == it->second.zc) field_ms = it->second.ms;
   }
 
   // enough waves to cover the chip a few times over (8 per SIMD), with the
@@ -661,7 +688,8 @@ struct Grid final : GridBase {
     if (int rc = tune_field()) return rc;
     {
       std::lock_guard<std::mutex> lk(g_plan_mu);
-      g_plans[plan_key()] = {plan, tuned_ms, field_zc, field_ms};
+      g_plans[plan_key()] = {plan, tuned_ms, field_zc};
+      g_marches[march_key()] = {field_zc, field_ms};
     }
     return out ? get_plan(out) : 0;
   }
@@ -770,8 +798,10 @@ struct Grid final : GridBase {
           set_error("interfacial DMI is implemented for one sublattice");
           return MMP_E_ARG;
         }
-    if (!allocated || a_nsub != p.nsub || a_elastic != (p.elastic != 0) ||
-        a_demag != (p.demag != 0) || a_pbc[0] != p.pbc[0] || a_pbc[1] != p.pbc[1]) {
+    const bool fresh = !allocated || a_nsub != p.nsub || a_elastic != (p.elastic != 0) ||
+                       a_demag != (p.demag != 0) || a_pbc[0] != p.pbc[0] ||
+                       a_pbc[1] != p.pbc[1];
+    if (fresh) {
       p.elastic = p.elastic != 0;
       p.demag = p.demag != 0;
       const int rc = alloc_layout();
@@ -847,6 +877,7 @@ struct Grid final : GridBase {
     a.per_y = p.pbc[1] > 0 ? 1 : 0;
     fa = a;
     db.ns = RK::t[p.solver].ns;
+    find_march(fresh);
     set_field_zc(field_zc > 0 ? field_zc : default_field_zc());
     // the pair in use: its stage count and index, read by every stage kernel
     if (a_rk != p.solver) {

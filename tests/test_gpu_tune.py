@@ -107,3 +107,34 @@ def test_march_is_not_tuned_on_a_stale_strain():
         ms.append(min(g.autotune()["field_ms"] for _ in range(3)))
         g.close()
     assert ms[1] < 2.0 * ms[0], ms
+
+
+def test_march_is_kept_per_field_kernel():
+    """Grids of one shape share the tuned pads and march; a march's time is
+    reported for the kernel it was measured on, and the last tuned kernel does
+    not take another's place."""
+    n = (28, 18, 12)
+    p = {}
+    for nsub in (1, 2):
+        p[nsub] = inputs.base_params(n, (2e-9, 2e-9, 2e-9), nsub=nsub)
+        p[nsub].update(Ms=[9e5] * nsub, A11=[1.3e-11] * nsub, alpha=[0.1] * nsub, demag=True)
+    a = mmp.Grid(p[1], mmp.FP32)
+    one = a.autotune()
+    assert one["field_ms"] > 0
+    b = mmp.Grid(p[2], mmp.FP32)
+    pl = b.plan()
+    assert pl["pad"] == one["pad"] and pl["field_zplanes"] == one["field_zplanes"]
+    assert pl["field_ms"] == 0
+    two = b.autotune()
+    assert two["field_ms"] > 0
+    for q, was in ((p[1], one), (p[2], two)):
+        g = mmp.Grid(q, mmp.FP32)
+        pl = g.plan()
+        assert (pl["field_zplanes"], pl["field_ms"]) == (was["field_zplanes"], was["field_ms"])
+        # the pair is part of the kernel: another keeps the march, not its time
+        g.set_params(dict(q, solver="heun"), mmp.FP32)
+        pl = g.plan()
+        assert (pl["field_zplanes"], pl["field_ms"]) == (was["field_zplanes"], 0)
+        g.close()
+    a.close()
+    b.close()
