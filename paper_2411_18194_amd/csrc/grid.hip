@@ -140,6 +140,12 @@ struct Buf {
   }
 };
 
+// a buffer of one scope
+template <typename T>
+struct ScopeBuf : Buf<T> {
+  ~ScopeBuf() { this->release(); }
+};
+
 // Many buffers in one device allocation.  A call of hipMalloc takes about
 // 30 us and one of hipFree 11, whatever the size: the 28 buffers of a grid
 // were 1.2 ms of the 1.7 that setting one up for a single field took.  `place`
@@ -440,7 +446,7 @@ struct Grid final : GridBase {
     // grids' steps); later ones, beside a state, in an allocation of their own
     const size_t need = demag_build_doubles(plan);
     const bool fresh = !state_set && idle_end - idle_begin >= need * sizeof(double);
-    Buf<double> own;
+    ScopeBuf<double> own;
     if (!fresh && own.alloc(need)) {
       set_error("device allocation failed (demag kernel build)");
       return MMP_E_HIP;
@@ -448,7 +454,6 @@ struct Grid final : GridBase {
     double* scratch = fresh ? reinterpret_cast<double*>(mem.p + idle_begin) : own.p;
     build_all_twiddles(db, plan);
     const int rc = demag_kernel_build<T>(plan, d[0], d[1], d[2], scratch, db.K, stream);
-    own.release();
     if (rc) {
       set_error("demag kernel build failed");
       return MMP_E_HIP;
@@ -640,7 +645,7 @@ struct Grid final : GridBase {
   }
 
   int tune_field() {
-    Buf<Ctrl> tc;
+    ScopeBuf<Ctrl> tc;
     if (tc.alloc(1)) { set_error("device allocation failed"); return MMP_E_NOMEM; }
     Ctrl c{};
     c.h = 1e-15;
@@ -723,11 +728,8 @@ struct Grid final : GridBase {
       const bool cur =
           c.Px == plan.Px && c.Py == plan.Py && c.Pz == plan.Pz && c.fuse == plan.fuse;
       DemagBufs<T> tb = db;
-      Buf<cpx<T>> s1, s2, twb;
-      Buf<T> kb;
-      auto drop = [&] {
-        s1.release(); s2.release(); kb.release(); twb.release();
-      };
+      ScopeBuf<cpx<T>> s1, s2, twb;
+      ScopeBuf<T> kb;
       if (cur) {
         c.tyf = plan.tyf; c.tyi = plan.tyi;
         if (nz == 1) c.nk = plan.nk;
@@ -739,26 +741,14 @@ struct Grid final : GridBase {
         if (demag_plan_check(c, (int)sizeof(T)) != 0) c = plan;
       } else {
         if (s1.alloc(c.s1_elems) || s2.alloc(c.s2_elems) || kb.alloc(c.k_elems) ||
-            twb.alloc(demag_tw_elems(c))) {
-          drop();
+            twb.alloc(demag_tw_elems(c)))
           return 0;  // this pad set does not fit next to the grid
-        }
         set_demag_ptrs(tb, s1.p, s2.p, kb.p, twb.p, c);
-        const hipError_t e = hipMemsetAsync(kb.p, 0, c.k_elems * sizeof(T), stream);
-        if (e != hipSuccess) {
-          drop();
-          set_error(std::string("autotune: ") + hipGetErrorString(e));
-          return MMP_E_HIP;
-        }
+        MMP_HIP_TRY(hipMemsetAsync(kb.p, 0, c.k_elems * sizeof(T), stream));
         build_all_twiddles(tb, c);
       }
       const double ms = demag_tune<T>(&c, tb, dtbl.p, ms0, ms1, p.nsub, stream, ms2);
-      const hipError_t e = hipStreamSynchronize(stream);
-      drop();
-      if (e != hipSuccess) {
-        set_error(std::string("autotune: ") + hipGetErrorString(e));
-        return MMP_E_HIP;
-      }
+      MMP_HIP_TRY(hipStreamSynchronize(stream));
       if (ms > 0.0 && (best_ms < 0.0 || ms < best_ms)) {
         best_ms = ms;
         best = c;
@@ -1625,6 +1615,11 @@ struct Batch final : BatchBase {
     if (st) (void)hipStreamSynchronize(st);
     DeviceLock lk(device_mutex());
     if (gexec) (void)hipGraphExecDestroy(gexec);
+    d_args.release();
+    d_work.release();
+    d_step.release();
+    d_cptr.release();
+    d_cgather.release();
     for (int i = 0; i < 2; ++i) {
       if (h_c[i]) (void)hipHostFree(h_c[i]);
       if (ev[i]) (void)hipEventDestroy(ev[i]);

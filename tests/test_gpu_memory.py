@@ -1,0 +1,49 @@
+"""Device memory that calls take for themselves is given back: tuning a grid,
+and servers with their batches, many times over, leave the device's free
+memory where it was.  (4000 tunings of a controller each, or 160 sets of batch
+tables, are 8 MiB; the driver counts in steps of 2.)
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2411_18194_amd import inputs, mmp
+
+pytestmark = pytest.mark.gpu
+
+
+def _used():
+    torch.cuda.synchronize()
+    free, total = torch.cuda.mem_get_info()
+    return total - free
+
+
+def _grows(call, warm, times):
+    for _ in range(warm):
+        call()
+    before = _used()
+    for _ in range(times):
+        call()
+    return _used() - before
+
+
+def test_tuning_gives_its_memory_back():
+    p = inputs.base_params((4, 4, 1), (2e-9, 2e-9, 2e-9))
+    p.update(Ms=[9e5], A11=[1.3e-11], alpha=[0.1])
+    g = mmp.Grid(p, mmp.FP32)
+    assert _grows(g.autotune, 20, 4000) < 4 << 20
+    g.close()
+
+
+def test_servers_give_their_tables_back():
+    n = (1, 1, 16384)     # one field block per cell: the largest tables
+    p = inputs.base_params(n, (2e-9, 2e-9, 2e-9))
+    p.update(Ms=[9e5], A11=[1.3e-11], alpha=[0.1])
+    m = inputs.random_unit(inputs.rng(131), 1, n)
+
+    def serve():
+        s = mmp.Server(1 << 30, max_active=2, precision=mmp.FP32)
+        assert s.wait(s.submit(p, m, 1e-15)).status == 0
+        s.close()
+
+    assert _grows(serve, 5, 160) < 4 << 20
