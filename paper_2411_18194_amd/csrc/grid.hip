@@ -1721,11 +1721,12 @@ struct Batch final : BatchBase {
                          g->ms_of(2), g->p.nsub});
       if (int rc = dm.build(dms, st)) return rc;
     }
-    // the tables only grow: freeing one waits for every stream of the device
+    // the tables only grow, twice what is needed each time: freeing one waits
+    // for every stream of the device
     auto fit = [](auto& b, size_t count) {
       if (b.p && b.n >= count) return 0;
       b.release();
-      return b.alloc(count);
+      return b.alloc(2 * count);
     };
     if (fit(d_args, n) || fit(d_work, work.size()) || fit(d_step, n) || fit(d_cptr, n) ||
         fit(d_cgather, n)) {
