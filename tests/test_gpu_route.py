@@ -157,3 +157,47 @@ def test_tuner_keeps_its_choice(prec):
     assert h.set_plan(**pl)["xy_cols"] == pl["xy_cols"] and _run(h, ref)[0] == one
     g.close()
     h.close()
+
+
+@pytest.mark.parametrize("prec", [mmp.FP64, mmp.FP32])
+def test_batch_of_every_route(prec):
+    """One batch of 2-D grids, of fused ones with short and long z columns and
+    of ones whose y and z are separate passes: each result bitwise as served
+    alone, and as the grid run alone on the LDS kernels (FP64 the same steps and
+    <m> to 1e-12, energy to 1e-12 of its terms; FP32 the trajectory bar 1e-4)."""
+    sizes = [((12, 10, 1), True), ((9, 11, 3), True), ((10, 8, 7), True), ((11, 9, 8), True),
+             ((8, 10, 12), False), ((5, 600, 8), False)]
+    reqs = []
+    for i, (n, _) in enumerate(sizes):
+        p = inputs.base_params(n, (2e-9, 2e-9, 2e-9))
+        p.update(Ms=[1.0e6], A11=[1.4e-11], Ku1=[4e5], alpha=[0.1], B_ext=(0.0, 0.0, 0.05),
+                 demag=True)
+        reqs.append((p, inputs.smoothed_random_unit(inputs.rng(141 + i), 1, n, sigma=1.5)))
+    t = 1e-11
+
+    def serve(rs):
+        srv = mmp.Server(hbm_budget=8 << 30, max_active=8, precision=prec)
+        out = [srv.wait(k) for k in [srv.submit(p, m, t) for p, m in rs]]
+        srv.close()
+        assert all(r.status == 0 for r in out)
+        return out
+
+    mixed = serve(reqs)
+    assert max(r.t_admit for r in mixed) < min(r.t_done for r in mixed)
+    for (p, m), (n, fused), r in zip(reqs, sizes, mixed):
+        alone = serve([(p, m)])[0]
+        assert (r.steps, r.rejects, r.energy) == (alone.steps, alone.rejects, alone.energy), n
+        assert np.array_equal(np.array(r.m_avg), np.array(alone.m_avg)), n
+        g = mmp.Grid(p, prec)
+        g.set_plan(lds_axes=7)
+        g.set_state(m)
+        if n[2] > 1:
+            assert _run(g, 1.0)[0] == fused, n
+        info, _, _ = g.run(t)
+        avg = g.get_state()[0].mean(axis=(0, 2, 3, 4))
+        _, e = g.eval_heff(mmp.T_ALL, want_b=False)
+        g.close()
+        bar = 1e-12 if prec == mmp.FP64 else 1e-4
+        assert prec == mmp.FP32 or (r.steps, r.rejects) == (info.steps, info.rejects), n
+        assert np.abs(np.array([r.m_avg[0][c] for c in range(3)]) - avg).max() <= bar, n
+        assert abs(r.energy - sum(e.values())) <= bar * sum(abs(v) for v in e.values()), n
