@@ -387,8 +387,9 @@ typedef struct {
   int32_t lds_axes;       /* bits 0/1/2: run the x/y/z passes through the
                              mixed-radix LDS kernels even where the pad is
                              a power of two (0 = the register kernels
-                             there); such a grid computes its field bitwise
-                             as the server's batched demag does            */
+                             there); with all three a grid computes its
+                             field as the server's batched demag does, up to
+                             rounding                                      */
   double demag_ms;        /* out: time of one demag evaluation measured by
                              mmp_autotune for this plan, 0 if not tuned    */
   double field_ms;        /* out: time of one field-kernel stage measured

@@ -72,9 +72,8 @@ struct DemagBufs {
   int ns = 7;               // stages of the pair in use (where stage inputs are)
 };
 
-// B_d for the stage input of `stage` (see stage_src) or, with stage == 0, for
-// the array `src` directly.  M = Ms0 m0 + Ms1 m1 (+ Ms2 m2 for three
-// sublattices).
+// B_d for the input of stage `stage` (0 and 1: the accepted state).
+// M = Ms0 m0 + Ms1 m1 (+ Ms2 m2 for three sublattices).
 template <typename T>
 void demag_field(const DemagPlan& p, const DemagBufs<T>& b, const Table<T>* tbl, int stage,
                  const Ctrl* ctrl, T ms0, T ms1, int nsub, hipStream_t st, Prof* prof,
@@ -88,10 +87,12 @@ void demag_pass(int pass, const DemagPlan& p, const DemagBufs<T>& b, const Table
 
 // Times the candidate launch shapes of every pass for the pads of *p on the
 // buffers b and keeps the fastest in *p.  Returns the time of one demag
-// evaluation with the chosen shapes in ms (< 0 on a HIP error).
+// evaluation with the chosen shapes in ms (< 0 on a HIP error).  With give_up
+// > 0 an evaluation with the shapes of *p is timed first, and returned, *p
+// unchanged, where it takes longer than that.
 template <typename T>
 double demag_tune(DemagPlan* p, const DemagBufs<T>& b, const Table<T>* tbl, T ms0, T ms1,
-                  int nsub, hipStream_t st, T ms2 = T(0));
+                  int nsub, hipStream_t st, T ms2 = T(0), double give_up = 0.0);
 
 // FP64 tensor on the non-negative offsets and its transformed octant
 // spectrum: kout receives the scaled spectrum (k_elems values of type T,
@@ -124,10 +125,10 @@ struct DemagMember {
 
 // The demag passes of many grids of any pads, each pass one launch for all
 // of them over a device work table of (grid, block) entries, through the
-// mixed-radix LDS kernels with 256-thread blocks.  A grid's field is bitwise
-// the one its own plan gives with every axis on those kernels (force_lds =
-// 7): the per-line arithmetic of the LDS kernels does not depend on how
-// lines are grouped into blocks.
+// mixed-radix LDS kernels with 256-thread blocks.  A grid's field does not
+// depend on the other members, and is the one its own plan gives with every axis
+// on those kernels (force_lds = 7) up to rounding: the same arithmetic per
+// line, however lines are grouped into blocks, in kernels of its own.
 // Whether a grid with plan p can join a batched demag evaluation (its lines
 // fit one 256-thread block of the LDS kernels).
 bool demag_multi_fits(const DemagPlan& p);

@@ -154,8 +154,8 @@ __device__ __forceinline__ void fftx_inv_body(const XArgs<T>& a, int zero, int b
     b[pk] = cmk<T>(xa.x - xb.y, xa.y + xb.x);
     if (kx > 0 && 2 * kx < a.f.L) b[pm] = cmk<T>(xa.x + xb.y, xb.x - xa.y);
   }
-  if (stop) return;
   lds_copies_done();
+  if (stop) return;
   __syncthreads();
   const long N = (long)a.nx * a.ny * a.nz;
   T* out = a.Bd + (long)c * N + (long)z * a.ny * a.nx;
@@ -533,7 +533,12 @@ static int line_threads(const LineFft& f, long lines, int most) {
 // The fused y-z pass takes a 3-D grid when its z length is one it is built
 // for and the 3 nz lines of a kx column fit the LDS of a block (128 of the
 // 160 KiB of a CU; a block that size still moves a quarter of what the
-// separate passes move through memory).
+// separate passes move through memory).  This is the default, not a rule for
+// every grid: up to about 90 KiB it wins (steps in one pass / two, default
+// shapes, FP32: 128x128x8 195 / 223 us, 200x240x8 357 / 423), from about 100
+// KiB, one block per CU, it wins or loses by the number of blocks (FP32
+// 256x256x8 463 / 441, 512x512x4 663 / 647; FP64 256x128x8 502 / 436, 128x128x8
+// 299 / 299, 1024x256x4 1694 / 1779), which the tuner finds out.
 static constexpr long kYzLds = 131072;
 static bool yz_built(int Pz) {
   switch (Pz) {
@@ -1125,7 +1130,7 @@ static double time_passes(const int* seq, int ns, const DemagPlan& p, const Dema
 
 template <typename T>
 double demag_tune(DemagPlan* pp, const DemagBufs<T>& b, const Table<T>* tbl, T ms0, T ms1,
-                  int nsub, hipStream_t st, T ms2) {
+                  int nsub, hipStream_t st, T ms2, double give_up) {
   constexpr int rb = (int)sizeof(T);
   DemagPlan best = *pp;
   int passes[DP_COUNT];
@@ -1134,6 +1139,10 @@ double demag_tune(DemagPlan* pp, const DemagBufs<T>& b, const Table<T>* tbl, T m
   // and run-to-run spread of a few percent on large ones
   const long work = (long)best.Hx * best.Py * best.Pz;
   const int reps = work >= (1L << 22) ? 8 : work >= (1L << 16) ? 10 : 30;
+  if (give_up > 0.0) {
+    const double t = time_passes<T>(passes, n, best, b, tbl, ms0, ms1, nsub, st, reps, ms2);
+    if (t < 0.0 || t > give_up) return t;
+  }
   for (int i = 0; i < n; ++i) {
     const int pass = passes[i];
     std::vector<DemagPlan> cand;
@@ -1218,7 +1227,7 @@ double demag_tune(DemagPlan* pp, const DemagBufs<T>& b, const Table<T>* tbl, T m
   template void demag_pass<T>(int, const DemagPlan&, const DemagBufs<T>&, const Table<T>*, int,  \
                               const Ctrl*, T, T, int, hipStream_t, T);                          \
   template double demag_tune<T>(DemagPlan*, const DemagBufs<T>&, const Table<T>*, T, T, int,    \
-                                hipStream_t, T);
+                                hipStream_t, T, double);
 INST(float)
 INST(double)
 #undef INST

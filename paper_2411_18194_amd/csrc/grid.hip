@@ -723,8 +723,11 @@ struct Grid final : GridBase {
     // y and z as one pass, where it fits, and as two: near the limit of the
     // LDS, where a block fills a CU alone, either may win (steps of a 256x128x8
     // FP64 film take 502 us in one pass and 408 with the best two, of a
-    // 200x240x8 FP32 one 357 and 423)
-    auto tune = [&](DemagPlan c) -> int {
+    // 200x240x8 FP32 one 357 and 423).  Two are given up where their default
+    // shapes take more than 1.3 times the best so far: tuned shapes gained up to
+    // 1.2, and the search is most of the tuner's time (183x77x5: 35 ms, 102
+    // without the limit).
+    auto tune = [&](DemagPlan c, double give_up) -> int {
       const bool cur =
           c.Px == plan.Px && c.Py == plan.Py && c.Pz == plan.Pz && c.fuse == plan.fuse;
       DemagBufs<T> tb = db;
@@ -747,7 +750,7 @@ struct Grid final : GridBase {
         MMP_HIP_TRY(hipMemsetAsync(kb.p, 0, c.k_elems * sizeof(T), stream));
         build_all_twiddles(tb, c);
       }
-      const double ms = demag_tune<T>(&c, tb, dtbl.p, ms0, ms1, p.nsub, stream, ms2);
+      const double ms = demag_tune<T>(&c, tb, dtbl.p, ms0, ms1, p.nsub, stream, ms2, give_up);
       MMP_HIP_TRY(hipStreamSynchronize(stream));
       if (ms > 0.0 && (best_ms < 0.0 || ms < best_ms)) {
         best_ms = ms;
@@ -761,10 +764,10 @@ struct Grid final : GridBase {
           const int pads[3] = {cx[i], cy[j], cz[k]};
           DemagPlan c;
           if (demag_plan(nx, ny, nz, (int)sizeof(T), pads, &c, p.pbc) != 0) continue;
-          if (int rc = tune(c)) return rc;
+          if (int rc = tune(c, 0.0)) return rc;
           if (c.fuse) {
             demag_plan_separate(&c);
-            if (int rc = tune(c)) return rc;
+            if (int rc = tune(c, best_ms > 0.0 ? 1.3 * best_ms : 0.0)) return rc;
           }
         }
     if (best_ms < 0.0) {

@@ -56,9 +56,9 @@ struct Req {
 // Grid<T>::alloc_layout makes for its parameters (state pair, stage pair, 7
 // slopes; with elasticity u and v pairs, their stage pairs, 14 slopes and
 // room for three symmetric tensors, of which it keeps strain and stress; grain
-// ids and axes; the demag spectra, kernel and field), the FP64 tensor of the
-// demag build (which lies in the stage buffers where it fits), and 1 MiB of
-// small buffers.
+// ids and axes; the demag spectra of the default plan, kernel and field), the
+// FP64 tensor of the demag build (which lies in the stage buffers where it
+// fits), and 1 MiB of small buffers.
 int64_t estimate_bytes(const mmp_request& r, int precision) {
   const int64_t N = (int64_t)r.nx * r.ny * r.nz;
   const int64_t rb = precision == MMP_FP64 ? 8 : 4;
