@@ -262,10 +262,21 @@ std::recursive_mutex& device_mutex();
 using DeviceLock = std::lock_guard<std::recursive_mutex>;
 const char* get_error();
 
+// hipMalloc without a trace: the error of a refused allocation would be
+// reported once more by the next launch's hipGetLastError, of another call.
+template <typename U>
+inline bool device_alloc(U** p, size_t bytes) {
+  if (hipMalloc((void**)p, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  *p = nullptr;
+  return false;
+}
+
 #define MMP_HIP_TRY(expr)                                                   \
   do {                                                                      \
     hipError_t e_ = (expr);                                                 \
     if (e_ != hipSuccess) {                                                 \
+      (void)hipGetLastError();                                              \
       ::mmp::set_error(std::string(#expr) + ": " + hipGetErrorString(e_)); \
       return MMP_E_HIP;                                                     \
     }                                                                       \

@@ -988,8 +988,7 @@ int DemagMulti<T>::build(const std::vector<DemagMember<T>>& members, hipStream_t
     if (mem_) (void)hipFree(mem_);
     mem_ = nullptr;
     cap_ = 0;
-    if (hipMalloc(&mem_, 2 * off) != hipSuccess) {
-      mem_ = nullptr;
+    if (!device_alloc(&mem_, 2 * off)) {
       release();
       set_error("device allocation failed (batched demag tables)");
       return MMP_E_NOMEM;

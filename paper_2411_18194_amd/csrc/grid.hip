@@ -128,7 +128,7 @@ struct Buf {
     own = true;
     if (count == 0) return 0;
     DeviceLock lk(device_mutex());
-    return hipMalloc(&p, count * sizeof(T)) == hipSuccess ? 0 : -1;
+    return device_alloc(&p, count * sizeof(T)) ? 0 : -1;
   }
   void release() {
     if (p && own) {
@@ -1512,11 +1512,11 @@ struct Grid final : GridBase {
     double *k6 = nullptr, *dout = nullptr;
     DeviceLock lk(device_mutex());
     MMP_HIP_TRY(hipStreamSynchronize(stream));
-    if (hipMalloc(&k6, nk * sizeof(double)) != hipSuccess) {
+    if (!device_alloc(&k6, nk * sizeof(double))) {
       set_error("stray field: device allocation failed");
       return MMP_E_NOMEM;
     }
-    if (hipMalloc(&dout, no * sizeof(double)) != hipSuccess) {
+    if (!device_alloc(&dout, no * sizeof(double))) {
       (void)hipFree(k6);
       set_error("stray field: device allocation failed");
       return MMP_E_NOMEM;

@@ -47,3 +47,19 @@ def test_servers_give_their_tables_back():
         s.close()
 
     assert _grows(serve, 5, 160) < 4 << 20
+
+
+def test_refused_allocation_leaves_no_error_behind():
+    """A grid larger than the device is refused; the next one is set up."""
+    p, _ = inputs.config_c4_crop()
+    with pytest.raises(mmp.MMPError) as ei:
+        mmp.Grid(dict(p, n=(4096, 4096, 16)), mmp.FP64)     # 309 GB
+    assert ei.value.code == -2
+    n = (12, 10, 3)
+    q = inputs.base_params(n, (2e-9, 2e-9, 2e-9))
+    q.update(Ms=[9e5], A11=[1.3e-11], alpha=[0.1], demag=True)
+    g = mmp.Grid(q, mmp.FP64)
+    g.set_state(inputs.random_unit(inputs.rng(132), 1, n))
+    assert np.isfinite(g.eval_heff()[0]).all()
+    g.run_fixed(1e-15, 2)
+    g.close()
