@@ -221,7 +221,9 @@ mmp_status mmp_grid_destroy(mmp_grid g);
 /* Copy the material, precision and solver settings (p->struct_size must
  * match).  Builds the demagnetising kernel (FP64 Newell / quadrature /
  * asymptotic tensor, transformed on the GPU) when p->demag is set and the
- * geometry changed.  Invalidates the FSAL stage. */
+ * geometry changed.  Invalidates the FSAL stage.  MMP_E_ARG leaves the grid
+ * as it was; after any other error it has no parameters, and calls that need
+ * them return MMP_E_STATE until a later one succeeds. */
 mmp_status mmp_set_params(mmp_grid g, const mmp_params* p);
 
 /* Upload the state: m (nsub*3*N, normalised by the caller), u and v (3*N

@@ -229,6 +229,7 @@ mmp_status mmp_set_params(mmp_grid g, const mmp_params* p) {
   if (p->ngrains > 0)
     for (long i = 0; i < N; ++i)
       if (p->grain[i] >= p->ngrains) { set_error("grain id out of range"); return MMP_E_ARG; }
+  if (int rc = check_params(g->nx, g->ny, g->nz, *p)) return rc;
   if (!g->impl || g->impl->precision != p->precision) {
     hipStream_t keep = g->user_stream;
     if (g->impl) {

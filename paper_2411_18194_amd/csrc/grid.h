@@ -66,6 +66,10 @@ struct GridBase {
 
 GridBase* make_grid(int precision);
 
+// MMP_E_ARG for parameters that no grid of this size takes: asked before
+// anything of a grid changes, so that a refused call leaves it as it was
+int check_params(int nx, int ny, int nz, const mmp_params& p);
+
 // Many grids stepped together: each stage of every member is one launch
 // (a device work table of (grid, block)), the step controllers and stage-2
 // combinations one launch each, 8 attempts per captured HIP graph, on the

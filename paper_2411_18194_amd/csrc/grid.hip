@@ -37,6 +37,26 @@ static std::mutex g_plan_mu;
 static std::map<PlanKey, TunedPlan> g_plans;
 static std::map<MarchKey, TunedMarch> g_marches;
 
+static int bad_pads() {
+  set_error("unsupported demag pads: each open axis pads to at most 4096, a periodic "
+            "axis needs n = 1 or n even and 7-smooth");
+  return MMP_E_ARG;
+}
+
+int check_params(int nx, int ny, int nz, const mmp_params& p) {
+  if (p.nsub >= 2)
+    for (int s = 0; s < p.nsub; ++s)
+      if (p.sub[s].Dint != 0.0) {
+        set_error("interfacial DMI is implemented for one sublattice");
+        return MMP_E_ARG;
+      }
+  DemagPlan d;
+  if (p.demag &&
+      demag_plan(nx, ny, nz, p.precision == MMP_FP64 ? 8 : 4, nullptr, &d, p.pbc) != 0)
+    return bad_pads();
+  return 0;
+}
+
 static int current_device() {
   int dev = 0;
   (void)hipGetDevice(&dev);
@@ -230,6 +250,8 @@ struct Grid final : GridBase {
     plan = DemagPlan{};
     allocated = false;
     demag_built = false;
+    state_set = false;
+    k1_valid = false;
   }
 
   long long bytes() const override {
@@ -299,10 +321,8 @@ struct Grid final : GridBase {
     }
     if (p.demag) {
       if (!cached && demag_plan(nx, ny, nz, (int)sizeof(T), nullptr, &np, p.pbc) != 0) {
-        set_error("unsupported demag pads: each open axis pads to at most 4096, a periodic "
-                  "axis needs n = 1 or n even and 7-smooth");
         free_all();
-        return MMP_E_ARG;
+        return bad_pads();
       }
       db.Bd = Bd.p;
       rc = install_plan(np);
@@ -411,6 +431,18 @@ struct Grid final : GridBase {
     plan = np;
     set_demag_ptrs(db, S1.p, S2.p, K.p, tw.p, plan);
     return 0;
+  }
+
+  // Another plan for a grid in use.  If its buffers don't fit, the old ones are
+  // gone too: the grid is as before its first mmp_set_params.
+  int change_plan(const DemagPlan& np) {
+    int rc = install_plan(np);
+    if (rc && !S1.p) {
+      free_all();
+      params_set = false;
+    }
+    if (!rc && !demag_built) rc = build_demag();
+    return rc;
   }
 
   // twiddles: the line transforms' tables of the three axes, then the
@@ -597,9 +629,7 @@ struct Grid final : GridBase {
           copy_yz_shapes(def, &np);
         }
       }
-      int rc = install_plan(np);
-      if (!rc && !demag_built) rc = build_demag();
-      if (rc) return rc;
+      if (int rc = change_plan(np)) return rc;
       tuned_ms = 0.0;
     }
     if (in->field_zplanes != field_zc) field_ms = 0.0;
@@ -774,9 +804,7 @@ struct Grid final : GridBase {
       set_error("autotune: no candidate plan could be timed");
       return MMP_E_HIP;
     }
-    int rc = install_plan(best);
-    if (!rc && !demag_built) rc = build_demag();
-    if (rc) return rc;
+    if (int rc = change_plan(best)) return rc;
     tuned_ms = best_ms;
     return 0;
   }
@@ -785,12 +813,7 @@ struct Grid final : GridBase {
   T ms_of(int s) const { return (T)(s < p.nsub ? p.sub[s].Ms : 0.0); }
 
   int apply_params() override {
-    if (p.nsub >= 2)
-      for (int s = 0; s < p.nsub; ++s)
-        if (p.sub[s].Dint != 0.0) {
-          set_error("interfacial DMI is implemented for one sublattice");
-          return MMP_E_ARG;
-        }
+    params_set = false;   // until every buffer and argument fits them
     const bool fresh = !allocated || a_nsub != p.nsub || a_elastic != (p.elastic != 0) ||
                        a_demag != (p.demag != 0) || a_pbc[0] != p.pbc[0] ||
                        a_pbc[1] != p.pbc[1];
@@ -905,6 +928,7 @@ struct Grid final : GridBase {
   }
 
   int set_state(const double* m, const double* uu, const double* vv, double t) override {
+    if (!params_set) { set_error("mmp_set_params has not been called"); return MMP_E_STATE; }
     // work enqueued without a host synchronisation (mmp_step with a fixed
     // dt, mmp_run_fixed) may still swap the pointer table or write the
     // state and controller: let it finish before they are replaced
@@ -938,6 +962,7 @@ struct Grid final : GridBase {
   }
 
   int set_state_device(const double* m, const double* uu, const double* vv, double t) override {
+    if (!params_set) { set_error("mmp_set_params has not been called"); return MMP_E_STATE; }
     if (int rc = check_device_buffer(m, stream, "m")) return rc;
     if (int rc = check_device_buffer(uu, stream, "u")) return rc;
     if (int rc = check_device_buffer(vv, stream, "v")) return rc;
@@ -1119,6 +1144,7 @@ struct Grid final : GridBase {
   int ensure_ready() {
     if (!params_set) { set_error("mmp_set_params has not been called"); return MMP_E_STATE; }
     if (!state_set) { set_error("mmp_set_state has not been called"); return MMP_E_STATE; }
+    if (p.demag && !demag_built) { set_error("the demag kernel is not built"); return MMP_E_STATE; }
     return 0;
   }
 

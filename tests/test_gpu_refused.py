@@ -1,0 +1,80 @@
+"""Parameters that mmp_set_params refuses, on a grid that is in use: a refused
+argument changes nothing, and a grid whose new buffers do not fit is as before
+its first parameters (every call that would use them returns MMP_E_STATE) until
+it gets some that fit.
+"""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2411_18194_amd import inputs, mmp
+
+pytestmark = pytest.mark.gpu
+
+
+def _film(n, **kw):
+    p = inputs.base_params(n, (2e-9, 2e-9, 2e-9), nsub=kw.pop("nsub", 1))
+    k = p["nsub"]
+    p.update(Ms=[9e5] * k, A11=[1.3e-11] * k, alpha=[0.1] * k, demag=True)
+    p.update(kw)
+    return p
+
+
+@pytest.mark.parametrize("prec", [mmp.FP64, mmp.FP32])
+def test_refused_arguments_change_nothing(prec):
+    n = (22, 10, 3)
+    p = _film(n)
+    m = inputs.smoothed_random_unit(inputs.rng(151), 1, n, sigma=1.5)
+    out = []
+    for refuse in (False, True):
+        g = mmp.Grid(p, prec)
+        g.set_state(m)
+        g.run_fixed(2e-14, 3)
+        if refuse:
+            pl, size = g.plan(), g.nbytes()
+            for bad in (_film(n, nsub=2, Dint=[1e-3] * 2), _film(n, pbc=(1, 0, 0)),
+                        _film(n, nsub=3, Dint=[0.0, 0.0, 1e-3])):
+                for other in (mmp.FP64, mmp.FP32):
+                    with pytest.raises(mmp.MMPError) as ei:
+                        g.set_params(bad, other)
+                    assert ei.value.code == -1
+            assert g.plan() == pl and g.nbytes() == size
+        g.run_fixed(2e-14, 3)
+        out.append((g.get_state()[0], g.eval_heff()[0]))
+        g.close()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+def test_a_grid_whose_buffers_do_not_fit():
+    n = (4096, 4096, 16)
+    small = _film(n, demag=False)
+    g = mmp.Grid(small, mmp.FP64)
+    big, _ = inputs.config_c4_crop()
+    with pytest.raises(mmp.MMPError) as ei:
+        g.set_params(dict(big, n=n), mmp.FP64)              # 309 GB
+    assert ei.value.code == -2
+    x = torch.zeros(8, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    d, h, lib = C.c_void_p(x.data_ptr()), (C.c_double * 8)(), g.lib
+    info = mmp.StepInfo()
+    pl = mmp.Plan(struct_size=C.sizeof(mmp.Plan))
+    for rc in (lib.mmp_set_state(g.h, h, None, None, 0.0),
+               lib.mmp_set_state_device(g.h, d, None, None, 0.0),
+               lib.mmp_get_state(g.h, h, None, None, None, None),
+               lib.mmp_get_state_device(g.h, d, None, None, None),
+               lib.mmp_eval_heff(g.h, mmp.T_ALL, None, h),
+               lib.mmp_eval_heff_device(g.h, mmp.T_ALL, d),
+               lib.mmp_step(g.h, 0.0, C.byref(info)),
+               lib.mmp_run_fixed(g.h, 1e-15, 2, C.byref(info)),
+               lib.mmp_run(g.h, 1e-12, None, None),
+               lib.mmp_stray_field(g.h, 2e-9, h),
+               lib.mmp_stray_field_noalloc(g.h, 2e-9, d),
+               lib.mmp_get_plan(g.h, C.byref(pl)),
+               lib.mmp_set_plan(g.h, C.byref(pl)),
+               lib.mmp_autotune(g.h, None)):
+        assert rc == -7
+    g.set_params(small, mmp.FP64)
+    assert g.plan()["field_zplanes"] >= 1
+    g.close()
