@@ -284,6 +284,7 @@ class Grid:
         _check(self.lib.mmp_set_params(self.h, C.byref(P)))
         self.precision = precision
         self.p = p
+        self.nsub = p["nsub"]
 
     def close(self):
         if getattr(self, "h", None):

@@ -78,3 +78,19 @@ def test_a_grid_whose_buffers_do_not_fit():
     g.set_params(small, mmp.FP64)
     assert g.plan()["field_zplanes"] >= 1
     g.close()
+
+
+def test_sublattices_may_change():
+    """The binding's buffers follow the parameters that the grid has now."""
+    n = (12, 10, 2)
+    g = mmp.Grid(_film(n), mmp.FP64)
+    for nsub in (3, 1, 2):
+        m = inputs.smoothed_random_unit(inputs.rng(152), nsub, n, sigma=1.5)
+        g.set_params(_film(n, nsub=nsub), mmp.FP64)
+        g.set_state(m)
+        assert np.array_equal(g.get_state()[0], m)
+        assert g.eval_heff()[0].shape == m.shape
+    with pytest.raises(mmp.MMPError):
+        g.set_params(_film(n, nsub=3, Dint=[1e-3] * 3), mmp.FP64)
+    assert g.get_state()[0].shape == m.shape
+    g.close()
