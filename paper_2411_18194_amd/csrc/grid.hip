@@ -1301,7 +1301,7 @@ struct Grid final : GridBase {
     }
     if (sampling && o && c.nsamples > 0) {
       DeviceLock lk(device_mutex());
-      const int ns = std::min(c.nsamples, samp_cap);
+      const int ns = std::min(c.nsamples, cap);   // (samp_cap may be an earlier run's)
       std::vector<double> tt(ns), mm((size_t)ns * 9);
       MMP_HIP_TRY(hipMemcpy(tt.data(), samp_t.p, ns * sizeof(double), hipMemcpyDeviceToHost));
       MMP_HIP_TRY(hipMemcpy(mm.data(), samp_m.p, ns * 9 * sizeof(double), hipMemcpyDeviceToHost));

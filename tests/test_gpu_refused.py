@@ -94,3 +94,23 @@ def test_sublattices_may_change():
         g.set_params(_film(n, nsub=3, Dint=[1e-3] * 3), mmp.FP64)
     assert g.get_state()[0].shape == m.shape
     g.close()
+
+
+def test_samples_stay_within_the_callers_buffers():
+    """A run with room for fewer samples than an earlier one's."""
+    n = (12, 10, 1)
+    g = mmp.Grid(_film(n), mmp.FP64)
+    g.set_state(inputs.smoothed_random_unit(inputs.rng(153), 1, n, sigma=1.5))
+    _, ts, _ = g.run(2e-13, sample_every=2e-14, max_samples=16)
+    assert len(ts) == 10
+    t = np.full(16, -1.0)
+    m = np.full((16, 1, 3), -7.0)
+    o = mmp.RunOpts()
+    o.struct_size = C.sizeof(mmp.RunOpts)
+    o.sample_every, o.max_samples = 2e-14, 2
+    o.sample_t, o.sample_m = mmp._dptr(t), mmp._dptr(m)
+    info = mmp.RunInfo()
+    assert g.lib.mmp_run(g.h, 4e-13, C.byref(o), C.byref(info)) == 0
+    assert info.nsamples == 10
+    assert (t[:2] > 0).all() and (t[2:] == -1.0).all() and (m[2:] == -7.0).all()
+    g.close()
