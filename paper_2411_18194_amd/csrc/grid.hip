@@ -252,6 +252,7 @@ struct Grid final : GridBase {
     demag_built = false;
     state_set = false;
     k1_valid = false;
+    samp_cap = 0;
   }
 
   long long bytes() const override {
@@ -1255,6 +1256,7 @@ struct Grid final : GridBase {
     if (every > 0.0 && cap > samp_cap) {
       drop_graphs();
       samp_t.release(); samp_m.release();
+      samp_cap = 0;
       if (samp_t.alloc(cap) || samp_m.alloc((size_t)cap * 9)) {
         set_error("device allocation failed");
         return MMP_E_NOMEM;

@@ -114,3 +114,23 @@ def test_samples_stay_within_the_callers_buffers():
     assert info.nsamples == 10
     assert (t[:2] > 0).all() and (t[2:] == -1.0).all() and (m[2:] == -7.0).all()
     g.close()
+
+
+def test_sampling_after_a_change_of_layout():
+    """New buffers (another sublattice count) take the sample buffers along: a
+    run with samples gets its own again, as a new grid does."""
+    n = (12, 10, 1)
+    g = mmp.Grid(_film(n), mmp.FP64)
+    g.set_state(inputs.smoothed_random_unit(inputs.rng(154), 1, n, sigma=1.5))
+    g.run(1e-13, sample_every=2e-14, max_samples=8)
+    m = inputs.smoothed_random_unit(inputs.rng(155), 2, n, sigma=1.5)
+    p = _film(n, nsub=2)
+    g.set_params(p, mmp.FP64)
+    h = mmp.Grid(p, mmp.FP64)
+    out = []
+    for x in (g, h):
+        x.set_state(m)
+        out.append(x.run(1e-13, sample_every=2e-14, max_samples=8)[1:] + x.get_state()[:1])
+        x.close()
+    assert len(out[0][0]) == 5
+    assert all(np.array_equal(a, b) for a, b in zip(*out))
