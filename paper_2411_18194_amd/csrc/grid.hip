@@ -588,6 +588,9 @@ struct Grid final : GridBase {
       set_error("field_zplanes must be in 1..nz");
       return MMP_E_ARG;
     }
+    // steps that were enqueued without a host synchronisation may still replay
+    // the graphs that a new plan drops
+    MMP_HIP_TRY(hipStreamSynchronize(stream));
     if (p.demag) {
       DemagPlan np;
       if (demag_plan(nx, ny, nz, (int)sizeof(T), in->pad, &np, p.pbc) != 0) {

@@ -134,3 +134,20 @@ def test_sampling_after_a_change_of_layout():
         x.close()
     assert len(out[0][0]) == 5
     assert all(np.array_equal(a, b) for a, b in zip(*out))
+
+
+@pytest.mark.parametrize("demag", [True, False])
+def test_a_plan_waits_for_enqueued_steps(demag):
+    """Steps on the stream replay graphs that a plan drops: it waits for them."""
+    n = (64, 48, 4)
+    m = inputs.smoothed_random_unit(inputs.rng(156), 1, n, sigma=1.5)
+    out = []
+    for sync in (True, False):
+        g = mmp.Grid(_film(n, demag=demag), mmp.FP32)
+        g.set_state(m)
+        for k in range(6):
+            g.run_fixed(2e-14, 40, sync=sync)
+            g.set_plan(field_zplanes=1 + k % 4)
+        out.append(g.get_state()[0])
+        g.close()
+    assert np.array_equal(out[0], out[1])
