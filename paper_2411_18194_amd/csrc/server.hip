@@ -418,10 +418,8 @@ struct mmp_server_s {
     for (Req* q : active) finish(q, MMP_E_STATE);
     active.clear();
     for (auto& B : batches) {
-      if (B.b) {
-        while (B.b->in_flight() > 0 && B.b->poll() == MMP_PENDING) {
-        }
-      }
+      // (two chunks may be in flight: none may still read a grid that goes)
+      if (B.b) B.b->abandon();
       for (Req* q : B.members) finish(q, MMP_E_STATE);
       for (Req* q : B.joining) finish(q, MMP_E_STATE);
       B.members.clear();

@@ -4,6 +4,7 @@ its first parameters (every call that would use them returns MMP_E_STATE) until
 it gets some that fit.
 """
 import ctypes as C
+import time
 
 import numpy as np
 import pytest
@@ -151,3 +152,27 @@ def test_a_plan_waits_for_enqueued_steps(demag):
         out.append(g.get_state()[0])
         g.close()
     assert np.array_equal(out[0], out[1])
+
+
+def test_a_server_ends_with_chunks_in_flight():
+    """Shutting down while a batch runs waits for its chunks; the next server
+    gives the result that a request gets by itself."""
+    n = (40, 30, 2)
+    p = _film(n)
+    m = inputs.smoothed_random_unit(inputs.rng(157), 1, n, sigma=1.5)
+
+    def one():
+        s = mmp.Server(1 << 30, max_active=4, precision=mmp.FP32)
+        r = s.wait(s.submit(p, m, 2e-12))
+        s.close()
+        return r.status, r.steps, list(r.m_avg[0])
+
+    ref = one()
+    assert ref[0] == 0
+    for wait in (0.0, 0.01, 0.05):
+        s = mmp.Server(1 << 30, max_active=4, precision=mmp.FP32)
+        for _ in range(3):
+            s.submit(p, m, 1e-8)
+        time.sleep(wait)
+        s.close()
+        assert one() == ref
