@@ -272,7 +272,12 @@ __device__ __forceinline__ void field_block(const FieldArgs<T>& a, const RKStage
       // The slope at a state has to be the same bits in every stage (a run
       // resumed from a saved state evaluates it as k_1, the run it continues
       // as the last slope).
-      int has_slots = uni(EVAL ? 0 : stage < ns ? max(stage - 1, 1) : fuse2 ? 0 : ns - 1), has_next = uni(stage < ns || fuse2),
+      // (has_slots: whether there are slots to load, with short pairs how many)
+      int has_slots = uni(NK == 6 ? !EVAL && (stage < ns || !fuse2)
+                              : stage < ns ? max(stage - 1, 1)
+                              : fuse2      ? 0
+                                           : ns - 1),
+          has_next = uni(stage < ns || fuse2),
           is_last = uni(stage >= ns);
       asm volatile("" : "+s"(has_slots), "+s"(has_next), "+s"(is_last));
       // the grain's axis is two loads one behind the other: first
