@@ -2,6 +2,8 @@
 // divergence, magnetoelastic force, and the (u, v) Runge-Kutta stages.
 #pragma once
 
+#include <type_traits>
+
 #include "common.h"
 #include "prof.h"
 
@@ -10,9 +12,9 @@ namespace mmp {
 // Blocks of the strain and force kernels over nz planes of nbx x nby tiles of
 // 64x4 cells: the tiles, whose rows share their y neighbours, or 256
 // consecutive cells each where more than a tenth of the tiles' lanes would lie
-// past the grid.  Steps in tiles / linear (FP64): 16x8192 514 / 339 us, 1x65536
-// 3520 / 1560, 65x4096 577 / 453, 160x1600 372 / 358, 300x200x4 396 / 403,
-// 128x2048 336 / 340.  While every tile has a CU to itself idle lanes cost
+// past the grid.  Steps in tiles / linear (FP64): 16x8192 514 / 340 us, 1x65536
+// 3525 / 1570, 65x4096 571 / 452, 160x1600 369 / 359, 300x200x4 382 / 395,
+// 128x2048 334 / 337.  While every tile has a CU to itself idle lanes cost
 // nothing (2048x1: 66 / 71).
 // (The kernels are built for each: with a branch on it steps of 2048x64 FP32
 // in tiles took 138 us instead of 137, linear ones of 16x8192 208 instead of 180.)
@@ -47,6 +49,19 @@ struct ElasticArgs {
   double V;
   double rho;
 };
+
+// The instance of an elastic kernel: f(LIN, ONE) with 256 consecutive cells a
+// block or tiles, and with an axis along x or y that may have one cell.  (The
+// masks of such an axis, in every kernel, would cost 0.8 % of a step.)
+template <typename T, typename F>
+void elastic_variant(const ElasticArgs<T>& a, F f) {
+  auto pick = [&](auto lin) {
+    if (a.nx == 1 || a.ny == 1) f(lin, std::true_type{});
+    else f(lin, std::false_type{});
+  };
+  if (a.nbx == 0) pick(std::true_type{});
+  else pick(std::false_type{});
+}
 
 // strain of the stage-s displacement into eps (consumed by the field
 // kernel's magnetoelastic term) and the stress with its traction rows into

@@ -28,19 +28,20 @@ __device__ __forceinline__ int voigt(int r, int c) {
 }
 
 // symmetrised gradient of the vector field f at the cell
-template <typename T>
-__device__ __forceinline__ void sym_grad(gcptr<T> f, long N, const Diff<T>& dx, const Diff<T>& dy,
-                                         const Diff<T>& dz, bool flat, T* e) {
+template <typename T, bool ONE>
+__device__ __forceinline__ void sym_grad(gcptr<T> f, long N, const Diff<T, ONE>& dx,
+                                         const Diff<T, ONE>& dy, const Diff<T, false>& dz,
+                                         bool flat, T* e) {
   T g[3][3];  // g[i][j] = d_i f_j
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    g[0][j] = deriv<T>(f + j * N, dx);
-    g[1][j] = deriv<T>(f + j * N, dy);
+    g[0][j] = deriv(f + j * N, dx);
+    g[1][j] = deriv(f + j * N, dy);
     g[2][j] = T(0);
   }
   if (!flat) {
 #pragma unroll
-    for (int j = 0; j < 3; ++j) g[2][j] = deriv<T>(f + j * N, dz);
+    for (int j = 0; j < 3; ++j) g[2][j] = deriv(f + j * N, dz);
   }
   e[0] = g[0][0];
   e[1] = g[1][1];
@@ -61,7 +62,7 @@ __device__ __forceinline__ void cubic_stress(const ElasticArgs<T>& a, const T* e
   s[5] = T(2) * a.C44 * e[5];
 }
 
-template <typename T, bool LIN>
+template <typename T, bool LIN, bool ONE>
 __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int ns, double cs, int eval) {
   const gcptr<T> u0 = u_in<T>(a.tbl, a.stage, ns), v0 = v_in<T>(a.tbl, a.stage, ns);
   if (ctrl_stopped(a.ctrl)) return;
@@ -71,11 +72,11 @@ __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int ns, double
   if (in) {
     const long N = a.N;
     const long i = ((long)z * a.ny + y) * a.nx + x;
-    const Diff<T> dx = diff_at<T>(x, a.nx, 1, a.dx), dy = diff_at<T>(y, a.ny, a.nx, a.dy),
-                  dz = diff_at<T>(z, a.nz, a.nx * a.ny, a.dz);
+    const auto dx = diff_at<T, ONE>(x, a.nx, 1, a.dx), dy = diff_at<T, ONE>(y, a.ny, a.nx, a.dy);
+    const auto dz = diff_at<T, false>(z, a.nz, a.nx * a.ny, a.dz);
     const bool flat = a.nz == 1;
     T e[6], s[6];
-    sym_grad<T>(u0 + i, N, dx, dy, dz, flat, e);
+    sym_grad(u0 + i, N, dx, dy, dz, flat, e);
     cubic_stress<T>(a, e, s);
 #pragma unroll
     for (int c = 0; c < 6; ++c) a.eps[c * N + i] = e[c];
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int ns, double
     if (a.beta != T(0)) {
       // viscous stress beta C : eps(v) (stiffness-proportional Rayleigh damping)
       T r[6], sr[6];
-      sym_grad<T>(v, N, dx, dy, dz, flat, r);
+      sym_grad(v, N, dx, dy, dz, flat, r);
       cubic_stress<T>(a, r, sr);
 #pragma unroll
       for (int c = 0; c < 6; ++c) s[c] += a.beta * sr[c];
@@ -123,9 +124,9 @@ __global__ __launch_bounds__(256) void k_strain(ElasticArgs<T> a, int ns, double
   }
 }
 
-template <typename T, bool LIN>
+template <typename T, bool LIN, bool ONE>
 __global__ __launch_bounds__(256) void k_force(ElasticArgs<T> a, const RKStage rk) {
-  force_block<T, LIN>(a, rk, (int)blockIdx.x);
+  force_block<T, LIN, ONE>(a, rk, (int)blockIdx.x);
 }
 
 template <typename T>
@@ -147,20 +148,20 @@ template <typename T>
 void launch_strain(const ElasticArgs<T>& a, bool eval, hipStream_t st, Prof* prof) {
   ProfScope ps(prof, P_ELASTIC, st);
   const RKTab& t = RK::t[a.rk];
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, elastic_grid(a), dim3(256), 0, st, a, t.ns,
-                       a.stage > 0 ? t.c[a.stage - 1] : 0.0, eval ? 1 : 0);
-  };
-  if (a.nbx == 0) go(k_strain<T, true>);
-  else go(k_strain<T, false>);
+  elastic_variant(a, [&](auto lin, auto one) {
+    hipLaunchKernelGGL((k_strain<T, lin.value, one.value>), elastic_grid(a), dim3(256), 0, st, a,
+                       t.ns, a.stage > 0 ? t.c[a.stage - 1] : 0.0, eval ? 1 : 0);
+  });
 }
 
 template <typename T>
 void launch_force(const ElasticArgs<T>& a, hipStream_t st, Prof* prof) {
   ProfScope ps(prof, P_ELASTIC, st);
   const RKStage rk = rk_stage(RK::t[a.rk], a.stage);
-  if (a.nbx == 0) hipLaunchKernelGGL((k_force<T, true>), elastic_grid(a), dim3(256), 0, st, a, rk);
-  else hipLaunchKernelGGL((k_force<T, false>), elastic_grid(a), dim3(256), 0, st, a, rk);
+  elastic_variant(a, [&](auto lin, auto one) {
+    hipLaunchKernelGGL((k_force<T, lin.value, one.value>), elastic_grid(a), dim3(256), 0, st, a,
+                       rk);
+  });
 }
 
 template <typename T>

@@ -697,12 +697,12 @@ __global__ __launch_bounds__(256) void k_field(const FieldArgs<T> a, const RKSta
 // stage input, strain and stress and write different things, and each alone
 // is a few microseconds of latency on a grid that leaves the chip half
 // empty.  The force's blocks come first (they take longer).
-template <typename T, int NSUB, bool LIN>
+template <typename T, int NSUB, bool LIN, bool ONE>
 __global__ __launch_bounds__(256) void k_field_force(const FieldArgs<T> a, const RKStage rk,
                                                      const ElasticArgs<T> e, int nforce) {
   const int b = (int)blockIdx.x;
   const int zero = warm_args<FieldArgs<T>>();
-  if (b < nforce) force_block<T, LIN>(e, rk, b);
+  if (b < nforce) force_block<T, LIN, ONE>(e, rk, b);
   else field_block<T, NSUB, false>(a, rk, zero, xcd_remap(b - nforce, a.nb_pad), a.stage, a.fuse2);
 }
 
@@ -790,14 +790,13 @@ void launch_field_force(const FieldArgs<T>& a, const ElasticArgs<T>& e, hipStrea
   const int nforce = elastic_blocks(e.N, e.nbx, e.nby, e.nz);
   const dim3 g(a.nb_pad + nforce), b(256);
   const RKStage rk = rk_stage(RK::t[a.rk], a.stage);
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, g, b, 0, st, a, rk, e, nforce); };
-  if (a.nsub == 1) {
-    if (e.nbx == 0) go(k_field_force<T, 1, true>);
-    else go(k_field_force<T, 1, false>);
-  } else {
-    if (e.nbx == 0) go(k_field_force<T, 2, true>);
-    else go(k_field_force<T, 2, false>);
-  }
+  elastic_variant(e, [&](auto lin, auto one) {
+    constexpr bool LIN = lin.value, ONE = one.value;
+    if (a.nsub == 1)
+      hipLaunchKernelGGL((k_field_force<T, 1, LIN, ONE>), g, b, 0, st, a, rk, e, nforce);
+    else
+      hipLaunchKernelGGL((k_field_force<T, 2, LIN, ONE>), g, b, 0, st, a, rk, e, nforce);
+  });
 }
 
 // --------------------------------------------------------- combine2 ----

@@ -41,3 +41,31 @@ def test_linear_blocks(n, beta):
     assert np.abs(mg - y[0]).max() < 1e-12
     assert np.abs(ug - y[1]).max() <= 1e-12 * np.abs(y[1]).max()
     assert np.abs(vg - y[2]).max() <= 1e-12 * np.abs(y[2]).max()
+
+
+# one displacement that is not finite, where the schemes of the axis leave it
+# out: two cells from a face, one cell from it, on it, and on axes of one cell
+@pytest.mark.parametrize("prec", [mmp.FP64, mmp.FP32])
+@pytest.mark.parametrize("n,at", [((9, 7, 6), (2, 4, 3)), ((9, 7, 6), (8, 5, 1)),
+                                  ((9, 7, 6), (4, 0, 5)), ((1, 8, 1), (0, 3, 0)),
+                                  ((6, 1, 5), (2, 0, 2)), ((2, 3, 4), (1, 1, 2)),
+                                  ((3, 150, 9), (1, 75, 4))])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_nonfinite_displacement_reaches_its_scheme_only(n, at, bad, prec):
+    p, _ = inputs.config_c4_crop()
+    p = dict(p, n=n)
+    nx, ny, nz = n
+    r = inputs.rng(122)
+    m = inputs.random_unit(r, 1, n)
+    m = np.concatenate([m, -m])
+    u = 1e-12 * r.standard_normal((3, nz, ny, nx))
+    u[:, at[2], at[1], at[0]] = bad
+    v = np.zeros_like(u)
+    g = mmp.Grid(p, prec)
+    g.set_state(m, u, v)
+    b, _ = g.eval_heff(mmp.T_MEL)
+    g.close()
+    with np.errstate(invalid="ignore"):
+        P = Problem(p)
+        ref = np.stack([P.term_field("mel", m, s, u) for s in range(2)])
+    assert np.array_equal(np.isfinite(b), np.isfinite(ref))
